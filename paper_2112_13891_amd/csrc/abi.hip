@@ -1116,8 +1116,16 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
 int step_impl(const ms_params* p, const float* X, int n, int d, float* seeds, int m, int n_iter,
               uint8_t* converged, int32_t* iters, float* shift2, hipStream_t s) {
     FMS_CHECK(ensure_pool_release_threshold());
+    // one stream-ordered allocation for the whole call, sized by a dry run: 13
+    // of them, with their frees, took the host longer than the kernels of a
+    // 512 x 200,000 step
+    Arena need(nullptr, 0);
+    FMS_CHECK(step_core(need, false, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s));
     Workspace ws(s);
-    return step_core(ws, true, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s);
+    char* base;
+    FMS_CHECK(ws.alloc(&base, need.used()));
+    Arena a(base, need.used());
+    return step_core(a, true, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s);
 }
 
 // Device address of this device's copy of `scratch`, looked up once per
