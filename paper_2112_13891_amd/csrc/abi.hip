@@ -629,6 +629,39 @@ void fill_batch(Batch& b, int n, int d, int B, const StepShape& sh, const ms_par
     b.ctl = ctl;
 }
 
+// Whether the update runs with a workgroup per seed, all iterations in one
+// launch (k_seed.hip): d <= 4, every batch run to convergence (a batch that
+// stops on its converged count needs its seeds in step).  Measured on
+// 200,000 x 3-D points (us per update): see k_seed.hip.
+bool seed_form(const ms_params* p, int d, bool in_step) {
+    return !p->plain && d <= 4 && !in_step;
+}
+
+// Arguments of that form from the batch; the tiles are the packed (n small,
+// no geometry) or the Morton-ordered rows.
+SeedArgs seed_args(const Batch& b, const ms_params* p, const float* tiles, const float* geom, int max_iter) {
+    SeedArgs a;
+    a.T = tiles;
+    a.tiles = (b.n + 63) / 64;
+    a.geom = geom;
+    a.geom_ld = (b.n + 63) / 64;
+    a.n = b.n;
+    a.S = b.S;
+    a.m = b.n_seeds;
+    a.status = b.status;
+    a.iters = b.iters;
+    a.shift2 = b.shift2;
+    a.ctl = b.ctl;
+    a.count_exact = p->precision == MS_PREC_BF16_REFINE;
+    a.max_iter = max_iter;
+    a.h2 = b.h * b.h;
+    a.scale = b.scale;
+    a.inv_scale = b.inv_scale;
+    a.thr2 = b.thr2;
+    a.metric = b.metric;
+    return a;
+}
+
 int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int32_t max_modes,
              int32_t* k_out, int32_t* labels, ms_diag* diag, hipStream_t s) {
     const auto t_start = std::chrono::steady_clock::now();
@@ -673,8 +706,10 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
     const float rm = p->merge_radius * p->h, rc = p->cover_radius * p->h;
     const float r2m = rm * rm, r2c = rc * rc;
 
+    const bool seedf = seed_form(p, d, p->gamma < 1.0f);
+    const size_t rows = seedf ? (size_t)(n + 63) / 64 * 64 : (size_t)n;   // whole tiles
     float* Xp;
-    FMS_CHECK(cache_get(C, budget, SL_XP, (size_t)n * DP, &Xp));
+    FMS_CHECK(cache_get(C, budget, SL_XP, rows * DP, &Xp));
     FMS_HIP(launch_pack_points(X, n, d, DP, scale, Xp, s));
     const bool bf16 = bf16_form(p, d);
     // FP32 on enough points: spatially ordered points and block culling
@@ -684,13 +719,16 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
     const bool sorted = bf16 || cull;
     SortedPoints sp;
     if (sorted) {
-        FMS_CHECK(cache_get(C, budget, SL_XS, (size_t)n * DP, &sp.Xs));
+        FMS_CHECK(cache_get(C, budget, SL_XS, rows * DP, &sp.Xs));
         FMS_CHECK(cache_get(C, budget, SL_PERM, n, &sp.perm));
-        FMS_CHECK(cache_get(C, budget, SL_GEOM, (size_t)((n + 255) / 256) * geom_stride(base.D), &sp.geom));
+        FMS_CHECK(cache_get(C, budget, SL_GEOM, seedf ? rows / 64 * (base.D + 1)
+                                                      : (size_t)((n + 255) / 256) * geom_stride(base.D), &sp.geom));
         FMS_CHECK(cache_get(C, budget, SL_SORTWS, sort_workspace_bytes(n), (char**)&sp.sws));
-        FMS_HIP(launch_spatial_sort(Xp, n, DP, base.D, sp.Xs, sp.perm, sp.geom, sp.sws, s));
+        FMS_HIP(launch_spatial_sort(Xp, n, DP, base.D, sp.Xs, sp.perm, seedf ? nullptr : sp.geom, sp.sws, s));
     }
-    if (bf16) {
+    float* tiles = sorted ? sp.Xs : Xp;
+    if (seedf) FMS_HIP(launch_tile_ball(tiles, n, base.D, sorted ? sp.geom : nullptr, (int)(rows / 64), s));
+    if (bf16 && !seedf) {
         FMS_CHECK(cache_get(C, budget, SL_FEAT, base.D <= 4 ? bf16_feature_bytes(n)
                                                            : bf16_wide_feature_bytes(n, base.D, p->kernel),
                             &sp.feat));
@@ -752,7 +790,7 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
                                   : (cull ? step_shape_cull(d, B, n) : step_shape_for(d, B));
         Batch b;
         fill_batch(b, n, d, B, sh, p, scale, Xp, nullptr, sorted ? &sp : nullptr);
-        const long long part_floats = step_part_floats(sh, B, b.grid);
+        const long long part_floats = seedf ? 1 : step_part_floats(sh, B, b.grid);
         const RbLayout L = rb_layout(B, DP);
         char* rbuf;
         FMS_CHECK(cache_get(C, budget, SL_RB, L.total, &rbuf));
@@ -780,7 +818,8 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
         }
         FMS_HIP(launch_round_init(X, d, DP, all ? nullptr : pool[cur], dpos, B, bids, removed,
                                   bstate, b, need, p->max_iter, s));
-        if (sorted) {
+        const SeedShape ssh = seed_shape(base.D, B);
+        if (sorted && (!seedf || ssh.R > 1)) {
             // seeds that are close in space share waves (refine work, culled blocks)
             if (all)
                 FMS_HIP(hipMemcpyAsync(b.act[0], sp.perm, (size_t)B * 4, hipMemcpyDeviceToDevice, s));
@@ -789,7 +828,13 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
         }
 
         FMS_HIP(hipEventRecord(ev[2], s));
-        FMS_CHECK(iterate_batch(b, p->max_iter, s, mirror));
+        if (seedf) {
+            SeedArgs a = seed_args(b, p, tiles, sorted ? sp.geom : nullptr, p->max_iter);
+            if (sorted && ssh.R > 1) a.order = b.act[0];
+            FMS_HIP(launch_seed_iterate(a, base.D, p->kernel, ssh, (B + ssh.R - 1) / ssh.R, s));
+        } else {
+            FMS_CHECK(iterate_batch(b, p->max_iter, s, mirror));
+        }
         FMS_HIP(hipEventRecord(ev[3], s));
         const auto t_merge = std::chrono::steady_clock::now();
 
@@ -1072,20 +1117,25 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
         FMS_RUN(launch_normalize_rows(X, n, d, Xn, nullptr, s));
         X = Xn;
     }
+    const bool seedf = seed_form(p, d, false);
+    const SeedShape ssh = seed_shape(sh.D, m);
+    const size_t rows = seedf ? (size_t)(n + 63) / 64 * 64 : (size_t)n;   // whole tiles
     float* Xp;
-    FMS_CHECK(ws.alloc(&Xp, (size_t)n * sh.DP));
+    FMS_CHECK(ws.alloc(&Xp, rows * sh.DP));
     FMS_RUN(launch_pack_points(X, n, d, sh.DP, scale, Xp, s));
     SortedPoints sp;
     if (sorted) {
         char* sws;
-        FMS_CHECK(ws.alloc(&sp.Xs, (size_t)n * sh.DP));
+        FMS_CHECK(ws.alloc(&sp.Xs, rows * sh.DP));
         FMS_CHECK(ws.alloc(&sp.perm, n));
-        FMS_CHECK(ws.alloc(&sp.geom, (size_t)((n + 255) / 256) * geom_stride(sh.D)));
+        FMS_CHECK(ws.alloc(&sp.geom, seedf ? rows / 64 * (sh.D + 1) : (size_t)((n + 255) / 256) * geom_stride(sh.D)));
         FMS_CHECK(ws.alloc(&sws, sort_workspace_bytes(n > m ? n : m)));
         sp.sws = sws;
-        FMS_RUN(launch_spatial_sort(Xp, n, sh.DP, sh.D, sp.Xs, sp.perm, sp.geom, sws, s));
+        FMS_RUN(launch_spatial_sort(Xp, n, sh.DP, sh.D, sp.Xs, sp.perm, seedf ? nullptr : sp.geom, sws, s));
     }
-    if (bf16) {
+    float* tiles = sorted ? sp.Xs : Xp;
+    if (seedf) FMS_RUN(launch_tile_ball(tiles, n, sh.D, sorted ? sp.geom : nullptr, (int)(rows / 64), s));
+    if (bf16 && !seedf) {
         FMS_CHECK(ws.alloc(&sp.feat, sh.D <= 4 ? bf16_feature_bytes(n)
                                                : bf16_wide_feature_bytes(n, sh.D, p->kernel)));
         if (sh.D <= 4) FMS_RUN(launch_bf16_features(sp.Xs, n, d, sp.geom, sp.feat, s));
@@ -1101,13 +1151,20 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
     FMS_CHECK(ws.alloc(&b.status, m));
     FMS_CHECK(ws.alloc(&b.iters, m));
     FMS_CHECK(ws.alloc(&b.shift2, m));
-    FMS_CHECK(ws.alloc(&b.part, (size_t)step_part_floats(sh, m, b.grid)));
+    FMS_CHECK(ws.alloc(&b.part, seedf ? 1 : (size_t)step_part_floats(sh, m, b.grid)));
     if (!run) return MS_OK;
     FMS_HIP(launch_ctl_reset(ctl, 0, INT_MAX, n_iter, s));
     FMS_HIP(launch_seed_init_from_array(seeds, converged, d, m, b, s));
-    if (sorted)   // seeds that are close in space share waves (refine work, culled blocks)
+    if (sorted && (!seedf || ssh.R > 1))   // seeds that are close in space share waves (refine work, culled blocks)
         FMS_HIP(launch_seed_order(b.S, sh.DP, sh.D, m, scale, b.status, sp.sws, b.act[0], Xp, n, s));
-    for (int t = 0; t < n_iter; ++t) FMS_HIP(launch_iteration(b, t, s));
+    if (seedf) {
+        SeedArgs a = seed_args(b, p, tiles, sorted ? sp.geom : nullptr, n_iter);
+        a.ctl = nullptr;
+        if (sorted && ssh.R > 1) a.order = b.act[0];
+        FMS_HIP(launch_seed_iterate(a, sh.D, p->kernel, ssh, (m + ssh.R - 1) / ssh.R, s));
+    } else {
+        for (int t = 0; t < n_iter; ++t) FMS_HIP(launch_iteration(b, t, s));
+    }
     FMS_HIP(launch_seed_export(b, m, seeds, converged, iters, shift2, s));
     return MS_OK;
 #undef FMS_RUN

@@ -166,6 +166,45 @@ struct BatchedArgs {
     const int32_t* boff;      // BF16 form: 256-point blocks before cloud c (ncl + 1), else NULL
 };
 
+// ---- launchers (k_seed.hip): a workgroup per seed, all iterations in one launch --
+// Coordinate of the rows that fill up a tile: its square is still finite or
+// overflows to +inf, so its Gaussian weight is +0 and its products are 0.
+constexpr float kPadCoord = 1e19f;
+struct SeedArgs {
+    const float* T = nullptr;      // 64-point tiles (packed units), see k_seed.hip
+    int tiles = 0;
+    const int32_t* ntiles = nullptr;   // device count of tiles, or NULL: `tiles`
+    const float* geom = nullptr;   // tile balls: centre k of tile t at [k * geom_ld + t], the radius
+    int geom_ld = 0;               // at [D * geom_ld + t]; NULL: every tile is evaluated
+    int n = 0;                     // points (pair count only)
+    float* S = nullptr;            // seed positions (original units, stride DP)
+    const int32_t* order = nullptr;   // seeds in the order they are grouped, or NULL
+    int m = 0;
+    uint8_t* status = nullptr;
+    int32_t* iters = nullptr;
+    float* shift2 = nullptr;
+    Ctl* ctl = nullptr;            // counts (iterations, pairs), or NULL
+    int count_exact = 0;           // also count the evaluated pairs
+    int max_iter = 1;
+    float h2 = 0.0f, scale = 1.0f, inv_scale = 1.0f, thr2 = 0.0f;
+    int metric = MS_METRIC_EUCLIDEAN;
+    // many clouds: workgroup, seed and tile ranges per cloud (ncl + 1 entries each)
+    int ncl = 0;
+    const int32_t* wg_off = nullptr;
+    const int32_t* seg = nullptr;
+    const int32_t* tile_off = nullptr;
+    float slack = 0.0f, flat_reach = 0.0f;   // set by the launcher
+};
+struct SeedShape {
+    int R;    // seeds per workgroup
+    int nw;   // waves per workgroup
+};
+SeedShape seed_shape(int D, long long m);
+hipError_t launch_seed_iterate(SeedArgs a, int D, int kernel, const SeedShape& sh, int wgs, hipStream_t s);
+// D <= 4: fills the tail of the last tile of n rows of 4 floats and writes the
+// tile balls (geom NULL: the tail only).
+hipError_t launch_tile_ball(float* T, int n, int D, float* geom, int ld, hipStream_t s);
+
 // ---- launchers (k_step_bf16.hip) -----------------------------------------
 StepShape step_shape_bf16(int d, int B);
 bool bf16_supported(int d);

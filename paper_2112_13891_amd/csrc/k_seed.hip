@@ -1,0 +1,579 @@
+// k_seed.hip -- the FP32 update with a workgroup per seed (or per few seeds)
+// that runs all of the seeds' iterations in one launch (gfx950).
+//
+// The update of Section II-B has no exchange between seeds: a seed's next
+// position needs the points and its own position only.  So a workgroup owns R
+// seeds, keeps them in registers, and iterates until they converge (Algorithms
+// 1-2, "while not converge") or max_iter updates are done.  Nothing leaves the
+// workgroup between two updates: no partial sums in memory, no reduction or
+// compaction launch, no host poll.  Only a batch that stops early on its
+// converged count (Section II-C with gamma < 1) needs all seeds in step; it
+// takes the forms that launch per iteration.
+//
+// Lanes hold POINTS and the seed is wave-uniform (scalar registers), the
+// reverse of the seed-tile forms.  Points come as tiles of 64 (one per lane),
+// coordinates in float4 groups: tile t, group g, lane l at
+// ((t * D/4 + g) * 64 + l) * 4, so that every load is 1 KB contiguous.  With a
+// ball (centre, radius) per tile, each wave tests 64 tiles at once (lane =
+// tile) and walks the set bits of the ballot: a seed evaluates only the tiles
+// within its own reach, where a 64-seed tile evaluates the union of 64
+// seeds' tiles.  On 200,000 x 3-D points that is about 8 % of the pairs
+// instead of 35 %.  The near tiles are neighbours in the spatial order, so the
+// workgroup lists them in LDS first and its waves take the entries in turn.
+//
+// What a tile may be left out for (the Gaussian): every pair of it is beyond
+// the distance where the FP32 weight is exactly zero (q >= 150; the test uses
+// 160), or has a weight below 2^-64 of the seed's weight sum W.  At most n
+// such terms are dropped, in total below n 2^-64 W <= 2^-33 W, where an FP32
+// sum rounds at 2^-25 W.  W is bounded from below without any sum: a tile of
+// radius r at distance c holds a point within c + r, so W >= 2^-(c + r)^2
+// for the nearest tile; after the first update the W of the previous one
+// serves (a mean-shift step never lowers the density).  The flat window
+// leaves out the tiles wholly outside it.
+//
+// With the list made beforehand the tiles' loads run ahead of the arithmetic
+// with no test between them.  The waves test consecutive groups of 64 tiles
+// (contiguous loads; with the tiles dealt to the waves one by one a pass over
+// 3,125 balls took 7 us instead of 2).  The list is kept while the seeds stay within kSlack packed units of where
+// it was made, the reach being that much longer; late iterations move far
+// less and skip the geometry.
+//
+// The lane sums are added by a fixed butterfly, the waves' sums in wave order:
+// no floating-point atomics, the same result on every run.
+
+#include <algorithm>
+
+#include "step_common.h"
+
+namespace fms {
+
+namespace {
+
+constexpr float kSeedZero = 160.0f;      // exp2(-q) == +0 in FP32 for q >= 150
+constexpr float kSeedNegligible = 64.0f; // weights below 2^-64 of the sum change no FP32 sum
+constexpr float kSeedFlatMargin = 1.001f;
+constexpr float kSlack = 0.25f;          // packed units
+constexpr int kSegGroups = 96;           // groups of 64 tiles listed at once (24 KB: six workgroups a CU)
+constexpr int kSeedMaxWaves = 16;
+// wide rows need the registers that 16 waves in one workgroup would not have
+constexpr int seed_max_waves(int D) { return D <= 4 ? kSeedMaxWaves : 8; }
+
+// Sum over the 64 lanes, in lane 63, by DPP additions: prefix sums within the
+// rows of 16 lanes, then row 0 into row 1 and row 2 into row 3, then the lower
+// half into the upper one.  A fixed order, no LDS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
+}
+__device__ __forceinline__ float wave_add63(float v) {
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);   // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);   // row_shr:8
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+template <int D, int R, int KERN>
+__global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(SeedArgs a) {
+    constexpr int DP = D <= 4 ? 4 : D;
+    constexpr int G4 = DP / 4;
+    constexpr int V = D + 1;
+    static_assert(R * DP <= 64, "one wave holds the coordinates of the seeds");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int NW = blockDim.x >> 6;
+
+    // this workgroup's seeds (a cloud's own in the batched form) and tiles
+    int j0 = blockIdx.x * R, jend = a.m, t0 = 0, t1 = a.tiles;
+    if (a.ntiles) t1 = *a.ntiles;
+    if (a.wg_off) {
+        const int c = upper_cloud(a.wg_off, a.ncl, blockIdx.x);
+        j0 = a.seg[c] + ((int)blockIdx.x - a.wg_off[c]) * R;
+        jend = a.seg[c + 1];
+        t0 = a.tile_off[c];
+        t1 = a.tile_off[c + 1];
+    }
+    t0 = __builtin_amdgcn_readfirstlane(t0);
+    t1 = __builtin_amdgcn_readfirstlane(t1);
+
+    __shared__ float red[2][kSeedMaxWaves][R * V];
+    __shared__ float wub[kSeedMaxWaves];
+    __shared__ unsigned wcnt[kSeedMaxWaves];
+    __shared__ unsigned list[kSegGroups * 64];
+    __shared__ unsigned long long near_mask[kSegGroups];
+    __shared__ unsigned char near_who[R > 1 ? kSegGroups * 64 : 1];
+
+    // lane (r, k) holds coordinate k of seed r, in every wave
+    const int r_of = lane / DP, k_of = lane % DP;
+    int id[R];
+    unsigned act = 0;   // bit r: seed r still iterates
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int slot = j0 + r;
+        id[r] = -1;
+        if (slot < jend) {
+            id[r] = __builtin_amdgcn_readfirstlane(a.order ? a.order[slot] : slot);
+            if (a.status[id[r]] == ST_ACTIVE) act |= 1u << r;
+        }
+    }
+    act = __builtin_amdgcn_readfirstlane(act);
+    if (!act) return;
+    float sv = 0.0f;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r_of == r && id[r] >= 0) sv = a.S[(long long)id[r] * DP + k_of];
+
+    // Tile t0 + g * 64 + l is lane l of group g.  A segment is as many groups
+    // as fit the list; with one segment the list may be kept from one update
+    // to the next.
+    const int ntile = t1 - t0;
+    const int groups = (ntile + 63) / 64;
+    const bool keep = groups <= kSegGroups;
+    const float4* __restrict__ T4 = reinterpret_cast<const float4*>(a.T);
+
+    float reach[R], wprev[R], last_sh2[R];
+    int nit[R];
+    int result[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        reach[r] = 0.0f;
+        wprev[r] = -1.0f;
+        last_sh2[r] = __builtin_nanf("");
+        nit[r] = 0;
+        result[r] = ST_ACTIVE;
+    }
+    float sref = 0.0f;       // where the masks were made
+    bool have_list = false;
+    int len = 0;             // listed tiles
+    unsigned evaluated = 0;  // tiles this wave evaluated, over seeds and iterations
+    int executed = 0;        // updates run, over the seeds
+
+    int it = 0;
+    for (; it < a.max_iter && act; ++it) {
+        const float svs = sv * a.scale;
+        float s[R][D];   // wave-uniform: scalar registers
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int k = 0; k < D; ++k) s[r][k] = lane_value(svs, r * DP + k);
+
+        auto tile_of = [&](int g) { return t0 + g * 64 + lane; };
+
+        // f(g, r, inside, distance of seed r from the ball's centre, radius)
+        // for the lane's tile of this wave's groups g0 + wave, + NW, ... < g1,
+        // several groups' loads at once
+        auto balls = [&](int g0, int g1, auto&& f) {
+            constexpr int B = D <= 4 ? 4 : (D <= 8 ? 2 : 1);
+            for (int g = g0 + wave; g < g1; g += B * NW) {
+                float c[B][D], rad[B];
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    const int t = tile_of(g + i * NW);
+                    const int tc = t < t1 ? t : t0;
+#pragma unroll
+                    for (int k = 0; k < D; ++k) c[i][k] = a.geom[k * a.geom_ld + tc];
+                    rad[i] = a.geom[D * a.geom_ld + tc];
+                }
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    if (g + i * NW < g1) {
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            float d2 = 0.0f;
+#pragma unroll
+                            for (int k = 0; k < D; ++k) {
+                                const float u = s[r][k] - c[i][k];
+                                d2 = fmaf(u, u, d2);
+                            }
+                            f(g + i * NW, r, tile_of(g + i * NW) < t1, __builtin_amdgcn_sqrtf(d2), rad[i]);
+                        }
+                    }
+                }
+            }
+        };
+
+        bool remake = a.geom != nullptr;
+        if (remake && have_list) {
+            float d2 = sv - sref;
+            d2 = d2 * d2;
+#pragma unroll
+            for (int off = DP / 2; off >= 1; off >>= 1) d2 += __shfl_xor(d2, off);
+            const float moved = sqrtf(d2) * a.scale;
+            const bool far = !(moved <= a.slack) && ((act >> r_of) & 1u);
+            remake = __ballot(far) != 0;
+        }
+        if (remake) {
+            sref = sv;
+            if (KERN == MS_KERNEL_GAUSSIAN && it == 0) {
+                // W >= 2^-(c + r)^2 for the nearest tile
+                float ub[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) ub[r] = 1e18f;
+                balls(0, groups, [&](int, int r, bool in, float dist, float rad) {
+                    if (in) ub[r] = fminf(ub[r], dist + rad);   // a NaN never lowers it
+                });
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+#pragma unroll
+                    for (int off = 32; off >= 1; off >>= 1) ub[r] = fminf(ub[r], __shfl_xor(ub[r], off));
+                    __syncthreads();
+                    if (lane == 0) wub[wave] = ub[r];
+                    __syncthreads();
+                    float u = wub[0];
+                    for (int w = 1; w < NW; ++w) u = fminf(u, wub[w]);
+                    const float q = fminf(kSeedZero, kSeedNegligible + 1.001f * u * u);
+                    reach[r] = sqrtf(q);
+                }
+            } else if (KERN == MS_KERNEL_GAUSSIAN) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    // -log2 W, at least: 1 of margin
+                    const float q = kSeedNegligible + 1.0f - __builtin_amdgcn_logf(wprev[r]);
+                    reach[r] = sqrtf(fminf(kSeedZero, fmaxf(q, 1.0f)));
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) reach[r] = a.flat_reach;
+            }
+            have_list = keep;
+        }
+
+        float acc[R][V];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int k = 0; k < V; ++k) acc[r][k] = 0.0f;
+
+        for (int g0 = 0; g0 < groups; g0 += kSegGroups) {
+            const int g1 = min(groups, g0 + kSegGroups);
+            if (remake) {
+                unsigned who = 0;   // seeds that reach the lane's tile
+                __syncthreads();   // the last list and its masks are no longer read
+                balls(g0, g1, [&](int g, int r, bool in, float dist, float rad) {
+                    // a NaN (a ball without a finite centre) stays near
+                    const bool near = in && !(dist - rad > reach[r] + (keep ? a.slack : 0.0f));
+                    who = (r == 0 ? 0u : who) | ((near && ((act >> r) & 1u)) ? 1u << r : 0u);
+                    if (r == R - 1) {
+                        const unsigned long long mk = __ballot(who != 0);
+                        if (lane == 0) near_mask[g - g0] = mk;
+                        if (R > 1) near_who[(g - g0) * 64 + lane] = (unsigned char)who;
+                    }
+                });
+                __syncthreads();
+                // entries before each group: a scan of the groups' counts
+                int before[(kSegGroups + 63) / 64];
+                len = 0;
+#pragma unroll
+                for (int q = 0; q < (kSegGroups + 63) / 64; ++q) {
+                    const int gi = q * 64 + lane;
+                    const int cnt = gi < g1 - g0 ? __popcll(near_mask[gi]) : 0;
+                    int x = cnt;
+#pragma unroll
+                    for (int off = 1; off < 64; off <<= 1) {
+                        const int y = __shfl_up(x, off);
+                        if (lane >= off) x += y;
+                    }
+                    before[q] = len + x - cnt;
+                    len += __builtin_amdgcn_readlane(x, 63);
+                }
+                for (int gi = wave; gi < g1 - g0; gi += NW) {
+                    const unsigned long long mk = (unsigned long long)wave_uniform((long long)near_mask[gi]);
+                    if (!mk) continue;
+                    const int at = __builtin_amdgcn_readlane(gi < 64 ? before[0] : before[1], gi & 63);
+                    if ((mk >> lane) & 1ull)
+                        list[at + __popcll(mk & ((1ull << lane) - 1ull))] =
+                            (unsigned)tile_of(g0 + gi) | (R > 1 ? (unsigned)near_who[gi * 64 + lane] << 28 : 0u);
+                }
+                __syncthreads();
+            } else if (!a.geom) {
+                len = min((g1 - g0) * 64, ntile - g0 * 64);
+            }
+            // this wave's entries: wave, wave + NW, ...
+            const int mine_n = len > wave ? (len - wave + NW - 1) / NW : 0;
+            if (mine_n == 0) continue;
+            evaluated += mine_n;
+            // walk the tiles in batches of U, the next batch's loads in flight
+            // while one computes; lane i of `ids` holds entry i of the current 64
+            constexpr int U = D <= 4 ? 4 : 1;
+            float4 xa[U][G4], xb[U][G4];
+            unsigned wa[U], wb[U];
+            unsigned ids = 0;
+            int next = 0;
+            auto fetch = [&](float4 (&x)[U][G4], unsigned (&who)[U]) {
+                const int cnt = min(U, mine_n - next);
+                if ((next & 63) == 0) {
+                    const int e = (next + lane < mine_n ? next + lane : 0) * NW + wave;
+                    ids = a.geom ? list[e] : (unsigned)(t0 + g0 * 64 + e);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    // past the end: the last entry again, not used
+                    const int e = (next + u < mine_n ? next + u : mine_n - 1) & 63;
+                    const unsigned v = (unsigned)__builtin_amdgcn_readlane((int)ids, e);
+                    who[u] = (R > 1 && a.geom) ? v >> 28 : (1u << R) - 1u;
+                    const long long t = (R > 1 && a.geom) ? (v & 0x0fffffffu) : v;
+#pragma unroll
+                    for (int q = 0; q < G4; ++q) x[u][q] = T4[(t * G4 + q) * 64 + lane];
+                }
+                next += U;
+                return cnt;
+            };
+            auto compute = [&](const float4 (&xv)[U][G4], const unsigned (&who)[U], int cnt) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (u >= cnt) break;
+                    float x[DP];
+#pragma unroll
+                    for (int q = 0; q < G4; ++q) {
+                        x[4 * q] = xv[u][q].x;
+                        x[4 * q + 1] = xv[u][q].y;
+                        x[4 * q + 2] = xv[u][q].z;
+                        x[4 * q + 3] = xv[u][q].w;
+                    }
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        if (R > 1 && !((who[u] & act) >> r & 1u)) continue;
+                        float dx[D];
+                        float q = 0.0f;
+#pragma unroll
+                        for (int k = 0; k < D; ++k) {
+                            dx[k] = x[k] - s[r][k];
+                            q = fmaf(dx[k], dx[k], q);
+                        }
+                        float w;
+                        if (KERN == MS_KERNEL_GAUSSIAN)
+                            w = __builtin_amdgcn_exp2f(-q);
+                        else
+                            w = (q <= a.h2) ? 1.0f : 0.0f;
+                        acc[r][D] += w;
+#pragma unroll
+                        for (int k = 0; k < D; ++k) acc[r][k] = fmaf(w, dx[k], acc[r][k]);
+                    }
+                }
+            };
+            int na = fetch(xa, wa);
+            for (;;) {
+                int nb = 0;
+                if (next < mine_n) nb = fetch(xb, wb);
+                compute(xa, wa, na);
+                if (!nb) break;
+                na = 0;
+                if (next < mine_n) na = fetch(xa, wa);
+                compute(xb, wb, nb);
+                if (!na) break;
+            }
+        }
+
+        // lanes, then waves in order; every wave makes the same update
+        const int par = it & 1;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                const float v = wave_add63(acc[r][k]);
+                if (lane == 63) red[par][wave][r * V + k] = v;
+            }
+        __syncthreads();
+        float v = 0.0f, W = 0.0f;
+        if (r_of < R) {
+            for (int w = 0; w < NW; ++w) {
+                if (k_of < D) v += red[par][w][r_of * V + k_of];
+                W += red[par][w][r_of * V + D];
+            }
+        }
+        const bool okW = W > 0.0f && isfinite(W);
+        const float inv = a.inv_scale / W;
+        float ns, dk;
+        if (a.metric == MS_METRIC_COSINE) {
+            const float u = sv + v * inv;
+            float nn = u * u;
+#pragma unroll
+            for (int off = DP / 2; off >= 1; off >>= 1) nn += __shfl_xor(nn, off);
+            const float rn = 1.0f / sqrtf(nn);
+            ns = u * rn;
+            dk = ns - sv;
+            if (!(nn > 0.0f) || !isfinite(rn)) dk = __builtin_nanf("");
+        } else {
+            dk = v * inv;
+            ns = sv + dk;
+        }
+        float sh2 = dk * dk;
+#pragma unroll
+        for (int off = DP / 2; off >= 1; off >>= 1) sh2 += __shfl_xor(sh2, off);
+        // a non-finite coordinate makes the sum of squares non-finite; a sum
+        // that only overflows is told apart by the coordinates themselves
+        const unsigned long long bad = __ballot(r_of < R && k_of < D && !(isfinite(dk) && isfinite(ns)));
+        bool mine = false;   // this lane's seed takes its new position
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (!((act >> r) & 1u)) continue;
+            const float Wr = lane_value(W, r * DP);
+            const float shr = lane_value(sh2, r * DP);
+            ++executed;
+            if (!(Wr > 0.0f) || !isfinite(Wr)) {
+                result[r] = ST_FAILED;
+                act &= ~(1u << r);
+                continue;
+            }
+            mine = mine || r_of == r;
+            ++nit[r];
+            last_sh2[r] = shr;
+            wprev[r] = Wr;
+            const unsigned long long lanes = ((DP == 64 ? 0ull : (1ull << DP)) - 1ull) << (r * DP);
+            if (bad & lanes) {
+                result[r] = ST_FAILED;
+                act &= ~(1u << r);
+            } else if (shr < a.thr2) {
+                result[r] = ST_CONVERGED;
+                act &= ~(1u << r);
+                if (a.ctl && threadIdx.x == 0) atomicAdd(&a.ctl->conv_it[it], 1);
+            }
+        }
+        if (mine && okW) sv = ns;
+    }
+
+    // the output pointers are read from the argument block here, so that they
+    // hold no scalar registers during the iterations
+    auto* ka = (const __attribute__((address_space(4))) SeedArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka));
+    if (wave == 0) {
+        float* S = ka->S;
+        int32_t* iters = ka->iters;
+        float* shift2 = ka->shift2;
+        uint8_t* status = ka->status;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (id[r] < 0) continue;
+            if (r_of == r && nit[r] > 0) S[(long long)id[r] * DP + k_of] = sv;
+            if (lane == 0) {
+                if (nit[r] > 0) {
+                    iters[id[r]] += nit[r];
+                    shift2[id[r]] = last_sh2[r];
+                }
+                if (result[r] != ST_ACTIVE) status[id[r]] = (uint8_t)result[r];
+            }
+        }
+    }
+    Ctl* ctl = ka->ctl;
+    if (ctl) {
+        if (lane == 0) wcnt[wave] = evaluated;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned long long e = 0;
+            for (int w = 0; w < NW; ++w) e += wcnt[w];
+            atomicMax(&ctl->iters_run, it);
+            atomicAdd((unsigned long long*)&ctl->pairs, (unsigned long long)executed * (unsigned long long)ka->n);
+            if (ka->count_exact)
+                atomicAdd((unsigned long long*)&ctl->refined[(blockIdx.x % kRefinedSlots) * kRefinedStride],
+                          e * 64ull);
+        }
+    }
+}
+
+// Points of 64-point tiles, D <= 4: ball of each tile (midpoint of the bounding
+// box, largest distance from it, rounded up) in structure-of-arrays form, and
+// the rows past the last point filled so that they weigh nothing.  One wave
+// per tile.  A tile with a coordinate that is not finite gets a NaN centre:
+// it is never left out.
+template <int D>
+__global__ __launch_bounds__(256) void tile_ball_kernel(float* T, int n, int tiles, float* geom, int ld) {
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (t >= tiles) return;
+    const int i = t * 64 + lane;
+    float4* row = reinterpret_cast<float4*>(T) + i;
+    const bool live = i < n;
+    if (!live) *row = make_float4(kPadCoord, kPadCoord, kPadCoord, kPadCoord);
+    if (!geom) return;
+    const float4 p = *row;
+    const float x[4] = {p.x, p.y, p.z, p.w};
+    float c[D], r2 = 0.0f;
+    bool fin = true;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        float lo = live ? x[k] : __builtin_inff(), hi = live ? x[k] : -__builtin_inff();
+        fin = fin && (!live || isfinite(x[k]));
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, off));
+            hi = fmaxf(hi, __shfl_xor(hi, off));
+        }
+        c[k] = 0.5f * (lo + hi);
+        const float u = live ? x[k] - c[k] : 0.0f;
+        r2 = fmaf(u, u, r2);
+    }
+    const bool allfin = __ballot(!fin) == 0;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) r2 = fmaxf(r2, __shfl_xor(r2, off));
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) geom[(long long)k * ld + t] = allfin ? c[k] : __builtin_nanf("");
+        geom[(long long)D * ld + t] = sqrtf(r2) * 1.0001f + 1e-30f;
+    }
+}
+
+template <int D, int R>
+hipError_t launch_seed_t(const SeedArgs& a, int kernel, int wgs, int nw, hipStream_t s) {
+    if (kernel == MS_KERNEL_GAUSSIAN)
+        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN>), dim3(wgs), dim3(64 * nw), 0, s, a);
+    else
+        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT>), dim3(wgs), dim3(64 * nw), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_tile_ball(float* T, int n, int D, float* geom, int ld, hipStream_t s) {
+    const int tiles = (n + 63) / 64;
+    const dim3 g((tiles + 3) / 4);
+    switch (D) {
+        case 1: hipLaunchKernelGGL((tile_ball_kernel<1>), g, dim3(256), 0, s, T, n, tiles, geom, ld); break;
+        case 2: hipLaunchKernelGGL((tile_ball_kernel<2>), g, dim3(256), 0, s, T, n, tiles, geom, ld); break;
+        case 3: hipLaunchKernelGGL((tile_ball_kernel<3>), g, dim3(256), 0, s, T, n, tiles, geom, ld); break;
+        case 4: hipLaunchKernelGGL((tile_ball_kernel<4>), g, dim3(256), 0, s, T, n, tiles, geom, ld); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// Seeds per workgroup and waves per workgroup for m seeds.  Few seeds: one per
+// workgroup, split over as many waves as fill the 1,024 SIMDs about four deep.
+// Many: four neighbours per workgroup share the loaded tiles.  Measured, 200,000
+// x 3-D points, all updates of a batch (7 or so) in one launch, us:
+//   m       1 seed: 4 / 8 / 16 waves     4 seeds: 1 / 2 / 4 waves
+//   128       46 / 33 / 33
+//   512       47 / 40 / 61
+//   1,024     58 / 69 / 109
+//   2,048     96 / 124 / 206
+//   8,192    315 / 424 / 752              555 / 316 / 209
+//   32,768                               1449 / 898 / 643
+// (one update launched as a step over 64-seed tiles and a finalize: 31 us at
+// 512 seeds, 220 us for a batch; 1.54 ms at 200,000 seeds against 1.28 here).
+SeedShape seed_shape(int D, long long m) {
+    (void)D;
+    SeedShape sh;
+    sh.R = m > 2048 ? 4 : 1;
+    sh.nw = m <= 512 ? 8 : 4;
+    return sh;
+}
+
+hipError_t launch_seed_iterate(SeedArgs a, int D, int kernel, const SeedShape& sh, int wgs, hipStream_t s) {
+    if (sh.nw < 1 || sh.nw > kSeedMaxWaves) return hipErrorInvalidValue;
+    a.slack = kernel == MS_KERNEL_GAUSSIAN ? kSlack : 0.25f * sqrtf(a.h2) * a.scale;
+    a.flat_reach = sqrtf(a.h2 * kSeedFlatMargin);
+    if (wgs < 1) return hipSuccess;
+#define FMS_CASE(DD, RR) \
+    if (D == DD && sh.R == RR) return launch_seed_t<DD, RR>(a, kernel, wgs, sh.nw, s);
+    FMS_CASE(1, 1) FMS_CASE(2, 1) FMS_CASE(3, 1) FMS_CASE(4, 1)
+    FMS_CASE(1, 4) FMS_CASE(2, 4) FMS_CASE(3, 4) FMS_CASE(4, 4)
+#undef FMS_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace fms

@@ -847,8 +847,9 @@ hipError_t launch_spatial_sort(const float* Xp, int n, int DP, int D, float* Xs,
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)(((long long)n * DP + 255) / 256)), dim3(256),
                        0, s, Xp, DP, D, perm, n, shift, Xs);
-    hipLaunchKernelGGL(block_geom_kernel, dim3((n + 255) / 256), dim3(256), 0, s, Xs, n, DP, D,
-                       geom_stride(D), geom);
+    if (geom)
+        hipLaunchKernelGGL(block_geom_kernel, dim3((n + 255) / 256), dim3(256), 0, s, Xs, n, DP, D,
+                           geom_stride(D), geom);
     return hipGetLastError();
 }
 

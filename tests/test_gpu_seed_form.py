@@ -1,0 +1,86 @@
+"""GPU parity of the seed-per-workgroup form (d <= 4) against the FP64 oracle at
+the edges of its tiles, lists and groups: point counts around a 64-point tile,
+around the 16,384 points from which the points are ordered, and past the 6,144
+tiles that one list holds; one seed per workgroup and four; a seed far from
+every point, whose nearest weights are far below those of the other seeds."""
+import numpy as np
+import pytest
+
+from parity import ragged_check
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2112_13891_amd import api  # noqa: E402
+
+DEV = "cuda:0"
+
+
+def _gpu(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def blobs(seed, n, d, k=12, box=60.0):
+    rng = np.random.default_rng(seed)
+    C = rng.uniform(0.0, box, (k, d))
+    return np.ascontiguousarray(C[rng.integers(0, k, n)] + rng.standard_normal((n, d)), dtype=np.float32)
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (63, 5), (64, 64), (65, 65), (3000, 2048), (3000, 2049), (16384, 513),
+                                 (16447, 2051), (393217, 9), (400001, 2050)])
+@pytest.mark.parametrize("d", [1, 3, 4])
+@pytest.mark.parametrize("kernel", ["gaussian", "flat"])
+def test_seed_form_edges(orc, n, m, d, kernel):
+    if n * m > 10 ** 8 and (d != 3 or kernel != "gaussian"):
+        pytest.skip("one large shape is enough for the oracle")
+    X = blobs(n + d, n, d)
+    S0 = X[np.random.default_rng(m).choice(n, m, replace=False)]
+    check = np.arange(m) if n * m <= 10 ** 8 else np.array([0, 1, 2, 3, 1024, 2047, 2048, 2049])
+    S, conv, it, sh = api.step(_gpu(X), _gpu(S0), 1.5, kernel=kernel, n_iter=2)
+    torch.cuda.synchronize()
+    ref, ost, oit, osh = orc.step(X, S0[check].astype(np.float64), 1.5, kernel, tol=1e-3, n_iter=2)
+    ragged_check(orc, X, S0[check], 1.5, kernel, 2, S.cpu().numpy()[check], it.cpu().numpy()[check],
+                 conv.cpu().numpy()[check], ref, oit, ost)
+
+
+@pytest.mark.parametrize("n", [500, 20000])
+def test_seed_form_far_seed(orc, n):
+    """Seeds 5, 9 and 13 h beyond the last point: W is about 2^-18, 2^-58 and
+    2^-122, and the nearest points alone decide the update.  The last one is
+    held to the plain FP32 form: next to its W the other weights fall below
+    FP32's smallest normal number, which every FP32 form drops."""
+    X = blobs(3, n, 2)
+    top = X[np.argmax(X[:, 0])].astype(np.float64)
+    S0 = np.stack([top + np.array([g * 1.5, 0.0]) for g in (5.0, 9.0, 13.0)]).astype(np.float32)
+    S, conv, it, sh = api.step(_gpu(X), _gpu(S0), 1.5, n_iter=1)
+    P, pconv, pit, psh = api.step(_gpu(X), _gpu(S0), 1.5, n_iter=1, plain=True)
+    torch.cuda.synchronize()
+    ref, ost, oit, osh = orc.step(X, S0.astype(np.float64), 1.5, "gaussian", tol=1e-3, n_iter=1)
+    assert np.array_equal(it.cpu().numpy(), oit)
+    # the exponent of a weight is q <= 130 with FP32 rounding: 1e-5 of it, on
+    # shifts of up to 13 h
+    err = np.abs(S.cpu().numpy() - ref)
+    assert err[:2].max() < 1e-4 * 1.5
+    assert (S - P).abs().max().item() < 1e-4 * 1.5
+
+
+def test_seed_form_repeats_bitwise():
+    X = _gpu(blobs(9, 50000, 3))
+    for m in (200, 3000):
+        a = api.step(X, X[:m].clone(), 1.5, n_iter=6)
+        b = api.step(X, X[:m].clone(), 1.5, n_iter=6)
+        assert all(torch.equal(u.nan_to_num(), v.nan_to_num()) if u.is_floating_point() else torch.equal(u, v)
+                   for u, v in zip(a, b))
+
+
+def test_seed_form_non_finite_point():
+    """A point that is not finite is seen by every seed, as without an order:
+    every seed fails."""
+    for n in (2000, 20000):
+        X = blobs(4, n, 3)
+        X[n // 2, 1] = np.inf
+        S, conv, it, sh = api.step(_gpu(X), _gpu(X[:50]), 1.5, n_iter=2)
+        torch.cuda.synchronize()
+        assert (conv.cpu().numpy() == 2).all()
