@@ -323,7 +323,9 @@ enum Slot {
     // ms_fit_batched's rounds and the batched steps they run
     SL_BCONV, SL_BITERS, SL_BS, SL_BSH2, SL_BNM, SL_BSTATE, SL_BSTEP_S, SL_BSTEP_ACT0, SL_BSTEP_ACT1, SL_BSTEP_STATUS,
     SL_BSTEP_ITERS, SL_BSTEP_SHIFT2, SL_BSTEP_CNT, SL_BSTEP_PLAN, SL_BSTEP_ITEMC, SL_BSTEP_SLOTC, SL_BSTEP_PART,
-    SL_COUNT
+    // the pivot runs of the points and the seeds' order over them
+    SL_RUNS0, SL_RUNS_END = SL_RUNS0 + 20, SL_RUNSEED0 = SL_RUNS_END, SL_RUNSEED_END = SL_RUNSEED0 + 8,
+    SL_COUNT = SL_RUNSEED_END
 };
 
 // Handed to the orphan list when the thread exits (freed by the next call on
@@ -629,12 +631,52 @@ void fill_batch(Batch& b, int n, int d, int B, const StepShape& sh, const ms_par
     b.ctl = ctl;
 }
 
-// Whether the update runs with a workgroup per seed, all iterations in one
-// launch (k_seed.hip): d <= 4, every batch run to convergence (a batch that
-// stops on its converged count needs its seeds in step).  Measured on
-// 200,000 x 3-D points (us per update): see k_seed.hip.
-bool seed_form(const ms_params* p, int d, bool in_step) {
-    return !p->plain && d <= 4 && !in_step;
+// How the update runs with a workgroup per seed, all iterations in one launch
+// (k_seed.hip), if it does.  d <= 4: over the packed or Morton-ordered rows.
+// 5 <= d <= 32: over pivot runs (k_runs.hip), or, where evaluating every pair
+// costs less than building them, over the rows as they are.  A batch that
+// stops on its converged count needs its seeds in step, and takes the forms
+// that launch per iteration, as `plain` does.
+//
+// Rows or runs: the runs take about 16 launches, 70 us for few points and 200
+// for 262,144 x 32, and a seed then reads the tiles around it alone; without
+// them every seed reads every row once an update, at about 20 TB/s from L2.
+// kDenseFloats is 50 us of that.
+enum SeedForm { SEED_NONE, SEED_ROWS, SEED_RUNS, SEED_DENSE };
+constexpr long long kDenseFloats = 1LL << 28;   // seeds x points x D x updates
+SeedForm seed_form(const ms_params* p, int n, int d, long long m, int updates, bool in_step) {
+    if (p->plain || in_step || d > 32) return SEED_NONE;
+    if (d <= 4) return SEED_ROWS;
+    const long long all = m * n;   // < 2^62
+    return all <= kDenseFloats / step_shape(d).D / std::max(1, std::min(updates, 8)) ? SEED_DENSE : SEED_RUNS;
+}
+
+// Units of the packed points per bandwidth, and the distance from which a
+// point counts as far from its nearest pivot: 8 packed units for the Gaussian
+// (about 9.4 h), the same multiple of h for the flat window.
+float run_far(const ms_params* p) {
+    return p->kernel == MS_KERNEL_GAUSSIAN ? 8.0f : 9.4f * p->h;
+}
+
+// Many seeds: grouped by their nearest pivot, so that neighbours share a
+// workgroup or at least an L2.
+bool seed_ordered(const SeedShape& sh, long long m) { return sh.R > 1 || m > 2048; }
+
+void seed_args_order(SeedArgs& a, const RunSeeds& q) {
+    a.order = q.order;
+    a.pnear = q.near;
+    a.pdist = q.dist;
+    a.ppair = q.ppair;
+}
+
+void seed_args_runs(SeedArgs& a, const RunIndex& r) {
+    a.T = r.tiles;
+    a.geom = r.pivots;
+    a.geom_ld = r.sz.ptot;
+    a.ncl = r.sz.ncl;
+    a.poff = r.poff;
+    a.run_bound = r.run_bound;
+    a.tile_start = r.tile_start;
 }
 
 // Arguments of that form from the batch; the tiles are the packed (n small,
@@ -706,18 +748,34 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
     const float rm = p->merge_radius * p->h, rc = p->cover_radius * p->h;
     const float r2m = rm * rm, r2c = rc * rc;
 
-    const bool seedf = seed_form(p, d, p->gamma < 1.0f);
+    const SeedForm form =
+        seed_form(p, n, d, all ? n : std::min<long long>(n, 4LL * p->n_initial), p->max_iter, p->gamma < 1.0f);
+    const bool seedf = form == SEED_ROWS;
     const size_t rows = seedf ? (size_t)(n + 63) / 64 * 64 : (size_t)n;   // whole tiles
-    float* Xp;
-    FMS_CHECK(cache_get(C, budget, SL_XP, rows * DP, &Xp));
-    FMS_HIP(launch_pack_points(X, n, d, DP, scale, Xp, s));
+    float* Xp = nullptr;
+    float* tiles = nullptr;
     const bool bf16 = bf16_form(p, d);
     // FP32 on enough points: spatially ordered points and block culling
     // (directions are at most 2 apart: nothing to cull when the reach is 2)
     const bool cull = !bf16 && !p->plain && cull_supported(d, n) &&
                       !(p->metric == MS_METRIC_COSINE && cull_reach(p->kernel, p->h) >= 2.0);
-    const bool sorted = bf16 || cull;
+    const bool wide_seed = form == SEED_RUNS || form == SEED_DENSE;
+    const bool sorted = (bf16 || cull) && !wide_seed;
     SortedPoints sp;
+    RunIndex ri;
+    if (form == SEED_RUNS) {
+        int slot = SL_RUNS0;
+        FMS_CHECK(run_index_alloc(ri, run_sizes_equal(1, n), d, false, [&](auto** out, size_t c) {
+            return cache_get(C, budget, (Slot)slot++, c, out);
+        }));
+        FMS_HIP(launch_run_index(ri, X, nullptr, n, scale, run_far(p), s));
+    } else if (form == SEED_DENSE) {
+        FMS_CHECK(cache_get(C, budget, SL_XP, (size_t)(n + 63) / 64 * 64 * DP, &tiles));
+        FMS_HIP(launch_pack_tiles(X, n, d, base.D, scale, tiles, s));
+    } else {
+        FMS_CHECK(cache_get(C, budget, SL_XP, rows * DP, &Xp));
+        FMS_HIP(launch_pack_points(X, n, d, DP, scale, Xp, s));
+    }
     if (sorted) {
         FMS_CHECK(cache_get(C, budget, SL_XS, rows * DP, &sp.Xs));
         FMS_CHECK(cache_get(C, budget, SL_PERM, n, &sp.perm));
@@ -726,9 +784,9 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
         FMS_CHECK(cache_get(C, budget, SL_SORTWS, sort_workspace_bytes(n), (char**)&sp.sws));
         FMS_HIP(launch_spatial_sort(Xp, n, DP, base.D, sp.Xs, sp.perm, seedf ? nullptr : sp.geom, sp.sws, s));
     }
-    float* tiles = sorted ? sp.Xs : Xp;
+    if (seedf) tiles = sorted ? sp.Xs : Xp;
     if (seedf) FMS_HIP(launch_tile_ball(tiles, n, base.D, sorted ? sp.geom : nullptr, (int)(rows / 64), s));
-    if (bf16 && !seedf) {
+    if (bf16 && !seedf && !wide_seed) {
         FMS_CHECK(cache_get(C, budget, SL_FEAT, base.D <= 4 ? bf16_feature_bytes(n)
                                                            : bf16_wide_feature_bytes(n, base.D, p->kernel),
                             &sp.feat));
@@ -790,7 +848,7 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
                                   : (cull ? step_shape_cull(d, B, n) : step_shape_for(d, B));
         Batch b;
         fill_batch(b, n, d, B, sh, p, scale, Xp, nullptr, sorted ? &sp : nullptr);
-        const long long part_floats = seedf ? 1 : step_part_floats(sh, B, b.grid);
+        const long long part_floats = form != SEED_NONE ? 1 : step_part_floats(sh, B, b.grid);
         const RbLayout L = rb_layout(B, DP);
         char* rbuf;
         FMS_CHECK(cache_get(C, budget, SL_RB, L.total, &rbuf));
@@ -828,9 +886,21 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
         }
 
         FMS_HIP(hipEventRecord(ev[2], s));
-        if (seedf) {
+        if (form != SEED_NONE) {
             SeedArgs a = seed_args(b, p, tiles, sorted ? sp.geom : nullptr, p->max_iter);
             if (sorted && ssh.R > 1) a.order = b.act[0];
+            if (form == SEED_RUNS) {
+                seed_args_runs(a, ri);
+                if (seed_ordered(ssh, B)) {
+                    RunSeeds rs;
+                    int slot = SL_RUNSEED0;
+                    FMS_CHECK(run_seeds_alloc(rs, ri, B, [&](auto** out, size_t c) {
+                        return cache_get(C, budget, (Slot)slot++, c, out);
+                    }));
+                    FMS_HIP(launch_run_seeds(ri, b.S, B, rs, s));
+                    seed_args_order(a, rs);
+                }
+            }
             FMS_HIP(launch_seed_iterate(a, base.D, p->kernel, ssh, (B + ssh.R - 1) / ssh.R, s));
         } else {
             FMS_CHECK(iterate_batch(b, p->max_iter, s, mirror));
@@ -1102,6 +1172,7 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
     do {                                \
         if (run) FMS_HIP(expr);         \
     } while (0)
+    const SeedForm form = seed_form(p, n, d, m, n_iter, false);
     const bool bf16 = bf16_form(p, d);
     const bool cull = !bf16 && !p->plain && cull_supported(d, n) &&
                       !(p->metric == MS_METRIC_COSINE && cull_reach(p->kernel, p->h) >= 2.0);
@@ -1117,8 +1188,44 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
         FMS_RUN(launch_normalize_rows(X, n, d, Xn, nullptr, s));
         X = Xn;
     }
-    const bool seedf = seed_form(p, d, false);
+    const bool seedf = form == SEED_ROWS;
     const SeedShape ssh = seed_shape(sh.D, m);
+    if (form == SEED_RUNS || form == SEED_DENSE) {
+        RunIndex ri;
+        float* tiles = nullptr;
+        if (form == SEED_RUNS)
+            FMS_CHECK(run_index_alloc(ri, run_sizes_equal(1, n), d, false,
+                                      [&](auto** out, size_t c) { return ws.alloc(out, c); }));
+        else
+            FMS_CHECK(ws.alloc(&tiles, (size_t)(n + 63) / 64 * 64 * sh.DP));
+        Batch b;
+        fill_batch(b, n, d, m, step_shape(d), p, scale, nullptr, nullptr);
+        FMS_CHECK(ws.alloc(&b.S, (size_t)m * sh.DP));
+        FMS_CHECK(ws.alloc(&b.act[0], m));
+        FMS_CHECK(ws.alloc(&b.status, m));
+        FMS_CHECK(ws.alloc(&b.iters, m));
+        FMS_CHECK(ws.alloc(&b.shift2, m));
+        FMS_CHECK(ws.alloc(&b.ctl, 1));
+        RunSeeds rs;
+        const bool ordered = form == SEED_RUNS && seed_ordered(ssh, m);
+        if (ordered)
+            FMS_CHECK(run_seeds_alloc(rs, ri, m, [&](auto** out, size_t c) { return ws.alloc(out, c); }));
+        if (!run) return MS_OK;
+        if (form == SEED_RUNS) FMS_HIP(launch_run_index(ri, X, nullptr, n, scale, run_far(p), s));
+        else FMS_HIP(launch_pack_tiles(X, n, d, sh.D, scale, tiles, s));
+        FMS_HIP(launch_ctl_reset(b.ctl, 0, INT_MAX, n_iter, s));
+        FMS_HIP(launch_seed_init_from_array(seeds, converged, d, m, b, s));
+        SeedArgs a = seed_args(b, p, tiles, nullptr, n_iter);
+        a.ctl = nullptr;
+        if (form == SEED_RUNS) seed_args_runs(a, ri);
+        if (ordered) {
+            FMS_HIP(launch_run_seeds(ri, b.S, m, rs, s));
+            seed_args_order(a, rs);
+        }
+        FMS_HIP(launch_seed_iterate(a, sh.D, p->kernel, ssh, (m + ssh.R - 1) / ssh.R, s));
+        FMS_HIP(launch_seed_export(b, m, seeds, converged, iters, shift2, s));
+        return MS_OK;
+    }
     const size_t rows = seedf ? (size_t)(n + 63) / 64 * 64 : (size_t)n;   // whole tiles
     float* Xp;
     FMS_CHECK(ws.alloc(&Xp, rows * sh.DP));

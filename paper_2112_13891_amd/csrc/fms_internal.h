@@ -19,6 +19,8 @@ enum : int32_t { MG_SKIP = -3, MG_UNDECIDED = -2, MG_FOUNDER = -1 };
 
 constexpr int kMaxIterCap = 4096;   // hard cap on max_iter / n_iter
 constexpr int kMaxMergePasses = 64;
+constexpr int kFarRuns = 16;        // far runs of a cloud (k_runs.hip)
+constexpr int kRunPivotMax = 1024;  // pivots of a cloud (k_runs.hip)
 // BF16 forms: the refined-pair count is spread over counters 128 bytes apart
 // (a workgroup adds its count to counter workgroup % kRefinedSlots), so that
 // the workgroups of a launch do not queue on one address at the end of the
@@ -147,6 +149,17 @@ __device__ __forceinline__ int upper_cloud(const T* pre, int ncl, long long v) {
     return lo;
 }
 
+// The cloud whose runs [poff[c] + F c, poff[c + 1] + F (c + 1)) hold run r.
+__device__ __forceinline__ int upper_cloud_runs(const int32_t* poff, int ncl, int r) {
+    int lo = 0, hi = ncl;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (poff[mid] + kFarRuns * mid <= r) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
 // Device plan of one batched iteration (k_batched.hip fills it; the step
 // kernels read it).
 struct BatchedArgs {
@@ -173,9 +186,8 @@ constexpr float kPadCoord = 1e19f;
 struct SeedArgs {
     const float* T = nullptr;      // 64-point tiles (packed units), see k_seed.hip
     int tiles = 0;
-    const int32_t* ntiles = nullptr;   // device count of tiles, or NULL: `tiles`
-    const float* geom = nullptr;   // tile balls: centre k of tile t at [k * geom_ld + t], the radius
-    int geom_ld = 0;               // at [D * geom_ld + t]; NULL: every tile is evaluated
+    const float* geom = nullptr;   // rows: tile balls, centre k of tile t at [k * geom_ld + t], the radius
+    int geom_ld = 0;               // at [D * geom_ld + t]; NULL: every tile is evaluated.  Runs: the pivots
     int n = 0;                     // points (pair count only)
     float* S = nullptr;            // seed positions (original units, stride DP)
     const int32_t* order = nullptr;   // seeds in the order they are grouped, or NULL
@@ -188,12 +200,20 @@ struct SeedArgs {
     int max_iter = 1;
     float h2 = 0.0f, scale = 1.0f, inv_scale = 1.0f, thr2 = 0.0f;
     int metric = MS_METRIC_EUCLIDEAN;
-    // many clouds: workgroup, seed and tile ranges per cloud (ncl + 1 entries each)
-    int ncl = 0;
-    const int32_t* wg_off = nullptr;
+    // runs (poff set): see RunIndex; with seg (the seed ranges of the clouds,
+    // ncl + 1 entries) a workgroup's one seed belongs to one of many clouds
+    int ncl = 1;
+    const int32_t* poff = nullptr;
+    const float* run_bound = nullptr;
+    const int32_t* tile_start = nullptr;
     const int32_t* seg = nullptr;
-    const int32_t* tile_off = nullptr;
+    // one cloud, optional: each seed's nearest pivot, a bound of its distance,
+    // and the distances between the pivots
+    const int32_t* pnear = nullptr;
+    const float* pdist = nullptr;
+    const float* ppair = nullptr;
     float slack = 0.0f, flat_reach = 0.0f;   // set by the launcher
+    int wgs = 0;
 };
 struct SeedShape {
     int R;    // seeds per workgroup
@@ -204,6 +224,119 @@ hipError_t launch_seed_iterate(SeedArgs a, int D, int kernel, const SeedShape& s
 // D <= 4: fills the tail of the last tile of n rows of 4 floats and writes the
 // tile balls (geom NULL: the tail only).
 hipError_t launch_tile_ball(float* T, int n, int D, float* geom, int ld, hipStream_t s);
+// D >= 8: rows X (n x d) to tiles in their order (packed units, tail filled).
+hipError_t launch_pack_tiles(const float* X, int n, int d, int D, float scale, float* T, hipStream_t s);
+
+// ---- radix sort (k_sort.hip) ------------------------------------------------
+// Stable radix sort of n (key, value) pairs by the low 8 * passes bits of the
+// keys, between (k0, v0) and (k1, v1); *keys and *vals point at the result.
+// tmp: radix_pairs_bytes(n) bytes.
+size_t radix_pairs_bytes(int n);
+hipError_t launch_radix_pairs(unsigned* k0, unsigned* k1, int* v0, int* v1, void* tmp, int n, int passes,
+                              unsigned** keys, int** vals, hipStream_t s);
+
+// ---- launchers (k_runs.hip): points grouped around sampled pivots ---------------
+// Every cloud of a CSR batch (one cloud: ncl = 1) has one pivot per 256 points
+// (1 to 1,024); a run holds the points nearest to one pivot, and the points
+// far from every pivot form kFarRuns further runs by their distance.  Runs are
+// padded to whole tiles of 64 points, so a tile never spans two runs.
+struct RunSizes {
+    int ncl = 0;
+    int n = 0;
+    int ptot = 0;        // pivots
+    int ptiles = 0;      // 32-pivot tiles
+    int rtiles = 0;      // 256-row tiles
+    int runs = 0;        // ptot + kFarRuns * ncl
+    int max_tiles = 0;   // at least the 64-point tiles
+};
+int run_pivots(long long n_cloud);
+RunSizes run_sizes(const long long* x_off, int ncl);   // x_off on the host
+RunSizes run_sizes_equal(int ncl, int n_each);
+struct RunIndex {
+    RunSizes sz;
+    int D = 0, DP = 0, d = 0;
+    float* tiles = nullptr;      // max_tiles x 64 x DP, the layout of k_seed.hip
+    float* pivots = nullptr;     // coordinate k of pivot j (packed units) at [k * ptot + j]
+    float* run_bound = nullptr;  // largest distance of a near run's points from its pivot (at most this);
+                                 // of a far run, the least distance of its points from any pivot
+    int32_t* rows = nullptr;     // original row of each tile slot, -1 for padding (NULL: not kept)
+    int32_t* tile_start = nullptr;   // first tile of each run (runs + 1); a cloud's pivots, then its far runs
+    // scratch of the build; the pivot part also serves later seed orders
+    long long* xo = nullptr;
+    int32_t *poff = nullptr, *ptoff = nullptr, *rtoff = nullptr, *tile_run = nullptr, *run_start = nullptr;
+    char* frag = nullptr;
+    unsigned *k0 = nullptr, *k1 = nullptr;
+    int *v0 = nullptr, *v1 = nullptr;
+    float* dpiv = nullptr;
+    char* radix = nullptr;
+    float scale = 1.0f, far = 8.0f;
+    const float* X = nullptr;
+};
+// Takes the index's buffers through alloc(T** out, size_t count) -> int.
+template <class F>
+int run_index_alloc(RunIndex& r, const RunSizes& sz, int d, bool keep_rows, F&& alloc) {
+    const StepShape sh = step_shape(d);
+    r.sz = sz;
+    r.d = d;
+    r.D = sh.D;
+    r.DP = sh.DP;
+    const size_t T = (size_t)sz.max_tiles, n = (size_t)sz.n;
+    const int KB = sh.D <= 16 ? 1 : sh.D / 16;
+    int rc = 0;
+    auto get = [&](auto** p, size_t c) { if (rc == 0) rc = alloc(p, c); };
+    get(&r.tiles, T * 64 * sh.DP);
+    get(&r.pivots, (size_t)sz.ptot * sh.D);
+    get(&r.run_bound, (size_t)sz.runs);
+    if (keep_rows) get(&r.rows, T * 64);
+    get(&r.xo, (size_t)sz.ncl + 1);
+    get(&r.poff, (size_t)sz.ncl + 1);
+    get(&r.ptoff, (size_t)sz.ncl + 1);
+    get(&r.rtoff, (size_t)sz.ncl + 1);
+    get(&r.tile_start, (size_t)sz.runs + 1);
+    get(&r.tile_run, T);
+    get(&r.run_start, (size_t)sz.runs + 1);
+    get(&r.frag, (size_t)sz.ptiles * (2 * KB + 1) * 1024);
+    get(&r.k0, n);
+    get(&r.k1, n);
+    get(&r.v0, n);
+    get(&r.v1, n);
+    get(&r.dpiv, n);
+    get(&r.radix, radix_pairs_bytes(sz.n));
+    return rc;
+}
+// Builds the index of the rows X (n x d, FP32): xo_src holds the ncl + 1 row
+// offsets on the device, or NULL for clouds of n_each rows.  `scale` takes
+// coordinates to packed units, `far` is the distance (packed units) from which
+// a point counts as far from its nearest pivot.
+hipError_t launch_run_index(RunIndex& r, const float* X, const long long* xo_src, int n_each, float scale,
+                            float far, hipStream_t s);
+// One cloud: order[0 .. m) = the seeds S (stride DP, original units) grouped by
+// their nearest pivot, near[j] that pivot of seed j, dist[j] >= its distance,
+// and ppair[i * P + j] <= the distance between pivots i and j.
+struct RunSeeds {
+    unsigned *k0 = nullptr, *k1 = nullptr;
+    int *v0 = nullptr, *v1 = nullptr;
+    char* tmp = nullptr;
+    int32_t* near = nullptr;
+    float* dist = nullptr;
+    float* ppair = nullptr;
+    int32_t* order = nullptr;   // one of v0, v1
+};
+template <class F>
+int run_seeds_alloc(RunSeeds& q, const RunIndex& r, int m, F&& alloc) {
+    int rc = 0;
+    auto get = [&](auto** p, size_t c) { if (rc == 0) rc = alloc(p, c); };
+    get(&q.k0, (size_t)m);
+    get(&q.k1, (size_t)m);
+    get(&q.v0, (size_t)m);
+    get(&q.v1, (size_t)m);
+    get(&q.tmp, radix_pairs_bytes(m));
+    get(&q.near, (size_t)m);
+    get(&q.dist, (size_t)m);
+    get(&q.ppair, (size_t)r.sz.ptot * r.sz.ptot);
+    return rc;
+}
+hipError_t launch_run_seeds(const RunIndex& r, const float* S, int m, RunSeeds& q, hipStream_t s);
 
 // ---- launchers (k_step_bf16.hip) -----------------------------------------
 StepShape step_shape_bf16(int d, int B);

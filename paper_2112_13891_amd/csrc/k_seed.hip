@@ -21,24 +21,33 @@
 // instead of 35 %.  The near tiles are neighbours in the spatial order, so the
 // workgroup lists them in LDS first and its waves take the entries in turn.
 //
+// The tiles come in one of two orders.
+//   Rows (d <= 4): the packed rows as they are (few points: every tile is
+//     evaluated), or in Morton order with a ball per tile.
+//   Runs (k_runs.hip; every d up to 32, one cloud or many): runs of tiles
+//     around sampled pivots.  The ball of a run is its pivot and its farthest
+//     point; a run of points far from every pivot has a lower bound of that
+//     distance, and a seed within u of some pivot sees none of its points
+//     closer than the bound minus u.
+//
 // What a tile may be left out for (the Gaussian): every pair of it is beyond
 // the distance where the FP32 weight is exactly zero (q >= 150; the test uses
 // 160), or has a weight below 2^-64 of the seed's weight sum W.  At most n
 // such terms are dropped, in total below n 2^-64 W <= 2^-33 W, where an FP32
-// sum rounds at 2^-25 W.  W is bounded from below without any sum: a tile of
-// radius r at distance c holds a point within c + r, so W >= 2^-(c + r)^2
-// for the nearest tile; after the first update the W of the previous one
-// serves (a mean-shift step never lowers the density).  The flat window
-// leaves out the tiles wholly outside it.
+// sum rounds at 2^-25 W.  W is bounded from below without any sum: a ball of
+// radius r at distance c holds a point within c + r (a pivot is a point
+// itself), so W >= 2^-(c + r)^2 for the nearest one; after the first update
+// the W of the previous one serves (a mean-shift step never lowers the
+// density).  The flat window leaves out the tiles wholly outside it.
 //
 // With the list made beforehand the tiles' loads run ahead of the arithmetic
-// with no test between them.  The waves test consecutive groups of 64 tiles
+// with no test between them.  The waves test consecutive groups of 64 balls
 // (contiguous loads; with the tiles dealt to the waves one by one a pass over
-// 3,125 balls took 7 us instead of 2).  The list is kept while the seeds stay within kSlack packed units of where
-// it was made, the reach being that much longer; late iterations move far
-// less and skip the geometry.
+// 3,125 balls took 7 us instead of 2).  The list is kept while the seeds stay
+// within a slack of where it was made, the reach being that much longer; late
+// iterations move far less and skip the geometry.
 //
-// The lane sums are added by a fixed butterfly, the waves' sums in wave order:
+// The lane sums are added by fixed DPP steps, the waves' sums in wave order:
 // no floating-point atomics, the same result on every run.
 
 #include <algorithm>
@@ -53,34 +62,15 @@ constexpr float kSeedZero = 160.0f;      // exp2(-q) == +0 in FP32 for q >= 150
 constexpr float kSeedNegligible = 64.0f; // weights below 2^-64 of the sum change no FP32 sum
 constexpr float kSeedFlatMargin = 1.001f;
 constexpr float kSlack = 0.25f;          // packed units
+constexpr int kRunListMax = kRunPivotMax + 64;   // runs of a cloud, whole groups
 constexpr int kSegGroups = 96;           // groups of 64 tiles listed at once (24 KB: six workgroups a CU)
 constexpr int kSeedMaxWaves = 16;
+constexpr int kXcdRun = 64;
 // wide rows need the registers that 16 waves in one workgroup would not have
-constexpr int seed_max_waves(int D) { return D <= 4 ? kSeedMaxWaves : 8; }
+constexpr int seed_max_waves(int D, int R) { return R > 1 ? 4 : (D <= 4 ? kSeedMaxWaves : 8); }
 
-// Sum over the 64 lanes, in lane 63, by DPP additions: prefix sums within the
-// rows of 16 lanes, then row 0 into row 1 and row 2 into row 3, then the lower
-// half into the upper one.  A fixed order, no LDS.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
-}
-__device__ __forceinline__ float wave_add63(float v) {
-    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
-    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
-    v = dpp_add<0x114, 0xf>(v);   // row_shr:4
-    v = dpp_add<0x118, 0xf>(v);   // row_shr:8
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
-__device__ __forceinline__ float lane_value(float v, int lane) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
-template <int D, int R, int KERN>
-__global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(SeedArgs a) {
+template <int D, int R, int KERN, bool RUNS>
+__global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel(SeedArgs a) {
     constexpr int DP = D <= 4 ? 4 : D;
     constexpr int G4 = DP / 4;
     constexpr int V = D + 1;
@@ -89,25 +79,39 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int NW = blockDim.x >> 6;
 
-    // this workgroup's seeds (a cloud's own in the batched form) and tiles
-    int j0 = blockIdx.x * R, jend = a.m, t0 = 0, t1 = a.tiles;
-    if (a.ntiles) t1 = *a.ntiles;
-    if (a.wg_off) {
-        const int c = upper_cloud(a.wg_off, a.ncl, blockIdx.x);
-        j0 = a.seg[c] + ((int)blockIdx.x - a.wg_off[c]) * R;
-        jend = a.seg[c + 1];
-        t0 = a.tile_off[c];
-        t1 = a.tile_off[c + 1];
+    // this workgroup's seeds and its cloud's tiles.  Workgroups are dealt to
+    // the eight XCDs in turn; an XCD takes kXcdRun seed groups in a row, so
+    // that seeds that are close (or in one cloud) read their tiles through one
+    // L2, from the end of the order: the seeds far from every pivot come last
+    // in it and see every far tile, so they start first and on all XCDs.
+    const int xi = (int)blockIdx.x >> 3;
+    const int wg = a.wgs - 1 - (((xi / kXcdRun) * 8 + ((int)blockIdx.x & 7)) * kXcdRun + xi % kXcdRun);
+    if (wg < 0) return;
+    const int j0 = wg * R;
+    // rows: tiles [0, nball), a ball each; runs: the cloud's pivots
+    // [ball0, ball0 + nball), whose runs start at run0
+    int ball0 = 0, nball = a.tiles, run0 = 0;
+    if constexpr (RUNS) {
+        const int c = a.seg ? upper_cloud(a.seg, a.ncl, j0) : 0;
+        ball0 = __builtin_amdgcn_readfirstlane(a.poff[c]);
+        nball = __builtin_amdgcn_readfirstlane(a.poff[c + 1]) - ball0;
+        run0 = ball0 + kFarRuns * __builtin_amdgcn_readfirstlane(c);
     }
-    t0 = __builtin_amdgcn_readfirstlane(t0);
-    t1 = __builtin_amdgcn_readfirstlane(t1);
+    const bool culled = RUNS || a.geom != nullptr;
 
     __shared__ float red[2][kSeedMaxWaves][R * V];
-    __shared__ float wub[kSeedMaxWaves];
+    __shared__ float wub[R][kSeedMaxWaves];
     __shared__ unsigned wcnt[kSeedMaxWaves];
-    __shared__ unsigned list[kSegGroups * 64];
-    __shared__ unsigned long long near_mask[kSegGroups];
-    __shared__ unsigned char near_who[R > 1 ? kSegGroups * 64 : 1];
+    // rows: `list` holds tiles.  Runs: `list` holds the first tile of each
+    // listed run and `list_pre` the tiles listed before it; a lower bound of a
+    // seed's distance from every pivot stays in `dist_s`.  The top bits of an entry say which of
+    // the R seeds reach it.
+    constexpr int kList = RUNS ? kRunListMax : kSegGroups * 64;
+    __shared__ unsigned list[kList];
+    __shared__ int list_pre[RUNS ? kRunListMax + 1 : 1];
+    __shared__ float dist_s[RUNS ? kRunPivotMax * R : 1];
+    __shared__ unsigned long long near_mask[RUNS ? kRunListMax / 64 : kSegGroups];
+    __shared__ unsigned char near_who[R > 1 ? kList : 1];
 
     // lane (r, k) holds coordinate k of seed r, in every wave
     const int r_of = lane / DP, k_of = lane % DP;
@@ -117,7 +121,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
     for (int r = 0; r < R; ++r) {
         const int slot = j0 + r;
         id[r] = -1;
-        if (slot < jend) {
+        if (slot < a.m) {
             id[r] = __builtin_amdgcn_readfirstlane(a.order ? a.order[slot] : slot);
             if (a.status[id[r]] == ST_ACTIVE) act |= 1u << r;
         }
@@ -129,20 +133,22 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
     for (int r = 0; r < R; ++r)
         if (r_of == r && id[r] >= 0) sv = a.S[(long long)id[r] * DP + k_of];
 
-    // Tile t0 + g * 64 + l is lane l of group g.  A segment is as many groups
-    // as fit the list; with one segment the list may be kept from one update
-    // to the next.
-    const int ntile = t1 - t0;
-    const int groups = (ntile + 63) / 64;
-    const bool keep = groups <= kSegGroups;
+    // Ball g * 64 + l is lane l of group g.  A segment is as many groups as fit
+    // the list; with one segment (always, for runs) the list may be kept from
+    // one update to the next.
+    const int groups = (nball + 63) / 64;
+    const bool keep = RUNS || groups <= kSegGroups;
     const float4* __restrict__ T4 = reinterpret_cast<const float4*>(a.T);
 
-    float reach[R], wprev[R], last_sh2[R];
+    float reach[R], rq[R], wprev[R], last_sh2[R];   // reach and its square
+    float ub[R];             // some point (runs: some pivot) lies within ub
     int nit[R];
     int result[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         reach[r] = 0.0f;
+        rq[r] = __builtin_inff();   // nothing is left out without geometry
+        ub[r] = 1e18f;
         wprev[r] = -1.0f;
         last_sh2[r] = __builtin_nanf("");
         nit[r] = 0;
@@ -151,6 +157,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
     float sref = 0.0f;       // where the masks were made
     bool have_list = false;
     int len = 0;             // listed tiles
+    int nlisted = 0;         // listed runs
     unsigned evaluated = 0;  // tiles this wave evaluated, over seeds and iterations
     int executed = 0;        // updates run, over the seeds
 
@@ -163,22 +170,20 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
 #pragma unroll
             for (int k = 0; k < D; ++k) s[r][k] = lane_value(svs, r * DP + k);
 
-        auto tile_of = [&](int g) { return t0 + g * 64 + lane; };
-
         // f(g, r, inside, distance of seed r from the ball's centre, radius)
-        // for the lane's tile of this wave's groups g0 + wave, + NW, ... < g1,
+        // for the lane's ball of this wave's groups g0 + wave, + NW, ... < g1,
         // several groups' loads at once
         auto balls = [&](int g0, int g1, auto&& f) {
-            constexpr int B = D <= 4 ? 4 : (D <= 8 ? 2 : 1);
+            constexpr int B = D <= 4 ? 4 : (D <= 16 ? 2 : 1);
             for (int g = g0 + wave; g < g1; g += B * NW) {
                 float c[B][D], rad[B];
 #pragma unroll
                 for (int i = 0; i < B; ++i) {
-                    const int t = tile_of(g + i * NW);
-                    const int tc = t < t1 ? t : t0;
+                    const int e = (g + i * NW) * 64 + lane;
+                    const int t = ball0 + (e < nball ? e : 0);
 #pragma unroll
-                    for (int k = 0; k < D; ++k) c[i][k] = a.geom[k * a.geom_ld + tc];
-                    rad[i] = a.geom[D * a.geom_ld + tc];
+                    for (int k = 0; k < D; ++k) c[i][k] = a.geom[(long long)k * a.geom_ld + t];
+                    rad[i] = RUNS ? 0.0f : a.geom[(long long)D * a.geom_ld + t];
                 }
 #pragma unroll
                 for (int i = 0; i < B; ++i) {
@@ -191,14 +196,14 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
                                 const float u = s[r][k] - c[i][k];
                                 d2 = fmaf(u, u, d2);
                             }
-                            f(g + i * NW, r, tile_of(g + i * NW) < t1, __builtin_amdgcn_sqrtf(d2), rad[i]);
+                            f(g + i * NW, r, (g + i * NW) * 64 + lane < nball, __builtin_amdgcn_sqrtf(d2), rad[i]);
                         }
                     }
                 }
             }
         };
 
-        bool remake = a.geom != nullptr;
+        bool remake = culled;
         if (remake && have_list) {
             float d2 = sv - sref;
             d2 = d2 * d2;
@@ -209,37 +214,148 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
             remake = __ballot(far) != 0;
         }
         if (remake) {
-            sref = sv;
-            if (KERN == MS_KERNEL_GAUSSIAN && it == 0) {
-                // W >= 2^-(c + r)^2 for the nearest tile
-                float ub[R];
+            float moved[R];   // since the last list
+            if (RUNS && it > 0) {
+                float d2 = (sv - sref) * a.scale;
+                d2 = d2 * d2;
 #pragma unroll
-                for (int r = 0; r < R; ++r) ub[r] = 1e18f;
-                balls(0, groups, [&](int, int r, bool in, float dist, float rad) {
-                    if (in) ub[r] = fminf(ub[r], dist + rad);   // a NaN never lowers it
+                for (int off = DP / 2; off >= 1; off >>= 1) d2 += __shfl_xor(d2, off);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    moved[r] = 1.001f * sqrtf(lane_value(d2, r * DP));
+                    ub[r] += moved[r];
+                }
+            }
+            sref = sv;
+            const bool by_row = RUNS && it == 0 && a.pnear != nullptr;
+            if (by_row) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) ub[r] = id[r] >= 0 ? a.pdist[id[r]] : 0.0f;
+            }
+            if (RUNS) __syncthreads();   // the last list is no longer read
+            if (it == 0 && !by_row && (RUNS || KERN == MS_KERNEL_GAUSSIAN)) {
+                balls(0, groups, [&](int g, int r, bool in, float dist, float rad) {
+                    if (in) {
+                        ub[r] = fminf(ub[r], dist + rad);   // a NaN never lowers it
+                        if (RUNS) dist_s[r * kRunPivotMax + g * 64 + lane] = dist;
+                    }
                 });
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
 #pragma unroll
                     for (int off = 32; off >= 1; off >>= 1) ub[r] = fminf(ub[r], __shfl_xor(ub[r], off));
-                    __syncthreads();
-                    if (lane == 0) wub[wave] = ub[r];
-                    __syncthreads();
-                    float u = wub[0];
-                    for (int w = 1; w < NW; ++w) u = fminf(u, wub[w]);
-                    const float q = fminf(kSeedZero, kSeedNegligible + 1.001f * u * u);
-                    reach[r] = sqrtf(q);
+                    if (lane == 0) wub[r][wave] = ub[r];
                 }
-            } else if (KERN == MS_KERNEL_GAUSSIAN) {
+                __syncthreads();
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    // -log2 W, at least: 1 of margin
-                    const float q = kSeedNegligible + 1.0f - __builtin_amdgcn_logf(wprev[r]);
-                    reach[r] = sqrtf(fminf(kSeedZero, fmaxf(q, 1.0f)));
+                    float u = wub[r][0];
+                    for (int w = 1; w < NW; ++w) u = fminf(u, wub[r][w]);
+                    ub[r] = 1.001f * u;
                 }
-            } else {
+            }
 #pragma unroll
-                for (int r = 0; r < R; ++r) reach[r] = a.flat_reach;
+            for (int r = 0; r < R; ++r) {
+                if (KERN == MS_KERNEL_GAUSSIAN) {
+                    // -log2 W, at most (1 of margin on the previous update's)
+                    const float q = it == 0 ? ub[r] * ub[r] : 1.0f - __builtin_amdgcn_logf(wprev[r]);
+                    rq[r] = fminf(kSeedZero, fmaxf(kSeedNegligible + q, 1.0f));
+                    reach[r] = sqrtf(rq[r]);
+                } else {
+                    reach[r] = a.flat_reach;
+                    rq[r] = reach[r] * reach[r];
+                }
+            }
+            if constexpr (RUNS) {
+                // near runs by their balls, far runs by their bounds.  A
+                // pivot's distance is computed again only where the bound from
+                // the last list, or from the seed's nearest pivot
+                // (|s - p| >= |p' - p| - |s - p'|), does not rule it out: all
+                // 1,024 distances of 8,192 seeds at D = 32 read 1 GB and took
+                // 107 us a pass
+                auto test = [&](int e, float bound) {
+                    unsigned who = 0;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const float lim = reach[r] + a.slack;
+                        bool out;
+                        if (e < nball) {
+                            float l;
+                            float& kept = dist_s[r * kRunPivotMax + e];
+                            if (by_row) l = id[r] >= 0 ? a.ppair[(long long)a.pnear[id[r]] * nball + e] - ub[r] : 0.0f;
+                            else l = kept - (it > 0 ? moved[r] : 0.0f);
+                            if ((by_row || it > 0) && !(l - bound > lim)) {
+                                float d2 = 0.0f;
+#pragma unroll
+                                for (int k = 0; k < D; ++k) {
+                                    const float u = s[r][k] - a.geom[(long long)k * a.geom_ld + ball0 + e];
+                                    d2 = fmaf(u, u, d2);
+                                }
+                                l = __builtin_amdgcn_sqrtf(d2);
+                            }
+                            kept = l;
+                            out = l - bound > lim;   // a NaN is near
+                        } else {
+                            out = bound - ub[r] > lim;
+                        }
+                        who |= (!out && ((act >> r) & 1u)) ? 1u << r : 0u;
+                    }
+                    return who;
+                };
+                const int nrun = nball + kFarRuns;
+                const int rgroups = (nrun + 63) / 64;
+                for (int g = wave; g < rgroups; g += NW) {
+                    const int e = g * 64 + lane;
+                    unsigned who = 0;
+                    if (e < nrun) who = test(e, a.run_bound[run0 + e]);
+                    if (e < nrun && a.tile_start[run0 + e] == a.tile_start[run0 + e + 1]) who = 0;
+                    const unsigned long long mk = __ballot(who != 0);
+                    if (lane == 0) near_mask[g] = mk;
+                    if (R > 1) near_who[e] = (unsigned char)who;
+                }
+                __syncthreads();
+                // entries before each group, then the entries with their tiles
+                // counted in run order
+                int before = 0;
+                const int gc = lane < rgroups ? __popcll(near_mask[lane]) : 0;
+                int x = gc;
+#pragma unroll
+                for (int off = 1; off < 32; off <<= 1) {
+                    const int y = __shfl_up(x, off);
+                    if (lane >= off) x += y;
+                }
+                before = x - gc;
+                const int nlist = __builtin_amdgcn_readlane(x, 31);
+                for (int g = wave; g < rgroups; g += NW) {
+                    const unsigned long long mk = (unsigned long long)wave_uniform((long long)near_mask[g]);
+                    const int at = __builtin_amdgcn_readlane(before, g);
+                    if ((mk >> lane) & 1ull) {
+                        const int e = g * 64 + lane, q = at + __popcll(mk & ((1ull << lane) - 1ull));
+                        const int t = a.tile_start[run0 + e];
+                        list[q] = (unsigned)t | (R > 1 ? (unsigned)near_who[e] << 28 : 0u);
+                        list_pre[q] = a.tile_start[run0 + e + 1] - t;
+                    }
+                }
+                __syncthreads();
+                // prefix of the listed runs' tiles, by wave 0
+                if (wave == 0) {
+                    int total = 0;
+                    for (int q0 = 0; q0 < nlist; q0 += 64) {
+                        const int c = q0 + lane < nlist ? list_pre[q0 + lane] : 0;
+                        int v = c;
+#pragma unroll
+                        for (int off = 1; off < 64; off <<= 1) {
+                            const int y = __shfl_up(v, off);
+                            if (lane >= off) v += y;
+                        }
+                        if (q0 + lane < nlist) list_pre[q0 + lane] = total + v - c;
+                        total += __builtin_amdgcn_readlane(v, 63);
+                    }
+                    if (lane == 0) list_pre[nlist] = total;
+                }
+                __syncthreads();
+                nlisted = nlist;
+                len = __builtin_amdgcn_readfirstlane(list_pre[nlist]);
             }
             have_list = keep;
         }
@@ -250,49 +366,52 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
 #pragma unroll
             for (int k = 0; k < V; ++k) acc[r][k] = 0.0f;
 
-        for (int g0 = 0; g0 < groups; g0 += kSegGroups) {
-            const int g1 = min(groups, g0 + kSegGroups);
-            if (remake) {
-                unsigned who = 0;   // seeds that reach the lane's tile
-                __syncthreads();   // the last list and its masks are no longer read
-                balls(g0, g1, [&](int g, int r, bool in, float dist, float rad) {
-                    // a NaN (a ball without a finite centre) stays near
-                    const bool near = in && !(dist - rad > reach[r] + (keep ? a.slack : 0.0f));
-                    who = (r == 0 ? 0u : who) | ((near && ((act >> r) & 1u)) ? 1u << r : 0u);
-                    if (r == R - 1) {
-                        const unsigned long long mk = __ballot(who != 0);
-                        if (lane == 0) near_mask[g - g0] = mk;
-                        if (R > 1) near_who[(g - g0) * 64 + lane] = (unsigned char)who;
-                    }
-                });
-                __syncthreads();
-                // entries before each group: a scan of the groups' counts
-                int before[(kSegGroups + 63) / 64];
-                len = 0;
+        for (int g0 = 0; g0 < (RUNS ? 1 : groups); g0 += kSegGroups) {
+            if constexpr (!RUNS) {
+                const int g1 = min(groups, g0 + kSegGroups);
+                if (remake) {
+                    unsigned who = 0;   // seeds that reach the lane's tile
+                    __syncthreads();   // the last list and its masks are no longer read
+                    balls(g0, g1, [&](int g, int r, bool in, float dist, float rad) {
+                        // a NaN (a ball without a finite centre) stays near
+                        const bool near = in && !(dist - rad > reach[r] + (keep ? a.slack : 0.0f));
+                        who = (r == 0 ? 0u : who) | ((near && ((act >> r) & 1u)) ? 1u << r : 0u);
+                        if (r == R - 1) {
+                            const unsigned long long mk = __ballot(who != 0);
+                            if (lane == 0) near_mask[g - g0] = mk;
+                            if (R > 1) near_who[(g - g0) * 64 + lane] = (unsigned char)who;
+                        }
+                    });
+                    __syncthreads();
+                    // entries before each group: a scan of the groups' counts
+                    int before[(kSegGroups + 63) / 64];
+                    len = 0;
 #pragma unroll
-                for (int q = 0; q < (kSegGroups + 63) / 64; ++q) {
-                    const int gi = q * 64 + lane;
-                    const int cnt = gi < g1 - g0 ? __popcll(near_mask[gi]) : 0;
-                    int x = cnt;
+                    for (int q = 0; q < (kSegGroups + 63) / 64; ++q) {
+                        const int gi = q * 64 + lane;
+                        const int cnt = gi < g1 - g0 ? __popcll(near_mask[gi]) : 0;
+                        int x = cnt;
 #pragma unroll
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const int y = __shfl_up(x, off);
-                        if (lane >= off) x += y;
+                        for (int off = 1; off < 64; off <<= 1) {
+                            const int y = __shfl_up(x, off);
+                            if (lane >= off) x += y;
+                        }
+                        before[q] = len + x - cnt;
+                        len += __builtin_amdgcn_readlane(x, 63);
                     }
-                    before[q] = len + x - cnt;
-                    len += __builtin_amdgcn_readlane(x, 63);
+                    for (int gi = wave; gi < g1 - g0; gi += NW) {
+                        const unsigned long long mk = (unsigned long long)wave_uniform((long long)near_mask[gi]);
+                        if (!mk) continue;
+                        const int at = __builtin_amdgcn_readlane(gi < 64 ? before[0] : before[1], gi & 63);
+                        if ((mk >> lane) & 1ull)
+                            list[at + __popcll(mk & ((1ull << lane) - 1ull))] =
+                                (unsigned)((g0 + gi) * 64 + lane) |
+                                (R > 1 ? (unsigned)near_who[gi * 64 + lane] << 28 : 0u);
+                    }
+                    __syncthreads();
+                } else if (!culled) {
+                    len = min((g1 - g0) * 64, nball - g0 * 64);
                 }
-                for (int gi = wave; gi < g1 - g0; gi += NW) {
-                    const unsigned long long mk = (unsigned long long)wave_uniform((long long)near_mask[gi]);
-                    if (!mk) continue;
-                    const int at = __builtin_amdgcn_readlane(gi < 64 ? before[0] : before[1], gi & 63);
-                    if ((mk >> lane) & 1ull)
-                        list[at + __popcll(mk & ((1ull << lane) - 1ull))] =
-                            (unsigned)tile_of(g0 + gi) | (R > 1 ? (unsigned)near_who[gi * 64 + lane] << 28 : 0u);
-                }
-                __syncthreads();
-            } else if (!a.geom) {
-                len = min((g1 - g0) * 64, ntile - g0 * 64);
             }
             // this wave's entries: wave, wave + NW, ...
             const int mine_n = len > wave ? (len - wave + NW - 1) / NW : 0;
@@ -309,15 +428,26 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
                 const int cnt = min(U, mine_n - next);
                 if ((next & 63) == 0) {
                     const int e = (next + lane < mine_n ? next + lane : 0) * NW + wave;
-                    ids = a.geom ? list[e] : (unsigned)(t0 + g0 * 64 + e);
+                    if constexpr (RUNS) {
+                        // the listed run that holds tile e
+                        int lo = 0, hi = nlisted;
+                        while (hi - lo > 1) {
+                            const int mid = (lo + hi) >> 1;
+                            if (list_pre[mid] <= e) lo = mid;
+                            else hi = mid;
+                        }
+                        ids = list[lo] + (unsigned)(e - list_pre[lo]);
+                    } else {
+                        ids = culled ? list[e] : (unsigned)(g0 * 64 + e);
+                    }
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     // past the end: the last entry again, not used
                     const int e = (next + u < mine_n ? next + u : mine_n - 1) & 63;
                     const unsigned v = (unsigned)__builtin_amdgcn_readlane((int)ids, e);
-                    who[u] = (R > 1 && a.geom) ? v >> 28 : (1u << R) - 1u;
-                    const long long t = (R > 1 && a.geom) ? (v & 0x0fffffffu) : v;
+                    who[u] = (R > 1 && culled) ? v >> 28 : (1u << R) - 1u;
+                    const long long t = (R > 1 && culled) ? (v & 0x0fffffffu) : v;
 #pragma unroll
                     for (int q = 0; q < G4; ++q) x[u][q] = T4[(t * G4 + q) * 64 + lane];
                 }
@@ -341,10 +471,22 @@ __global__ __launch_bounds__(64 * seed_max_waves(D)) void seed_iterate_kernel(Se
                         if (R > 1 && !((who[u] & act) >> r & 1u)) continue;
                         float dx[D];
                         float q = 0.0f;
+                        constexpr int H = D >= 16 ? D / 2 : D;
 #pragma unroll
-                        for (int k = 0; k < D; ++k) {
+                        for (int k = 0; k < H; ++k) {
                             dx[k] = x[k] - s[r][k];
                             q = fmaf(dx[k], dx[k], q);
+                        }
+                        if constexpr (H < D) {
+                            // half the coordinates put every point of most far
+                            // tiles beyond the reach (a coordinate that is not
+                            // finite does not: it fails the seed)
+                            if (!__ballot(!(q > rq[r] && q < 3e38f))) continue;
+#pragma unroll
+                            for (int k = H; k < D; ++k) {
+                                dx[k] = x[k] - s[r][k];
+                                q = fmaf(dx[k], dx[k], q);
+                            }
                         }
                         float w;
                         if (KERN == MS_KERNEL_GAUSSIAN)
@@ -518,16 +660,36 @@ __global__ __launch_bounds__(256) void tile_ball_kernel(float* T, int n, int til
     }
 }
 
-template <int D, int R>
+// D >= 8: rows to tiles as they are, with the tail filled up (no balls).
+__global__ void pack_tiles_kernel(const float* __restrict__ X, int n, int d, int D, float scale, float* T) {
+    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int G4 = D / 4, tiles = (n + 63) / 64;
+    if (e >= (long long)tiles * G4 * 64) return;
+    const int lane = (int)(e & 63), q = (int)((e >> 6) % G4);
+    const long long i = (e >> 6) / G4 * 64 + lane;
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = (i < n && 4 * q + k < d) ? X[i * d + 4 * q + k] * scale : 0.0f;
+    if (i >= n && q == 0) v[0] = kPadCoord;
+    reinterpret_cast<float4*>(T)[e] = make_float4(v[0], v[1], v[2], v[3]);
+}
+
+template <int D, int R, bool RUNS>
 hipError_t launch_seed_t(const SeedArgs& a, int kernel, int wgs, int nw, hipStream_t s) {
     if (kernel == MS_KERNEL_GAUSSIAN)
-        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN>), dim3(wgs), dim3(64 * nw), 0, s, a);
+        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN, RUNS>), dim3(wgs), dim3(64 * nw), 0, s, a);
     else
-        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT>), dim3(wgs), dim3(64 * nw), 0, s, a);
+        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT, RUNS>), dim3(wgs), dim3(64 * nw), 0, s, a);
     return hipGetLastError();
 }
 
 }  // namespace
+
+hipError_t launch_pack_tiles(const float* X, int n, int d, int D, float scale, float* T, hipStream_t s) {
+    const long long total = (long long)((n + 63) / 64) * (D / 4) * 64;
+    hipLaunchKernelGGL(pack_tiles_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, X, n, d, D, scale, T);
+    return hipGetLastError();
+}
 
 hipError_t launch_tile_ball(float* T, int n, int D, float* geom, int ld, hipStream_t s) {
     const int tiles = (n + 63) / 64;
@@ -555,23 +717,39 @@ hipError_t launch_tile_ball(float* T, int n, int D, float* geom, int ld, hipStre
 //   32,768                               1449 / 898 / 643
 // (one update launched as a step over 64-seed tiles and a finalize: 31 us at
 // 512 seeds, 220 us for a batch; 1.54 ms at 200,000 seeds against 1.28 here).
+// Wide rows, 262,144 x 32-D points in runs, 3 updates, us:
+//   m       1 seed: 1 / 2 / 4 / 8 waves   2 seeds: 1 / 2 / 4 waves
+//   128      159 / 90 / 56 / 43
+//   1,024    229 / 159 / 151 / 175          325 / 182 / 125
+//   8,192    557 / 469 / 510 / 869          620 / 511 / 546
+// (64-seed tiles: 2,530 us an update at 8,192 seeds).  Two seeds share the
+// loads but leave two waves a SIMD: one seed per workgroup.
 SeedShape seed_shape(int D, long long m) {
-    (void)D;
     SeedShape sh;
-    sh.R = m > 2048 ? 4 : 1;
-    sh.nw = m <= 512 ? 8 : 4;
+    if (D <= 4) {
+        sh.R = m > 2048 ? 4 : 1;
+        sh.nw = m <= 512 ? 8 : 4;
+    } else {
+        sh.R = 1;
+        sh.nw = m <= 512 ? 8 : (m <= 2048 ? 4 : 2);
+    }
     return sh;
 }
 
 hipError_t launch_seed_iterate(SeedArgs a, int D, int kernel, const SeedShape& sh, int wgs, hipStream_t s) {
-    if (sh.nw < 1 || sh.nw > kSeedMaxWaves) return hipErrorInvalidValue;
+    if (sh.nw < 1 || sh.nw > seed_max_waves(D, sh.R)) return hipErrorInvalidValue;
     a.slack = kernel == MS_KERNEL_GAUSSIAN ? kSlack : 0.25f * sqrtf(a.h2) * a.scale;
     a.flat_reach = sqrtf(a.h2 * kSeedFlatMargin);
     if (wgs < 1) return hipSuccess;
-#define FMS_CASE(DD, RR) \
-    if (D == DD && sh.R == RR) return launch_seed_t<DD, RR>(a, kernel, wgs, sh.nw, s);
-    FMS_CASE(1, 1) FMS_CASE(2, 1) FMS_CASE(3, 1) FMS_CASE(4, 1)
-    FMS_CASE(1, 4) FMS_CASE(2, 4) FMS_CASE(3, 4) FMS_CASE(4, 4)
+    a.wgs = wgs;
+    wgs = (wgs + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
+#define FMS_CASE(DD, RR, RUNS) \
+    if (D == DD && sh.R == RR && (a.poff != nullptr) == RUNS) return launch_seed_t<DD, RR, RUNS>(a, kernel, wgs, sh.nw, s);
+    FMS_CASE(1, 1, false) FMS_CASE(2, 1, false) FMS_CASE(3, 1, false) FMS_CASE(4, 1, false)
+    FMS_CASE(1, 4, false) FMS_CASE(2, 4, false) FMS_CASE(3, 4, false) FMS_CASE(4, 4, false)
+    FMS_CASE(1, 1, true) FMS_CASE(2, 1, true) FMS_CASE(3, 1, true) FMS_CASE(4, 1, true)
+    FMS_CASE(8, 1, true) FMS_CASE(16, 1, true) FMS_CASE(32, 1, true)
+    FMS_CASE(8, 1, false) FMS_CASE(16, 1, false) FMS_CASE(32, 1, false)
 #undef FMS_CASE
     return hipErrorInvalidValue;
 }

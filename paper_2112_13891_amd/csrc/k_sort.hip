@@ -939,6 +939,25 @@ hipError_t launch_batched_seed_order(const float* S, int DP, int D, int M, float
     return hipGetLastError();
 }
 
+size_t radix_pairs_bytes(int n) {
+    const size_t nblocks = ((size_t)n + kSortThreads - 1) / kSortThreads;
+    return 4 * 256 * 4 + nblocks * 256 * 4 + 256;
+}
+
+hipError_t launch_radix_pairs(unsigned* k0, unsigned* k1, int* v0, int* v1, void* tmp, int n, int passes,
+                              unsigned** keys, int** vals, hipStream_t s) {
+    SortWs w{};
+    w.dtot = (int*)tmp;
+    w.hist = w.dtot + 4 * 256;
+    w.k0 = k0;
+    w.k1 = k1;
+    w.v0 = v0;
+    w.v1 = v1;
+    *vals = radix_sort_pairs(w, n, s, passes);
+    *keys = passes % 2 ? k1 : k0;
+    return hipGetLastError();
+}
+
 const float* sort_frame_shift(const void* ws) {
     return (const float*)ws + kShiftOff;
 }

@@ -81,6 +81,27 @@ __device__ __forceinline__ void step_prologue(const StepArgs& a, int t, int m) {
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Sum over the 64 lanes, in lane 63, by DPP additions: prefix sums within the
+// rows of 16 lanes, then row 0 into row 1 and row 2 into row 3, then the lower
+// half into the upper one.  A fixed order, no LDS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
+}
+__device__ __forceinline__ float wave_add63(float v) {
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);   // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);   // row_shr:8
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
 // Update and convergence test of seed j from its sums v[0..D) = sum w (x - s)
 // (packed units) and v[D] = sum w.  Returns 1 if the seed stays active, 2 if
 // it converged, 0 otherwise.  update_seed takes a slot of the active list.
