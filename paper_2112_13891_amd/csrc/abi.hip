@@ -677,6 +677,7 @@ void seed_args_runs(SeedArgs& a, const RunIndex& r) {
     a.poff = r.poff;
     a.run_bound = r.run_bound;
     a.tile_start = r.tile_start;
+    a.run_cap = (r.sz.pmax + kFarRuns + 63) / 64 * 64;
 }
 
 // Arguments of that form from the batch; the tiles are the packed (n small,
@@ -1139,6 +1140,17 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
     return MS_OK;
 }
 
+// Seeds of a step call into the batch of the seed form.
+int load_seeds(const float* seeds, const uint8_t* converged, int d, int m, Batch& b, int n_iter, hipStream_t s) {
+    if (b.metric == MS_METRIC_COSINE) {
+        FMS_HIP(launch_ctl_reset(b.ctl, 0, INT_MAX, n_iter, s));
+        FMS_HIP(launch_seed_init_from_array(seeds, converged, d, m, b, s));
+    } else {
+        FMS_HIP(launch_seed_load(seeds, converged, d, m, b, s));
+    }
+    return MS_OK;
+}
+
 // Bump allocation out of one device buffer of fixed size, with no allocation
 // call: every request is rounded up to 256 bytes.  With a NULL base it only
 // counts, so that a dry run can size a call before anything is launched.
@@ -1213,8 +1225,7 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
         if (!run) return MS_OK;
         if (form == SEED_RUNS) FMS_HIP(launch_run_index(ri, X, nullptr, n, scale, run_far(p), s));
         else FMS_HIP(launch_pack_tiles(X, n, d, sh.D, scale, tiles, s));
-        FMS_HIP(launch_ctl_reset(b.ctl, 0, INT_MAX, n_iter, s));
-        FMS_HIP(launch_seed_init_from_array(seeds, converged, d, m, b, s));
+        FMS_CHECK(load_seeds(seeds, converged, d, m, b, n_iter, s));
         SeedArgs a = seed_args(b, p, tiles, nullptr, n_iter);
         a.ctl = nullptr;
         if (form == SEED_RUNS) seed_args_runs(a, ri);
@@ -1223,7 +1234,7 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
             seed_args_order(a, rs);
         }
         FMS_HIP(launch_seed_iterate(a, sh.D, p->kernel, ssh, (m + ssh.R - 1) / ssh.R, s));
-        FMS_HIP(launch_seed_export(b, m, seeds, converged, iters, shift2, s));
+        FMS_HIP(launch_seed_store(b, m, seeds, converged, iters, shift2, s));
         return MS_OK;
     }
     const size_t rows = seedf ? (size_t)(n + 63) / 64 * 64 : (size_t)n;   // whole tiles
@@ -1260,8 +1271,12 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
     FMS_CHECK(ws.alloc(&b.shift2, m));
     FMS_CHECK(ws.alloc(&b.part, seedf ? 1 : (size_t)step_part_floats(sh, m, b.grid)));
     if (!run) return MS_OK;
-    FMS_HIP(launch_ctl_reset(ctl, 0, INT_MAX, n_iter, s));
-    FMS_HIP(launch_seed_init_from_array(seeds, converged, d, m, b, s));
+    if (seedf) {
+        FMS_CHECK(load_seeds(seeds, converged, d, m, b, n_iter, s));
+    } else {
+        FMS_HIP(launch_ctl_reset(ctl, 0, INT_MAX, n_iter, s));
+        FMS_HIP(launch_seed_init_from_array(seeds, converged, d, m, b, s));
+    }
     if (sorted && (!seedf || ssh.R > 1))   // seeds that are close in space share waves (refine work, culled blocks)
         FMS_HIP(launch_seed_order(b.S, sh.DP, sh.D, m, scale, b.status, sp.sws, b.act[0], Xp, n, s));
     if (seedf) {
@@ -1269,9 +1284,10 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
         a.ctl = nullptr;
         if (sorted && ssh.R > 1) a.order = b.act[0];
         FMS_HIP(launch_seed_iterate(a, sh.D, p->kernel, ssh, (m + ssh.R - 1) / ssh.R, s));
-    } else {
-        for (int t = 0; t < n_iter; ++t) FMS_HIP(launch_iteration(b, t, s));
+        FMS_HIP(launch_seed_store(b, m, seeds, converged, iters, shift2, s));
+        return MS_OK;
     }
+    for (int t = 0; t < n_iter; ++t) FMS_HIP(launch_iteration(b, t, s));
     FMS_HIP(launch_seed_export(b, m, seeds, converged, iters, shift2, s));
     return MS_OK;
 #undef FMS_RUN
@@ -1377,7 +1393,18 @@ struct BatchedPrepared {
     const int32_t* so_dev;
     DevCache* cache;          // the calling fit's cache for the step's buffers (kept across calls), or NULL
     const BatchedBf16* bb;    // the BF16 form: the points' order and features (prepared once), else NULL
+    const RunIndex* ri;       // the seed form: the clouds' pivot runs, else NULL
 };
+
+// Whether a batched call runs a workgroup per seed over the clouds' pivot runs
+// (k_seed.hip): FP32, up to d = 32, and no launch shape asked for or tuned
+// for this kind of input (those name shapes of the tile form).
+bool batched_seed_form(const ms_params* p, int d, long long n, long long M, int ncl, int R_force) {
+    if (p->precision != MS_PREC_FP32 || d > 32 || n < 1 || M < 1) return false;
+    if (R_force || p->tile_R || p->tile_chunk || p->tile_grid) return false;
+    std::lock_guard<std::mutex> lock(g_tune_mu);
+    return g_tune.find(tune_key(d, n, M, ncl, p->precision)) == g_tune.end();
+}
 
 // The BF16 form over many clouds (Gaussian, padded D in {8, 16, 32}): each
 // cloud's points in the spatial order of the one-cloud form (its own pivots),
@@ -1455,6 +1482,59 @@ int prepare_batched_bf16_seeds(Workspace& ws, const std::vector<int32_t>& so, in
     return MS_OK;
 }
 
+// The seed form of a batched step call: all updates in one launch.
+int step_batched_seeds(const ms_params* p, const float* X, const int64_t* x_off, float* seeds,
+                       const int64_t* s_off, int ncl, int d, int n_iter, uint8_t* converged, int32_t* iters,
+                       float* shift2, hipStream_t s, const BatchedPrepared* pre) {
+    const int M = (int)s_off[ncl];
+    const float scale = packed_scale(p);
+    const StepShape sh = step_shape(d);
+    Batch b;
+    fill_batch(b, (int)x_off[ncl], d, M, sh, p, scale, nullptr, nullptr);
+    RunIndex own;
+    const RunSizes sz = pre ? RunSizes{} : run_sizes(reinterpret_cast<const long long*>(x_off), ncl);
+    long long* xod = nullptr;
+    int32_t* sod = nullptr;
+    auto take = [&](auto& ws) -> int {
+        auto alloc = [&](auto** out, size_t c) { return ws.alloc(out, c); };
+        if (!pre) {
+            FMS_CHECK(run_index_alloc(own, sz, d, false, alloc));
+            FMS_CHECK(ws.alloc(&xod, (size_t)ncl + 1));
+            FMS_CHECK(ws.alloc(&sod, (size_t)ncl + 1));
+        }
+        FMS_CHECK(ws.alloc(&b.S, (size_t)M * sh.DP));
+        FMS_CHECK(ws.alloc(&b.status, (size_t)M));
+        FMS_CHECK(ws.alloc(&b.iters, (size_t)M));
+        return ws.alloc(&b.shift2, (size_t)M);
+    };
+    Arena need(nullptr, 0);
+    FMS_CHECK(take(need));
+    Workspace ws(s);
+    AllocBudget budget;
+    char* base;
+    if (pre && pre->cache) FMS_CHECK(cache_get(*pre->cache, budget, SL_BSTEP_S, need.used(), &base));
+    else FMS_CHECK(ws.alloc(&base, need.used()));
+    Arena mem(base, need.used());
+    FMS_CHECK(take(mem));
+    const RunIndex* ri = pre ? pre->ri : &own;
+    const int32_t* so_dev = pre ? pre->so_dev : sod;
+    if (!pre) {
+        std::vector<int32_t> so(s_off, s_off + ncl + 1);
+        FMS_HIP(hipMemcpyAsync(xod, x_off, (size_t)(ncl + 1) * sizeof(long long), hipMemcpyHostToDevice, s));
+        FMS_HIP(hipMemcpyAsync(sod, so.data(), (size_t)(ncl + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
+        FMS_HIP(hipStreamSynchronize(s));   // the host copies of the offsets go out of scope
+        FMS_HIP(launch_run_index(own, X, xod, 0, scale, run_far(p), s));
+    }
+    FMS_HIP(launch_seed_load(seeds, converged, d, M, b, s));
+    SeedArgs a = seed_args(b, p, nullptr, nullptr, n_iter);
+    a.ctl = nullptr;
+    seed_args_runs(a, *ri);
+    a.seg = so_dev;
+    FMS_HIP(launch_seed_iterate(a, sh.D, p->kernel, seed_shape_batched(M), M, s));
+    FMS_HIP(launch_seed_store(b, M, seeds, converged, iters, shift2, s));
+    return MS_OK;
+}
+
 int step_batched_impl(const ms_params* p, const float* X, const int64_t* x_off, float* seeds,
                       const int64_t* s_off, int ncl, int d, int n_iter, uint8_t* converged,
                       int32_t* iters, float* shift2, hipStream_t s, int R_force = 0,
@@ -1466,6 +1546,8 @@ int step_batched_impl(const ms_params* p, const float* X, const int64_t* x_off, 
     if (bf && !batched_bf16_ok(p, d))
         return fail(MS_E_INVALID, "the batched BF16 form is built for the Gaussian kernel at 5 <= d <= 32");
     if (bf && pre && !pre->bb) return fail(MS_E_HIP, "the batched BF16 form needs its prepared points");
+    if (pre ? pre->ri != nullptr : batched_seed_form(p, d, n, M, ncl, R_force))
+        return step_batched_seeds(p, X, x_off, seeds, s_off, ncl, d, n_iter, converged, iters, shift2, s, pre);
     StepShape sh = step_shape_for(d, std::max(1, M / ncl));
     // default: at most two seeds per lane up to D = 8 and one above (timed on
     // 512 uneven clouds: more seeds per lane cost occupancy here, and the
@@ -1731,17 +1813,37 @@ int fit_batched_impl(const ms_params* p, const float* X, const int64_t* x_off, i
     q.graph = 0;
     q.tile_R = 0;
     const int DP = step_shape(d).DP;
-    float* Xp;
+    float* Xp = nullptr;
     int32_t* so32_dev;
-    FMS_CHECK(cache_get(C, budget, SL_XP, (size_t)n * DP, &Xp));
     FMS_CHECK(ws.alloc(&so32_dev, (size_t)ncl + 1));
-    FMS_HIP(launch_pack_points(X, (int)n, d, DP, packed_scale(&q), Xp, s));
+    // the clouds' pivot runs, or the packed points for the tile forms (the
+    // kind of input is the first round's)
+    long long M0 = 0;
+    for (int c = 0; c < ncl; ++c) M0 += all ? x_off[c + 1] - x_off[c] : std::min<long long>(p->n_initial, x_off[c + 1] - x_off[c]);
+    RunIndex ri;
+    const bool seedf = batched_seed_form(&q, d, n, M0, ncl, 0);
+    if (seedf) {
+        const RunSizes sz = run_sizes(xo.data(), ncl);
+        auto take = [&](Arena& mem) {
+            return run_index_alloc(ri, sz, d, false, [&](auto** out, size_t c) { return mem.alloc(out, c); });
+        };
+        Arena need(nullptr, 0);
+        FMS_CHECK(take(need));
+        char* base;
+        FMS_CHECK(cache_get(C, budget, SL_XP, need.used(), &base));
+        Arena mem(base, need.used());
+        FMS_CHECK(take(mem));
+        FMS_HIP(launch_run_index(ri, X, xo_dev, 0, packed_scale(&q), run_far(p), s));
+    } else {
+        FMS_CHECK(cache_get(C, budget, SL_XP, (size_t)n * DP, &Xp));
+        FMS_HIP(launch_pack_points(X, (int)n, d, DP, packed_scale(&q), Xp, s));
+    }
     // the BF16 form: the clouds' spatial order and block features, once per
     // call (a round's seeds are never more than the points)
     BatchedBf16 bb;
     const bool bf = p->precision == MS_PREC_BF16_REFINE;
     if (bf) FMS_CHECK(prepare_batched_bf16_points(ws, Xp, (int)n, step_shape(d).D, xo, xo_dev, ncl, (int)n, bb, s));
-    const BatchedPrepared pre{Xp, DP, xo_dev, so32_dev, &C, bf ? &bb : nullptr};
+    const BatchedPrepared pre{Xp, DP, xo_dev, so32_dev, &C, bf ? &bb : nullptr, seedf ? &ri : nullptr};
     FMS_HIP(launch_bf_iota(xo_dev, ncl, pool[0], n, s));
     FMS_HIP(launch_bf_fill_i32(kcnt_dev, ncl, 0, s));
     FMS_HIP(launch_fill_u8(removed, (int)n, 0, s));
@@ -1798,7 +1900,11 @@ int fit_batched_impl(const ms_params* p, const float* X, const int64_t* x_off, i
         FMS_HIP(launch_fill_u8(conv_dev, (int)M, 0, s));
         t_draw = ms_since(t_round);
         // iterations until the round is over for every seed
-        for (int done = 0; done < p->max_iter;) {
+        if (seedf) {   // every seed to its end in one launch
+            FMS_CHECK(step_batched_impl(&q, X, x_off, S_dev, hso, ncl, d, p->max_iter, conv_dev, it_dev, sh2_dev, s, 0,
+                                        nullptr, &pre));
+        }
+        for (int done = 0; !seedf && done < p->max_iter;) {
             const int k = std::min(kChunk, p->max_iter - done);
             FMS_CHECK(step_batched_impl(&q, X, x_off, S_dev, hso, ncl, d, k, conv_dev, it_dev, sh2_dev, s, 0,
                                         nullptr, &pre));

@@ -206,6 +206,7 @@ struct SeedArgs {
     const int32_t* poff = nullptr;
     const float* run_bound = nullptr;
     const int32_t* tile_start = nullptr;
+    int run_cap = 0;               // runs of the largest cloud, rounded up to 64
     const int32_t* seg = nullptr;
     // one cloud, optional: each seed's nearest pivot, a bound of its distance,
     // and the distances between the pivots
@@ -220,6 +221,12 @@ struct SeedShape {
     int nw;   // waves per workgroup
 };
 SeedShape seed_shape(int D, long long m);
+SeedShape seed_shape_batched(long long m);
+// Seeds of a step call in and out (Euclidean metric; cosine seeds are made
+// unit vectors by launch_seed_init_from_array).
+hipError_t launch_seed_load(const float* seeds, const uint8_t* conv_in, int d, int m, Batch& b, hipStream_t s);
+hipError_t launch_seed_store(const Batch& b, int m, float* seeds, uint8_t* conv, int32_t* iters, float* shift2,
+                             hipStream_t s);
 hipError_t launch_seed_iterate(SeedArgs a, int D, int kernel, const SeedShape& sh, int wgs, hipStream_t s);
 // D <= 4: fills the tail of the last tile of n rows of 4 floats and writes the
 // tile balls (geom NULL: the tail only).
@@ -244,6 +251,7 @@ struct RunSizes {
     int ncl = 0;
     int n = 0;
     int ptot = 0;        // pivots
+    int pmax = 0;        // pivots of the largest cloud
     int ptiles = 0;      // 32-pivot tiles
     int rtiles = 0;      // 256-row tiles
     int runs = 0;        // ptot + kFarRuns * ncl

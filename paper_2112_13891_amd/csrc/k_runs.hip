@@ -414,6 +414,7 @@ __global__ __launch_bounds__(256) void pivot_pairs_kernel(const float* __restric
 void add_cloud(RunSizes& z, long long nc) {
     const int P = run_pivots(nc);
     z.ptot += P;
+    z.pmax = std::max(z.pmax, P);
     z.ptiles += (P + 31) / 32;
     z.rtiles += (int)((nc + 255) / 256);
 }

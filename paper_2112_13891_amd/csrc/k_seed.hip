@@ -32,9 +32,9 @@
 //
 // What a tile may be left out for (the Gaussian): every pair of it is beyond
 // the distance where the FP32 weight is exactly zero (q >= 150; the test uses
-// 160), or has a weight below 2^-64 of the seed's weight sum W.  At most n
-// such terms are dropped, in total below n 2^-64 W <= 2^-33 W, where an FP32
-// sum rounds at 2^-25 W.  W is bounded from below without any sum: a ball of
+// 160), or has a weight below 2^-33 / n of the seed's weight sum W.  At most n
+// such terms are dropped, in total below 2^-33 W, where an FP32 sum rounds at
+// 2^-25 W.  W is bounded from below without any sum: a ball of
 // radius r at distance c holds a point within c + r (a pivot is a point
 // itself), so W >= 2^-(c + r)^2 for the nearest one; after the first update
 // the W of the previous one serves (a mean-shift step never lowers the
@@ -59,18 +59,19 @@ namespace fms {
 namespace {
 
 constexpr float kSeedZero = 160.0f;      // exp2(-q) == +0 in FP32 for q >= 150
-constexpr float kSeedNegligible = 64.0f; // weights below 2^-64 of the sum change no FP32 sum
+constexpr float kSeedDropped = 33.0f;    // the terms left out are below 2^-33 of the sum in all
 constexpr float kSeedFlatMargin = 1.001f;
 constexpr float kSlack = 0.25f;          // packed units
-constexpr int kRunListMax = kRunPivotMax + 64;   // runs of a cloud, whole groups
 constexpr int kSegGroups = 96;           // groups of 64 tiles listed at once (24 KB: six workgroups a CU)
 constexpr int kSeedMaxWaves = 16;
+// waves per SIMD the register count must allow
+constexpr int seed_min_waves(int D) { return D == 32 ? 3 : 4; }
 constexpr int kXcdRun = 64;
 // wide rows need the registers that 16 waves in one workgroup would not have
 constexpr int seed_max_waves(int D, int R) { return R > 1 ? 4 : (D <= 4 ? kSeedMaxWaves : 8); }
 
 template <int D, int R, int KERN, bool RUNS>
-__global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel(SeedArgs a) {
+__global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void seed_iterate_kernel(SeedArgs a) {
     constexpr int DP = D <= 4 ? 4 : D;
     constexpr int G4 = DP / 4;
     constexpr int V = D + 1;
@@ -106,12 +107,18 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel
     // listed run and `list_pre` the tiles listed before it; a lower bound of a
     // seed's distance from every pivot stays in `dist_s`.  The top bits of an entry say which of
     // the R seeds reach it.
-    constexpr int kList = RUNS ? kRunListMax : kSegGroups * 64;
-    __shared__ unsigned list[kList];
-    __shared__ int list_pre[RUNS ? kRunListMax + 1 : 1];
-    __shared__ float dist_s[RUNS ? kRunPivotMax * R : 1];
-    __shared__ unsigned long long near_mask[RUNS ? kRunListMax / 64 : kSegGroups];
-    __shared__ unsigned char near_who[R > 1 ? kList : 1];
+    // (Runs: sized by the largest cloud, so that many small clouds' workgroups
+    // fit a CU.)
+    __shared__ unsigned rows_list[RUNS ? 1 : kSegGroups * 64];
+    __shared__ unsigned long long rows_mask[RUNS ? 1 : kSegGroups];
+    __shared__ unsigned char near_who[RUNS || R == 1 ? 1 : kSegGroups * 64];
+    extern __shared__ __attribute__((aligned(16))) unsigned long long dyn[];
+    static_assert(!RUNS || R == 1, "runs: one seed per workgroup");
+    const int cap = a.run_cap;   // whole groups
+    unsigned long long* const near_mask = RUNS ? dyn : rows_mask;
+    unsigned* const list = RUNS ? reinterpret_cast<unsigned*>(dyn + cap / 64) : rows_list;
+    int* const list_pre = reinterpret_cast<int*>(list + cap);   // cap + 1
+    float* const dist_s = reinterpret_cast<float*>(list_pre + cap + 1);
 
     // lane (r, k) holds coordinate k of seed r, in every wave
     const int r_of = lane / DP, k_of = lane % DP;
@@ -138,6 +145,9 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel
     // one update to the next.
     const int groups = (nball + 63) / 64;
     const bool keep = RUNS || groups <= kSegGroups;
+    int points = nball * 64;
+    if constexpr (RUNS) points = (a.tile_start[run0 + nball + kFarRuns] - a.tile_start[run0]) * 64;
+    const float negligible = kSeedDropped + __builtin_amdgcn_logf((float)points) + 0.01f;
     const float4* __restrict__ T4 = reinterpret_cast<const float4*>(a.T);
 
     float reach[R], rq[R], wprev[R], last_sh2[R];   // reach and its square
@@ -237,7 +247,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel
                 balls(0, groups, [&](int g, int r, bool in, float dist, float rad) {
                     if (in) {
                         ub[r] = fminf(ub[r], dist + rad);   // a NaN never lowers it
-                        if (RUNS) dist_s[r * kRunPivotMax + g * 64 + lane] = dist;
+                        if (RUNS) dist_s[g * 64 + lane] = dist;
                     }
                 });
 #pragma unroll
@@ -259,7 +269,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel
                 if (KERN == MS_KERNEL_GAUSSIAN) {
                     // -log2 W, at most (1 of margin on the previous update's)
                     const float q = it == 0 ? ub[r] * ub[r] : 1.0f - __builtin_amdgcn_logf(wprev[r]);
-                    rq[r] = fminf(kSeedZero, fmaxf(kSeedNegligible + q, 1.0f));
+                    rq[r] = fminf(kSeedZero, fmaxf(negligible + q, 1.0f));
                     reach[r] = sqrtf(rq[r]);
                 } else {
                     reach[r] = a.flat_reach;
@@ -281,7 +291,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel
                         bool out;
                         if (e < nball) {
                             float l;
-                            float& kept = dist_s[r * kRunPivotMax + e];
+                            float& kept = dist_s[e];
                             if (by_row) l = id[r] >= 0 ? a.ppair[(long long)a.pnear[id[r]] * nball + e] - ub[r] : 0.0f;
                             else l = kept - (it > 0 ? moved[r] : 0.0f);
                             if ((by_row || it > 0) && !(l - bound > lim)) {
@@ -311,7 +321,6 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel
                     if (e < nrun && a.tile_start[run0 + e] == a.tile_start[run0 + e + 1]) who = 0;
                     const unsigned long long mk = __ballot(who != 0);
                     if (lane == 0) near_mask[g] = mk;
-                    if (R > 1) near_who[e] = (unsigned char)who;
                 }
                 __syncthreads();
                 // entries before each group, then the entries with their tiles
@@ -332,7 +341,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel
                     if ((mk >> lane) & 1ull) {
                         const int e = g * 64 + lane, q = at + __popcll(mk & ((1ull << lane) - 1ull));
                         const int t = a.tile_start[run0 + e];
-                        list[q] = (unsigned)t | (R > 1 ? (unsigned)near_who[e] << 28 : 0u);
+                        list[q] = (unsigned)t;
                         list_pre[q] = a.tile_start[run0 + e + 1] - t;
                     }
                 }
@@ -487,6 +496,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R)) void seed_iterate_kernel
                                 dx[k] = x[k] - s[r][k];
                                 q = fmaf(dx[k], dx[k], q);
                             }
+                            if (!__ballot(!(q > rq[r] && q < 3e38f))) continue;
                         }
                         float w;
                         if (KERN == MS_KERNEL_GAUSSIAN)
@@ -660,6 +670,35 @@ __global__ __launch_bounds__(256) void tile_ball_kernel(float* T, int n, int til
     }
 }
 
+// Seeds of a step call in (m x d, stride d) and out, one coordinate per thread.
+__global__ void seed_load_kernel(const float* __restrict__ seeds, const uint8_t* __restrict__ conv_in, int d, int DP,
+                                 int m, float* S, uint8_t* status, int32_t* iters, float* shift2) {
+    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (long long)m * DP) return;
+    const int j = (int)(e / DP), k = (int)(e % DP);
+    S[e] = k < d ? seeds[(long long)j * d + k] : 0.0f;
+    if (k == 0) {
+        status[j] = conv_in[j];
+        iters[j] = 0;
+        shift2[j] = __builtin_nanf("");
+    }
+}
+
+__global__ void seed_store_kernel(const float* __restrict__ S, int DP, int d, int m,
+                                  const uint8_t* __restrict__ status, const int32_t* __restrict__ it,
+                                  const float* __restrict__ sh, float* seeds, uint8_t* conv, int32_t* iters,
+                                  float* shift2) {
+    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (long long)m * d) return;
+    const int j = (int)(e / d), k = (int)(e % d);
+    seeds[e] = S[(long long)j * DP + k];
+    if (k == 0) {
+        conv[j] = status[j];
+        iters[j] = it[j];
+        if (it[j] > 0) shift2[j] = sh[j];
+    }
+}
+
 // D >= 8: rows to tiles as they are, with the tail filled up (no balls).
 __global__ void pack_tiles_kernel(const float* __restrict__ X, int n, int d, int D, float scale, float* T) {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -676,14 +715,33 @@ __global__ void pack_tiles_kernel(const float* __restrict__ X, int n, int d, int
 
 template <int D, int R, bool RUNS>
 hipError_t launch_seed_t(const SeedArgs& a, int kernel, int wgs, int nw, hipStream_t s) {
+    // masks, list, counts, pivot distances
+    const size_t lds = RUNS ? (size_t)a.run_cap / 64 * 8 + (size_t)a.run_cap * 12 + 16 : 0;
     if (kernel == MS_KERNEL_GAUSSIAN)
-        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN, RUNS>), dim3(wgs), dim3(64 * nw), 0, s, a);
+        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN, RUNS>), dim3(wgs), dim3(64 * nw), lds, s,
+                           a);
     else
-        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT, RUNS>), dim3(wgs), dim3(64 * nw), 0, s, a);
+        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT, RUNS>), dim3(wgs), dim3(64 * nw), lds, s, a);
     return hipGetLastError();
 }
 
 }  // namespace
+
+hipError_t launch_seed_load(const float* seeds, const uint8_t* conv_in, int d, int m, Batch& b, hipStream_t s) {
+    if (b.metric == MS_METRIC_COSINE) return hipErrorInvalidValue;   // unit seeds: launch_seed_init_from_array
+    const long long total = (long long)m * b.sh.DP;
+    hipLaunchKernelGGL(seed_load_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, seeds, conv_in, d,
+                       b.sh.DP, m, b.S, b.status, b.iters, b.shift2);
+    return hipGetLastError();
+}
+
+hipError_t launch_seed_store(const Batch& b, int m, float* seeds, uint8_t* conv, int32_t* iters, float* shift2,
+                             hipStream_t s) {
+    const long long total = (long long)m * b.d;
+    hipLaunchKernelGGL(seed_store_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, b.S, b.sh.DP, b.d,
+                       m, b.status, b.iters, b.shift2, seeds, conv, iters, shift2);
+    return hipGetLastError();
+}
 
 hipError_t launch_pack_tiles(const float* X, int n, int d, int D, float scale, float* T, hipStream_t s) {
     const long long total = (long long)((n + 63) / 64) * (D / 4) * 64;
@@ -733,6 +791,14 @@ SeedShape seed_shape(int D, long long m) {
         sh.R = 1;
         sh.nw = m <= 512 ? 8 : (m <= 2048 ? 4 : 2);
     }
+    return sh;
+}
+
+// The seeds of many clouds: one per workgroup.
+SeedShape seed_shape_batched(long long m) {
+    SeedShape sh;
+    sh.R = 1;
+    sh.nw = m <= 512 ? 8 : (m <= 2048 ? 4 : (m <= 8192 ? 2 : 1));
     return sh;
 }
 
