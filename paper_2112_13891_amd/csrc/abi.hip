@@ -2215,6 +2215,12 @@ int ms_forward_update(const void* X, int32_t nbatch, int64_t n, const void* S_in
     FMS_CHECK(ensure_pool_release_threshold());
     Workspace ws(s);
     char* w;
+    if (dtype_bytes == 4 && adjoint_runs_ok(nbatch, (int)n, (int)m, d, false)) {
+        FMS_CHECK(ws.alloc(&w, adjoint_runs_bytes(nbatch, (int)n, (int)m, d, S_in == X && m == n, false)));
+        FMS_HIP(launch_adjoint_runs((const float*)X, nbatch, (int)n, (const float*)S_in, (int)m, d, h, (float*)S_out,
+                                    nullptr, nullptr, nullptr, w, s));
+        return MS_OK;
+    }
     FMS_CHECK(ws.alloc(&w, adjoint_workspace_bytes(nbatch, (int)n, (int)m, d, dtype_bytes)));
     FMS_HIP(launch_forward_update(X, nbatch, (int)n, S_in, (int)m, d, h, S_out, dtype_bytes, w, s));
     return MS_OK;
@@ -2229,6 +2235,12 @@ int ms_step_adjoint(const void* X, int32_t nbatch, int64_t n, const void* S, int
     FMS_CHECK(ensure_pool_release_threshold());
     Workspace ws(s);
     char* w;
+    if (dtype_bytes == 4 && adjoint_runs_ok(nbatch, (int)n, (int)m, d, true)) {
+        FMS_CHECK(ws.alloc(&w, adjoint_runs_bytes(nbatch, (int)n, (int)m, d, S == X && m == n, true)));
+        FMS_HIP(launch_adjoint_runs((const float*)X, nbatch, (int)n, (const float*)S, (int)m, d, h, nullptr,
+                                    (const float*)G, (float*)dS, (float*)dX, w, s));
+        return MS_OK;
+    }
     FMS_CHECK(ws.alloc(&w, adjoint_workspace_bytes(nbatch, (int)n, (int)m, d, dtype_bytes)));
     FMS_HIP(launch_step_adjoint(X, nbatch, (int)n, S, (int)m, d, h, G, dS, dX, dtype_bytes, w, s));
     return MS_OK;

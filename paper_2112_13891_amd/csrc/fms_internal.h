@@ -21,6 +21,7 @@ constexpr int kMaxIterCap = 4096;   // hard cap on max_iter / n_iter
 constexpr int kMaxMergePasses = 64;
 constexpr int kFarRuns = 16;        // far runs of a cloud (k_runs.hip)
 constexpr int kRunPivotMax = 1024;  // pivots of a cloud (k_runs.hip)
+constexpr int kRunPoints = 128;     // points per pivot, below that many pivots
 // BF16 forms: the refined-pair count is spread over counters 128 bytes apart
 // (a workgroup adds its count to counter workgroup % kRefinedSlots), so that
 // the workgroups of a launch do not queue on one address at the end of the
@@ -264,6 +265,9 @@ struct RunIndex {
     RunSizes sz;
     int D = 0, DP = 0, d = 0;
     float* tiles = nullptr;      // max_tiles x 64 x DP, the layout of k_seed.hip
+    float* pivot_rows = nullptr; // the pivots' rows (tile units, stride DP; row-major indexes only)
+    float* ball_rows = nullptr;  // centre of each near run's points and, at DP, their largest distance from it
+                                 // (packed units; stride DP + 4; row-major indexes only)
     float* pivots = nullptr;     // coordinate k of pivot j (packed units) at [k * ptot + j]
     float* run_bound = nullptr;  // largest distance of a near run's points from its pivot (at most this);
                                  // of a far run, the least distance of its points from any pivot
@@ -279,6 +283,9 @@ struct RunIndex {
     char* radix = nullptr;
     float scale = 1.0f, far = 8.0f;
     const float* X = nullptr;
+    // tiles as 64 rows of DP coordinates in the input's own units (bounds stay
+    // in packed units), for kernels that stream rows through scalar loads
+    bool row_major = false;
 };
 // Takes the index's buffers through alloc(T** out, size_t count) -> int.
 template <class F>
@@ -293,7 +300,12 @@ int run_index_alloc(RunIndex& r, const RunSizes& sz, int d, bool keep_rows, F&& 
     int rc = 0;
     auto get = [&](auto** p, size_t c) { if (rc == 0) rc = alloc(p, c); };
     get(&r.tiles, T * 64 * sh.DP);
-    get(&r.pivots, (size_t)sz.ptot * sh.D);
+    if (r.row_major) {
+        get(&r.pivot_rows, (size_t)sz.ptot * sh.DP);
+        get(&r.ball_rows, (size_t)sz.ptot * (sh.DP + 4));
+    } else {
+        get(&r.pivots, (size_t)sz.ptot * sh.D);
+    }
     get(&r.run_bound, (size_t)sz.runs);
     if (keep_rows) get(&r.rows, T * 64);
     get(&r.xo, (size_t)sz.ncl + 1);
@@ -536,6 +548,14 @@ hipError_t launch_assign(const float* X, int n, int d, const float* modes, int k
                          int32_t* labels, float* margin, hipStream_t s);
 hipError_t launch_check_finite(const float* X, long long count, int32_t* flag,
                                hipStream_t s);
+
+// ---- launchers (k_adjoint_runs.hip): FP32 differentiable form over pivot runs --
+// For n_each points and m_each seeds in each of nb clouds; ws:
+// adjoint_runs_bytes() bytes.
+bool adjoint_runs_ok(int nb, int n, int m, int d, bool adjoint);
+size_t adjoint_runs_bytes(int nb, int n, int m, int d, bool same, bool adjoint);
+hipError_t launch_adjoint_runs(const float* X, int nb, int n, const float* S, int m, int d, double h, float* S_out,
+                               const float* G, float* dS, float* dX, void* ws, hipStream_t s);
 
 // ---- launchers (k_adjoint.hip) -------------------------------------------
 // ws: device workspace of adjoint_workspace_bytes() bytes.

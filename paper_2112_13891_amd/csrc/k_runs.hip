@@ -34,7 +34,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 __device__ __forceinline__ int pivots_of(long long nc) {
     if (nc <= 0) return 0;
-    const long long P = nc / 256;
+    const long long P = nc / kRunPoints;
     return (int)(P < 1 ? 1 : (P > kRunPivotMax ? kRunPivotMax : P));
 }
 
@@ -106,8 +106,8 @@ template <int KB>
 __global__ __launch_bounds__(64) void run_pivots_kernel(const float* __restrict__ X, int d, float scale,
                                                         const long long* __restrict__ xo,
                                                         const int32_t* __restrict__ poff,
-                                                        const int32_t* __restrict__ ptoff, int ncl, int D, int ptot,
-                                                        float* pivots, char* frag) {
+                                                        const int32_t* __restrict__ ptoff, int ncl, int D, int DP, int ptot,
+                                                        float* pivots, float* pivot_rows, char* frag) {
     const int c = upper_cloud(ptoff, ncl, blockIdx.x);
     const int lane = threadIdx.x, half = lane >> 5;
     const int P = poff[c + 1] - poff[c];
@@ -125,7 +125,8 @@ __global__ __launch_bounds__(64) void run_pivots_kernel(const float* __restrict_
         for (int e = 0; e < 8; ++e) {
             const int k = kb * 16 + half * 8 + e;
             const float v = (live && k < d) ? (row[k] - ref[k]) * scale : 0.0f;
-            if (live && k < D) pivots[(long long)k * ptot + poff[c] + j] = k < d ? row[k] * scale : 0.0f;
+            if (pivots && live && k < D) pivots[(long long)k * ptot + poff[c] + j] = k < d ? row[k] * scale : 0.0f;
+            if (pivot_rows && live && k < DP) pivot_rows[(long long)(poff[c] + j) * DP + k] = k < d ? row[k] : 0.0f;
             nn = fmaf(v, v, nn);
             hi[e] = (__bf16)v;
             lo[e] = (__bf16)(v - (float)hi[e]);
@@ -349,8 +350,8 @@ __global__ __launch_bounds__(256) void run_fill_kernel(const float* __restrict__
                                                        const int32_t* __restrict__ start,
                                                        const int32_t* __restrict__ tile_start,
                                                        const int32_t* __restrict__ tile_run, int runs,
-                                                       const int32_t* __restrict__ poff, int ncl, float* tiles,
-                                                       float* bound, int32_t* rows) {
+                                                       const int32_t* __restrict__ poff, int ncl, int row_major,
+                                                       float* tiles, float* bound, int32_t* rows) {
     constexpr int DP = D <= 4 ? 4 : D;
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (t >= tile_start[runs]) return;
@@ -393,10 +394,65 @@ __global__ __launch_bounds__(256) void run_fill_kernel(const float* __restrict__
         else atomicMax(reinterpret_cast<int*>(bound) + r, __float_as_int(fmaxf(v, 0.0f)));
     }
     if (!live) x[0] = kPadCoord;
-    float4* out = reinterpret_cast<float4*>(tiles) + (long long)t * (DP / 4) * 64 + lane;
+    const int ostep = row_major ? 1 : 64;
+    float4* out = reinterpret_cast<float4*>(tiles) + (long long)t * (DP / 4) * 64 + lane * (row_major ? DP / 4 : 1);
 #pragma unroll
-    for (int q = 0; q < DP / 4; ++q) out[q * 64] = make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+    for (int q = 0; q < DP / 4; ++q) out[q * ostep] = make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
     if (rows) rows[t * 64 + lane] = row;
+}
+
+// Ball of each near run of a row-major index, one wave per run: the mean of its
+// rows and the largest distance from it (packed units, rounded up).  In 16-D a
+// ball around the mean of 256 points has 0.7 of the radius around one of them.
+template <int D>
+__global__ __launch_bounds__(256) void run_ball_kernel(const float* __restrict__ tiles,
+                                                       const int32_t* __restrict__ start,
+                                                       const int32_t* __restrict__ tile_start,
+                                                       const int32_t* __restrict__ poff, int ncl, float scale,
+                                                       float* balls) {
+    constexpr int DP = D <= 4 ? 4 : D;
+    const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (j >= poff[ncl]) return;
+    const int r = j + kFarRuns * upper_cloud(poff, ncl, j);
+    const int cnt = start[r + 1] - start[r];
+    const float4* src = reinterpret_cast<const float4*>(tiles) + (long long)tile_start[r] * 64 * (DP / 4);
+    auto row = [&](int i, float (&x)[DP]) {
+#pragma unroll
+        for (int q = 0; q < DP / 4; ++q) {
+            const float4 v = src[(long long)i * (DP / 4) + q];
+            x[4 * q] = v.x;
+            x[4 * q + 1] = v.y;
+            x[4 * q + 2] = v.z;
+            x[4 * q + 3] = v.w;
+        }
+    };
+    float c[DP];
+#pragma unroll
+    for (int k = 0; k < DP; ++k) c[k] = 0.0f;
+    for (int i = lane; i < cnt; i += 64) {
+        float x[DP];
+        row(i, x);
+#pragma unroll
+        for (int k = 0; k < DP; ++k) c[k] += x[k];
+    }
+    const float inv = 1.0f / (float)(cnt > 0 ? cnt : 1);
+#pragma unroll
+    for (int k = 0; k < DP; ++k) c[k] = k < D ? lane_value(wave_add63(c[k]), 63) * inv : 0.0f;
+    float r2 = 0.0f;
+    for (int i = lane; i < cnt; i += 64) {
+        float x[DP], q = 0.0f;
+        row(i, x);
+#pragma unroll
+        for (int k = 0; k < D; ++k) q = fmaf(x[k] - c[k], x[k] - c[k], q);
+        r2 = fmaxf(r2, q);
+    }
+    r2 = -lane_value(wave_min63(-r2), 63);
+    if (lane == 0) {
+        float* o = balls + (long long)j * (DP + 4);
+#pragma unroll
+        for (int k = 0; k < DP; ++k) o[k] = c[k];
+        o[DP] = sqrtf(r2) * scale * 1.0001f + 1e-30f;
+    }
 }
 
 // Distances between the pivots, rounded down (1e-4 relative).
@@ -442,7 +498,7 @@ int radix_passes(int runs) {
 
 int run_pivots(long long nc) {
     if (nc <= 0) return 0;
-    return (int)std::max(1LL, std::min((long long)kRunPivotMax, nc / 256));
+    return (int)std::max(1LL, std::min((long long)kRunPivotMax, nc / kRunPoints));
 }
 
 RunSizes run_sizes(const long long* x_off, int ncl) {
@@ -473,7 +529,7 @@ hipError_t launch_run_index(RunIndex& r, const float* X, const long long* xo_src
     hipLaunchKernelGGL(run_plan_kernel, dim3(1), dim3(1024), 0, s, xo_src, n_each, z.ncl, r.xo, r.poff, r.ptoff,
                        r.rtoff);
     FMS_KB(r.D, hipLaunchKernelGGL((run_pivots_kernel<KB>), dim3(z.ptiles), dim3(64), 0, s, X, r.d, scale, r.xo,
-                                   r.poff, r.ptoff, z.ncl, r.D, z.ptot, r.pivots, r.frag));
+                                   r.poff, r.ptoff, z.ncl, r.D, r.DP, z.ptot, r.pivots, r.pivot_rows, r.frag));
     const int vec4 = r.d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
     auto near = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(z.rtiles), dim3(256), 0, s, X, r.d, r.d, scale, r.xo, r.rtoff, z.ncl, -1, X,
@@ -491,9 +547,21 @@ hipError_t launch_run_index(RunIndex& r, const float* X, const long long* xo_src
     const dim3 fg((z.max_tiles + 3) / 4);
 #define FMS_CASE(DD)                                                                                          \
     case DD:                                                                                                  \
-        hipLaunchKernelGGL((run_fill_kernel<DD>), fg, dim3(256), 0, s, X, r.d, scale, vec4, vals, r.dpiv,     \
-                           r.run_start, r.tile_start, r.tile_run, z.runs, r.poff, z.ncl, r.tiles,             \
-                           r.run_bound, r.rows);                                                              \
+        hipLaunchKernelGGL((run_fill_kernel<DD>), fg, dim3(256), 0, s, X, r.d, r.row_major ? 1.0f : scale,    \
+                           vec4, vals, r.dpiv, r.run_start, r.tile_start, r.tile_run, z.runs, r.poff, z.ncl,  \
+                           r.row_major ? 1 : 0, r.tiles, r.run_bound, r.rows);                                                              \
+        break;
+    switch (r.D) {
+        FMS_CASE(1) FMS_CASE(2) FMS_CASE(3) FMS_CASE(4) FMS_CASE(8) FMS_CASE(16) FMS_CASE(32)
+        default: return hipErrorInvalidValue;
+    }
+#undef FMS_CASE
+    if (!r.row_major) return hipGetLastError();
+    const dim3 bg((z.ptot + 3) / 4);
+#define FMS_CASE(DD)                                                                                           \
+    case DD:                                                                                                   \
+        hipLaunchKernelGGL((run_ball_kernel<DD>), bg, dim3(256), 0, s, r.tiles, r.run_start, r.tile_start,      \
+                           r.poff, z.ncl, scale, r.ball_rows);                                                 \
         break;
     switch (r.D) {
         FMS_CASE(1) FMS_CASE(2) FMS_CASE(3) FMS_CASE(4) FMS_CASE(8) FMS_CASE(16) FMS_CASE(32)

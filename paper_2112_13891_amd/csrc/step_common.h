@@ -102,6 +102,22 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+// Minimum over the 64 lanes, in lane 63 (the same steps; a NaN is passed over).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_min(float v) {
+    return fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROWS, 0xf,
+                                                               false)));
+}
+__device__ __forceinline__ float wave_min63(float v) {
+    v = dpp_min<0x111, 0xf>(v);
+    v = dpp_min<0x112, 0xf>(v);
+    v = dpp_min<0x114, 0xf>(v);
+    v = dpp_min<0x118, 0xf>(v);
+    v = dpp_min<0x142, 0xa>(v);
+    v = dpp_min<0x143, 0xc>(v);
+    return v;
+}
+
 // Update and convergence test of seed j from its sums v[0..D) = sum w (x - s)
 // (packed units) and v[D] = sum w.  Returns 1 if the seed stays active, 2 if
 // it converged, 0 otherwise.  update_seed takes a slot of the active list.

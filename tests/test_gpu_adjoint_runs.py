@@ -1,0 +1,90 @@
+"""The FP32 differentiable form over pivot runs against the FP64 autograd
+reference: sizes from which the runs are used, dimensions padded and exact,
+seeds that are the points and seeds that are not, several clouds, data with
+nothing to leave out, and what is added into the caller's arrays."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2112_13891_amd import api  # noqa: E402
+
+DEV = "cuda:0"
+
+
+def _ref(X, S, h, G):
+    """S', dL/dS and dL/dX of one update in FP64 (the whole matrix, on the GPU)."""
+    X, S, G = X.double(), S.double(), G.double()
+    q = (S * S).sum(1)[:, None] + (X * X).sum(1)[None, :] - 2.0 * (S @ X.T)   # FP64: 1e-13 of |x|^2
+    w = torch.exp(-q.clamp_(min=0.0) / (2 * h * h))
+    p = w / w.sum(1, keepdim=True)
+    new = p @ X
+    beta = p * (G @ X.T - (G * new).sum(1, keepdim=True)) / (h * h)
+    dS = beta @ X - beta.sum(1, keepdim=True) * S
+    dX = p.T @ G + beta.T @ S - beta.sum(0)[:, None] * X
+    return new, dS, dX
+
+
+def _cloud(seed, n, d, k, spread=3.0, sigma=0.4):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    c = spread * torch.randn(k, d, generator=g, device=DEV)
+    y = torch.randint(0, k, (n,), generator=g, device=DEV)
+    return (c[y] + sigma * torch.randn(n, d, generator=g, device=DEV)).contiguous()
+
+
+def _close(got, ref, what):
+    # sums of a few thousand FP32 terms, each with some ulps of exp2 and of its
+    # distance: 1e-5 of the largest entry is ten times their worst case
+    err = (got.double() - ref).abs().max().item() / ref.abs().max().item()
+    assert err < 1e-5, (what, err)
+
+
+# nb n m above 2^27
+@pytest.mark.parametrize("nb,n,m,d,k", [(1, 12000, 12000, 3, 15), (2, 8192, 8192, 16, 20), (1, 16385, 8200, 13, 7),
+                                        (3, 7001, 6500, 8, 12), (1, 11700, 11700, 32, 30), (1, 11700, 11700, 4, 1),
+                                        (1, 150001, 900, 16, 40)])
+def test_runs_update_and_adjoint(nb, n, m, d, k):
+    X = torch.stack([_cloud(10 * n + d + b, n, d, k) for b in range(nb)])
+    same = m == n
+    S = X if same else torch.stack([_cloud(7 * m + d + b, m, d, k) + 0 for b in range(nb)])
+    if not same:   # seeds near the points: a subset, moved a little
+        S = (X[:, :m] + 0.3 * torch.sin(torch.arange(m * d, device=DEV, dtype=torch.float32).view(m, d))).contiguous()
+    G = torch.randn(nb, m, d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(1))
+    new = api.forward_update(X, S, 1.0)
+    dS, dX = api.step_adjoint(X, S, 1.0, G)
+    for b in range(nb):
+        rn, rS, rX = _ref(X[b], S[b], 1.0, G[b])
+        _close(new[b], rn, "update")
+        _close(dS[b], rS, "dS")
+        _close(dX[b], rX, "dX")
+
+
+def test_runs_nothing_left_out_and_accumulates():
+    """A bandwidth as wide as the data: every pair counts.  The gradients are
+    added to what the arrays hold, also where dS is dX (S is X)."""
+    X = _cloud(3, 11700, 6, 1, sigma=1.0)
+    G = torch.randn(11700, 6, device=DEV, generator=torch.Generator(device=DEV).manual_seed(2))
+    rn, rS, rX = _ref(X, X, 2.0, G)
+    _close(api.forward_update(X, X, 2.0), rn, "update")
+    both = torch.full_like(X, 0.25)
+    api.step_adjoint_accumulate(X, X, 2.0, G, both, both)
+    _close(both, rS + rX + 0.25, "dS + dX")
+
+
+def test_runs_repeat_bitwise():
+    X = _cloud(5, 12000, 16, 20)
+    G = torch.randn(12000, 16, device=DEV, generator=torch.Generator(device=DEV).manual_seed(3))
+    a = api.step_adjoint(X, X, 1.0, G)
+    b = api.step_adjoint(X, X, 1.0, G)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    assert torch.equal(api.forward_update(X, X, 1.0), api.forward_update(X, X, 1.0))
+
+
+def test_runs_non_finite_point():
+    """A point that is not finite reaches every seed, as without runs."""
+    X = _cloud(6, 12000, 16, 20)
+    X[500, 2] = float("nan")
+    assert int(torch.isfinite(api.forward_update(X, X.clone(), 1.0)).all(1).sum()) == 0
