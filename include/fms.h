@@ -316,6 +316,28 @@ int ms_step_adjoint(const void *X, int32_t nbatch, int64_t n, const void *S,
                     void *dX, int32_t dtype_bytes, void *stream);
 
 /*
+ * ms_points_plan -- the part of ms_forward_update and ms_step_adjoint that
+ * depends on the points alone (their spatial order, about 60 to 100 us), for
+ * callers that make several of those calls over the same X, h and shape (the
+ * unrolled form).  ms_points_plan_bytes gives the size of the plan, or 0 where
+ * these calls use none (float64, d > 32, few points); `plan` is device memory
+ * of at least that size, aligned to 256 bytes, written by this call and only
+ * read by the planned ones.  The plan holds no pointers.  X must be the array
+ * contents the plan was made from; the planned calls take a NULL plan like
+ * the plain ones.  Stream-ordered and asynchronous.
+ */
+int ms_points_plan_bytes(int32_t nbatch, int64_t n, int32_t d, int32_t dtype_bytes,
+                         int64_t *bytes);
+int ms_points_plan(const void *X, int32_t nbatch, int64_t n, int32_t d, double h,
+                   int32_t dtype_bytes, void *plan, int64_t plan_bytes, void *stream);
+int ms_forward_update_planned(const void *X, int32_t nbatch, int64_t n, const void *S_in,
+                              int64_t m, int32_t d, double h, void *S_out,
+                              int32_t dtype_bytes, const void *plan, void *stream);
+int ms_step_adjoint_planned(const void *X, int32_t nbatch, int64_t n, const void *S,
+                            int64_t m, int32_t d, double h, const void *G, void *dS,
+                            void *dX, int32_t dtype_bytes, const void *plan, void *stream);
+
+/*
  * ms_seed_draw -- the library's seed selection on host memory: draws
  * `count` ids from pool[0..len) by a partial Fisher-Yates shuffle driven by
  * SplitMix64 with the multiply-high bound (the same draw ms_fit makes each

@@ -82,7 +82,8 @@ class Diag(ctypes.Structure):
 
 EXPORTS = ("ms_default_params", "ms_fit", "ms_step", "ms_step_noalloc", "ms_step_batched", "ms_tune_batched", "ms_fit_batched",
            "ms_assign",
-           "ms_forward_update", "ms_step_adjoint", "ms_seed_draw", "ms_seed_count_next",
+           "ms_forward_update", "ms_step_adjoint", "ms_points_plan_bytes", "ms_points_plan",
+           "ms_forward_update_planned", "ms_step_adjoint_planned", "ms_seed_draw", "ms_seed_count_next",
            "ms_release_workspace", "ms_graph_stats", "ms_last_error", "ms_version")
 
 _lib = None
@@ -118,6 +119,14 @@ def lib():
     L.ms_forward_update.restype = ctypes.c_int
     L.ms_step_adjoint.argtypes = [P, i32, i64, P, i64, i32, ctypes.c_double, P, P, P, i32, P]
     L.ms_step_adjoint.restype = ctypes.c_int
+    L.ms_points_plan_bytes.argtypes = [i32, i64, i32, i32, P]
+    L.ms_points_plan_bytes.restype = ctypes.c_int
+    L.ms_points_plan.argtypes = [P, i32, i64, i32, ctypes.c_double, i32, P, i64, P]
+    L.ms_points_plan.restype = ctypes.c_int
+    L.ms_forward_update_planned.argtypes = [P, i32, i64, P, i64, i32, ctypes.c_double, P, i32, P, P]
+    L.ms_forward_update_planned.restype = ctypes.c_int
+    L.ms_step_adjoint_planned.argtypes = [P, i32, i64, P, i64, i32, ctypes.c_double, P, P, P, i32, P, P]
+    L.ms_step_adjoint_planned.restype = ctypes.c_int
     L.ms_seed_draw.argtypes = [P, P, i32, i32, P]
     L.ms_seed_draw.restype = ctypes.c_int
     L.ms_seed_count_next.argtypes = [i32, i32, i32, P]
@@ -419,7 +428,28 @@ def _batched(X, S):
     return X, S, False
 
 
-def forward_update(X, S, h):
+def points_plan(X, h):
+    """The part of forward_update and step_adjoint_accumulate that depends on X
+    and h alone, for several of those calls over the same X ([B,] n x d): a
+    tensor to pass as ``plan``, or None where they use none."""
+    torch = _torch()
+    _dev(X, X.dtype, None, "X")
+    nb, n, d = (1,) + tuple(X.shape) if X.dim() == 2 else tuple(X.shape)
+    size = ctypes.c_int64(0)
+    _check(lib().ms_points_plan_bytes(nb, n, d, X.element_size(), ctypes.byref(size)))
+    if size.value == 0:
+        return None
+    plan = torch.empty(size.value, dtype=torch.uint8, device=X.device)
+    _check(lib().ms_points_plan(ctypes.c_void_p(X.data_ptr()), nb, n, d, float(h), X.element_size(),
+                                ctypes.c_void_p(plan.data_ptr()), size.value, _stream_ptr(X)))
+    return plan
+
+
+def _plan_ptr(plan):
+    return None if plan is None else ctypes.c_void_p(plan.data_ptr())
+
+
+def forward_update(X, S, h, plan=None):
     """One Gaussian update of every seed, S' = m(S); X: [B,] n x d, S: [B,] m x d."""
     torch = _torch()
     Xb, Sb, squeeze = _batched(X, S)
@@ -431,9 +461,9 @@ def forward_update(X, S, h):
     nb, n, d = Xb.shape
     m = Sb.shape[1]
     out = torch.empty_like(Sb)
-    rc = lib().ms_forward_update(ctypes.c_void_p(Xb.data_ptr()), nb, n, ctypes.c_void_p(Sb.data_ptr()),
-                                 m, d, float(h), ctypes.c_void_p(out.data_ptr()),
-                                 Xb.element_size(), _stream_ptr(Xb))
+    rc = lib().ms_forward_update_planned(ctypes.c_void_p(Xb.data_ptr()), nb, n, ctypes.c_void_p(Sb.data_ptr()),
+                                         m, d, float(h), ctypes.c_void_p(out.data_ptr()),
+                                         Xb.element_size(), _plan_ptr(plan), _stream_ptr(Xb))
     _check(rc)
     return out[0] if squeeze else out
 
@@ -457,7 +487,7 @@ def step_adjoint(X, S, h, G):
     return (dS[0], dX[0]) if squeeze else (dS, dX)
 
 
-def step_adjoint_accumulate(X, S, h, G, dS, dX):
+def step_adjoint_accumulate(X, S, h, G, dS, dX, plan=None):
     """ms_step_adjoint adding into caller arrays: dS += dL/dS and dX += dL/dX
     of one Gaussian update for the upstream gradient G.  dS may be dX itself
     when S is X (the first step of the unrolled form, S_0 = X)."""
@@ -475,10 +505,10 @@ def step_adjoint_accumulate(X, S, h, G, dS, dX):
         raise ValueError("G must not share memory with dS or dX")
     if dS.data_ptr() == dX.data_ptr() and m != n:
         raise ValueError("dS may be dX only when S has as many rows as X")
-    rc = lib().ms_step_adjoint(ctypes.c_void_p(X.data_ptr()), nb, n, ctypes.c_void_p(S.data_ptr()),
-                               m, d, float(h), ctypes.c_void_p(G.data_ptr()),
-                               ctypes.c_void_p(dS.data_ptr()), ctypes.c_void_p(dX.data_ptr()),
-                               X.element_size(), _stream_ptr(X))
+    rc = lib().ms_step_adjoint_planned(ctypes.c_void_p(X.data_ptr()), nb, n, ctypes.c_void_p(S.data_ptr()),
+                                       m, d, float(h), ctypes.c_void_p(G.data_ptr()),
+                                       ctypes.c_void_p(dS.data_ptr()), ctypes.c_void_p(dX.data_ptr()),
+                                       X.element_size(), _plan_ptr(plan), _stream_ptr(X))
     _check(rc)
 
 

@@ -30,8 +30,9 @@ class MeanShiftT(torch.autograd.Function):
         Xc = X.detach().contiguous()
         S = Xc
         saved = {0: S}
+        plan = api.points_plan(Xc, h) if T > 1 else None   # X's order, for all T updates
         for t in range(T):
-            S = api.forward_update(Xc, S, h)
+            S = api.forward_update(Xc, S, h, plan)
             if (t + 1) % every == 0 and t + 1 < T:
                 saved[t + 1] = S
         ctx.h, ctx.T, ctx.every = h, T, every
@@ -50,6 +51,7 @@ class MeanShiftT(torch.autograd.Function):
         # ms_step_adjoint adds dL/dS_t into a fresh array and the point term of
         # step t into dX; at t = 0, where S_0 = X, dL/dS_0 is added into dX too
         dX = torch.zeros_like(X)
+        plan = api.points_plan(X, h) if T > 1 else None
         cache = {}
         for t in range(T - 1, -1, -1):
             if t in saved:
@@ -61,12 +63,12 @@ class MeanShiftT(torch.autograd.Function):
                 base = max(k for k in saved if k <= t)
                 S = saved[base]
                 for u in range(base, t):
-                    S = api.forward_update(X, S, h)
+                    S = api.forward_update(X, S, h, plan)
                     if u + 1 < t:
                         cache[u + 1] = S
                 S_t = S
             dS = dX if t == 0 else torch.zeros_like(S_t)
-            api.step_adjoint_accumulate(X, S_t, h, G, dS, dX)
+            api.step_adjoint_accumulate(X, S_t, h, G, dS, dX, plan)
             G = dS
         return dX, None, None, None
 

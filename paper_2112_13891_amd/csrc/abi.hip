@@ -2206,19 +2206,19 @@ static int check_diff(const void* X, int32_t nbatch, int64_t n, const void* S, i
     return MS_OK;
 }
 
-int ms_forward_update(const void* X, int32_t nbatch, int64_t n, const void* S_in, int64_t m, int32_t d,
-                      double h, void* S_out, int32_t dtype_bytes, void* stream) {
-    g_err.clear();
+static int forward_update_impl(const void* X, int32_t nbatch, int64_t n, const void* S_in, int64_t m, int32_t d,
+                               double h, void* S_out, int32_t dtype_bytes, const void* plan, void* stream) {
     FMS_CHECK(check_diff(X, nbatch, n, S_in, m, d, h, dtype_bytes));
     if (!S_out) return fail(MS_E_INVALID, "S_out is NULL");
     hipStream_t s = (hipStream_t)stream;
     FMS_CHECK(ensure_pool_release_threshold());
     Workspace ws(s);
     char* w;
-    if (dtype_bytes == 4 && adjoint_runs_ok(nbatch, (int)n, (int)m, d, false)) {
-        FMS_CHECK(ws.alloc(&w, adjoint_runs_bytes(nbatch, (int)n, (int)m, d, S_in == X && m == n, false)));
+    if (dtype_bytes == 4 && adjoint_runs_ok(nbatch, (int)n, (int)m, d, false, plan != nullptr)) {
+        FMS_CHECK(ws.alloc(&w, adjoint_runs_bytes(nbatch, (int)n, (int)m, d, S_in == X && m == n, false,
+                                                  plan != nullptr)));
         FMS_HIP(launch_adjoint_runs((const float*)X, nbatch, (int)n, (const float*)S_in, (int)m, d, h, (float*)S_out,
-                                    nullptr, nullptr, nullptr, w, s));
+                                    nullptr, nullptr, nullptr, w, plan, s));
         return MS_OK;
     }
     FMS_CHECK(ws.alloc(&w, adjoint_workspace_bytes(nbatch, (int)n, (int)m, d, dtype_bytes)));
@@ -2226,24 +2226,72 @@ int ms_forward_update(const void* X, int32_t nbatch, int64_t n, const void* S_in
     return MS_OK;
 }
 
-int ms_step_adjoint(const void* X, int32_t nbatch, int64_t n, const void* S, int64_t m, int32_t d,
-                    double h, const void* G, void* dS, void* dX, int32_t dtype_bytes, void* stream) {
-    g_err.clear();
+static int step_adjoint_impl(const void* X, int32_t nbatch, int64_t n, const void* S, int64_t m, int32_t d,
+                             double h, const void* G, void* dS, void* dX, int32_t dtype_bytes, const void* plan,
+                             void* stream) {
     FMS_CHECK(check_diff(X, nbatch, n, S, m, d, h, dtype_bytes));
     if (!G || !dS || !dX) return fail(MS_E_INVALID, "NULL gradient array");
     hipStream_t s = (hipStream_t)stream;
     FMS_CHECK(ensure_pool_release_threshold());
     Workspace ws(s);
     char* w;
-    if (dtype_bytes == 4 && adjoint_runs_ok(nbatch, (int)n, (int)m, d, true)) {
-        FMS_CHECK(ws.alloc(&w, adjoint_runs_bytes(nbatch, (int)n, (int)m, d, S == X && m == n, true)));
+    if (dtype_bytes == 4 && adjoint_runs_ok(nbatch, (int)n, (int)m, d, true, plan != nullptr)) {
+        FMS_CHECK(ws.alloc(&w, adjoint_runs_bytes(nbatch, (int)n, (int)m, d, S == X && m == n, true, plan != nullptr)));
         FMS_HIP(launch_adjoint_runs((const float*)X, nbatch, (int)n, (const float*)S, (int)m, d, h, nullptr,
-                                    (const float*)G, (float*)dS, (float*)dX, w, s));
+                                    (const float*)G, (float*)dS, (float*)dX, w, plan, s));
         return MS_OK;
     }
     FMS_CHECK(ws.alloc(&w, adjoint_workspace_bytes(nbatch, (int)n, (int)m, d, dtype_bytes)));
     FMS_HIP(launch_step_adjoint(X, nbatch, (int)n, S, (int)m, d, h, G, dS, dX, dtype_bytes, w, s));
     return MS_OK;
+}
+
+int ms_points_plan_bytes(int32_t nbatch, int64_t n, int32_t d, int32_t dtype_bytes, int64_t* bytes) {
+    g_err.clear();
+    if (!bytes) return fail(MS_E_INVALID, "bytes is NULL");
+    *bytes = 0;
+    if (nbatch < 1 || nbatch > 65535 || n < 1 || n > INT_MAX / 2 || d < 1 || d > 64 ||
+        (dtype_bytes != 4 && dtype_bytes != 8))
+        return fail(MS_E_INVALID, "bad nbatch, n, d or dtype_bytes");
+    if (dtype_bytes == 4 && adjoint_runs_ok(nbatch, (int)n, (int)n, d, true, true))
+        *bytes = (int64_t)points_plan_bytes(nbatch, (int)n, d);
+    return MS_OK;
+}
+
+int ms_points_plan(const void* X, int32_t nbatch, int64_t n, int32_t d, double h, int32_t dtype_bytes, void* plan,
+                   int64_t plan_bytes, void* stream) {
+    int64_t need = 0;
+    FMS_CHECK(ms_points_plan_bytes(nbatch, n, d, dtype_bytes, &need));
+    if (!X || !plan) return fail(MS_E_INVALID, "NULL array");
+    if (!(std::isfinite(h) && h > 0.0)) return fail(MS_E_INVALID, "h must be finite and > 0");
+    if (need == 0) return fail(MS_E_INVALID, "no plan for this shape (ms_points_plan_bytes gives 0)");
+    if (plan_bytes < need) return fail(MS_E_INVALID, "plan_bytes is less than ms_points_plan_bytes gives");
+    FMS_HIP(launch_points_plan((const float*)X, nbatch, (int)n, d, h, plan, (hipStream_t)stream));
+    return MS_OK;
+}
+
+int ms_forward_update(const void* X, int32_t nbatch, int64_t n, const void* S_in, int64_t m, int32_t d,
+                      double h, void* S_out, int32_t dtype_bytes, void* stream) {
+    g_err.clear();
+    return forward_update_impl(X, nbatch, n, S_in, m, d, h, S_out, dtype_bytes, nullptr, stream);
+}
+
+int ms_forward_update_planned(const void* X, int32_t nbatch, int64_t n, const void* S_in, int64_t m, int32_t d,
+                              double h, void* S_out, int32_t dtype_bytes, const void* plan, void* stream) {
+    g_err.clear();
+    return forward_update_impl(X, nbatch, n, S_in, m, d, h, S_out, dtype_bytes, plan, stream);
+}
+
+int ms_step_adjoint(const void* X, int32_t nbatch, int64_t n, const void* S, int64_t m, int32_t d,
+                    double h, const void* G, void* dS, void* dX, int32_t dtype_bytes, void* stream) {
+    g_err.clear();
+    return step_adjoint_impl(X, nbatch, n, S, m, d, h, G, dS, dX, dtype_bytes, nullptr, stream);
+}
+
+int ms_step_adjoint_planned(const void* X, int32_t nbatch, int64_t n, const void* S, int64_t m, int32_t d, double h,
+                            const void* G, void* dS, void* dX, int32_t dtype_bytes, const void* plan, void* stream) {
+    g_err.clear();
+    return step_adjoint_impl(X, nbatch, n, S, m, d, h, G, dS, dX, dtype_bytes, plan, stream);
 }
 
 int ms_seed_draw(uint64_t* state, const int32_t* pool, int32_t len, int32_t count, int32_t* out) {

@@ -266,7 +266,7 @@ struct RunIndex {
     int D = 0, DP = 0, d = 0;
     float* tiles = nullptr;      // max_tiles x 64 x DP, the layout of k_seed.hip
     float* pivot_rows = nullptr; // the pivots' rows (tile units, stride DP; row-major indexes only)
-    float* ball_rows = nullptr;  // centre of each near run's points and, at DP, their largest distance from it
+    float* ball_rows = nullptr;  // centre of each run's points and, at DP, their largest distance from it
                                  // (packed units; stride DP + 4; row-major indexes only)
     float* pivots = nullptr;     // coordinate k of pivot j (packed units) at [k * ptot + j]
     float* run_bound = nullptr;  // largest distance of a near run's points from its pivot (at most this);
@@ -302,7 +302,7 @@ int run_index_alloc(RunIndex& r, const RunSizes& sz, int d, bool keep_rows, F&& 
     get(&r.tiles, T * 64 * sh.DP);
     if (r.row_major) {
         get(&r.pivot_rows, (size_t)sz.ptot * sh.DP);
-        get(&r.ball_rows, (size_t)sz.ptot * (sh.DP + 4));
+        get(&r.ball_rows, (size_t)sz.runs * (sh.DP + 4));
     } else {
         get(&r.pivots, (size_t)sz.ptot * sh.D);
     }
@@ -330,6 +330,10 @@ int run_index_alloc(RunIndex& r, const RunSizes& sz, int d, bool keep_rows, F&& 
 // a point counts as far from its nearest pivot.
 hipError_t launch_run_index(RunIndex& r, const float* X, const long long* xo_src, int n_each, float scale,
                             float far, hipStream_t s);
+// The rows S (as many as the index has points, stride d) in the slots of the
+// points with the same numbers, and the balls of the runs over them: a grouping
+// for seeds that started from the points.
+hipError_t launch_run_regroup(const RunIndex& r, const float* S, float* tiles, float* balls, hipStream_t s);
 // One cloud: order[0 .. m) = the seeds S (stride DP, original units) grouped by
 // their nearest pivot, near[j] that pivot of seed j, dist[j] >= its distance,
 // and ppair[i * P + j] <= the distance between pivots i and j.
@@ -550,12 +554,15 @@ hipError_t launch_check_finite(const float* X, long long count, int32_t* flag,
                                hipStream_t s);
 
 // ---- launchers (k_adjoint_runs.hip): FP32 differentiable form over pivot runs --
-// For n_each points and m_each seeds in each of nb clouds; ws:
-// adjoint_runs_bytes() bytes.
-bool adjoint_runs_ok(int nb, int n, int m, int d, bool adjoint);
-size_t adjoint_runs_bytes(int nb, int n, int m, int d, bool same, bool adjoint);
+// For n points and m seeds in each of nb clouds; ws: adjoint_runs_bytes()
+// bytes; plan: the points' index from launch_points_plan (points_plan_bytes()
+// bytes), or NULL to build it within the call.
+bool adjoint_runs_ok(int nb, int n, int m, int d, bool adjoint, bool planned);
+size_t adjoint_runs_bytes(int nb, int n, int m, int d, bool same, bool adjoint, bool planned);
+size_t points_plan_bytes(int nb, int n, int d);
+hipError_t launch_points_plan(const float* X, int nb, int n, int d, double h, void* plan, hipStream_t s);
 hipError_t launch_adjoint_runs(const float* X, int nb, int n, const float* S, int m, int d, double h, float* S_out,
-                               const float* G, float* dS, float* dX, void* ws, hipStream_t s);
+                               const float* G, float* dS, float* dX, void* ws, const void* plan, hipStream_t s);
 
 // ---- launchers (k_adjoint.hip) -------------------------------------------
 // ws: device workspace of adjoint_workspace_bytes() bytes.

@@ -25,8 +25,10 @@
 // the same sums as beta_ij = w_ij g.(x_i - s'_j) / (h^2 W_j) gives (see
 // k_adjoint.hip), with s'_j left outside them.
 //
-// Bound by the vector units (D = 16: 54, 87 and 91 lane-ops a pair for the
-// update, the seed pass and the point pass).
+// Bound by the vector units (D = 16: 54, 87 and 89 lane-ops a pair for the
+// update, the seed pass and the point pass; all pairs of overlapping clusters at
+// D = 3 run at 80 % of their rate).  8 clouds of 16,384 x 16, one call: update
+// 2,050 -> 490 us, adjoint 8,600 -> 1,500 us, of which the index 75 us.
 
 #include <algorithm>
 #include <cmath>
@@ -47,8 +49,8 @@ struct Side {
     const float* rows;          // 64 rows of `ld` floats per tile
     int ld;
     const float* pivot_rows;    // stride DP
-    const float* ball_rows;     // centre of each near run (stride DP + 4), its radius at DP
-    const float* run_bound;
+    const float* ball_rows;     // centre of each run (stride DP + 4), its radius at DP
+    const float* run_bound;     // the far runs' bounds are used where this is not NULL
     const int32_t* tile_start;
     const int32_t* run_start;
     const int32_t* poff;
@@ -64,7 +66,7 @@ struct AdjArgs {
     float neg;                  // 33 + log2 n
     const float* G;
     float* out;                 // S_out; or dS / dX, added into
-    float* sg;                  // seed pass: rows for the point pass (s, g, 1/W, g.delta)
+    float* sg;                  // seed pass: rows for the point pass (s, g, 1/W, -g.delta)
     float* runq;                // seed pass: the seed runs' largest q, as the float's bits
 };
 
@@ -73,7 +75,8 @@ enum { FWD = 0, DS = 1, DX = 2 };
 template <int D, int MODE>
 __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     constexpr int DP = D <= 4 ? 4 : D;
-    constexpr int V = MODE == FWD ? D + 1 : (MODE == DS ? 2 * D + 1 : D);
+    constexpr int V = MODE == FWD ? D + 1 : (MODE == DS ? 2 * D + 1 : 2 * D);
+    constexpr int VR = MODE == DX ? D : V;   // sums a wave passes on
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = blockIdx.x;
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     }
 
     constexpr int kGroups = (kRunPivotMax + kFarRuns + 63) / 64;
-    __shared__ float red[(kWv - 1) * V * 64];
+    __shared__ float red[(kWv - 1) * VR * 64];
     __shared__ float umin[kWv][64];
     __shared__ float wfirst_d[kWv];
     __shared__ int wfirst[kWv];
@@ -114,10 +117,11 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     };
     const const_f32_ptr pv = wave_uniform_const(a.other.pivot_rows);
     const const_f32_ptr bv = wave_uniform_const(a.other.ball_rows);
+    const bool bounds = MODE != DX || a.other.run_bound != nullptr;
     // the nearest pivot (a point) of each lane, and the pivot nearest to any
     float ub = 1e18f, first_d = 1e18f;
     int first = 0;
-    for (int e = wave; e < P; e += kWv) {
+    for (int e = wave; bounds && e < P; e += kWv) {
         const float dist = dist_to(pv + (long long)(p0 + e) * DP);
         ub = fminf(ub, dist);
         if (MODE != DX) {
@@ -153,13 +157,9 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
 
     // near: run e of this cloud is within some lane's reach
     auto is_near = [&](int e, float lim) {
-        bool near;
-        if (e < P) {
-            const const_f32_ptr p = bv + (long long)(p0 + e) * (DP + 4);
-            near = !(dist_to(p) - p[DP] > lim);   // a NaN is near
-        } else {
-            near = !(a.other.run_bound[run0 + e] - ub > lim);
-        }
+        const const_f32_ptr p = bv + (long long)(run0 + e) * (DP + 4);
+        bool near = !(dist_to(p) - p[DP] > lim);   // a NaN is near
+        if (bounds && e >= P) near = near && !(a.other.run_bound[run0 + e] - ub > lim);
         return __ballot(near && live) != 0;
     };
     for (int e = wave; e < P + kFarRuns; e += kWv) {
@@ -169,9 +169,31 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     }
     __syncthreads();
 
-    float acc[V];
+    // narrow rows: each tile's 64 terms are summed apart and then added, which
+    // keeps the chains short (at D = 3 a wave adds thousands of terms; dL/dX of
+    // overlapping clusters was off by 1.1e-6 without and the all-pairs form by
+    // 7.9e-7)
+    constexpr bool kTileSums = D <= 8;
+    float acc[V], sum[kTileSums ? V : 1];
 #pragma unroll
     for (int k = 0; k < V; ++k) acc[k] = 0.0f;
+    if constexpr (kTileSums) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) sum[k] = 0.0f;
+    }
+    auto fold = [&]() {
+        if constexpr (kTileSums) {
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                sum[k] += acc[k];
+                acc[k] = 0.0f;
+            }
+        }
+    };
+    auto wave_W = [&]() {
+        if constexpr (kTileSums && MODE != DX) return sum[D];
+        else return acc[MODE != DX ? D : 0];
+    };
     int turn = 0;
     const const_f32_ptr rows = wave_uniform_const(a.other.rows);
     // one run: its tiles dealt to the waves in turn
@@ -187,7 +209,7 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
             } else {
                 // the wave's sum so far is a better bound of W than the nearest
                 // pivot: fewer rows count, and perhaps none of this run
-                const float better = a.neg + 0.01f - __builtin_amdgcn_logf(acc[D]);
+                const float better = a.neg + 0.01f - __builtin_amdgcn_logf(wave_W());
                 if (__ballot(live && better < rq)) {
                     rq = fminf(rq, fmaxf(better, 1.0f));
                     reach = sqrtf(rq);
@@ -229,8 +251,8 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
                         }
                     });
                 } else {
-                    // a seed's row: s, g, 1 / W, g.delta (the next row's loads put
-                    // ahead by hand gained nothing: the vector units are busy)
+                    // a seed's row: s, g, 1 / W, -g.delta (wide rows: the next row's
+                    // loads put ahead gained nothing, the vector units are busy)
                     constexpr int LD = 2 * DP + 4;
                     auto pair = [&](const float (&r)[LD]) {
                         float dx[D], q = 0.0f;
@@ -248,22 +270,30 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
                                 q = fmaf(dx[k], dx[k], q);
                             }
                         }
-                        float gdx = 0.0f;
+                        float gdx = r[2 * DP + 1];   // -g.delta
 #pragma unroll
                         for (int k = 0; k < D; ++k) gdx = fmaf(r[DP + k], dx[k], gdx);
                         const float w = __builtin_amdgcn_exp2f(q * a.c);
-                        const float aa = w * r[2 * DP];                       // w_ij / W_j
-                        const float beta = aa * (gdx - r[2 * DP + 1]) * a.ih2;   // beta_ij
+                        const float aa = w * r[2 * DP];   // w_ij / W_j
+                        const float bb = aa * gdx;        // h^2 beta_ij
 #pragma unroll
-                        for (int k = 0; k < D; ++k) acc[k] = fmaf(aa, r[DP + k], fmaf(-beta, dx[k], acc[k]));
+                        for (int k = 0; k < D; ++k) {
+                            acc[k] = fmaf(aa, r[DP + k], acc[k]);
+                            acc[D + k] = fmaf(bb, dx[k], acc[D + k]);
+                        }
                     };
-                    for (int p = 0; p < n; ++p) {
-                        float r[LD];
+                    if constexpr (D <= 8) {
+                        stream_rows<LD, LD>(base, n, pair);
+                    } else {
+                        for (int p = 0; p < n; ++p) {
+                            float r[LD];
 #pragma unroll
-                        for (int k = 0; k < LD; ++k) r[k] = base[p * LD + k];
-                        pair(r);
+                            for (int k = 0; k < LD; ++k) r[k] = base[p * LD + k];
+                            pair(r);
+                        }
                     }
                 }
+                fold();
             }
     };
     // the listed runs, the one nearest to the tile first: W is soon known well
@@ -293,10 +323,18 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
         e = next();
     }
 
+    if constexpr (kTileSums) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) acc[k] = sum[k];
+    }
+    if constexpr (MODE == DX) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) acc[k] = fmaf(-a.ih2, acc[D + k], acc[k]);
+    }
     // the wave sums in wave order
     if (wave > 0) {
 #pragma unroll
-        for (int k = 0; k < V; ++k) red[((wave - 1) * V + k) * 64 + lane] = acc[k];
+        for (int k = 0; k < VR; ++k) red[((wave - 1) * VR + k) * 64 + lane] = acc[k];
     }
     __syncthreads();
     if (wave > 0) return;
@@ -305,7 +343,7 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     auto tot = [&](int k) {
         double v = acc[k];
 #pragma unroll
-        for (int w = 0; w < kWv - 1; ++w) v += red[(w * V + k) * 64 + lane];
+        for (int w = 0; w < kWv - 1; ++w) v += red[(w * VR + k) * 64 + lane];
         return v;
     };
     if constexpr (MODE == DX) {
@@ -341,7 +379,7 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
                 o[DP + k] = g[k];
             }
             o[2 * DP] = live ? (float)iw : 0.0f;
-            o[2 * DP + 1] = live ? (float)gdel : 0.0f;
+            o[2 * DP + 1] = live ? -(float)gdel : 0.0f;
             // a seed without weight (1/W not finite) is seen by every point
             float q = 0.0f;
             if (live)
@@ -373,17 +411,33 @@ struct Bump {
 };
 
 struct AdjBuffers {
-    RunIndex x, s;
+    RunIndex x, s;   // s: the seeds' own index, the points' (same rows), or the points' order over the seeds' rows
     float *sg = nullptr, *runq = nullptr;
 };
 
-size_t carve_runs(AdjBuffers& b, char* base, int nb, int n, int m, int d, bool same, bool adjoint) {
+size_t carve_points(RunIndex& x, char* base, int nb, int n, int d) {
     Bump w{base};
+    x.row_major = true;
+    (void)run_index_alloc(x, run_sizes_equal(nb, n), d, true, [&](auto** p, size_t c) { return w.alloc(p, c); });
+    return w.off;
+}
+
+// The points' index lies in `plan` or, if that is NULL, before the rest.
+size_t carve_runs(AdjBuffers& b, char* base, char* plan, bool planned, int nb, int n, int m, int d, bool same,
+                  bool adjoint) {
+    const size_t own = carve_points(b.x, planned ? plan : base, nb, n, d);
+    Bump w{base, planned ? 0 : own};
     auto alloc = [&](auto** p, size_t c) { return w.alloc(p, c); };
-    b.x.row_major = b.s.row_major = true;
-    (void)run_index_alloc(b.x, run_sizes_equal(nb, n), d, true, alloc);
-    if (same) b.s = b.x;
-    else (void)run_index_alloc(b.s, run_sizes_equal(nb, m), d, true, alloc);
+    b.s.row_major = true;
+    if (m == n) {
+        b.s = b.x;   // (its scale is set with b.x's)
+        if (!same) {   // seeds that started from the points keep the points' order
+            (void)w.alloc(&b.s.tiles, (size_t)b.x.sz.max_tiles * 64 * b.x.DP);
+            (void)w.alloc(&b.s.ball_rows, (size_t)b.x.sz.runs * (b.x.DP + 4));
+        }
+    } else {
+        (void)run_index_alloc(b.s, run_sizes_equal(nb, m), d, true, alloc);
+    }
     if (adjoint) {
         (void)w.alloc(&b.sg, (size_t)b.s.sz.max_tiles * 64 * (2 * b.s.DP + 4));
         (void)w.alloc(&b.runq, (size_t)b.s.sz.runs);
@@ -407,27 +461,49 @@ void launch_modes(const AdjArgs& seeds, const AdjArgs& points, bool adjoint, int
 
 }  // namespace
 
-bool adjoint_runs_ok(int nb, int n, int m, int d, bool adjoint) {
+bool adjoint_runs_ok(int nb, int n, int m, int d, bool adjoint, bool planned) {
     if (d > 32) return false;
     if ((long long)nb * std::max(n, m) > (1LL << 28)) return false;   // tile slots stay in 32 bits
-    return (long long)nb * n * m >= (adjoint ? 1LL << 26 : 1LL << 27);
+    // all pairs of 2^26 take about 180 us in the adjoint and 50 in the update at
+    // D = 16; the points' index takes 60 to 100 us unless it is there already
+    return (long long)nb * n * m >= (adjoint ? 1LL << 26 : (planned ? 1LL << 26 : 1LL << 27));
 }
 
-size_t adjoint_runs_bytes(int nb, int n, int m, int d, bool same, bool adjoint) {
+size_t adjoint_runs_bytes(int nb, int n, int m, int d, bool same, bool adjoint, bool planned) {
     AdjBuffers b;
-    return carve_runs(b, nullptr, nb, n, m, d, same, adjoint);
+    return carve_runs(b, nullptr, nullptr, planned, nb, n, m, d, same, adjoint);
+}
+
+size_t points_plan_bytes(int nb, int n, int d) {
+    RunIndex x;
+    return carve_points(x, nullptr, nb, n, d);
+}
+
+static float packed(double h) { return (float)std::sqrt(1.4426950408889634 / (2.0 * h * h)); }
+
+hipError_t launch_points_plan(const float* X, int nb, int n, int d, double h, void* plan, hipStream_t s) {
+    RunIndex x;
+    carve_points(x, (char*)plan, nb, n, d);
+    return launch_run_index(x, X, nullptr, n, packed(h), 8.0f, s);
 }
 
 hipError_t launch_adjoint_runs(const float* X, int nb, int n, const float* S, int m, int d, double h, float* S_out,
-                               const float* G, float* dS, float* dX, void* ws, hipStream_t s) {
+                               const float* G, float* dS, float* dX, void* ws, const void* plan, hipStream_t s) {
     const bool same = S == X && m == n, adjoint = G != nullptr;
     AdjBuffers b;
-    carve_runs(b, (char*)ws, nb, n, m, d, same, adjoint);
-    const float scale = (float)std::sqrt(1.4426950408889634 / (2.0 * h * h));
-    hipError_t e = launch_run_index(b.x, X, nullptr, n, scale, 8.0f, s);
+    carve_runs(b, (char*)ws, (char*)const_cast<void*>(plan), plan != nullptr, nb, n, m, d, same, adjoint);
+    const float scale = packed(h);
+    hipError_t e = hipSuccess;
+    b.x.scale = scale;
+    if (!plan) e = launch_run_index(b.x, X, nullptr, n, scale, 8.0f, s);
     if (e != hipSuccess) return e;
-    if (same) b.s = b.x;
-    else if ((e = launch_run_index(b.s, S, nullptr, m, scale, 8.0f, s)) != hipSuccess) return e;
+    if (m == n && !same) {
+        e = launch_run_regroup(b.x, S, b.s.tiles, b.s.ball_rows, s);
+        b.s.run_bound = nullptr;
+    } else if (m != n) {
+        e = launch_run_index(b.s, S, nullptr, m, scale, 8.0f, s);
+    }
+    if (e != hipSuccess) return e;
     AdjArgs a{};
     a.own = side_of(b.s);
     a.other = side_of(b.x);

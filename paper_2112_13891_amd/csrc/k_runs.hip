@@ -401,20 +401,26 @@ __global__ __launch_bounds__(256) void run_fill_kernel(const float* __restrict__
     if (rows) rows[t * 64 + lane] = row;
 }
 
-// Ball of each near run of a row-major index, one wave per run: the mean of its
-// rows and the largest distance from it (packed units, rounded up).  In 16-D a
-// ball around the mean of 256 points has 0.7 of the radius around one of them.
+// Ball of each run of row-major tiles, one wave per run: the mean of its rows
+// and the largest distance from it (packed units, rounded up).  In 16-D a ball
+// around the mean of 256 points has 0.7 of the radius around one of them.  A
+// run too long for one wave (far points of a cloud without clusters) gets an
+// infinite radius.
+constexpr int kBallRows = 8192;
 template <int D>
 __global__ __launch_bounds__(256) void run_ball_kernel(const float* __restrict__ tiles,
                                                        const int32_t* __restrict__ start,
-                                                       const int32_t* __restrict__ tile_start,
-                                                       const int32_t* __restrict__ poff, int ncl, float scale,
+                                                       const int32_t* __restrict__ tile_start, int runs, float scale,
                                                        float* balls) {
     constexpr int DP = D <= 4 ? 4 : D;
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (j >= poff[ncl]) return;
-    const int r = j + kFarRuns * upper_cloud(poff, ncl, j);
+    const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (r >= runs) return;
     const int cnt = start[r + 1] - start[r];
+    if (cnt > kBallRows) {
+        if (lane < DP) balls[(long long)r * (DP + 4) + lane] = 0.0f;
+        if (lane == 0) balls[(long long)r * (DP + 4) + DP] = __builtin_inff();
+        return;
+    }
     const float4* src = reinterpret_cast<const float4*>(tiles) + (long long)tile_start[r] * 64 * (DP / 4);
     auto row = [&](int i, float (&x)[DP]) {
 #pragma unroll
@@ -448,11 +454,46 @@ __global__ __launch_bounds__(256) void run_ball_kernel(const float* __restrict__
     }
     r2 = -lane_value(wave_min63(-r2), 63);
     if (lane == 0) {
-        float* o = balls + (long long)j * (DP + 4);
+        float* o = balls + (long long)r * (DP + 4);
 #pragma unroll
         for (int k = 0; k < DP; ++k) o[k] = c[k];
         o[DP] = sqrtf(r2) * scale * 1.0001f + 1e-30f;
     }
+}
+
+// Row-major tiles of other rows in an index's order (a row per slot).
+template <int D>
+__global__ __launch_bounds__(256) void run_regroup_kernel(const float* __restrict__ S, int d,
+                                                          const int32_t* __restrict__ rows,
+                                                          const int32_t* __restrict__ tile_start, int runs,
+                                                          float* tiles) {
+    constexpr int DP = D <= 4 ? 4 : D;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= tile_start[runs] * 64) return;
+    const int row = rows[e];
+    float4* out = reinterpret_cast<float4*>(tiles) + (long long)e * (DP / 4);
+#pragma unroll
+    for (int q = 0; q < DP / 4; ++q) {
+        float x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = (row >= 0 && 4 * q + k < d) ? S[(long long)row * d + 4 * q + k] : 0.0f;
+        out[q] = make_float4(x[0], x[1], x[2], x[3]);
+    }
+}
+
+hipError_t launch_balls(const RunIndex& r, const float* tiles, float* balls, hipStream_t s) {
+    const dim3 bg((r.sz.runs + 3) / 4);
+#define FMS_CASE(DD)                                                                                            \
+    case DD:                                                                                                    \
+        hipLaunchKernelGGL((run_ball_kernel<DD>), bg, dim3(256), 0, s, tiles, r.run_start, r.tile_start,         \
+                           r.sz.runs, r.scale, balls);                                                          \
+        break;
+    switch (r.D) {
+        FMS_CASE(1) FMS_CASE(2) FMS_CASE(3) FMS_CASE(4) FMS_CASE(8) FMS_CASE(16) FMS_CASE(32)
+        default: return hipErrorInvalidValue;
+    }
+#undef FMS_CASE
+    return hipGetLastError();
 }
 
 // Distances between the pivots, rounded down (1e-4 relative).
@@ -556,19 +597,23 @@ hipError_t launch_run_index(RunIndex& r, const float* X, const long long* xo_src
         default: return hipErrorInvalidValue;
     }
 #undef FMS_CASE
-    if (!r.row_major) return hipGetLastError();
-    const dim3 bg((z.ptot + 3) / 4);
+    if (r.row_major) return launch_balls(r, r.tiles, r.ball_rows, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_run_regroup(const RunIndex& r, const float* S, float* tiles, float* balls, hipStream_t s) {
+    const dim3 g((unsigned)(((long long)r.sz.max_tiles * 64 + 255) / 256));
 #define FMS_CASE(DD)                                                                                           \
     case DD:                                                                                                   \
-        hipLaunchKernelGGL((run_ball_kernel<DD>), bg, dim3(256), 0, s, r.tiles, r.run_start, r.tile_start,      \
-                           r.poff, z.ncl, scale, r.ball_rows);                                                 \
+        hipLaunchKernelGGL((run_regroup_kernel<DD>), g, dim3(256), 0, s, S, r.d, r.rows, r.tile_start,          \
+                           r.sz.runs, tiles);                                                                  \
         break;
     switch (r.D) {
         FMS_CASE(1) FMS_CASE(2) FMS_CASE(3) FMS_CASE(4) FMS_CASE(8) FMS_CASE(16) FMS_CASE(32)
         default: return hipErrorInvalidValue;
     }
 #undef FMS_CASE
-    return hipGetLastError();
+    return launch_balls(r, tiles, balls, s);
 }
 
 hipError_t launch_run_seeds(const RunIndex& r, const float* S, int m, RunSeeds& q, hipStream_t s) {
