@@ -83,9 +83,11 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 //
 // A workgroup of four waves takes 256 points, a wave two column tiles of 32;
 // the modes pass in tiles of 32, split to bf16 in LDS by the workgroup (the
-// next tile's rows loaded ahead).  Bound by the matrix unit (7 products of
-// 32 x 32 x 16 a tile and pass at D = 32).  262,144 points x 928 modes, D = 32:
-// see launch_assign.
+// next tile's rows loaded ahead).  The matrix unit (7 products of 32 x 32 x 16
+// a tile and pass at D = 32), the rest of the two passes on the VALU and the
+// barriers take a similar time each.  Rows of exactly D coordinates are read
+// in wide loads: by single coordinates, the points' and the candidates' rows
+// alone cost 50 us of the first form's 194 us.
 constexpr int kAsgCand = 10;
 
 template <int D, bool MARGIN>
@@ -108,12 +110,26 @@ __global__ __launch_bounds__(kT) void assign_mfma_kernel(const float* __restrict
         const int p = base + ct * 32 + (lane & 31);
         const float* row = X + (long long)(p < n ? p : n - 1) * d;
         float nn = 0.0f;
+        float xv[KB][8];
+        if (D >= 16 && d == D) {   // whole rows, in wide loads
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xv[kb][e] = row[kb * 16 + half * 8 + e] - modes[kb * 16 + half * 8 + e];
+        } else {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int c = kb * 16 + half * 8 + e;
+                    xv[kb][e] = c < d ? row[c] - modes[c] : 0.0f;
+                }
+        }
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int c = kb * 16 + half * 8 + e;
-                const float v = c < d ? row[c] - modes[c] : 0.0f;
+                const float v = xv[kb][e];
                 nn = fmaf(v, v, nn);
                 bh[ct][kb][e] = (__bf16)(2.0f * v);
                 bl[ct][kb][e] = (__bf16)(2.0f * v - (float)bh[ct][kb][e]);
@@ -134,17 +150,25 @@ __global__ __launch_bounds__(kT) void assign_mfma_kernel(const float* __restrict
 
     // mode tiles: row threadIdx / 8 of the tile, coordinates EPT (threadIdx % 8) ..
     const int mrow = threadIdx.x >> 3, mseg = threadIdx.x & 7;
-    float mv[EPT];
+    float mv[EPT], ref[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) ref[e] = mseg * EPT + e < d ? modes[mseg * EPT + e] : 0.0f;
     auto load = [&](int t) {
         const int j = t * 32 + mrow;
+        const float* src = modes + (long long)(j < k ? j : 0) * d;
+        if (d == D) {
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int c = mseg * EPT + e;
-            mv[e] = (j < k && c < d) ? modes[(long long)j * d + c] - modes[c] : 0.0f;
+            for (int e = 0; e < EPT; ++e) mv[e] = src[mseg * EPT + e] - ref[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) {
+                const int c = mseg * EPT + e;
+                mv[e] = c < d ? src[c] - ref[e] : 0.0f;
+            }
         }
     };
-    auto store = [&](int t, int buf) {
-        __bf16* f = sf[buf];
+    auto store = [&](int t) {
+        __bf16* f = sf[t & 1];
         float nn = 0.0f;
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
@@ -170,43 +194,39 @@ __global__ __launch_bounds__(kT) void assign_mfma_kernel(const float* __restrict
             nv[2] = (__bf16)(r - (float)m);
             nv[3] = nv[4] = nv[5] = (__bf16)1.0f;
             *reinterpret_cast<bf16x8*>(f + 2 * KB * 512 + mrow * 8) = nv;
-            *reinterpret_cast<bf16x8*>(f + 2 * KB * 512 + (mrow + 32) * 8) = bf16x8{};
         }
     };
-    if (D < 16) {   // the padding coordinates of the only block stay zero
-        for (int e = threadIdx.x; e < 2 * F * 512; e += kT) sf[0][e] = (__bf16)0.0f;
-        __syncthreads();
-    }
+    // what the stores leave alone stays zero: the norms' upper half, and the
+    // padding coordinates of a single block
+    for (int e = threadIdx.x; e < 2 * F * 512 / 8; e += kT) reinterpret_cast<bf16x8*>(sf)[e] = bf16x8{};
+    __syncthreads();
 
     const int tiles = (k + 31) / 32;
-    // f(tile, column tile, E) for every tile of modes
+    // f(tile, E of the first column tile, E of the second) for every tile of modes
     auto pass = [&](auto&& f) {
         load(0);
-        store(0, 0);
+        store(0);
         if (tiles > 1) load(1);
         __syncthreads();
         for (int t = 0; t < tiles; ++t) {
-            if (t + 1 < tiles) store(t + 1, (t + 1) & 1);
+            if (t + 1 < tiles) store(t + 1);
             if (t + 2 < tiles) load(t + 2);
             const bf16x8* af = reinterpret_cast<const bf16x8*>(sf[t & 1]) + lane;
-            bf16x8 ah[KB], al[KB];
+            const bf16x8 an = af[2 * KB * 64];
+            f32x16 E0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(an, bn[0], f32x16{}, 0, 0, 0);
+            f32x16 E1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(an, bn[1], f32x16{}, 0, 0, 0);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
-                ah[kb] = af[(2 * kb) * 64];
-                al[kb] = af[(2 * kb + 1) * 64];
+                const bf16x8 ah = af[(2 * kb) * 64], al = af[(2 * kb + 1) * 64];
+                E0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[0][kb], E0, 0, 0, 0);
+                E1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[1][kb], E1, 0, 0, 0);
+                E0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[0][kb], E0, 0, 0, 0);
+                E1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[1][kb], E1, 0, 0, 0);
+                E0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[0][kb], E0, 0, 0, 0);
+                E1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[1][kb], E1, 0, 0, 0);
             }
-            const bf16x8 an = af[2 * KB * 64];
-#pragma unroll
-            for (int ct = 0; ct < 2; ++ct) {
-                f32x16 E = __builtin_amdgcn_mfma_f32_32x32x16_bf16(an, bn[ct], f32x16{}, 0, 0, 0);
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) {
-                    E = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[kb], bl[ct][kb], E, 0, 0, 0);
-                    E = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[kb], bh[ct][kb], E, 0, 0, 0);
-                    E = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[kb], bh[ct][kb], E, 0, 0, 0);
-                }
-                f(t, ct, E);
-            }
+            f(t, 0, E0);
+            f(t, 1, E1);
             __syncthreads();
         }
     };
@@ -251,6 +271,16 @@ __global__ __launch_bounds__(kT) void assign_mfma_kernel(const float* __restrict
         }
     });
 
+    // a row by its lane, zeros past d; a full row in wide loads
+    auto load_padded = [&](const float* row, float* v) {
+        if (d == D) {
+#pragma unroll
+            for (int q = 0; q < D; ++q) v[q] = row[q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < D; ++q) v[q] = q < d ? row[q] : 0.0f;
+        }
+    };
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
         const int p = base + ct * 32 + (lane & 31);
@@ -258,8 +288,7 @@ __global__ __launch_bounds__(kT) void assign_mfma_kernel(const float* __restrict
         const bool all = over || __shfl_xor((int)over, 32);   // either half's list
         float x[D];
         const float* row = X + (long long)(p < n ? p : n - 1) * d;
-#pragma unroll
-        for (int q = 0; q < D; ++q) x[q] = q < d ? row[q] : 0.0f;
+        load_padded(row, x);
         float best = __builtin_inff(), second = __builtin_inff();
         int arg = 0x7fffffff;
         // the scan's halves: even and odd modes
@@ -267,10 +296,11 @@ __global__ __launch_bounds__(kT) void assign_mfma_kernel(const float* __restrict
         for (int i = 0; __ballot(i < count); ++i) {
             if (i < count) {
                 const int j = all ? 2 * i + half : cand[wave][ct][i < kAsgCand ? i : 0][lane];
-                float dd = 0.0f;
+                float dd = 0.0f, y[D];
+                load_padded(modes + (long long)j * d, y);
 #pragma unroll
                 for (int q = 0; q < D; ++q) {
-                    const float t = q < d ? x[q] - modes[(long long)j * d + q] : 0.0f;
+                    const float t = x[q] - y[q];
                     dd = fmaf(t, t, dd);
                 }
                 // the lowest index among equals, in whatever order they come
@@ -309,14 +339,23 @@ __global__ void check_finite_kernel(const float* __restrict__ X, long long count
 
 }  // namespace
 
-// Modes from which the candidates come from the matrix cores.
-constexpr int kAsgModes = 64;
+// Modes from which the candidates come from the matrix cores: under them the
+// points' setup and the exact distances cost more than the passes save.
+// Measured against the direct form (assign_kernel), us:
+//   D = 32, 262,144 points: k = 64 44 -> 27, 500 210 -> 76
+//   D = 64,  50,000 points: k = 64 44 -> 22, 500 276 -> 73
+//   D = 16,  30,000 points: k = 64 13.5 -> 11.4, 500 78 -> 43
+//   D = 8,  100,000 points: k = 64 10.5 -> 11.1, 128 18 -> 15, 500 63 -> 37
+//   d = 9,  200,000 points (rows short of D): k = 64 16 -> 20, 500 101 -> 55
+bool assign_by_matrix(int D, int d, int k) {
+    return D >= 8 && D <= 64 && k >= (D >= 16 && d == D ? 64 : 128);
+}
 
 hipError_t launch_assign(const float* X, int n, int d, const float* modes, int k,
                          int32_t* labels, float* margin, hipStream_t s) {
     const int blocks = (n + kT - 1) / kT;
     const int Dw = step_shape(d).D;
-    if (Dw >= 8 && Dw <= 64 && k >= kAsgModes) {
+    if (assign_by_matrix(Dw, d, k)) {
 #define FMS_CASE(DD)                                                                                             \
     if (Dw == DD) {                                                                                              \
         if (margin)                                                                                              \

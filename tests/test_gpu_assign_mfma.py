@@ -1,4 +1,4 @@
-"""Labels by candidates from the matrix cores (d > 4, 64 modes or more) against
+"""Labels by candidates from the matrix cores (d > 4, 64 or 128 modes or more) against
 FP64 distances: padded and exact dimensions, tails of points and modes,
 coincident modes (lowest index), points whose candidate list overflows, data
 far from the origin, and values that are not finite."""
@@ -41,7 +41,7 @@ def _check(X, M):
 
 
 @pytest.mark.parametrize("d", [5, 8, 13, 16, 31, 32, 33, 64])
-@pytest.mark.parametrize("n,k", [(1, 64), (257, 65), (3000, 100), (5001, 927)])
+@pytest.mark.parametrize("n,k", [(1, 64), (257, 65), (257, 129), (3000, 100), (5001, 927)])
 def test_labels_and_margins(d, n, k):
     X, M = _data(n + k + d, n, k, d)
     _check(X, M)
