@@ -10,11 +10,20 @@
 //     beta_ij = w_ij * g_j.(x_i - s'_j) / (h^2 W_j)
 //     dL/ds_j += sum_i beta_ij (x_i - s_j)
 //     dL/dx_i += sum_j (w_ij / W_j) g_j + beta_ij (s_j - x_i)
-// Three passes over the pairs recompute the weights each time; no m x n
-// weight matrix is ever stored.  Each pass splits its inner sum into kP
-// chunks (one partial per chunk) that a reduction kernel adds in chunk
-// order, so results are bitwise reproducible.  The inner loop of every pass
-// streams the other set's rows through wave-uniform (scalar) loads.
+// Two passes over the pairs (three for wide rows: one_pass()) recompute the
+// weights each time; no m x n weight matrix is ever stored.  Lanes are rows of one set (64 to a wave);
+// the other set's rows stream past in wave-uniform (scalar) loads, split over
+// the four waves of a workgroup, whose sums join in LDS in wave order, and over
+// chunk_count() workgroups, whose partials a reduction kernel adds in chunk
+// order: results are bitwise reproducible.
+//
+// These sizes (FP64, and FP32 under the run form's line) leave the chip idle
+// before they fill it, so the split follows the sizes.  2 clouds of 1,501
+// points, d = 8, FP64, two updates and their adjoints, with 8 fixed chunks of
+// 256-row blocks (96 workgroups a pass) and now: update 42 -> 15 us, update and
+// dS 90 -> 18, dX 102 -> 21, reductions 6 -> 4 each; what is left is the FP64
+// VALU (an exponential and 3 to 6 operations a coordinate) and the latency of
+// the reductions.
 
 #include "fms_internal.h"
 
@@ -23,7 +32,48 @@ namespace fms {
 namespace {
 
 constexpr int kT = 256;
-constexpr int kP = 8;   // inner-sum chunks per pass
+constexpr int kRows = 64;        // rows of a workgroup: its lanes
+constexpr int kW = kT / kRows;   // waves, each with its share of the inner rows
+
+// Inner-sum chunks of a pass over `rows` x `inner` pairs of nb clouds: enough
+// workgroups for three waves a SIMD while a wave keeps 16 inner rows, and never
+// under two, so that no partial sum is longer than an eighth of the whole.
+int chunk_count(int nb, long long rows, long long inner) {
+    const long long blocks = nb * ((rows + kRows - 1) / kRows);
+    long long c = (768 + blocks - 1) / blocks;
+    const long long most = inner / (16 * kW);
+    if (c > most) c = most;
+    if (c > 64) c = 64;
+    return c < 2 ? 2 : (int)c;
+}
+
+// Sums acc over the workgroup's waves in wave order; the last wave ends with the total.
+template <typename T, int N>
+__device__ __forceinline__ void join_waves(T* acc) {
+    __shared__ T red[N][kRows];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int w = 0; w < kW; ++w) {
+        if (wave == w) {
+            if (w > 0) {
+#pragma unroll
+                for (int k = 0; k < N; ++k) acc[k] += red[k][lane];
+            }
+            if (w < kW - 1) {
+#pragma unroll
+                for (int k = 0; k < N; ++k) red[k][lane] = acc[k];
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The inner rows [first, last) of this wave.
+__device__ __forceinline__ void inner_range(int inner, int& first, int& last) {
+    const long long part = (long long)blockIdx.y * kW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long parts = (long long)gridDim.y * kW;
+    first = (int)(inner * part / parts);
+    last = (int)(inner * (part + 1) / parts);
+}
 
 template <typename T>
 __device__ __forceinline__ T expw(T q, T c);   // exp(c q), c = -1/(2h^2)
@@ -56,19 +106,20 @@ __device__ __forceinline__ void load_row(const T* __restrict__ A, long long row,
     }
 }
 
-// Forward partials: lane = seed j, chunk of points.  part[(b*kP + c)*(D+1) + k][m]
+// Forward partials: lane = seed j, chunk of points.  part[(b*chunks + c)*(D+1) + k][m]
 template <typename T, int D, bool EXACT>
 __global__ __launch_bounds__(kT) void fwd_partial_kernel(const T* __restrict__ X, int n,
                                                          const T* __restrict__ S, int m, int d,
                                                          T c, T* __restrict__ part) {
-    const int b = blockIdx.z, chunk = blockIdx.y;
-    const int j = blockIdx.x * kT + threadIdx.x;
+    const int b = blockIdx.z, chunk = blockIdx.y, lane = threadIdx.x & 63;
+    const int j = blockIdx.x * kRows + lane;
     const T* Xb = X + (long long)b * n * d;
     T s[D], acc[D + 1];
     load_row<T, D, EXACT>(S + (long long)b * m * d, j < m ? j : 0, d, s);
 #pragma unroll
     for (int k = 0; k <= D; ++k) acc[k] = T(0);
-    const int p0 = (int)((long long)n * chunk / kP), p1 = (int)((long long)n * (chunk + 1) / kP);
+    int p0, p1;
+    inner_range(n, p0, p1);
     for (int i = p0; i < p1; ++i) {
         T x[D];
         load_row<T, D, EXACT>(Xb, i, d, x);
@@ -83,39 +134,122 @@ __global__ __launch_bounds__(kT) void fwd_partial_kernel(const T* __restrict__ X
 #pragma unroll
         for (int k = 0; k < D; ++k) acc[k] = fma(w, dx[k], acc[k]);
     }
-    if (j < m) {
-        T* out = part + (long long)(b * kP + chunk) * (D + 1) * m + j;
+    join_waves<T, D + 1>(acc);
+    if (threadIdx.x >= kT - kRows && j < m) {
+        T* out = part + ((long long)b * gridDim.y + chunk) * (D + 1) * m + j;
 #pragma unroll
         for (int k = 0; k <= D; ++k) out[(long long)k * m] = acc[k];
     }
 }
 
 // Reduce forward partials: S_out = s + delta; keeps delta and 1/W per seed.
+// A thread per coordinate and seed; W is summed by each.
 template <typename T, int D>
 __global__ void fwd_reduce_kernel(const T* __restrict__ part, const T* __restrict__ S, int m,
-                                  int d, T* S_out, T* delta, T* invW) {
-    const int b = blockIdx.y;
+                                  int d, int chunks, T* S_out, T* delta, T* invW) {
+    const int b = blockIdx.z, k = blockIdx.y;
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= m) return;
-    T a[D + 1];
-#pragma unroll
-    for (int k = 0; k <= D; ++k) a[k] = T(0);
-    for (int c = 0; c < kP; ++c) {
-        const T* p = part + (long long)(b * kP + c) * (D + 1) * m + j;
-#pragma unroll
-        for (int k = 0; k <= D; ++k) a[k] += p[(long long)k * m];
+    T a = T(0), w = T(0);
+    const T* p = part + (long long)b * chunks * (D + 1) * m + j;
+#pragma unroll 8
+    for (int c = 0; c < chunks; ++c) {
+        a += p[((long long)c * (D + 1) + k) * m];
+        w += p[((long long)c * (D + 1) + D) * m];
     }
-    const T iw = T(1) / a[D];
+    const T iw = T(1) / w;
     const long long row = (long long)b * m + j;
-    if (invW) invW[row] = iw;
+    if (invW && k == 0) invW[row] = iw;
+    const T dk = a * iw;
+    if (delta) delta[row * d + k] = dk;
+    if (S_out) S_out[row * d + k] = S[row * d + k] + dk;
+}
+
+// The update and dS in one pass over the pairs: with W and delta not known
+// before its end, dS is taken from
+//     sum_i beta_ij (x_i - s_j) = (B_j - (g_j.delta_j) A_j) / (h^2 W_j),
+//     A_j = sum_i w_ij (x_i - s_j),  B_j = sum_i w_ij g_j.(x_i - s_j) (x_i - s_j) .
+// part[(b*chunks + c)*(2D+1) + k][m]: A, W, B.
+template <typename T, int D, bool EXACT>
+__global__ __launch_bounds__(kT) void fwd_ds_partial_kernel(const T* __restrict__ X, int n,
+                                                            const T* __restrict__ S, int m, int d,
+                                                            T c, const T* __restrict__ G,
+                                                            T* __restrict__ part) {
+    const int b = blockIdx.z, chunk = blockIdx.y, lane = threadIdx.x & 63;
+    const int j = blockIdx.x * kRows + lane;
+    const T* Xb = X + (long long)b * n * d;
+    T s[D], g[D], acc[2 * D + 1];
+    load_row<T, D, EXACT>(S + (long long)b * m * d, j < m ? j : 0, d, s);
+    load_row<T, D, EXACT>(G + (long long)b * m * d, j < m ? j : 0, d, g);
 #pragma unroll
-    for (int k = 0; k < D; ++k) {   // constant indices keep a[] in registers
-        if (k < d) {
-            const T dk = a[k] * iw;
-            if (delta) delta[row * d + k] = dk;
-            if (S_out) S_out[row * d + k] = S[row * d + k] + dk;
+    for (int k = 0; k <= 2 * D; ++k) acc[k] = T(0);
+    int p0, p1;
+    inner_range(n, p0, p1);
+    for (int i = p0; i < p1; ++i) {
+        T x[D];
+        load_row<T, D, EXACT>(Xb, i, d, x);
+        T dx[D], q = T(0), gdx = T(0);
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            dx[k] = x[k] - s[k];
+            q = fma(dx[k], dx[k], q);
+            gdx = fma(g[k], dx[k], gdx);
+        }
+        const T w = expw<T>(q, c);
+        const T wg = w * gdx;
+        acc[D] += w;
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            acc[k] = fma(w, dx[k], acc[k]);
+            acc[D + 1 + k] = fma(wg, dx[k], acc[D + 1 + k]);
         }
     }
+    join_waves<T, 2 * D + 1>(acc);
+    if (threadIdx.x >= kT - kRows && j < m) {
+        T* out = part + ((long long)b * gridDim.y + chunk) * (2 * D + 1) * m + j;
+#pragma unroll
+        for (int k = 0; k <= 2 * D; ++k) out[(long long)k * m] = acc[k];
+    }
+}
+
+// dS += from the partials above, and 1/W and g.delta for the dX pass.  Lanes
+// are seeds, the waves share the sums; these are in FP64, so that the
+// difference loses nothing.
+template <typename T, int D>
+__global__ __launch_bounds__(kT) void fwd_ds_reduce_kernel(const T* __restrict__ part, int m, int d, int chunks,
+                                                           double inv_h2, const T* __restrict__ G, T* dS,
+                                                           T* __restrict__ invW, T* __restrict__ gdel_out) {
+    __shared__ double sum[2 * D + 1][kRows];
+    const int b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = blockIdx.x * kRows + lane;
+    const T* p = part + (long long)b * chunks * (2 * D + 1) * m + (j < m ? j : 0);
+    for (int k = wave; k <= 2 * D; k += kW) {
+        double a = 0.0;
+#pragma unroll 8
+        for (int c = 0; c < chunks; ++c) a += (double)p[((long long)c * (2 * D + 1) + k) * m];
+        sum[k][lane] = a;
+    }
+    __syncthreads();
+    if (j >= m) return;
+    const long long row = (long long)b * m + j;
+    const double iw = 1.0 / sum[D][lane];
+    double gd = 0.0;
+#pragma unroll
+    for (int k = 0; k < D; ++k)
+        if (k < d) gd = fma((double)G[row * d + k], sum[k][lane] * iw, gd);
+    if (wave == 0) {
+        invW[row] = (T)iw;
+        gdel_out[row] = (T)gd;
+    }
+    for (int k = wave; k < d; k += kW)
+        dS[row * d + k] += (T)((sum[D + 1 + k][lane] - gd * sum[k][lane]) * (inv_h2 * iw));
+}
+
+// Rows up to which the one pass keeps its sums in registers: past it (FP32
+// D = 64, FP64 D >= 32) the update and dS are passes of their own.
+template <typename T, int D>
+constexpr bool one_pass() {
+    return D * sizeof(T) <= 128;
 }
 
 // dS partials: lane = seed j, chunk of points.
@@ -127,8 +261,8 @@ __global__ __launch_bounds__(kT) void ds_partial_kernel(const T* __restrict__ X,
                                                         const T* __restrict__ invW,
                                                         T* __restrict__ gdel_out,
                                                         T* __restrict__ part) {
-    const int b = blockIdx.z, chunk = blockIdx.y;
-    const int j = blockIdx.x * kT + threadIdx.x;
+    const int b = blockIdx.z, chunk = blockIdx.y, lane = threadIdx.x & 63;
+    const int j = blockIdx.x * kRows + lane;
     const int jj = j < m ? j : 0;
     const long long row = (long long)b * m + jj;
     const T* Xb = X + (long long)b * n * d;
@@ -139,11 +273,12 @@ __global__ __launch_bounds__(kT) void ds_partial_kernel(const T* __restrict__ X,
 #pragma unroll
     for (int k = 0; k < D; ++k)
         if (k < d) gdel = fma(g[k], delta[row * d + k], gdel);
-    if (chunk == 0 && j < m) gdel_out[row] = gdel;   // g_j . delta_j, read by the dX pass
+    if (chunk == 0 && threadIdx.x < kRows && j < m) gdel_out[row] = gdel;   // g_j . delta_j, read by the dX pass
     const T coef = inv_h2 * invW[row];
 #pragma unroll
     for (int k = 0; k < D; ++k) acc[k] = T(0);
-    const int p0 = (int)((long long)n * chunk / kP), p1 = (int)((long long)n * (chunk + 1) / kP);
+    int p0, p1;
+    inner_range(n, p0, p1);
     for (int i = p0; i < p1; ++i) {
         T x[D];
         load_row<T, D, EXACT>(Xb, i, d, x);
@@ -159,8 +294,9 @@ __global__ __launch_bounds__(kT) void ds_partial_kernel(const T* __restrict__ X,
 #pragma unroll
         for (int k = 0; k < D; ++k) acc[k] = fma(beta, dx[k], acc[k]);
     }
-    if (j < m) {
-        T* out = part + (long long)(b * kP + chunk) * D * m + j;
+    join_waves<T, D>(acc);
+    if (threadIdx.x >= kT - kRows && j < m) {
+        T* out = part + ((long long)b * gridDim.y + chunk) * D * m + j;
 #pragma unroll
         for (int k = 0; k < D; ++k) out[(long long)k * m] = acc[k];
     }
@@ -174,8 +310,8 @@ __global__ __launch_bounds__(kT) void dx_partial_kernel(const T* __restrict__ X,
                                                         const T* __restrict__ gdel,
                                                         const T* __restrict__ invW,
                                                         T* __restrict__ part) {
-    const int b = blockIdx.z, chunk = blockIdx.y;
-    const int i = blockIdx.x * kT + threadIdx.x;
+    const int b = blockIdx.z, chunk = blockIdx.y, lane = threadIdx.x & 63;
+    const int i = blockIdx.x * kRows + lane;
     const T* Sb = S + (long long)b * m * d;
     const T* Gb = G + (long long)b * m * d;
     const T* Eb = gdel + (long long)b * m;
@@ -184,7 +320,8 @@ __global__ __launch_bounds__(kT) void dx_partial_kernel(const T* __restrict__ X,
     load_row<T, D, EXACT>(X + (long long)b * n * d, i < n ? i : 0, d, x);
 #pragma unroll
     for (int k = 0; k < D; ++k) acc[k] = T(0);
-    const int j0 = (int)((long long)m * chunk / kP), j1 = (int)((long long)m * (chunk + 1) / kP);
+    int j0, j1;
+    inner_range(m, j0, j1);
     for (int j = j0; j < j1; ++j) {
         T s[D], g[D];
         load_row<T, D, EXACT>(Sb, j, d, s);
@@ -204,24 +341,24 @@ __global__ __launch_bounds__(kT) void dx_partial_kernel(const T* __restrict__ X,
 #pragma unroll
         for (int k = 0; k < D; ++k) acc[k] = fma(a, g[k], fma(-beta, dx[k], acc[k]));
     }
-    if (i < n) {
-        T* out = part + (long long)(b * kP + chunk) * D * n + i;
+    join_waves<T, D>(acc);
+    if (threadIdx.x >= kT - kRows && i < n) {
+        T* out = part + ((long long)b * gridDim.y + chunk) * D * n + i;
 #pragma unroll
         for (int k = 0; k < D; ++k) out[(long long)k * n] = acc[k];
     }
 }
 
-// out[row, k] += sum over chunks of part (chunk order).
+// out[row, k] += sum over chunks of part (chunk order).  A thread per element.
 template <typename T, int D>
-__global__ void add_reduce_kernel(const T* __restrict__ part, int rows, int d, T* out) {
-    const int b = blockIdx.y;
+__global__ void add_reduce_kernel(const T* __restrict__ part, int rows, int d, int chunks, T* out) {
+    const int b = blockIdx.z, k = blockIdx.y;
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= rows) return;
-    for (int k = 0; k < d; ++k) {
-        T a = T(0);
-        for (int c = 0; c < kP; ++c) a += part[((long long)(b * kP + c) * D + k) * rows + r];
-        out[((long long)b * rows + r) * d + k] += a;
-    }
+    T a = T(0);
+#pragma unroll 8
+    for (int c = 0; c < chunks; ++c) a += part[(((long long)b * chunks + c) * D + k) * rows + r];
+    out[((long long)b * rows + r) * d + k] += a;
 }
 
 template <typename T>
@@ -232,42 +369,51 @@ T weight_coef(double h) {
 template <typename T, int D>
 hipError_t fwd_t(const T* X, int nb, int n, const T* S, int m, int d, double h, T* S_out,
                  T* delta, T* invW, T* part, hipStream_t s) {
-    dim3 g1((m + kT - 1) / kT, kP, nb);
+    const int chunks = chunk_count(nb, m, n);
+    dim3 g1((m + kRows - 1) / kRows, chunks, nb);
     if (d == D)
         hipLaunchKernelGGL((fwd_partial_kernel<T, D, true>), g1, dim3(kT), 0, s, X, n, S, m, d,
                            weight_coef<T>(h), part);
     else
         hipLaunchKernelGGL((fwd_partial_kernel<T, D, false>), g1, dim3(kT), 0, s, X, n, S, m, d,
                            weight_coef<T>(h), part);
-    dim3 g2((m + 255) / 256, nb);
-    hipLaunchKernelGGL((fwd_reduce_kernel<T, D>), g2, dim3(256), 0, s, part, S, m, d, S_out,
+    dim3 g2((m + 255) / 256, d, nb);
+    hipLaunchKernelGGL((fwd_reduce_kernel<T, D>), g2, dim3(256), 0, s, part, S, m, d, chunks, S_out,
                        delta, invW);
     return hipGetLastError();
 }
 
 template <typename T, int D, bool EXACT>
-void adj_passes(const T* X, int nb, int n, const T* S, int m, int d, T c, T ih2, const T* G,
-                const T* delta, const T* invW, T* gdel, T* part, T* dS, T* dX, hipStream_t s) {
-    hipLaunchKernelGGL((ds_partial_kernel<T, D, EXACT>), dim3((m + kT - 1) / kT, kP, nb), dim3(kT), 0,
-                       s, X, n, S, m, d, c, ih2, G, delta, invW, gdel, part);
-    hipLaunchKernelGGL((add_reduce_kernel<T, D>), dim3((m + 255) / 256, nb), dim3(256), 0, s,
-                       part, m, d, dS);
-    hipLaunchKernelGGL((dx_partial_kernel<T, D, EXACT>), dim3((n + kT - 1) / kT, kP, nb), dim3(kT), 0,
+hipError_t adj_passes(const T* X, int nb, int n, const T* S, int m, int d, double h, const T* G,
+                      T* delta, T* invW, T* gdel, T* part, T* dS, T* dX, hipStream_t s) {
+    const T c = weight_coef<T>(h);
+    const T ih2 = T(1.0 / (h * h));
+    const int cs = chunk_count(nb, m, n), cx = chunk_count(nb, n, m);
+    const dim3 gs((m + kRows - 1) / kRows, cs, nb);
+    if constexpr (one_pass<T, D>()) {
+        hipLaunchKernelGGL((fwd_ds_partial_kernel<T, D, EXACT>), gs, dim3(kT), 0, s, X, n, S, m, d, c, G, part);
+        hipLaunchKernelGGL((fwd_ds_reduce_kernel<T, D>), dim3(gs.x, nb), dim3(kT), 0, s, part, m, d, cs,
+                           1.0 / (h * h), G, dS, invW, gdel);
+    } else {
+        const hipError_t e = fwd_t<T, D>(X, nb, n, S, m, d, h, nullptr, delta, invW, part, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((ds_partial_kernel<T, D, EXACT>), gs, dim3(kT), 0, s, X, n, S, m, d, c, ih2, G, delta,
+                           invW, gdel, part);
+        hipLaunchKernelGGL((add_reduce_kernel<T, D>), dim3((m + 255) / 256, d, nb), dim3(256), 0, s,
+                           part, m, d, cs, dS);
+    }
+    hipLaunchKernelGGL((dx_partial_kernel<T, D, EXACT>), dim3((n + kRows - 1) / kRows, cx, nb), dim3(kT), 0,
                        s, X, n, S, m, d, c, ih2, G, gdel, invW, part);
-    hipLaunchKernelGGL((add_reduce_kernel<T, D>), dim3((n + 255) / 256, nb), dim3(256), 0, s,
-                       part, n, d, dX);
+    hipLaunchKernelGGL((add_reduce_kernel<T, D>), dim3((n + 255) / 256, d, nb), dim3(256), 0, s,
+                       part, n, d, cx, dX);
+    return hipGetLastError();
 }
 
 template <typename T, int D>
 hipError_t adj_t(const T* X, int nb, int n, const T* S, int m, int d, double h, const T* G,
                  T* dS, T* dX, T* delta, T* invW, T* gdel, T* part, hipStream_t s) {
-    hipError_t e = fwd_t<T, D>(X, nb, n, S, m, d, h, nullptr, delta, invW, part, s);
-    if (e != hipSuccess) return e;
-    const T c = weight_coef<T>(h);
-    const T ih2 = T(1.0 / (h * h));
-    if (d == D) adj_passes<T, D, true>(X, nb, n, S, m, d, c, ih2, G, delta, invW, gdel, part, dS, dX, s);
-    else adj_passes<T, D, false>(X, nb, n, S, m, d, c, ih2, G, delta, invW, gdel, part, dS, dX, s);
-    return hipGetLastError();
+    if (d == D) return adj_passes<T, D, true>(X, nb, n, S, m, d, h, G, delta, invW, gdel, part, dS, dX, s);
+    return adj_passes<T, D, false>(X, nb, n, S, m, d, h, G, delta, invW, gdel, part, dS, dX, s);
 }
 
 struct Ws {
@@ -277,11 +423,11 @@ struct Ws {
 
 Ws carve(void* ws, int nb, int n, int m, int d, int bytes) {
     const int D = step_shape(d).D;
-    const long long rows = n > m ? n : m;
+    const long long rs = (long long)chunk_count(nb, m, n) * m, rx = (long long)chunk_count(nb, n, m) * n;
     Ws w;
     w.base = (char*)ws;
     w.part = 0;
-    size_t off = (size_t)nb * kP * (D + 1) * rows * bytes;
+    size_t off = (size_t)nb * (2 * D + 1) * (size_t)(rs > rx ? rs : rx) * bytes;
     off = (off + 255) & ~(size_t)255;
     w.delta = off;
     off += (size_t)nb * m * d * bytes;
