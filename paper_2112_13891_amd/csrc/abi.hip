@@ -324,7 +324,7 @@ enum Slot {
     SL_BCONV, SL_BITERS, SL_BS, SL_BSH2, SL_BNM, SL_BSTATE, SL_BSTEP_S, SL_BSTEP_ACT0, SL_BSTEP_ACT1, SL_BSTEP_STATUS,
     SL_BSTEP_ITERS, SL_BSTEP_SHIFT2, SL_BSTEP_CNT, SL_BSTEP_PLAN, SL_BSTEP_ITEMC, SL_BSTEP_SLOTC, SL_BSTEP_PART,
     // the pivot runs of the points and the seeds' order over them
-    SL_RUNS0, SL_RUNS_END = SL_RUNS0 + 20, SL_RUNSEED0 = SL_RUNS_END, SL_RUNSEED_END = SL_RUNSEED0 + 8,
+    SL_SCREEN, SL_RUNS0, SL_RUNS_END = SL_RUNS0 + 20, SL_RUNSEED0 = SL_RUNS_END, SL_RUNSEED_END = SL_RUNSEED0 + 8,
     SL_COUNT = SL_RUNSEED_END
 };
 
@@ -840,6 +840,7 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
     long long pairs = 0, refined = 0, drawn_total = 0;
     double iterate_ms = 0.0, merge_ms = 0.0;
     int cur = 0;
+    bool screened = false;   // the screen's points are in place
     if (trace) std::fprintf(stderr, "[fms] fit n=%d d=%d setup %.3f ms\n", n, d, ms_since(t_start));
 
     for (;;) {
@@ -865,6 +866,14 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
         FMS_CHECK(cache_get(C, budget, SL_ACT1, B, &b.act[1]));
         FMS_CHECK(cache_get(C, budget, SL_SHIFT2, B, &b.shift2));
         FMS_CHECK(cache_get(C, budget, SL_PART, (size_t)part_floats, &b.part));
+        if (form == SEED_NONE && !bf16 && !p->plain && wide_screen_ok(sh.D, n, B)) {
+            char* base;
+            FMS_CHECK(cache_get(C, budget, SL_SCREEN, wide_screen_carve(b.screen, nullptr, sh.D, n, B), &base,
+                                screened, s));   // the points' part comes first
+            wide_screen_carve(b.screen, base, sh.D, n, B);
+            if (!screened) FMS_HIP(launch_wide_screen_points(b.screen, Xp, n, sh.D, 1.0f, nullptr, sh.D, s));
+            screened = true;
+        }
 
         const int need = (int)std::ceil((double)p->gamma * (double)B);
         int32_t* dpos = nullptr;
@@ -1176,15 +1185,16 @@ class Arena {
 
 // The body of ms_step over device buffers taken from `ws` (a Workspace or an
 // Arena).  With run = false only the buffers are requested (nothing is
-// launched): the dry run that sizes an Arena.
+// launched): the dry run that sizes an Arena.  `lean` keeps to the forms that
+// launch per iteration and take the least memory.
 template <class A>
-int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d, float* seeds, int m,
+int step_core(A& ws, bool run, bool lean, const ms_params* p, const float* X, int n, int d, float* seeds, int m,
               int n_iter, uint8_t* converged, int32_t* iters, float* shift2, hipStream_t s) {
 #define FMS_RUN(expr)                   \
     do {                                \
         if (run) FMS_HIP(expr);         \
     } while (0)
-    const SeedForm form = seed_form(p, n, d, m, n_iter, false);
+    const SeedForm form = lean ? SEED_NONE : seed_form(p, n, d, m, n_iter, false);
     const bool bf16 = bf16_form(p, d);
     const bool cull = !bf16 && !p->plain && cull_supported(d, n) &&
                       !(p->metric == MS_METRIC_COSINE && cull_reach(p->kernel, p->h) >= 2.0);
@@ -1238,9 +1248,10 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
         return MS_OK;
     }
     const size_t rows = seedf ? (size_t)(n + 63) / 64 * 64 : (size_t)n;   // whole tiles
+    const bool screen = !lean && !bf16 && !p->plain && wide_screen_ok(sh.D, n, m);
     float* Xp;
     FMS_CHECK(ws.alloc(&Xp, rows * sh.DP));
-    FMS_RUN(launch_pack_points(X, n, d, sh.DP, scale, Xp, s));
+    if (!screen) FMS_RUN(launch_pack_points(X, n, d, sh.DP, scale, Xp, s));
     SortedPoints sp;
     if (sorted) {
         char* sws;
@@ -1270,12 +1281,19 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
     FMS_CHECK(ws.alloc(&b.iters, m));
     FMS_CHECK(ws.alloc(&b.shift2, m));
     FMS_CHECK(ws.alloc(&b.part, seedf ? 1 : (size_t)step_part_floats(sh, m, b.grid)));
+    if (screen) {
+        char* base;
+        FMS_CHECK(ws.alloc(&base, wide_screen_carve(b.screen, nullptr, sh.D, n, m)));
+        wide_screen_carve(b.screen, base, sh.D, n, m);
+    }
     if (!run) return MS_OK;
+    if (screen) FMS_HIP(launch_wide_screen_points(b.screen, X, n, d, scale, Xp, sh.D, s));   // and packs them
     if (seedf) {
         FMS_CHECK(load_seeds(seeds, converged, d, m, b, n_iter, s));
     } else {
         FMS_HIP(launch_ctl_reset(ctl, 0, INT_MAX, n_iter, s));
-        FMS_HIP(launch_seed_init_from_array(seeds, converged, d, m, b, s));
+        if (screen && p->metric != MS_METRIC_COSINE) FMS_HIP(launch_wide_screen_load(seeds, converged, b, s));
+        else FMS_HIP(launch_seed_init_from_array(seeds, converged, d, m, b, s));
     }
     if (sorted && (!seedf || ssh.R > 1))   // seeds that are close in space share waves (refine work, culled blocks)
         FMS_HIP(launch_seed_order(b.S, sh.DP, sh.D, m, scale, b.status, sp.sws, b.act[0], Xp, n, s));
@@ -1288,7 +1306,7 @@ int step_core(A& ws, bool run, const ms_params* p, const float* X, int n, int d,
         return MS_OK;
     }
     for (int t = 0; t < n_iter; ++t) FMS_HIP(launch_iteration(b, t, s));
-    FMS_HIP(launch_seed_export(b, m, seeds, converged, iters, shift2, s));
+    FMS_HIP(launch_seed_store(b, m, seeds, converged, iters, shift2, s));
     return MS_OK;
 #undef FMS_RUN
 }
@@ -1300,12 +1318,12 @@ int step_impl(const ms_params* p, const float* X, int n, int d, float* seeds, in
     // of them, with their frees, took the host longer than the kernels of a
     // 512 x 200,000 step
     Arena need(nullptr, 0);
-    FMS_CHECK(step_core(need, false, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s));
+    FMS_CHECK(step_core(need, false, false, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s));
     Workspace ws(s);
     char* base;
     FMS_CHECK(ws.alloc(&base, need.used()));
     Arena a(base, need.used());
-    return step_core(a, true, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s);
+    return step_core(a, true, false, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s);
 }
 
 // Device address of this device's copy of `scratch`, looked up once per
@@ -1335,7 +1353,12 @@ int scratch_base(char** out) {
 int step_noalloc_impl(const ms_params* p, const float* X, int n, int d, float* seeds, int m, int n_iter,
                       uint8_t* converged, int32_t* iters, float* shift2, hipStream_t s) {
     Arena need(nullptr, 0);
-    FMS_CHECK(step_core(need, false, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s));
+    FMS_CHECK(step_core(need, false, false, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s));
+    const bool lean = need.used() > kScratchBytes;
+    if (lean) {
+        need = Arena(nullptr, 0);
+        FMS_CHECK(step_core(need, false, true, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s));
+    }
     if (need.used() > kScratchBytes)
         return fail(MS_E_INVALID, "ms_step_noalloc: this call needs " + std::to_string(need.used()) +
                                       " bytes of device scratch, more than the fixed " +
@@ -1343,7 +1366,7 @@ int step_noalloc_impl(const ms_params* p, const float* X, int n, int d, float* s
     char* base = nullptr;
     FMS_CHECK(scratch_base(&base));
     Arena ws(base, kScratchBytes);
-    return step_core(ws, true, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s);
+    return step_core(ws, true, lean, p, X, n, d, seeds, m, n_iter, converged, iters, shift2, s);
 }
 
 // Seeds per lane that the batched step is built for, by padded dimension.
@@ -1706,7 +1729,7 @@ int step_batched_impl(const ms_params* p, const float* X, const int64_t* x_off, 
             FMS_HIP(launch_batched_iteration(b, xo_dev, so_dev, ncl, cnt, plan, item_cloud, slot_cloud, t, s));
     }
     if (ev) FMS_HIP(hipEventRecord(ev[1], s));
-    FMS_HIP(launch_seed_export(b, M, seeds, converged, iters, shift2, s));
+    FMS_HIP(launch_seed_store(b, M, seeds, converged, iters, shift2, s));
     return MS_OK;
 }
 

@@ -68,6 +68,18 @@ StepShape step_shape(int d);
 StepShape step_shape_for(int d, int B);
 
 
+// Buffers of the wide step's screen (k_wide_screen.hip); points and seeds as
+// operands of the matrix unit, and a bit per seed and point.
+struct WideScreen {
+    void* pf = nullptr;                  // points' operands
+    float* nx = nullptr;                 // per point: its share of the test (NaN: always kept)
+    void* sf = nullptr;                  // seeds' operands
+    float* crow = nullptr;               // per seed: its share of the test
+    unsigned long long* mask = nullptr;  // seeds x words
+    int words = 0;
+    bool loaded = false;                 // the seeds' operands are made where the seeds are loaded
+};
+
 // Packed device state of one batch (all pointers device memory).
 struct Batch {
     int n;                 // points
@@ -101,6 +113,7 @@ struct Batch {
     const int32_t* boff = nullptr;   // BF16 form over many clouds: blocks before each cloud
     unsigned long long* prog = nullptr;   // host-mapped progress word (t << 32 | m), or NULL
     int metric = MS_METRIC_EUCLIDEAN;     // cosine: seeds are renormalized after each update
+    WideScreen screen;                    // rows of padded D >= 64: mask == NULL runs the all-pairs form
     Ctl* ctl;
 };
 
@@ -122,12 +135,22 @@ hipError_t launch_seed_init_from_array(const float* seeds, const uint8_t* conv_i
                                        int d, int m, Batch& b, hipStream_t s);
 hipError_t launch_ctl_reset(Ctl* ctl, int B, int need, int max_iter, hipStream_t s);
 hipError_t launch_iteration(Batch& b, int t, hipStream_t s);
-hipError_t launch_seed_export(const Batch& b, int m, float* seeds, uint8_t* conv,
-                              int32_t* iters, float* shift2, hipStream_t s);
 int step_grid(const StepShape& sh, int B, int n);
 
 // ---- launchers (k_step_wide.hip): FP32 step for padded D = 128, 256 --------
 hipError_t launch_iteration_wide(Batch& b, int t, hipStream_t s);
+
+// ---- launchers (k_wide_screen.hip): FP32 step for padded D = 64, 128, 256 by a screen of the pairs ----
+bool wide_screen_ok(int D, long long n, long long m);
+// Points the buffers of w into `base` (NULL only counts); returns their bytes.
+size_t wide_screen_carve(WideScreen& w, char* base, int D, int n, int m);
+// The points' operands from rows of d coordinates times scale, packed into Xp
+// (n x D) on the way unless that is NULL.
+hipError_t launch_wide_screen_points(const WideScreen& w, const float* X, int n, int d, float scale, float* Xp, int D,
+                                     hipStream_t s);
+// Seeds of a step call in, with their operands (the euclidean metric).
+hipError_t launch_wide_screen_load(const float* seeds, const uint8_t* conv_in, Batch& b, hipStream_t s);
+hipError_t launch_iteration_screen(Batch& b, int t, hipStream_t s);
 
 // ---- launchers (k_step_cull.hip): FP32 step over Morton-ordered points, d <= 4 --
 bool cull_supported(int d, int n);

@@ -190,19 +190,6 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a, int t) {
     }
 }
 
-__global__ void seed_export_kernel(const float* __restrict__ S, int DP, int d, int m,
-                                   const uint8_t* __restrict__ status,
-                                   const int32_t* __restrict__ it,
-                                   const float* __restrict__ sh, float* seeds,
-                                   uint8_t* conv, int32_t* iters, float* shift2) {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= m) return;
-    for (int k = 0; k < d; ++k) seeds[(long long)j * d + k] = S[(long long)j * DP + k];
-    conv[j] = status[j];
-    iters[j] = it[j];
-    if (it[j] > 0) shift2[j] = sh[j];
-}
-
 template <int D, int DP, int R>
 hipError_t launch_step_t(Batch& b, int t, hipStream_t s) {
     StepArgs a;
@@ -324,18 +311,11 @@ hipError_t launch_seed_init_from_array(const float* seeds, const uint8_t* conv_i
     return hipGetLastError();
 }
 
-hipError_t launch_seed_export(const Batch& b, int m, float* seeds, uint8_t* conv,
-                              int32_t* iters, float* shift2, hipStream_t s) {
-    hipLaunchKernelGGL(seed_export_kernel, dim3((m + 255) / 256), dim3(256), 0, s, b.S,
-                       b.sh.DP, b.d, m, b.status, b.iters, b.shift2, seeds, conv, iters,
-                       shift2);
-    return hipGetLastError();
-}
-
 // One iteration: the fused step (and the partial reduction when needed).
 hipError_t launch_iteration(Batch& b, int t, hipStream_t s) {
     if (b.prec == MS_PREC_BF16_REFINE) return launch_iteration_bf16(b, t, s);
     if (b.Xs && b.geom) return launch_iteration_cull(b, t, s);
+    if (b.screen.mask) return launch_iteration_screen(b, t, s);
     if (b.sh.D > 64) return launch_iteration_wide(b, t, s);
     const int D = b.sh.D, R = b.sh.R;
 #define FMS_CASE(DD, DPP, RR) \

@@ -1,4 +1,6 @@
-// k_step_wide.hip -- the FP32 fused step for wide rows (padded D = 128, 256).
+// k_step_wide.hip -- the FP32 fused step for wide rows (padded D = 128, 256)
+// over all pairs: `plain` calls, and batches whose screen (k_wide_screen.hip)
+// would take more memory than it may.
 //
 // Same update as the narrow step (Section II-B: every active seed moves to
 // the kernel-weighted mean of all n points, eq. (12)-(15) for the flat
