@@ -65,7 +65,7 @@ constexpr float kSlack = 0.25f;          // packed units
 constexpr int kSegGroups = 96;           // groups of 64 tiles listed at once (24 KB: six workgroups a CU)
 constexpr int kSeedMaxWaves = 16;
 // waves per SIMD the register count must allow
-constexpr int seed_min_waves(int D) { return D == 32 ? 3 : 4; }
+constexpr int seed_min_waves(int D) { return D >= 16 ? 3 : 4; }
 constexpr int kXcdRun = 64;
 // wide rows need the registers that 16 waves in one workgroup would not have
 constexpr int seed_max_waves(int D, int R) { return R > 1 ? 4 : (D <= 4 ? kSeedMaxWaves : 8); }
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
             evaluated += mine_n;
             // walk the tiles in batches of U, the next batch's loads in flight
             // while one computes; lane i of `ids` holds entry i of the current 64
-            constexpr int U = D <= 4 ? 4 : 1;
+            constexpr int U = D <= 8 ? 4 : (D <= 16 ? 2 : 1);
             float4 xa[U][G4], xb[U][G4];
             unsigned wa[U], wb[U];
             unsigned ids = 0;
@@ -496,6 +496,8 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                                 dx[k] = x[k] - s[r][k];
                                 q = fmaf(dx[k], dx[k], q);
                             }
+                        }
+                        if constexpr (D >= 8) {
                             if (!__ballot(!(q > rq[r] && q < 3e38f))) continue;
                         }
                         float w;
