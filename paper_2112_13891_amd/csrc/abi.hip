@@ -1429,6 +1429,24 @@ bool batched_seed_form(const ms_params* p, int d, long long n, long long M, int 
     return g_tune.find(tune_key(d, n, M, ncl, p->precision)) == g_tune.end();
 }
 
+// Whether a step call gains by the clouds' runs, which it builds for these
+// updates alone: fitted to calls of 20 to 150 clouds of up to 64,000 points, in
+// us.  The tile form takes about 140, the runs 60 and 0.105 per 1,000 points;
+// then per 10^6 pairs the tile form 0.3 (d = 2), 0.35 (3), 0.73 (8) and 1.15 (16),
+// the seed form 0.22, 0.16, 0.79 and 0.5: at d = 8 it leaves out half of the
+// tiles, but every seed reads its own ones through L2 (17 GB at 19 TB/s), where
+// the tile form reads a point once for 64 or more seeds.  Both forms, tile and
+// seed: 2.8 million points, 250 seeds a cloud, d = 3, one update 386 and 485,
+// two 628 and 600; 1.9 million, d = 8, three 979 and 1,150; 0.6 million, d = 8,
+// three 371 and 308.
+bool batched_runs_pay(const int64_t* x_off, const int64_t* s_off, int ncl, int d, int n_iter) {
+    const int D = step_shape(d).D;
+    double pairs = 0.0;
+    for (int c = 0; c < ncl; ++c) pairs += (double)(x_off[c + 1] - x_off[c]) * (double)(s_off[c + 1] - s_off[c]);
+    const double gain = D <= 2 ? 0.08 : (D <= 4 ? 0.19 : (D <= 8 ? -0.06 : 0.65));   // per 10^6 pairs
+    return 0.105e-3 * (double)x_off[ncl] - 80.0 < gain * 1e-6 * pairs * n_iter;
+}
+
 // The BF16 form over many clouds (Gaussian, padded D in {8, 16, 32}): each
 // cloud's points in the spatial order of the one-cloud form (its own pivots),
 // their block features, and the per-cloud offsets the kernels use.  The
@@ -1569,7 +1587,8 @@ int step_batched_impl(const ms_params* p, const float* X, const int64_t* x_off, 
     if (bf && !batched_bf16_ok(p, d))
         return fail(MS_E_INVALID, "the batched BF16 form is built for the Gaussian kernel at 5 <= d <= 32");
     if (bf && pre && !pre->bb) return fail(MS_E_HIP, "the batched BF16 form needs its prepared points");
-    if (pre ? pre->ri != nullptr : batched_seed_form(p, d, n, M, ncl, R_force))
+    if (pre ? pre->ri != nullptr
+            : batched_seed_form(p, d, n, M, ncl, R_force) && batched_runs_pay(x_off, s_off, ncl, d, n_iter))
         return step_batched_seeds(p, X, x_off, seeds, s_off, ncl, d, n_iter, converged, iters, shift2, s, pre);
     StepShape sh = step_shape_for(d, std::max(1, M / ncl));
     // default: at most two seeds per lane up to D = 8 and one above (timed on

@@ -204,27 +204,19 @@ __global__ __launch_bounds__(1024) void seed_order_small_kernel(
 }
 
 // Stable LSD radix sort, 8 bits per pass.  Per-block digit counts go to
-// hist (digit-major, 256 x nblocks); the digit totals are summed into dtot with
-// integer atomics (order-independent).
+// hist (digit-major, 256 x nblocks); the scan leaves the digits' totals in
+// dtot, and every block of the scatter adds up the smaller digits' by itself
+// (totals by one atomic per block and digit took 16 of 26 us at 1.9 million keys).
 __global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(const unsigned* __restrict__ keys,
                                                                   int n, int shift, int nblocks,
-                                                                  int* hist, int* dtot) {
+                                                                  int* hist) {
     __shared__ int h[256];
     if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
     const int i = blockIdx.x * kSortThreads + threadIdx.x;
     if (i < n) atomicAdd(&h[(keys[i] >> shift) & 255u], 1);
     __syncthreads();
-    if (threadIdx.x < 256) {
-        const int c = h[threadIdx.x];
-        hist[threadIdx.x * nblocks + blockIdx.x] = c;
-        if (c) atomicAdd(&dtot[threadIdx.x], c);
-    }
-}
-
-__global__ void zero_ints_kernel(int* a, int count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) a[i] = 0;
+    if (threadIdx.x < 256) hist[threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
 // Inclusive scan of one value per thread over a 256-thread block; returns the
@@ -245,15 +237,12 @@ __device__ __forceinline__ int block_scan256(int v, int* wsum, int* total) {
     return v + before;
 }
 
-// Exclusive offsets: one workgroup per digit.  The digit's base is the sum of
-// the totals of all smaller digits; its row of per-block counts is then
-// scanned in 256-wide steps (coalesced).
-__global__ __launch_bounds__(256) void radix_scan_kernel(int* hist, int nblocks,
-                                                         const int* __restrict__ dtot) {
+// Exclusive offsets within each digit, and the digits' totals: one workgroup
+// per digit scans its row of per-block counts in 256-wide steps (coalesced).
+__global__ __launch_bounds__(256) void radix_scan_kernel(int* hist, int nblocks, int* dtot) {
     __shared__ int wsum[4];
     const int dig = blockIdx.x;
-    int base;   // sum of the totals of the digits below this one
-    (void)block_scan256(threadIdx.x < dig ? dtot[threadIdx.x] : 0, wsum, &base);
+    int base = 0;
     int* row = hist + (long long)dig * nblocks;
     for (int c0 = 0; c0 < nblocks; c0 += 256) {
         const int i = c0 + threadIdx.x;
@@ -263,12 +252,14 @@ __global__ __launch_bounds__(256) void radix_scan_kernel(int* hist, int nblocks,
         if (i < nblocks) row[i] = base + incl - v;
         base += step;
     }
+    if (threadIdx.x == 0) dtot[dig] = base;
 }
 
 __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
     const unsigned* __restrict__ kin, const int* __restrict__ vin, int n, int shift, int nblocks,
-    const int* __restrict__ offs, unsigned* kout, int* vout) {
+    const int* __restrict__ offs, const int* __restrict__ dtot, unsigned* kout, int* vout) {
     __shared__ int wcount[kSortWaves][256];
+    __shared__ int dbase[256], dsum[4];   // the keys of smaller digits
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int e = threadIdx.x; e < kSortWaves * 256; e += kSortThreads) (&wcount[0][0])[e] = 0;
     __syncthreads();
@@ -285,6 +276,16 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
     const int rank = __popcll(peers & ((1ull << lane) - 1ull));
     // the lowest peer lane records the wave's count for this digit
     if (live && rank == 0) wcount[wave][dig] = __popcll(peers);
+    int dincl = 0, dv = 0;
+    if (threadIdx.x < 256) {
+        dv = dincl = dtot[threadIdx.x];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int u = __shfl_up(dincl, off);
+            if (lane >= off) dincl += u;
+        }
+        if (lane == 63) dsum[wave] = dincl;
+    }
     __syncthreads();
     // exclusive prefix over waves, per digit (wave order = index order)
     if (threadIdx.x < 256) {
@@ -294,10 +295,12 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
             wcount[w][threadIdx.x] = s;
             s += c;
         }
+        for (int w = 0; w < wave; ++w) dincl += dsum[w];
+        dbase[threadIdx.x] = dincl - dv;
     }
     __syncthreads();
     if (live) {
-        const int pos = offs[dig * nblocks + blockIdx.x] + wcount[wave][dig] + rank;
+        const int pos = dbase[dig] + offs[dig * nblocks + blockIdx.x] + wcount[wave][dig] + rank;
         kout[pos] = key;
         vout[pos] = vin[i];
     }
@@ -771,17 +774,16 @@ SortWs carve(void* ws, int count) {
 // passes, v1 after an odd one).
 int* radix_sort_pairs(const SortWs& w, int n, hipStream_t s, int passes = 4) {
     const int nblocks = (n + kSortThreads - 1) / kSortThreads;
-    hipLaunchKernelGGL(zero_ints_kernel, dim3(4), dim3(256), 0, s, w.dtot, 4 * 256);
     unsigned* ka = w.k0; unsigned* kb = w.k1;
     int* va = w.v0; int* vb = w.v1;
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = pass * 8;
         int* dt = w.dtot + pass * 256;
         hipLaunchKernelGGL(radix_hist_kernel, dim3(nblocks), dim3(kSortThreads), 0, s, ka, n, shift,
-                           nblocks, w.hist, dt);
+                           nblocks, w.hist);
         hipLaunchKernelGGL(radix_scan_kernel, dim3(256), dim3(256), 0, s, w.hist, nblocks, dt);
         hipLaunchKernelGGL(radix_scatter_kernel, dim3(nblocks), dim3(kSortThreads), 0, s, ka, va, n,
-                           shift, nblocks, w.hist, kb, vb);
+                           shift, nblocks, w.hist, dt, kb, vb);
         unsigned* tk = ka; ka = kb; kb = tk;
         int* tv = va; va = vb; vb = tv;
     }

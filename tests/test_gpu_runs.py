@@ -108,3 +108,23 @@ def test_dense_rows(orc, d):
         X = embed(n + d, n, d, k=5)
         S0 = np.ascontiguousarray(X[:m])
         _check(orc, X, S0, 1.2, "gaussian", 2, np.arange(m))
+
+
+@pytest.mark.parametrize("d,ncl,n_each,m,few", [(2, 40, 40000, 30, 3), (3, 40, 40000, 20, 2), (8, 30, 40000, 40, 2),
+                                                (16, 45, 32000, 10, 3)])
+def test_batched_both_sides_of_the_line(d, ncl, n_each, m, few):
+    """A batched step that is large enough for the tile form against the same
+    clouds in a small call, which runs over their pivot runs."""
+    X = np.concatenate([embed(100 + c, n_each - 7 * c, d, 20, 0.0) for c in range(ncl)])
+    off = np.concatenate([[0], np.cumsum([n_each - 7 * c for c in range(ncl)])])
+    rng = np.random.default_rng(d)
+    S0 = np.concatenate([X[off[c] + rng.choice(n_each - 7 * c, m, replace=False)] for c in range(ncl)])
+    so = np.arange(ncl + 1) * m
+    Xg, Sg = _gpu(X), _gpu(S0)
+    a = api.step_batched(Xg, off, Sg, so, 1.2, n_iter=2)
+    b = api.step_batched(Xg[:off[few]].contiguous(), off[:few + 1], Sg[:so[few]].contiguous(), so[:few + 1], 1.2,
+                         n_iter=2)
+    k = few * m
+    assert torch.equal(a[1][:k], b[1]) and torch.equal(a[2][:k], b[2])
+    # two FP32 orders of sums over a cluster of 2,000 points, coordinates up to 30
+    assert float((a[0][:k] - b[0]).abs().max()) < 1e-4
