@@ -44,6 +44,17 @@ __device__ __forceinline__ int cloud_of(const long long* __restrict__ off, int n
     return lo;
 }
 
+// The cloud of a wave's first row where all its rows (consecutive, up to n)
+// are in it, as a wave-uniform value: its modes then come by scalar loads.
+__device__ __forceinline__ bool wave_cloud(const long long* __restrict__ off, int ncl, long long e, long long n,
+                                           int* c) {
+    const long long first = e - (threadIdx.x & 63);
+    const long long last = first + 63 < n ? first + 63 : n - 1;
+    const int c0 = __builtin_amdgcn_readfirstlane(cloud_of(off, ncl, first));
+    *c = c0;
+    return last < off[c0 + 1];
+}
+
 // Initial pools: every point of its cloud, pool[e] = e - x_off[c].
 __global__ void bf_iota_kernel(const long long* __restrict__ x_off, int ncl, int32_t* pool, long long n) {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -106,18 +117,22 @@ __global__ void bf_cover_kernel(const float* __restrict__ X, int d, const long l
                                 const int32_t* __restrict__ k_new, float r2, uint8_t* removed, long long n) {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
-    const int c = cloud_of(x_off, ncl, e);
-    if (e - x_off[c] >= pool_len[c] || removed[e]) return;
-    const float* x = X + (x_off[c] + pool[e]) * d;
-    float xr[D > 0 ? D : 1];
-    load_point<D>(x, xr);
-    const float* ms = mstore + x_off[c] * d;
-    for (int j = k_old[c]; j < k_new[c]; ++j) {
-        if (row_dist2<D>(x, xr, ms + (long long)j * d, d) <= r2) {
-            removed[e] = 1;
-            return;
+    auto cover = [&](long long x0, int len, int j0, int j1) {
+        if (e - x0 >= len || removed[e]) return;
+        const float* x = X + (x0 + pool[e]) * d;
+        float xr[D > 0 ? D : 1];
+        load_point<D>(x, xr);
+        const float* ms = mstore + x0 * d;
+        for (int j = j0; j < j1; ++j) {
+            if (row_dist2<D>(x, xr, ms + (long long)j * d, d) <= r2) {
+                removed[e] = 1;
+                return;
+            }
         }
-    }
+    };
+    int c;
+    if (!wave_cloud(x_off, ncl, e, n, &c)) c = cloud_of(x_off, ncl, e);
+    cover(x_off[c], pool_len[c], k_old[c], k_new[c]);
 }
 
 // The greedy merge of a round (Algorithms 1-2, prune modes): cloud c's
@@ -137,16 +152,7 @@ enum : int32_t { BF_SKIP = -3, BF_UNDECIDED = -2, BF_FOUNDER = -1, BF_JOINED = 0
 constexpr int kDecideWaves = 4;
 constexpr int kCTF = 1024;   // threads of the founders kernel
 
-__device__ __forceinline__ float seed_dist2(const float* __restrict__ a, const float* __restrict__ b, int d) {
-    float q = 0.0f;
-    for (int k = 0; k < d; ++k) {
-        const float t = a[k] - b[k];
-        q = fmaf(t, t, q);
-    }
-    return q;
-}
-
-template <bool kFirst>
+template <bool kFirst, int D>
 __global__ __launch_bounds__(64 * kDecideWaves) void bf_decide_kernel(
     const float* __restrict__ S, int d, const uint8_t* __restrict__ conv, const long long* __restrict__ s_off,
     int ncl, const float* __restrict__ mstore, const long long* __restrict__ x_off, const int32_t* __restrict__ k_cnt,
@@ -161,12 +167,14 @@ __global__ __launch_bounds__(64 * kDecideWaves) void bf_decide_kernel(
     if (__atomic_load_n(&state[g], __ATOMIC_RELAXED) != BF_UNDECIDED) return;
     const int c = cloud_of(s_off, ncl, g);
     const float* sg = S + (long long)g * d;
+    float sr[D > 0 ? D : 1];
+    load_point<D>(sg, sr);
     if (kFirst) {
         const float* ms = mstore + x_off[c] * d;
         const int K = k_cnt[c];
         for (int base = 0; base < K; base += 64) {
             const int j = base + lane;
-            const bool hit = j < K && seed_dist2(sg, ms + (long long)j * d, d) <= r2;
+            const bool hit = j < K && row_dist2<D>(sg, sr, ms + (long long)j * d, d) <= r2;
             if (__ballot(hit)) {
                 if (lane == 0) __atomic_store_n(&state[g], (int32_t)BF_JOINED, __ATOMIC_RELAXED);
                 return;
@@ -180,7 +188,7 @@ __global__ __launch_bounds__(64 * kDecideWaves) void bf_decide_kernel(
         bool hit = false;
         if (j < g) {
             sj = __atomic_load_n(&state[j], __ATOMIC_RELAXED);
-            if (sj == BF_FOUNDER || sj == BF_UNDECIDED) hit = seed_dist2(sg, S + j * d, d) <= r2;
+            if (sj == BF_FOUNDER || sj == BF_UNDECIDED) hit = row_dist2<D>(sg, sr, S + j * d, d) <= r2;
         }
         const unsigned long long bal = __ballot(hit);
         if (bal) {
@@ -259,37 +267,58 @@ __global__ void bf_fill_i32_kernel(int32_t* a, long long count, int32_t v) {
 }
 
 // Stable compaction of each cloud's pool slice, one workgroup of kCT
-// threads per cloud: entries not removed keep their order (the pool stays
+// threads per cloud, a chain over the slice's rows (65,536 entries: 52 us a row at a
+// time, 39 by fours; the barriers wait for the rows' loads and stores): entries not removed keep their order (the pool stays
 // ascending); the removed flags of the slice are cleared for the next round.
 constexpr int kCT = 1024;
 
 __global__ __launch_bounds__(kCT) void bf_compact_kernel(const long long* __restrict__ x_off,
                                                         const int32_t* __restrict__ pool_in, uint8_t* removed,
                                                         int32_t* pool_len, int32_t* pool_out) {
-    __shared__ int wsum[kCT / 64];
+    constexpr int U = 4;   // rows of kCT entries at once: 64 wave counts, scanned by one wave
+    static_assert(U * kCT / 64 == 64, "a lane per wave count");
+    __shared__ int wsum[U * kCT / 64];
+    __shared__ int total;
     const int c = blockIdx.x;
     const long long base = x_off[c];
     const int len = pool_len[c];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int carry = 0;
-    for (int e0 = 0; e0 < len; e0 += kCT) {
-        const int e = e0 + threadIdx.x;
-        bool keep = false;
-        int32_t v = 0;
-        if (e < len) {
-            keep = !removed[base + e];
-            v = pool_in[base + e];
-            removed[base + e] = 0;
+    for (int e0 = 0; e0 < len; e0 += U * kCT) {
+        bool keep[U];
+        int32_t v[U];
+        unsigned long long bal[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * kCT + threadIdx.x;
+            keep[u] = e < len && !removed[base + e];
+            v[u] = e < len ? pool_in[base + e] : 0;
         }
-        const unsigned long long bal = __ballot(keep);
-        if (lane == 0) wsum[wave] = __popcll(bal);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * kCT + threadIdx.x;
+            if (e < len) removed[base + e] = 0;
+            bal[u] = __ballot(keep[u]);
+            if (lane == 0) wsum[u * (kCT / 64) + wave] = __popcll(bal[u]);
+        }
         __syncthreads();
-        int before = carry, total = 0;
-        for (int w = 0; w < kCT / 64; ++w) {
-            if (w < wave) before += wsum[w];
-            total += wsum[w];
+        if (wave == 0) {
+            const int w = wsum[lane];
+            int x = w;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int y = __shfl_up(x, off);
+                if (lane >= off) x += y;
+            }
+            wsum[lane] = x - w;
+            if (lane == 63) total = x;
         }
-        if (keep) pool_out[base + before + __popcll(bal & ((1ull << lane) - 1ull))] = v;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int before = carry + wsum[u * (kCT / 64) + wave];
+            if (keep[u]) pool_out[base + before + __popcll(bal[u] & ((1ull << lane) - 1ull))] = v[u];
+        }
         carry += total;
         __syncthreads();
     }
@@ -305,18 +334,26 @@ __global__ void bf_assign_kernel(const float* __restrict__ X, int d, const long 
                                  int32_t* labels, long long n) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int c = cloud_of(x_off, ncl, i);
     const float* x = X + i * d;
     float xr[D > 0 ? D : 1];
     load_point<D>(x, xr);
     float best = __builtin_inff();
     int arg = 0;
-    for (int j = m_off[c]; j < m_off[c + 1]; ++j) {
-        const float q = row_dist2<D>(x, xr, modes + (long long)j * d, d);
-        if (q < best) {
-            best = q;
-            arg = j - m_off[c];
+    auto nearest = [&](int j0, int j1) {
+        for (int j = j0; j < j1; ++j) {
+            const float q = row_dist2<D>(x, xr, modes + (long long)j * d, d);
+            if (q < best) {
+                best = q;
+                arg = j - j0;
+            }
         }
+    };
+    int c;
+    if (wave_cloud(x_off, ncl, i, n, &c)) {
+        nearest(__builtin_amdgcn_readfirstlane(m_off[c]), __builtin_amdgcn_readfirstlane(m_off[c + 1]));
+    } else {
+        c = cloud_of(x_off, ncl, i);
+        nearest(m_off[c], m_off[c + 1]);
     }
     labels[i] = arg;
 }
@@ -363,12 +400,15 @@ hipError_t launch_bf_decide_pass(const float* S, int d, const uint8_t* conv, con
     hipLaunchKernelGGL(bf_fill_i32_kernel, dim3(1), dim3(64), 0, s, und, 1LL, 0);
     if (M <= 0) return hipGetLastError();
     const dim3 grid((M + kDecideWaves - 1) / kDecideWaves);
-    if (first)
-        hipLaunchKernelGGL(bf_decide_kernel<true>, grid, dim3(64 * kDecideWaves), 0, s, S, d, conv, s_off, ncl,
-                           mstore, x_off, k_cnt, r2, state, und, M);
-    else
-        hipLaunchKernelGGL(bf_decide_kernel<false>, grid, dim3(64 * kDecideWaves), 0, s, S, d, conv, s_off, ncl,
-                           mstore, x_off, k_cnt, r2, state, und, M);
+#define FMS_DECIDE(DD)                                                                                          \
+    if (first)                                                                                                  \
+        hipLaunchKernelGGL((bf_decide_kernel<true, DD>), grid, dim3(64 * kDecideWaves), 0, s, S, d, conv, s_off, \
+                           ncl, mstore, x_off, k_cnt, r2, state, und, M);                                       \
+    else                                                                                                        \
+        hipLaunchKernelGGL((bf_decide_kernel<false, DD>), grid, dim3(64 * kDecideWaves), 0, s, S, d, conv,       \
+                           s_off, ncl, mstore, x_off, k_cnt, r2, state, und, M)
+    FMS_DSWITCH_ROWS(d, FMS_DECIDE);
+#undef FMS_DECIDE
     return hipGetLastError();
 }
 

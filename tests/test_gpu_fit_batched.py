@@ -194,3 +194,14 @@ def test_fit_batched_bf16_rejects_what_is_not_built():
     Xs, xo = _clouds(3, [300, 500], 16)
     with pytest.raises(api.MeanShiftError, match="Gaussian kernel at 5 <= d <= 32"):
         api.fit_batched(torch.from_numpy(np.concatenate(Xs)).to(DEV), xo, 1.0, kernel="flat", precision="bf16")
+
+
+@pytest.mark.parametrize("d", [8, 11])
+def test_fit_batched_pool_rows(orc, d):
+    """Pools at the edges of the rows that a compaction takes at once (4,096
+    entries), and clouds that end inside a wave."""
+    sizes = [4095, 4096, 63, 4097, 65, 8193, 1, 12289]
+    Xs, xo = _clouds(40 + d, sizes, d)
+    per, lab, k_off, rounds = api.fit_batched(torch.from_numpy(np.concatenate(Xs)).to(DEV), xo, 1.0, rng_seed=5)
+    torch.cuda.synchronize()
+    _compare(orc, Xs, xo, 1.0, "gaussian", False, 5, per, lab, k_off)
