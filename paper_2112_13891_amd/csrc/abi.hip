@@ -646,9 +646,12 @@ enum SeedForm { SEED_NONE, SEED_ROWS, SEED_RUNS, SEED_DENSE };
 constexpr long long kDenseFloats = 1LL << 28;   // seeds x points x D x updates
 SeedForm seed_form(const ms_params* p, int n, int d, long long m, int updates, bool in_step) {
     if (p->plain || in_step || d > 32) return SEED_NONE;
-    if (d <= 4) return SEED_ROWS;
     const long long all = m * n;   // < 2^62
-    return all <= kDenseFloats / step_shape(d).D / std::max(1, std::min(updates, 8)) ? SEED_DENSE : SEED_RUNS;
+    const bool small = all <= kDenseFloats / step_shape(d).DP / std::max(1, std::min(updates, 8));
+    // directions are at most 2 apart: with that reach every seed would read every row
+    if (p->metric == MS_METRIC_COSINE && cull_reach(p->kernel, p->h) >= 2.0 && !small) return SEED_NONE;
+    if (d <= 4) return SEED_ROWS;
+    return small ? SEED_DENSE : SEED_RUNS;
 }
 
 // Units of the packed points per bandwidth, and the distance from which a
@@ -669,6 +672,9 @@ void seed_args_order(SeedArgs& a, const RunSeeds& q) {
     a.ppair = q.ppair;
 }
 
+// A seed per wave needs seeds for most of the waves.
+constexpr int kOwnSeeds = 512;
+
 void seed_args_runs(SeedArgs& a, const RunIndex& r) {
     a.T = r.tiles;
     a.geom = r.pivots;
@@ -678,6 +684,7 @@ void seed_args_runs(SeedArgs& a, const RunIndex& r) {
     a.run_bound = r.run_bound;
     a.tile_start = r.tile_start;
     a.run_cap = (r.sz.pmax + kFarRuns + 63) / 64 * 64;
+    a.dense = a.m >= kOwnSeeds ? r.dense : nullptr;
 }
 
 // Arguments of that form from the batch; the tiles are the packed (n small,

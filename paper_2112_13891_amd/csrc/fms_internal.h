@@ -20,6 +20,7 @@ enum : int32_t { MG_SKIP = -3, MG_UNDECIDED = -2, MG_FOUNDER = -1 };
 constexpr int kMaxIterCap = 4096;   // hard cap on max_iter / n_iter
 constexpr int kMaxMergePasses = 64;
 constexpr int kFarRuns = 16;        // far runs of a cloud (k_runs.hip)
+constexpr unsigned long long kDensePart = 8;   // an eighth of the tiles in reach: see k_seed.hip
 constexpr int kRunPivotMax = 1024;  // pivots of a cloud (k_runs.hip)
 constexpr int kRunPoints = 128;     // points per pivot, below that many pivots
 // BF16 forms: the refined-pair count is spread over counters 128 bytes apart
@@ -237,6 +238,7 @@ struct SeedArgs {
     const int32_t* pnear = nullptr;
     const float* pdist = nullptr;
     const float* ppair = nullptr;
+    const unsigned long long* dense = nullptr;   // one cloud, optional: RunIndex::dense
     float slack = 0.0f, flat_reach = 0.0f;   // set by the launcher
     int wgs = 0;
 };
@@ -267,7 +269,7 @@ hipError_t launch_radix_pairs(unsigned* k0, unsigned* k1, int* v0, int* v1, void
                               unsigned** keys, int** vals, hipStream_t s);
 
 // ---- launchers (k_runs.hip): points grouped around sampled pivots ---------------
-// Every cloud of a CSR batch (one cloud: ncl = 1) has one pivot per 256 points
+// Every cloud of a CSR batch (one cloud: ncl = 1) has one pivot per 128 points
 // (1 to 1,024); a run holds the points nearest to one pivot, and the points
 // far from every pivot form kFarRuns further runs by their distance.  Runs are
 // padded to whole tiles of 64 points, so a tile never spans two runs.
@@ -294,6 +296,10 @@ struct RunIndex {
     float* pivots = nullptr;     // coordinate k of pivot j (packed units) at [k * ptot + j]
     float* run_bound = nullptr;  // largest distance of a near run's points from its pivot (at most this);
                                  // of a far run, the least distance of its points from any pivot
+    // one cloud at D >= 16: tiles within a usual reach of sampled pivots, and all
+    // tiles, over the pivots.  With more than one in kDensePart, seeds that share a
+    // workgroup read much the same tiles
+    unsigned long long* dense = nullptr;
     int32_t* rows = nullptr;     // original row of each tile slot, -1 for padding (NULL: not kept)
     int32_t* tile_start = nullptr;   // first tile of each run (runs + 1); a cloud's pivots, then its far runs
     // scratch of the build; the pivot part also serves later seed orders
@@ -328,6 +334,7 @@ int run_index_alloc(RunIndex& r, const RunSizes& sz, int d, bool keep_rows, F&& 
         get(&r.ball_rows, (size_t)sz.runs * (sh.DP + 4));
     } else {
         get(&r.pivots, (size_t)sz.ptot * sh.D);
+        if (sz.ncl == 1 && sh.D >= 16) get(&r.dense, (size_t)2);
     }
     get(&r.run_bound, (size_t)sz.runs);
     if (keep_rows) get(&r.rows, T * 64);

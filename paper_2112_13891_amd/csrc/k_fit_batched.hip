@@ -2,8 +2,8 @@
 // (Algorithm 2, seed pool of Section II-D) for many independent clouds at
 // once: seed gather from each cloud's pool, pool coverage by each cloud's new
 // modes, per-cloud stable pool compaction, and nearest-mode labels within a
-// cloud.  The iterations themselves are the batched fused step
-// (k_batched.hip); the greedy merge runs here too, in parallel decision passes
+// cloud.  The iterations themselves are the seed form over the clouds' runs
+// (k_seed.hip) or the batched fused step (k_batched.hip); the greedy merge runs here too, in parallel decision passes
 // per cloud; the draws and the seed-count control run on the host between
 // rounds.
 //

@@ -1,7 +1,7 @@
 // k_runs.hip -- points grouped into 64-point tiles around sampled pivots, for
 // the seed form (k_seed.hip) at D >= 8, for one cloud or many (gfx950).
 //
-// Each cloud samples one pivot per 256 points (at fixed strides, at most
+// Each cloud samples one pivot per 128 points (at fixed strides, at most
 // 1,024).  A point belongs to the run of its nearest pivot, or, farther than
 // `far` from every pivot, to one of kFarRuns runs by that distance.  Runs are
 // padded to whole tiles, so that no tile spans two runs: the order of the runs
@@ -42,7 +42,8 @@ __device__ __forceinline__ int pivots_of(long long nc) {
 // workgroup; each thread takes a stretch of clouds.
 __global__ __launch_bounds__(1024) void run_plan_kernel(const long long* __restrict__ src, int n_each, int ncl,
                                                         long long* xo, int32_t* poff, int32_t* ptoff,
-                                                        int32_t* rtoff) {
+                                                        int32_t* rtoff, unsigned long long* dense) {
+    if (dense && threadIdx.x < 2) dense[threadIdx.x] = 0;
     __shared__ int s[3][1024];
     const int per = (ncl + 1023) / 1024;
     const int c0 = min(ncl, (int)threadIdx.x * per), c1 = min(ncl, c0 + per);
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(256) void run_fill_kernel(const float* __restrict__
 
 // Ball of each run of row-major tiles, one wave per run: the mean of its rows
 // and the largest distance from it (packed units, rounded up).  In 16-D a ball
-// around the mean of 256 points has 0.7 of the radius around one of them.  A
+// around the mean of a run has 0.7 of the radius around one of its points.  A
 // run too long for one wave (far points of a cloud without clusters) gets an
 // infinite radius.
 constexpr int kBallRows = 8192;
@@ -523,6 +524,45 @@ __global__ __launch_bounds__(256) void pivot_pairs_kernel(const float* __restric
     out[(long long)i * P + j] = sqrtf(q) * 0.9999f;
 }
 
+// RunIndex::dense from every kDenseRow-th pivot: a workgroup each.  kDenseReach
+// is the reach of a seed amid 2^12 to 2^18 points (k_seed.hip).  Sums of whole
+// numbers: any order.
+constexpr int kDenseRow = 8;
+constexpr float kDenseReach = 7.0f;
+__global__ __launch_bounds__(256) void run_dense_kernel(const float* __restrict__ pv, int P, int D,
+                                                        const float* __restrict__ bound,
+                                                        const int32_t* __restrict__ tile_start, float reach,
+                                                        unsigned long long* dense) {
+    __shared__ int s[2][4];
+    const int i = blockIdx.x * kDenseRow;
+    int near = 0, all = 0;
+    for (int j = threadIdx.x; j < P; j += 256) {
+        float q = 0.0f;
+        for (int k = 0; k < D; ++k) {
+            const float u = pv[(long long)k * P + j] - pv[(long long)k * P + i];
+            q = fmaf(u, u, q);
+        }
+        const int tiles = tile_start[j + 1] - tile_start[j];
+        all += tiles;
+        if (sqrtf(q) - bound[j] <= reach) near += tiles;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        near += __shfl_xor(near, off);
+        all += __shfl_xor(all, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        s[0][threadIdx.x >> 6] = near;
+        s[1][threadIdx.x >> 6] = all;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const unsigned long long w = (unsigned long long)(tile_start[i + 1] - tile_start[i]);
+        const int* v = s[threadIdx.x];
+        atomicAdd(&dense[threadIdx.x], w * (unsigned long long)(v[0] + v[1] + v[2] + v[3]));
+    }
+}
+
 void add_cloud(RunSizes& z, long long nc) {
     const int P = run_pivots(nc);
     z.ptot += P;
@@ -583,7 +623,7 @@ hipError_t launch_run_index(RunIndex& r, const float* X, const long long* xo_src
     r.X = X;
     if (z.n <= 0) return hipSuccess;
     hipLaunchKernelGGL(run_plan_kernel, dim3(1), dim3(1024), 0, s, xo_src, n_each, z.ncl, r.xo, r.poff, r.ptoff,
-                       r.rtoff);
+                       r.rtoff, r.dense);
     FMS_KB(r.D, hipLaunchKernelGGL((run_pivots_kernel<KB>), dim3(z.ptiles), dim3(64), 0, s, X, r.d, scale, r.xo,
                                    r.poff, r.ptoff, z.ncl, r.D, r.DP, z.ptot, r.pivots, r.pivot_rows, r.frag));
     const int vec4 = r.d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
@@ -614,6 +654,9 @@ hipError_t launch_run_index(RunIndex& r, const float* X, const long long* xo_src
     }
 #undef FMS_CASE
     if (r.row_major) return launch_balls(r, r.tiles, r.ball_rows, s);
+    if (r.dense)   // far: 8 packed units, whatever the kernel's units are
+        hipLaunchKernelGGL(run_dense_kernel, dim3((z.ptot + kDenseRow - 1) / kDenseRow), dim3(256), 0, s, r.pivots,
+                           z.ptot, r.D, r.run_bound, r.tile_start, kDenseReach / 8.0f * far, r.dense);
     return hipGetLastError();
 }
 

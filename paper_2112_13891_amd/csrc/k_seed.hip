@@ -70,15 +70,40 @@ constexpr int kXcdRun = 64;
 // wide rows need the registers that 16 waves in one workgroup would not have
 constexpr int seed_max_waves(int D, int R) { return R > 1 ? 4 : (D <= 4 ? kSeedMaxWaves : 8); }
 
-template <int D, int R, int KERN, bool RUNS>
-__global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void seed_iterate_kernel(SeedArgs a) {
+// LDS of a seed's list over runs: masks, entries, counts, pivot distances.
+__host__ __device__ constexpr size_t run_lds(int cap) { return ((size_t)cap / 64 * 8 + (size_t)cap * 12 + 16 + 15) / 16 * 16; }
+
+// PW: every wave of a workgroup has a seed of its own (and a list), instead of
+// a share of one seed's tiles.  Where seeds reach an eighth of the tiles and
+// more, all these reads through L2 bound the update; waves that walk nearly the
+// same list at nearly the same time find them in L1.  262,144 x 32-D points,
+// seeds sharing and own, us: 2 clusters, 8,192 seeds, three updates 45,000 and
+// 14,900; 7 clusters, 4,000 seeds, two 3,300 and 2,000; 80 clusters, 8,192
+// seeds, three 1,100 and 1,900.  Registers for two waves a SIMD: with three,
+// 250 bytes of scratch a lane and 15,500.
+constexpr int kOwnWaves = 4;
+template <int D, int R, int KERN, bool RUNS, bool PW>
+__global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(D)) void seed_iterate_kernel(SeedArgs a) {
     constexpr int DP = D <= 4 ? 4 : D;
     constexpr int G4 = DP / 4;
     constexpr int V = D + 1;
     static_assert(R * DP <= 64, "one wave holds the coordinates of the seeds");
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int NW = blockDim.x >> 6;
+    const int hwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = PW ? 0 : hwave;
+    const int NW = PW ? 1 : blockDim.x >> 6;
+    static_assert(!PW || RUNS, "a seed per wave: runs only");
+    // the waves that share a seed wait for each other
+    auto sync = [&] {
+        if constexpr (PW) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        } else {
+            __syncthreads();
+        }
+    };
+
+    if (RUNS && a.dense && (kDensePart * a.dense[0] > a.dense[1]) != PW) return;
 
     // this workgroup's seeds and its cloud's tiles.  Workgroups are dealt to
     // the eight XCDs in turn; an XCD takes kXcdRun seed groups in a row, so
@@ -88,7 +113,8 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
     const int xi = (int)blockIdx.x >> 3;
     const int wg = a.wgs - 1 - (((xi / kXcdRun) * 8 + ((int)blockIdx.x & 7)) * kXcdRun + xi % kXcdRun);
     if (wg < 0) return;
-    const int j0 = wg * R;
+    const int j0 = PW ? wg * (int)(blockDim.x >> 6) + hwave : wg * R;
+    if (PW && j0 >= a.m) return;
     // rows: tiles [0, nball), a ball each; runs: the cloud's pivots
     // [ball0, ball0 + nball), whose runs start at run0
     int ball0 = 0, nball = a.tiles, run0 = 0;
@@ -115,8 +141,9 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
     extern __shared__ __attribute__((aligned(16))) unsigned long long dyn[];
     static_assert(!RUNS || R == 1, "runs: one seed per workgroup");
     const int cap = a.run_cap;   // whole groups
-    unsigned long long* const near_mask = RUNS ? dyn : rows_mask;
-    unsigned* const list = RUNS ? reinterpret_cast<unsigned*>(dyn + cap / 64) : rows_list;
+    unsigned long long* const dyn_s = dyn + (PW ? hwave * (int)(run_lds(cap) / 8) : 0);
+    unsigned long long* const near_mask = RUNS ? dyn_s : rows_mask;
+    unsigned* const list = RUNS ? reinterpret_cast<unsigned*>(dyn_s + cap / 64) : rows_list;
     int* const list_pre = reinterpret_cast<int*>(list + cap);   // cap + 1
     float* const dist_s = reinterpret_cast<float*>(list_pre + cap + 1);
 
@@ -185,6 +212,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
         // several groups' loads at once
         auto balls = [&](int g0, int g1, auto&& f) {
             constexpr int B = D <= 4 ? 4 : (D <= 16 ? 2 : 1);
+#pragma unroll 1
             for (int g = g0 + wave; g < g1; g += B * NW) {
                 float c[B][D], rad[B];
 #pragma unroll
@@ -242,7 +270,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
 #pragma unroll
                 for (int r = 0; r < R; ++r) ub[r] = id[r] >= 0 ? a.pdist[id[r]] : 0.0f;
             }
-            if (RUNS) __syncthreads();   // the last list is no longer read
+            if (RUNS) sync();   // the last list is no longer read
             if (it == 0 && !by_row && (RUNS || KERN == MS_KERNEL_GAUSSIAN)) {
                 balls(0, groups, [&](int g, int r, bool in, float dist, float rad) {
                     if (in) {
@@ -254,12 +282,12 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                 for (int r = 0; r < R; ++r) {
 #pragma unroll
                     for (int off = 32; off >= 1; off >>= 1) ub[r] = fminf(ub[r], __shfl_xor(ub[r], off));
-                    if (lane == 0) wub[r][wave] = ub[r];
+                    if (lane == 0) wub[r][hwave] = ub[r];
                 }
-                __syncthreads();
+                sync();
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    float u = wub[r][0];
+                    float u = wub[r][PW ? hwave : 0];
                     for (int w = 1; w < NW; ++w) u = fminf(u, wub[r][w]);
                     ub[r] = 1.001f * u;
                 }
@@ -314,6 +342,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                 };
                 const int nrun = nball + kFarRuns;
                 const int rgroups = (nrun + 63) / 64;
+#pragma unroll 1
                 for (int g = wave; g < rgroups; g += NW) {
                     const int e = g * 64 + lane;
                     unsigned who = 0;
@@ -322,7 +351,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                     const unsigned long long mk = __ballot(who != 0);
                     if (lane == 0) near_mask[g] = mk;
                 }
-                __syncthreads();
+                sync();
                 // entries before each group, then the entries with their tiles
                 // counted in run order
                 int before = 0;
@@ -335,6 +364,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                 }
                 before = x - gc;
                 const int nlist = __builtin_amdgcn_readlane(x, 31);
+#pragma unroll 1
                 for (int g = wave; g < rgroups; g += NW) {
                     const unsigned long long mk = (unsigned long long)wave_uniform((long long)near_mask[g]);
                     const int at = __builtin_amdgcn_readlane(before, g);
@@ -345,7 +375,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                         list_pre[q] = a.tile_start[run0 + e + 1] - t;
                     }
                 }
-                __syncthreads();
+                sync();
                 // prefix of the listed runs' tiles, by wave 0
                 if (wave == 0) {
                     int total = 0;
@@ -362,7 +392,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                     }
                     if (lane == 0) list_pre[nlist] = total;
                 }
-                __syncthreads();
+                sync();
                 nlisted = nlist;
                 len = __builtin_amdgcn_readfirstlane(list_pre[nlist]);
             }
@@ -380,7 +410,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                 const int g1 = min(groups, g0 + kSegGroups);
                 if (remake) {
                     unsigned who = 0;   // seeds that reach the lane's tile
-                    __syncthreads();   // the last list and its masks are no longer read
+                    sync();   // the last list and its masks are no longer read
                     balls(g0, g1, [&](int g, int r, bool in, float dist, float rad) {
                         // a NaN (a ball without a finite centre) stays near
                         const bool near = in && !(dist - rad > reach[r] + (keep ? a.slack : 0.0f));
@@ -391,7 +421,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                             if (R > 1) near_who[(g - g0) * 64 + lane] = (unsigned char)who;
                         }
                     });
-                    __syncthreads();
+                    sync();
                     // entries before each group: a scan of the groups' counts
                     int before[(kSegGroups + 63) / 64];
                     len = 0;
@@ -417,7 +447,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
                                 (unsigned)((g0 + gi) * 64 + lane) |
                                 (R > 1 ? (unsigned)near_who[gi * 64 + lane] << 28 : 0u);
                     }
-                    __syncthreads();
+                    sync();
                 } else if (!culled) {
                     len = min((g1 - g0) * 64, nball - g0 * 64);
                 }
@@ -531,14 +561,14 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
 #pragma unroll
             for (int k = 0; k < V; ++k) {
                 const float v = wave_add63(acc[r][k]);
-                if (lane == 63) red[par][wave][r * V + k] = v;
+                if (lane == 63) red[par][hwave][r * V + k] = v;
             }
-        __syncthreads();
+        sync();
         float v = 0.0f, W = 0.0f;
         if (r_of < R) {
             for (int w = 0; w < NW; ++w) {
-                if (k_of < D) v += red[par][w][r_of * V + k_of];
-                W += red[par][w][r_of * V + D];
+                if (k_of < D) v += red[par][PW ? hwave : w][r_of * V + k_of];
+                W += red[par][PW ? hwave : w][r_of * V + D];
             }
         }
         const bool okW = W > 0.0f && isfinite(W);
@@ -586,7 +616,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
             } else if (shr < a.thr2) {
                 result[r] = ST_CONVERGED;
                 act &= ~(1u << r);
-                if (a.ctl && threadIdx.x == 0) atomicAdd(&a.ctl->conv_it[it], 1);
+                if (a.ctl && wave == 0 && lane == 0) atomicAdd(&a.ctl->conv_it[it], 1);
             }
         }
         if (mine && okW) sv = ns;
@@ -616,11 +646,11 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), seed_min_waves(D)) void 
     }
     Ctl* ctl = ka->ctl;
     if (ctl) {
-        if (lane == 0) wcnt[wave] = evaluated;
-        __syncthreads();
-        if (threadIdx.x == 0) {
+        if (lane == 0) wcnt[hwave] = evaluated;
+        sync();
+        if (wave == 0 && lane == 0) {
             unsigned long long e = 0;
-            for (int w = 0; w < NW; ++w) e += wcnt[w];
+            for (int w = 0; w < NW; ++w) e += wcnt[PW ? hwave : w];
             atomicMax(&ctl->iters_run, it);
             atomicAdd((unsigned long long*)&ctl->pairs, (unsigned long long)executed * (unsigned long long)ka->n);
             if (ka->count_exact)
@@ -715,15 +745,14 @@ __global__ void pack_tiles_kernel(const float* __restrict__ X, int n, int d, int
     reinterpret_cast<float4*>(T)[e] = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-template <int D, int R, bool RUNS>
+template <int D, int R, bool RUNS, bool PW = false>
 hipError_t launch_seed_t(const SeedArgs& a, int kernel, int wgs, int nw, hipStream_t s) {
-    // masks, list, counts, pivot distances
-    const size_t lds = RUNS ? (size_t)a.run_cap / 64 * 8 + (size_t)a.run_cap * 12 + 16 : 0;
+    const size_t lds = RUNS ? run_lds(a.run_cap) * (PW ? nw : 1) : 0;
     if (kernel == MS_KERNEL_GAUSSIAN)
-        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN, RUNS>), dim3(wgs), dim3(64 * nw), lds, s,
+        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN, RUNS, PW>), dim3(wgs), dim3(64 * nw), lds, s,
                            a);
     else
-        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT, RUNS>), dim3(wgs), dim3(64 * nw), lds, s, a);
+        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT, RUNS, PW>), dim3(wgs), dim3(64 * nw), lds, s, a);
     return hipGetLastError();
 }
 
@@ -809,6 +838,16 @@ hipError_t launch_seed_iterate(SeedArgs a, int D, int kernel, const SeedShape& s
     a.slack = kernel == MS_KERNEL_GAUSSIAN ? kSlack : 0.25f * sqrtf(a.h2) * a.scale;
     a.flat_reach = sqrtf(a.h2 * kSeedFlatMargin);
     if (wgs < 1) return hipSuccess;
+    // one of two launches runs, by the index's estimate (RunIndex::dense)
+    if (a.dense) {
+        SeedArgs b = a;
+        b.wgs = (wgs + kOwnWaves - 1) / kOwnWaves;
+        const int g = (b.wgs + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
+        hipError_t e = hipErrorInvalidValue;
+        if (D == 16) e = launch_seed_t<16, 1, true, true>(b, kernel, g, kOwnWaves, s);
+        if (D == 32) e = launch_seed_t<32, 1, true, true>(b, kernel, g, kOwnWaves, s);
+        if (e != hipSuccess) return e;
+    }
     a.wgs = wgs;
     wgs = (wgs + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
 #define FMS_CASE(DD, RR, RUNS) \

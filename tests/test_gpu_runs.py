@@ -128,3 +128,26 @@ def test_batched_both_sides_of_the_line(d, ncl, n_each, m, few):
     assert torch.equal(a[1][:k], b[1]) and torch.equal(a[2][:k], b[2])
     # two FP32 orders of sums over a cluster of 2,000 points, coordinates up to 30
     assert float((a[0][:k] - b[0]).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("d,n,m,k", [(16, 30001, 511, 1), (16, 30001, 512, 2), (16, 20000, 2050, 3), (32, 20000, 514, 1),
+                                     (32, 16385, 2061, 2), (29, 30000, 1001, 4)])
+@pytest.mark.parametrize("kernel", ["gaussian", "flat"])
+def test_runs_many_tiles_in_reach(orc, d, n, m, k, kernel):
+    """Few clusters: a seed per wave from 512 seeds on, remainders of a workgroup's four."""
+    X = embed(n + d + k, n, d, k)
+    S0 = X[np.random.default_rng(m).choice(n, m, replace=False)]
+    sample = np.concatenate([np.arange(8), np.random.default_rng(1).choice(m, 24, replace=False), np.arange(m - 8, m)])
+    _check(orc, X, S0, 1.2, kernel, 2, sample)
+
+
+@pytest.mark.parametrize("d", [3, 16, 32])
+def test_cosine_all_within_reach(d):
+    """Directions with every pair within reach: a small call and one above its line."""
+    rng = np.random.default_rng(d)
+    X = rng.standard_normal((30000, d)).astype(np.float32)
+    S0 = np.ascontiguousarray(X[:1500])
+    a = api.step(_gpu(X), _gpu(S0), 0.4, n_iter=2, metric="cosine")
+    b = api.step(_gpu(X), _gpu(S0[:5]), 0.4, n_iter=2, metric="cosine")
+    p = api.step(_gpu(X), _gpu(S0), 0.4, n_iter=2, metric="cosine", plain=True)
+    assert float((a[0] - p[0]).abs().max()) < 1e-5 and float((a[0][:5] - b[0]).abs().max()) < 1e-5
