@@ -1360,8 +1360,8 @@ int scratch_base(char** out) {
 }
 
 // ms_step with every buffer in the fixed device scratch: a dry run sizes the
-// call, a call that needs more than the scratch holds is rejected before
-// anything is launched, and the kernels are those of ms_step.
+// call; one that does not fit takes the forms that need the least memory, and
+// one that does not fit so either is rejected before anything is launched.
 int step_noalloc_impl(const ms_params* p, const float* X, int n, int d, float* seeds, int m, int n_iter,
                       uint8_t* converged, int32_t* iters, float* shift2, hipStream_t s) {
     Arena need(nullptr, 0);
