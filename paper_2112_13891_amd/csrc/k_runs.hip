@@ -524,10 +524,10 @@ __global__ __launch_bounds__(256) void pivot_pairs_kernel(const float* __restric
     out[(long long)i * P + j] = sqrtf(q) * 0.9999f;
 }
 
-// RunIndex::dense from every kDenseRow-th pivot: a workgroup each.  kDenseReach
+// RunIndex::dense from every kDenseRow-th pivot, 256 runs to a workgroup.  kDenseReach
 // is the reach of a seed amid 2^12 to 2^18 points (k_seed.hip).  Sums of whole
 // numbers: any order.
-constexpr int kDenseRow = 8;
+constexpr int kDenseRow = 16;
 constexpr float kDenseReach = 7.0f;
 __global__ __launch_bounds__(256) void run_dense_kernel(const float* __restrict__ pv, int P, int D,
                                                         const float* __restrict__ bound,
@@ -536,8 +536,10 @@ __global__ __launch_bounds__(256) void run_dense_kernel(const float* __restrict_
     __shared__ int s[2][4];
     const int i = blockIdx.x * kDenseRow;
     int near = 0, all = 0;
-    for (int j = threadIdx.x; j < P; j += 256) {
+    const int j = blockIdx.y * 256 + threadIdx.x;
+    if (j < P) {
         float q = 0.0f;
+#pragma unroll 16
         for (int k = 0; k < D; ++k) {
             const float u = pv[(long long)k * P + j] - pv[(long long)k * P + i];
             q = fmaf(u, u, q);
@@ -655,7 +657,7 @@ hipError_t launch_run_index(RunIndex& r, const float* X, const long long* xo_src
 #undef FMS_CASE
     if (r.row_major) return launch_balls(r, r.tiles, r.ball_rows, s);
     if (r.dense)   // far: 8 packed units, whatever the kernel's units are
-        hipLaunchKernelGGL(run_dense_kernel, dim3((z.ptot + kDenseRow - 1) / kDenseRow), dim3(256), 0, s, r.pivots,
+        hipLaunchKernelGGL(run_dense_kernel, dim3((z.ptot + kDenseRow - 1) / kDenseRow, (z.ptot + 255) / 256), dim3(256), 0, s, r.pivots,
                            z.ptot, r.D, r.run_bound, r.tile_start, kDenseReach / 8.0f * far, r.dense);
     return hipGetLastError();
 }
