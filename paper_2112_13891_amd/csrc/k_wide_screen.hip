@@ -181,7 +181,7 @@ template <int D>
 __global__ __launch_bounds__(kThreads) void wide_mask_kernel(StepArgs a, int t, WideScreen w, int stiles) {
     constexpr int KB = D / 16;
     const int m = active_count(a.ctl, t);
-    step_prologue(a, t, m);
+    if (blockIdx.y == 0) step_prologue(a, t, m);   // one workgroup of the whole grid
     if (m == 0) return;
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int word = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -101,3 +101,13 @@ def test_screen_fit_matches_plain():
     assert r[0].modes.shape == r[1].modes.shape
     assert float((r[0].modes - r[1].modes).abs().max()) < 1e-3
     assert torch.equal(r[0].labels, r[1].labels)
+
+
+@pytest.mark.parametrize("n,d,B", [(20001, 100, 256), (1500, 40, 512)])
+def test_screen_fit_counts_each_pair_once(n, d, B):
+    """The mask launch has a grid of points x seed tiles; each iteration's
+    active seeds x points are counted once, whatever its second dimension."""
+    X = embed(n + d, n, d, 12)
+    g = api.fit(_gpu(X), 1.5 * np.sqrt(d / 32.0), n_initial=B, rng_seed=4, trace=True)
+    assert (g.drawn_status != 2).all()
+    assert g.pairs == int(g.drawn_iters.astype(np.int64).sum()) * n
