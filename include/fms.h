@@ -315,27 +315,40 @@ int ms_step_adjoint(const void *X, int32_t nbatch, int64_t n, const void *S,
                     int64_t m, int32_t d, double h, const void *G, void *dS,
                     void *dX, int32_t dtype_bytes, void *stream);
 
+/* A points' index made by ms_points_plan: what it was made for, and where it
+ * lies.  Host memory; the planned calls read it before they return. */
+typedef struct {
+    double h;
+    int64_t n;
+    int32_t nbatch, d;
+    void *data;       /* device memory of the caller */
+    int64_t bytes;    /* its size */
+} ms_plan;
+
 /*
  * ms_points_plan -- the part of ms_forward_update and ms_step_adjoint that
  * depends on the points alone (their spatial order, about 60 to 100 us), for
  * callers that make several of those calls over the same X, h and shape (the
- * unrolled form).  ms_points_plan_bytes gives the size of the plan, or 0 where
- * these calls use none (float64, d > 32, few points); `plan` is device memory
+ * unrolled form).  ms_points_plan_bytes gives the size of the index, or 0 where
+ * these calls use none (float64, d > 32, few points); `data` is device memory
  * of at least that size, aligned to 256 bytes, written by this call and only
- * read by the planned ones.  The plan holds no pointers.  X must be the array
- * contents the plan was made from; the planned calls take a NULL plan like
- * the plain ones.  Stream-ordered and asynchronous.
+ * read by the planned ones, and *plan is filled with what the index is for.
+ * The index holds no pointers.  The planned calls refuse (MS_E_INVALID) a plan
+ * of another nbatch, n, d or h or of fewer bytes than it needs; X must have the
+ * contents that the plan was made from.  With a NULL plan they are the plain
+ * calls; with one, an update of 2^26 to 2^27 pairs takes the pairs in another
+ * order than the plain call.  Stream-ordered and asynchronous.
  */
 int ms_points_plan_bytes(int32_t nbatch, int64_t n, int32_t d, int32_t dtype_bytes,
                          int64_t *bytes);
 int ms_points_plan(const void *X, int32_t nbatch, int64_t n, int32_t d, double h,
-                   int32_t dtype_bytes, void *plan, int64_t plan_bytes, void *stream);
+                   int32_t dtype_bytes, void *data, int64_t bytes, ms_plan *plan, void *stream);
 int ms_forward_update_planned(const void *X, int32_t nbatch, int64_t n, const void *S_in,
                               int64_t m, int32_t d, double h, void *S_out,
-                              int32_t dtype_bytes, const void *plan, void *stream);
+                              int32_t dtype_bytes, const ms_plan *plan, void *stream);
 int ms_step_adjoint_planned(const void *X, int32_t nbatch, int64_t n, const void *S,
                             int64_t m, int32_t d, double h, const void *G, void *dS,
-                            void *dX, int32_t dtype_bytes, const void *plan, void *stream);
+                            void *dX, int32_t dtype_bytes, const ms_plan *plan, void *stream);
 
 /*
  * ms_seed_draw -- the library's seed selection on host memory: draws

@@ -121,7 +121,7 @@ def lib():
     L.ms_step_adjoint.restype = ctypes.c_int
     L.ms_points_plan_bytes.argtypes = [i32, i64, i32, i32, P]
     L.ms_points_plan_bytes.restype = ctypes.c_int
-    L.ms_points_plan.argtypes = [P, i32, i64, i32, ctypes.c_double, i32, P, i64, P]
+    L.ms_points_plan.argtypes = [P, i32, i64, i32, ctypes.c_double, i32, P, i64, P, P]
     L.ms_points_plan.restype = ctypes.c_int
     L.ms_forward_update_planned.argtypes = [P, i32, i64, P, i64, i32, ctypes.c_double, P, i32, P, P]
     L.ms_forward_update_planned.restype = ctypes.c_int
@@ -428,10 +428,24 @@ def _batched(X, S):
     return X, S, False
 
 
+class PlanDesc(ctypes.Structure):
+    _fields_ = [("h", ctypes.c_double), ("n", ctypes.c_int64), ("nbatch", ctypes.c_int32), ("d", ctypes.c_int32),
+                ("data", ctypes.c_void_p), ("bytes", ctypes.c_int64)]
+
+
+class PointsPlan:
+    """A points' index (points_plan): its memory, and what it was made for."""
+
+    def __init__(self, data):
+        self.data = data
+        self.desc = PlanDesc()
+
+
 def points_plan(X, h):
     """The part of forward_update and step_adjoint_accumulate that depends on X
-    and h alone, for several of those calls over the same X ([B,] n x d): a
-    tensor to pass as ``plan``, or None where they use none."""
+    and h alone, for several of those calls over the same X ([B,] n x d): to
+    pass as ``plan``, or None where they use none.  The calls refuse a plan of
+    another shape, h or device."""
     torch = _torch()
     _dev(X, X.dtype, None, "X")
     nb, n, d = (1,) + tuple(X.shape) if X.dim() == 2 else tuple(X.shape)
@@ -439,14 +453,19 @@ def points_plan(X, h):
     _check(lib().ms_points_plan_bytes(nb, n, d, X.element_size(), ctypes.byref(size)))
     if size.value == 0:
         return None
-    plan = torch.empty(size.value, dtype=torch.uint8, device=X.device)
+    plan = PointsPlan(torch.empty(size.value, dtype=torch.uint8, device=X.device))
     _check(lib().ms_points_plan(ctypes.c_void_p(X.data_ptr()), nb, n, d, float(h), X.element_size(),
-                                ctypes.c_void_p(plan.data_ptr()), size.value, _stream_ptr(X)))
+                                ctypes.c_void_p(plan.data.data_ptr()), size.value, ctypes.byref(plan.desc),
+                                _stream_ptr(X)))
     return plan
 
 
-def _plan_ptr(plan):
-    return None if plan is None else ctypes.c_void_p(plan.data_ptr())
+def _plan_ptr(plan, X):
+    if plan is None:
+        return None
+    if not isinstance(plan, PointsPlan) or plan.data.device != X.device:
+        raise ValueError("plan must come from points_plan on X's device")
+    return ctypes.byref(plan.desc)
 
 
 def forward_update(X, S, h, plan=None):
@@ -463,7 +482,7 @@ def forward_update(X, S, h, plan=None):
     out = torch.empty_like(Sb)
     rc = lib().ms_forward_update_planned(ctypes.c_void_p(Xb.data_ptr()), nb, n, ctypes.c_void_p(Sb.data_ptr()),
                                          m, d, float(h), ctypes.c_void_p(out.data_ptr()),
-                                         Xb.element_size(), _plan_ptr(plan), _stream_ptr(Xb))
+                                         Xb.element_size(), _plan_ptr(plan, Xb), _stream_ptr(Xb))
     _check(rc)
     return out[0] if squeeze else out
 
@@ -508,7 +527,7 @@ def step_adjoint_accumulate(X, S, h, G, dS, dX, plan=None):
     rc = lib().ms_step_adjoint_planned(ctypes.c_void_p(X.data_ptr()), nb, n, ctypes.c_void_p(S.data_ptr()),
                                        m, d, float(h), ctypes.c_void_p(G.data_ptr()),
                                        ctypes.c_void_p(dS.data_ptr()), ctypes.c_void_p(dX.data_ptr()),
-                                       X.element_size(), _plan_ptr(plan), _stream_ptr(X))
+                                       X.element_size(), _plan_ptr(plan, X), _stream_ptr(X))
     _check(rc)
 
 

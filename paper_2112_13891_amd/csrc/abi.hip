@@ -2260,10 +2260,29 @@ static int check_diff(const void* X, int32_t nbatch, int64_t n, const void* S, i
     return MS_OK;
 }
 
+// The device memory of a plan in *data (NULL without one), if the plan is for
+// these points: the kernels take its layout from nbatch, n and d alone.
+static int check_plan(const ms_plan* plan, int32_t nbatch, int64_t n, int32_t d, double h, int32_t dtype_bytes,
+                      const void** data) {
+    *data = nullptr;
+    if (!plan) return MS_OK;
+    if (dtype_bytes != 4) return fail(MS_E_INVALID, "a plan is for float32 points");
+    if (plan->nbatch != nbatch || plan->n != n || plan->d != d || plan->h != h)
+        return fail(MS_E_INVALID, "the plan was made for another nbatch, n, d or h");
+    int64_t need = 0;
+    FMS_CHECK(ms_points_plan_bytes(nbatch, n, d, dtype_bytes, &need));
+    if (need == 0 || !plan->data || plan->bytes < need || reinterpret_cast<uintptr_t>(plan->data) % 256)
+        return fail(MS_E_INVALID, "the plan's memory is not that of a plan for these points");
+    *data = plan->data;
+    return MS_OK;
+}
+
 static int forward_update_impl(const void* X, int32_t nbatch, int64_t n, const void* S_in, int64_t m, int32_t d,
-                               double h, void* S_out, int32_t dtype_bytes, const void* plan, void* stream) {
+                               double h, void* S_out, int32_t dtype_bytes, const ms_plan* of, void* stream) {
     FMS_CHECK(check_diff(X, nbatch, n, S_in, m, d, h, dtype_bytes));
     if (!S_out) return fail(MS_E_INVALID, "S_out is NULL");
+    const void* plan;
+    FMS_CHECK(check_plan(of, nbatch, n, d, h, dtype_bytes, &plan));
     hipStream_t s = (hipStream_t)stream;
     FMS_CHECK(ensure_pool_release_threshold());
     Workspace ws(s);
@@ -2281,10 +2300,12 @@ static int forward_update_impl(const void* X, int32_t nbatch, int64_t n, const v
 }
 
 static int step_adjoint_impl(const void* X, int32_t nbatch, int64_t n, const void* S, int64_t m, int32_t d,
-                             double h, const void* G, void* dS, void* dX, int32_t dtype_bytes, const void* plan,
+                             double h, const void* G, void* dS, void* dX, int32_t dtype_bytes, const ms_plan* of,
                              void* stream) {
     FMS_CHECK(check_diff(X, nbatch, n, S, m, d, h, dtype_bytes));
     if (!G || !dS || !dX) return fail(MS_E_INVALID, "NULL gradient array");
+    const void* plan;
+    FMS_CHECK(check_plan(of, nbatch, n, d, h, dtype_bytes, &plan));
     hipStream_t s = (hipStream_t)stream;
     FMS_CHECK(ensure_pool_release_threshold());
     Workspace ws(s);
@@ -2312,15 +2333,17 @@ int ms_points_plan_bytes(int32_t nbatch, int64_t n, int32_t d, int32_t dtype_byt
     return MS_OK;
 }
 
-int ms_points_plan(const void* X, int32_t nbatch, int64_t n, int32_t d, double h, int32_t dtype_bytes, void* plan,
-                   int64_t plan_bytes, void* stream) {
+int ms_points_plan(const void* X, int32_t nbatch, int64_t n, int32_t d, double h, int32_t dtype_bytes, void* data,
+                   int64_t bytes, ms_plan* plan, void* stream) {
     int64_t need = 0;
     FMS_CHECK(ms_points_plan_bytes(nbatch, n, d, dtype_bytes, &need));
-    if (!X || !plan) return fail(MS_E_INVALID, "NULL array");
+    if (!X || !data || !plan) return fail(MS_E_INVALID, "NULL array");
     if (!(std::isfinite(h) && h > 0.0)) return fail(MS_E_INVALID, "h must be finite and > 0");
     if (need == 0) return fail(MS_E_INVALID, "no plan for this shape (ms_points_plan_bytes gives 0)");
-    if (plan_bytes < need) return fail(MS_E_INVALID, "plan_bytes is less than ms_points_plan_bytes gives");
-    FMS_HIP(launch_points_plan((const float*)X, nbatch, (int)n, d, h, plan, (hipStream_t)stream));
+    if (bytes < need) return fail(MS_E_INVALID, "fewer bytes than ms_points_plan_bytes gives");
+    if (reinterpret_cast<uintptr_t>(data) % 256) return fail(MS_E_INVALID, "a plan's memory must be aligned to 256 bytes");
+    FMS_HIP(launch_points_plan((const float*)X, nbatch, (int)n, d, h, data, (hipStream_t)stream));
+    *plan = ms_plan{h, n, nbatch, d, data, bytes};
     return MS_OK;
 }
 
@@ -2331,7 +2354,7 @@ int ms_forward_update(const void* X, int32_t nbatch, int64_t n, const void* S_in
 }
 
 int ms_forward_update_planned(const void* X, int32_t nbatch, int64_t n, const void* S_in, int64_t m, int32_t d,
-                              double h, void* S_out, int32_t dtype_bytes, const void* plan, void* stream) {
+                              double h, void* S_out, int32_t dtype_bytes, const ms_plan* plan, void* stream) {
     g_err.clear();
     return forward_update_impl(X, nbatch, n, S_in, m, d, h, S_out, dtype_bytes, plan, stream);
 }
@@ -2343,7 +2366,7 @@ int ms_step_adjoint(const void* X, int32_t nbatch, int64_t n, const void* S, int
 }
 
 int ms_step_adjoint_planned(const void* X, int32_t nbatch, int64_t n, const void* S, int64_t m, int32_t d, double h,
-                            const void* G, void* dS, void* dX, int32_t dtype_bytes, const void* plan, void* stream) {
+                            const void* G, void* dS, void* dX, int32_t dtype_bytes, const ms_plan* plan, void* stream) {
     g_err.clear();
     return step_adjoint_impl(X, nbatch, n, S, m, d, h, G, dS, dX, dtype_bytes, plan, stream);
 }

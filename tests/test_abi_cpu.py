@@ -205,3 +205,34 @@ def test_step_batched_rejects_bad_arguments(api):
     for kw, msg in cases:
         assert call(**kw) == api.MS_E_INVALID, kw
         assert msg in api.last_error(), (kw, api.last_error())
+
+
+def test_planned_calls_refuse_another_points_plan(api):
+    """The kernels take a plan's layout from the call's shape, so a plan of
+    another shape, h or size never reaches them."""
+    L = api.lib()
+    nb, n, d, h = 2, 9000, 16, 1.0
+    need = ctypes.c_int64(0)
+    assert L.ms_points_plan_bytes(nb, n, d, 4, ctypes.byref(need)) == 0 and need.value > 0
+
+    def desc(**kw):
+        v = dict(h=h, n=n, nbatch=nb, d=d, data=0x1000, bytes=need.value)
+        v.update(kw)
+        return api.PlanDesc(**v)
+
+    bad = [desc(h=2.0), desc(n=n - 1), desc(n=2 * n, nbatch=1), desc(nbatch=1), desc(d=15), desc(data=None),
+           desc(data=0x1010), desc(bytes=need.value - 1)]
+    for q in bad:
+        assert L.ms_forward_update_planned(FAKE, nb, n, FAKE, n, d, h, FAKE, 4, ctypes.byref(q), None) == -1
+        assert "plan" in api.last_error()
+        assert L.ms_step_adjoint_planned(FAKE, nb, n, FAKE, n, d, h, FAKE, FAKE, FAKE, 4, ctypes.byref(q),
+                                         None) == -1
+        assert "plan" in api.last_error()
+    # a plan where these calls use none: few points, float64
+    q = desc(n=100, bytes=1 << 30)
+    assert L.ms_forward_update_planned(FAKE, nb, 100, FAKE, n, d, h, FAKE, 4, ctypes.byref(q), None) == -1
+    assert L.ms_forward_update_planned(FAKE, nb, n, FAKE, n, d, h, FAKE, 8, ctypes.byref(desc()), None) == -1
+    q = api.PlanDesc()
+    assert L.ms_points_plan(FAKE, nb, n, d, h, 4, 0x1000, need.value - 1, ctypes.byref(q), None) == -1
+    assert L.ms_points_plan(FAKE, nb, n, d, h, 4, 0x1008, need.value, ctypes.byref(q), None) == -1
+    assert L.ms_points_plan(FAKE, nb, n, d, h, 4, 0x1000, need.value, None, None) == -1

@@ -88,3 +88,23 @@ def test_runs_non_finite_point():
     X = _cloud(6, 12000, 16, 20)
     X[500, 2] = float("nan")
     assert int(torch.isfinite(api.forward_update(X, X.clone(), 1.0)).all(1).sum()) == 0
+
+
+@pytest.mark.parametrize("nb,n,m,d", [(2, 8192, 8192, 16), (1, 12000, 11500, 3)])   # nb n m above 2^27: both over runs
+def test_planned_calls_same_bits(nb, n, m, d):
+    X = torch.stack([_cloud(31 + b, n, d, 12) for b in range(nb)])
+    S = X if m == n else X[:, :m].contiguous()
+    G = torch.randn(nb, m, d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(4))
+    plan = api.points_plan(X, 1.0)
+    assert plan is not None
+    assert torch.equal(api.forward_update(X, S, 1.0, plan), api.forward_update(X, S, 1.0))
+    out = [(torch.zeros_like(S), torch.zeros_like(X)) for _ in range(2)]
+    for (dS, dX), p in zip(out, (plan, None)):
+        api.step_adjoint_accumulate(X, S, 1.0, G, dS, dX, p)
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    with pytest.raises(api.MeanShiftError, match="plan"):
+        api.forward_update(X, S, 2.0, plan)
+    with pytest.raises(api.MeanShiftError, match="plan"):
+        api.forward_update(X[:, :-1].contiguous(), S, 1.0, plan)
+    with pytest.raises(ValueError, match="plan"):
+        api.forward_update(X, S, 1.0, plan.data)
