@@ -421,7 +421,8 @@ __global__ __launch_bounds__(256) void run_fill_kernel(const float* __restrict__
 // and the largest distance from it (packed units, rounded up).  In 16-D a ball
 // around the mean of a run has 0.7 of the radius around one of its points.  A
 // run too long for one wave (far points of a cloud without clusters) gets an
-// infinite radius.
+// infinite radius, and so does one with a point whose distance from the mean is
+// not finite: no distance from such a ball rules its points out.
 constexpr int kBallRows = 8192;
 template <int D>
 __global__ __launch_bounds__(256) void run_ball_kernel(const float* __restrict__ tiles,
@@ -461,19 +462,22 @@ __global__ __launch_bounds__(256) void run_ball_kernel(const float* __restrict__
 #pragma unroll
     for (int k = 0; k < DP; ++k) c[k] = k < D ? lane_value(wave_add63(c[k]), 63) * inv : 0.0f;
     float r2 = 0.0f;
+    bool fin = true;
     for (int i = lane; i < cnt; i += 64) {
         float x[DP], q = 0.0f;
         row(i, x);
 #pragma unroll
         for (int k = 0; k < D; ++k) q = fmaf(x[k] - c[k], x[k] - c[k], q);
-        r2 = fmaxf(r2, q);
+        r2 = fmaxf(r2, q);   // passes a NaN over
+        fin = fin && isfinite(q);
     }
+    const bool allfin = __ballot(!fin) == 0;
     r2 = -lane_value(wave_min63(-r2), 63);
     if (lane == 0) {
         float* o = balls + (long long)r * (DP + 4);
 #pragma unroll
         for (int k = 0; k < DP; ++k) o[k] = c[k];
-        o[DP] = sqrtf(r2) * scale * 1.0001f + 1e-30f;
+        o[DP] = allfin ? sqrtf(r2) * scale * 1.0001f + 1e-30f : __builtin_inff();
     }
 }
 

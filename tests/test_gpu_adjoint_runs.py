@@ -108,3 +108,39 @@ def test_planned_calls_same_bits(nb, n, m, d):
         api.forward_update(X[:, :-1].contiguous(), S, 1.0, plan)
     with pytest.raises(ValueError, match="plan"):
         api.forward_update(X, S, 1.0, plan.data)
+
+
+@pytest.mark.parametrize("d,bad", [(16, [float("inf")]), (16, [float("inf"), float("-inf")]), (3, [float("inf")]),
+                                   (8, [3e38, 3e38]), (8, [3e30, 3e30])])
+def test_runs_infinite_point_shares_a_run(d, bad):
+    """Points that are not finite lie in one run with far points; neither may
+    be left out.  An infinite coordinate makes that coordinate of every update of
+    its cloud NaN (0 inf) and with it all gradients, as over all pairs, and
+    leaves the other cloud alone; a finite one whose distance
+    overflows weighs nothing, and the far points beside it keep their weight."""
+    X = torch.stack([_cloud(6, 8200, d, 20), _cloud(7, 8200, d, 20)])
+    X[0, 100:140] += 400.0 * torch.arange(1, 41, device=DEV, dtype=torch.float32)[:, None]   # far, one by one
+    clean = X.clone()
+    for i, v in enumerate(bad):
+        X[0, 500 + i, 1] = v
+    S = clean.clone()
+    G = torch.randn(2, 8200, d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(5))
+    new = api.forward_update(X, S, 1.0)
+    dS, dX = api.step_adjoint(X, S, 1.0, G)
+    rn, rS, rX = _ref(clean[1], S[1], 1.0, G[1])
+    _close(new[1], rn, "update")
+    _close(dS[1], rS, "dS")
+    _close(dX[1], rX, "dX")
+    keep = torch.ones(8200, dtype=torch.bool, device=DEV)
+    keep[500:500 + len(bad)] = False
+    rn, rS, rX = _ref(clean[0][keep], S[0], 1.0, G[0])
+    if not np.isfinite(bad).all():
+        assert not torch.isfinite(new[0][:, 1]).any()
+        other = [k for k in range(d) if k != 1]
+        _close(new[0][:, other], rn[:, other], "update")
+        assert not torch.isfinite(dS[0]).any() and not torch.isfinite(dX[0]).any()
+        return
+    _close(new[0], rn, "update")
+    if max(bad) < 1e38:   # else g.dx overflows in FP32, in every form
+        _close(dS[0], rS, "dS")
+        _close(dX[0][keep], rX, "dX")
