@@ -264,8 +264,9 @@ int ms_step_noalloc(const ms_params *p, const float *X, int64_t n, int32_t d, fl
  * Stream-ordered; the call returns once the offsets are on the device (it
  * waits for the work already queued on the stream), the iterations
  * themselves run asynchronously -- with p->graph = 1 they are captured on a
- * private stream as one HIP graph (3 kernels per iteration, no memory
- * nodes), launched on `stream`, and the call returns when the graph is done.
+ * private stream as one HIP graph (3 kernels per iteration over tiles, one or
+ * two for all iterations in the seed form; no memory nodes), launched on
+ * `stream`, and the call returns when the graph is done.
  */
 int ms_step_batched(const ms_params *p, const float *X, const int64_t *x_off,
                     float *seeds, const int64_t *s_off, int32_t ncl, int32_t d,

@@ -1535,6 +1535,51 @@ int prepare_batched_bf16_seeds(Workspace& ws, const std::vector<int32_t>& so, in
     return MS_OK;
 }
 
+// Runs what enqueue(stream) launches as one HIP graph: captured on a private
+// stream (capture is not allowed on the null stream), then one graph launch on
+// the caller's stream, waited for (the workspace outlives the launch).  The
+// executable graph is kept (per host thread and device) and updated in place
+// when a later call captures the same topology, so that it is instantiated once
+// per shape.
+template <class F>
+int run_as_graph(F&& enqueue, hipStream_t s) {
+    int dev = 0;
+    FMS_HIP(hipGetDevice(&dev));
+    GraphCache& gc = g_graph;
+    if (gc.dev != dev) gc.clear();
+    gc.dev = dev;
+    if (!gc.cs) FMS_HIP(hipStreamCreateWithFlags(&gc.cs, hipStreamNonBlocking));
+    hipGraph_t g = nullptr;
+    hipError_t e = hipStreamBeginCapture(gc.cs, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+        e = enqueue(gc.cs);
+        const hipError_t e2 = hipStreamEndCapture(gc.cs, &g);
+        if (e == hipSuccess) e = e2;
+    }
+    if (e == hipSuccess && gc.ge) {
+        hipGraphNode_t bad = nullptr;
+        hipGraphExecUpdateResult res = hipGraphExecUpdateError;
+        const hipError_t eu = hipGraphExecUpdate(gc.ge, g, &bad, &res);
+        if (eu != hipSuccess || res != hipGraphExecUpdateSuccess) {
+            (void)hipGetLastError();   // another topology: instantiate anew
+            (void)hipGraphExecDestroy(gc.ge);
+            gc.ge = nullptr;
+        } else {
+            gc.updates += 1;
+        }
+    }
+    if (e == hipSuccess && !gc.ge) {
+        e = hipGraphInstantiate(&gc.ge, g, nullptr, nullptr, 0);
+        if (e == hipSuccess) gc.instantiations += 1;
+        else gc.ge = nullptr;
+    }
+    if (e == hipSuccess) e = hipGraphLaunch(gc.ge, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (g) (void)hipGraphDestroy(g);
+    if (e != hipSuccess) return hip_fail(e, "batched iterations as a graph");
+    return MS_OK;
+}
+
 // The seed form of a batched step call: all updates in one launch.
 int step_batched_seeds(const ms_params* p, const float* X, const int64_t* x_off, float* seeds,
                        const int64_t* s_off, int ncl, int d, int n_iter, uint8_t* converged, int32_t* iters,
@@ -1583,7 +1628,11 @@ int step_batched_seeds(const ms_params* p, const float* X, const int64_t* x_off,
     a.ctl = nullptr;
     seed_args_runs(a, *ri);
     a.seg = so_dev;
-    FMS_HIP(launch_seed_iterate(a, sh.D, p->kernel, seed_shape_batched(M), M, s));
+    auto updates = [&](hipStream_t q) {
+        return launch_seed_iterate(a, sh.D, p->kernel, seed_shape_batched(M), M, q);
+    };
+    if (p->graph && n_iter > 0) FMS_CHECK(run_as_graph(updates, s));
+    else FMS_HIP(updates(s));
     FMS_HIP(launch_seed_store(b, M, seeds, converged, iters, shift2, s));
     return MS_OK;
 }
@@ -1714,51 +1763,14 @@ int step_batched_impl(const ms_params* p, const float* X, const int64_t* x_off, 
                                           bb.count, bb.ptot, b.act[0], s));
     }
     if (ev) FMS_HIP(hipEventRecord(ev[0], s));
-    if (p->graph && n_iter > 0) {
-        // every iteration captured on a private stream (capture is not allowed
-        // on the null stream), then one graph launch on the caller's stream.
-        // The executable graph is kept (per host thread and device) and
-        // updated in place when a later call captures the same topology, so
-        // that it is instantiated once per shape.
-        int dev = 0;
-        FMS_HIP(hipGetDevice(&dev));
-        GraphCache& gc = g_graph;
-        if (gc.dev != dev) gc.clear();
-        gc.dev = dev;
-        if (!gc.cs) FMS_HIP(hipStreamCreateWithFlags(&gc.cs, hipStreamNonBlocking));
-        hipGraph_t g = nullptr;
-        hipError_t e = hipStreamBeginCapture(gc.cs, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess) {
-            for (int t = 0; t < n_iter && e == hipSuccess; ++t)
-                e = launch_batched_iteration(b, xo_dev, so_dev, ncl, cnt, plan, item_cloud, slot_cloud, t, gc.cs);
-            const hipError_t e2 = hipStreamEndCapture(gc.cs, &g);
-            if (e == hipSuccess) e = e2;
-        }
-        if (e == hipSuccess && gc.ge) {
-            hipGraphNode_t bad = nullptr;
-            hipGraphExecUpdateResult res = hipGraphExecUpdateError;
-            const hipError_t eu = hipGraphExecUpdate(gc.ge, g, &bad, &res);
-            if (eu != hipSuccess || res != hipGraphExecUpdateSuccess) {
-                (void)hipGetLastError();   // another topology: instantiate anew
-                (void)hipGraphExecDestroy(gc.ge);
-                gc.ge = nullptr;
-            } else {
-                gc.updates += 1;
-            }
-        }
-        if (e == hipSuccess && !gc.ge) {
-            e = hipGraphInstantiate(&gc.ge, g, nullptr, nullptr, 0);
-            if (e == hipSuccess) gc.instantiations += 1;
-            else gc.ge = nullptr;
-        }
-        if (e == hipSuccess) e = hipGraphLaunch(gc.ge, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);   // the workspace outlives the launch
-        if (g) (void)hipGraphDestroy(g);
-        if (e != hipSuccess) return hip_fail(e, "batched iterations as a graph");
-    } else {
-        for (int t = 0; t < n_iter; ++t)
-            FMS_HIP(launch_batched_iteration(b, xo_dev, so_dev, ncl, cnt, plan, item_cloud, slot_cloud, t, s));
-    }
+    auto iterations = [&](hipStream_t q) {
+        hipError_t e = hipSuccess;
+        for (int t = 0; t < n_iter && e == hipSuccess; ++t)
+            e = launch_batched_iteration(b, xo_dev, so_dev, ncl, cnt, plan, item_cloud, slot_cloud, t, q);
+        return e;
+    };
+    if (p->graph && n_iter > 0) FMS_CHECK(run_as_graph(iterations, s));
+    else FMS_HIP(iterations(s));
     if (ev) FMS_HIP(hipEventRecord(ev[1], s));
     FMS_HIP(launch_seed_store(b, M, seeds, converged, iters, shift2, s));
     return MS_OK;

@@ -256,3 +256,25 @@ def test_batched_full_size_sampled(orc):
         ref, ost, oit, osh = orc.step(Xs[c], Ss[c].astype(np.float64), 1.0, "gaussian", tol=1e-3, n_iter=3)
         say("cloud", c, "n", len(Xs[c]))
         ragged_check(orc, Xs[c], Ss[c], 1.0, "gaussian", 3, S[a:b], it[a:b], conv[a:b], ref, oit, ost)
+
+
+@pytest.mark.parametrize("sizes,d", [(SIZES[:8], 4), ([20000], 16), (SIZES[2:7], 32)])
+def test_batched_graph_of_the_seed_form(sizes, d):
+    """Without a launch shape the updates are one launch of all clouds' seeds
+    (two for one cloud of d >= 16): with graph=1 that is captured, kept,
+    updated in place by later calls of any clouds and iteration count, and done
+    when the call returns; the bits are those of the plain launch."""
+    api.release_workspace()
+    i0, u0 = api.graph_stats()
+    for rep, n_iter in enumerate((5, 5, 2, 7)):
+        Xs, Ss, xo, so = _batch(80 + rep, sizes, d, max_seeds=1500)
+        Xa = torch.from_numpy(np.concatenate(Xs)).to(DEV)
+        Sa = torch.from_numpy(np.concatenate(Ss)).to(DEV)
+        ref = [t.cpu() for t in api.step_batched(Xa, xo, Sa, so, 1.0, n_iter=n_iter)]
+        got = api.step_batched(Xa, xo, Sa, so, 1.0, n_iter=n_iter, graph=True)
+        torch.cuda.synchronize()
+        for a, b in zip(ref, got):
+            torch.testing.assert_close(b.cpu(), a, rtol=0, atol=0, equal_nan=True)
+        i, u = api.graph_stats()
+        assert (i + u) - (i0 + u0) == rep + 1   # every call ran its updates as a graph
+    assert api.graph_stats()[0] > i0
