@@ -240,7 +240,7 @@ struct SeedArgs {
     const float* ppair = nullptr;
     const unsigned long long* dense = nullptr;   // one cloud, optional: RunIndex::dense
     float slack = 0.0f, flat_reach = 0.0f;   // set by the launcher
-    int wgs = 0;
+    int wgs = 0, wg0 = 0;      // of this launch: workgroups, and the ones in earlier launches
 };
 struct SeedShape {
     int R;    // seeds per workgroup

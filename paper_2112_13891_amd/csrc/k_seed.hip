@@ -67,6 +67,8 @@ constexpr int kSeedMaxWaves = 16;
 // waves per SIMD the register count must allow
 constexpr int seed_min_waves(int D) { return D >= 16 ? 3 : 4; }
 constexpr int kXcdRun = 64;
+// Workgroups of one launch: fewer than 2^32 threads, with at most 16 waves each.
+constexpr int kSeedLaunch = 1 << 21;
 // wide rows need the registers that 16 waves in one workgroup would not have
 constexpr int seed_max_waves(int D, int R) { return R > 1 ? 4 : (D <= 4 ? kSeedMaxWaves : 8); }
 
@@ -113,7 +115,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(
     const int xi = (int)blockIdx.x >> 3;
     const int wg = a.wgs - 1 - (((xi / kXcdRun) * 8 + ((int)blockIdx.x & 7)) * kXcdRun + xi % kXcdRun);
     if (wg < 0) return;
-    const int j0 = PW ? wg * (int)(blockDim.x >> 6) + hwave : wg * R;
+    const int j0 = PW ? (a.wg0 + wg) * (int)(blockDim.x >> 6) + hwave : (a.wg0 + wg) * R;
     if (PW && j0 >= a.m) return;
     // rows: tiles [0, nball), a ball each; runs: the cloud's pivots
     // [ball0, ball0 + nball), whose runs start at run0
@@ -705,14 +707,15 @@ __global__ __launch_bounds__(256) void tile_ball_kernel(float* T, int n, int til
 // Seeds of a step call in (m x d, stride d) and out, one coordinate per thread.
 __global__ void seed_load_kernel(const float* __restrict__ seeds, const uint8_t* __restrict__ conv_in, int d, int DP,
                                  int m, float* S, uint8_t* status, int32_t* iters, float* shift2) {
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (long long)m * DP) return;
-    const int j = (int)(e / DP), k = (int)(e % DP);
-    S[e] = k < d ? seeds[(long long)j * d + k] : 0.0f;
-    if (k == 0) {
-        status[j] = conv_in[j];
-        iters[j] = 0;
-        shift2[j] = __builtin_nanf("");
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < (long long)m * DP; e += stride) {
+        const int j = (int)(e / DP), k = (int)(e % DP);
+        S[e] = k < d ? seeds[(long long)j * d + k] : 0.0f;
+        if (k == 0) {
+            status[j] = conv_in[j];
+            iters[j] = 0;
+            shift2[j] = __builtin_nanf("");
+        }
     }
 }
 
@@ -720,16 +723,21 @@ __global__ void seed_store_kernel(const float* __restrict__ S, int DP, int d, in
                                   const uint8_t* __restrict__ status, const int32_t* __restrict__ it,
                                   const float* __restrict__ sh, float* seeds, uint8_t* conv, int32_t* iters,
                                   float* shift2) {
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (long long)m * d) return;
-    const int j = (int)(e / d), k = (int)(e % d);
-    seeds[e] = S[(long long)j * DP + k];
-    if (k == 0) {
-        conv[j] = status[j];
-        iters[j] = it[j];
-        if (it[j] > 0) shift2[j] = sh[j];
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < (long long)m * d; e += stride) {
+        const int j = (int)(e / d), k = (int)(e % d);
+        seeds[e] = S[(long long)j * DP + k];
+        if (k == 0) {
+            conv[j] = status[j];
+            iters[j] = it[j];
+            if (it[j] > 0) shift2[j] = sh[j];
+        }
     }
 }
+
+// Blocks of 256 for that many elements, a stride more than once where a launch
+// of all of them would have 2^32 threads.
+dim3 element_grid(long long total) { return dim3((unsigned)std::min<long long>((total + 255) / 256, 1 << 22)); }
 
 // D >= 8: rows to tiles as they are, with the tail filled up (no balls).
 __global__ void pack_tiles_kernel(const float* __restrict__ X, int n, int d, int D, float scale, float* T) {
@@ -746,14 +754,21 @@ __global__ void pack_tiles_kernel(const float* __restrict__ X, int n, int d, int
 }
 
 template <int D, int R, bool RUNS, bool PW = false>
-hipError_t launch_seed_t(const SeedArgs& a, int kernel, int wgs, int nw, hipStream_t s) {
+hipError_t launch_seed_t(SeedArgs a, int kernel, int wgs, int nw, hipStream_t s) {
     const size_t lds = RUNS ? run_lds(a.run_cap) * (PW ? nw : 1) : 0;
-    if (kernel == MS_KERNEL_GAUSSIAN)
-        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN, RUNS, PW>), dim3(wgs), dim3(64 * nw), lds, s,
-                           a);
-    else
-        hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT, RUNS, PW>), dim3(wgs), dim3(64 * nw), lds, s, a);
-    return hipGetLastError();
+    // from the last seeds down, as within a launch: the far ones start first
+    for (int w1 = wgs; w1 > 0; w1 = a.wg0) {
+        a.wgs = std::min(w1, kSeedLaunch);
+        a.wg0 = w1 - a.wgs;
+        const dim3 g((a.wgs + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun));
+        if (kernel == MS_KERNEL_GAUSSIAN)
+            hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_GAUSSIAN, RUNS, PW>), g, dim3(64 * nw), lds, s, a);
+        else
+            hipLaunchKernelGGL((seed_iterate_kernel<D, R, MS_KERNEL_FLAT, RUNS, PW>), g, dim3(64 * nw), lds, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace
@@ -761,7 +776,7 @@ hipError_t launch_seed_t(const SeedArgs& a, int kernel, int wgs, int nw, hipStre
 hipError_t launch_seed_load(const float* seeds, const uint8_t* conv_in, int d, int m, Batch& b, hipStream_t s) {
     if (b.metric == MS_METRIC_COSINE) return hipErrorInvalidValue;   // unit seeds: launch_seed_init_from_array
     const long long total = (long long)m * b.sh.DP;
-    hipLaunchKernelGGL(seed_load_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, seeds, conv_in, d,
+    hipLaunchKernelGGL(seed_load_kernel, element_grid(total), dim3(256), 0, s, seeds, conv_in, d,
                        b.sh.DP, m, b.S, b.status, b.iters, b.shift2);
     return hipGetLastError();
 }
@@ -769,7 +784,7 @@ hipError_t launch_seed_load(const float* seeds, const uint8_t* conv_in, int d, i
 hipError_t launch_seed_store(const Batch& b, int m, float* seeds, uint8_t* conv, int32_t* iters, float* shift2,
                              hipStream_t s) {
     const long long total = (long long)m * b.d;
-    hipLaunchKernelGGL(seed_store_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, b.S, b.sh.DP, b.d,
+    hipLaunchKernelGGL(seed_store_kernel, element_grid(total), dim3(256), 0, s, b.S, b.sh.DP, b.d,
                        m, b.status, b.iters, b.shift2, seeds, conv, iters, shift2);
     return hipGetLastError();
 }
@@ -840,16 +855,12 @@ hipError_t launch_seed_iterate(SeedArgs a, int D, int kernel, const SeedShape& s
     if (wgs < 1) return hipSuccess;
     // one of two launches runs, by the index's estimate (RunIndex::dense)
     if (a.dense) {
-        SeedArgs b = a;
-        b.wgs = (wgs + kOwnWaves - 1) / kOwnWaves;
-        const int g = (b.wgs + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
+        const int g = (wgs + kOwnWaves - 1) / kOwnWaves;
         hipError_t e = hipErrorInvalidValue;
-        if (D == 16) e = launch_seed_t<16, 1, true, true>(b, kernel, g, kOwnWaves, s);
-        if (D == 32) e = launch_seed_t<32, 1, true, true>(b, kernel, g, kOwnWaves, s);
+        if (D == 16) e = launch_seed_t<16, 1, true, true>(a, kernel, g, kOwnWaves, s);
+        if (D == 32) e = launch_seed_t<32, 1, true, true>(a, kernel, g, kOwnWaves, s);
         if (e != hipSuccess) return e;
     }
-    a.wgs = wgs;
-    wgs = (wgs + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
 #define FMS_CASE(DD, RR, RUNS) \
     if (D == DD && sh.R == RR && (a.poff != nullptr) == RUNS) return launch_seed_t<DD, RR, RUNS>(a, kernel, wgs, sh.nw, s);
     FMS_CASE(1, 1, false) FMS_CASE(2, 1, false) FMS_CASE(3, 1, false) FMS_CASE(4, 1, false)

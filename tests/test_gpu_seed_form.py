@@ -84,3 +84,26 @@ def test_seed_form_non_finite_point():
         S, conv, it, sh = api.step(_gpu(X), _gpu(X[:50]), 1.5, n_iter=2)
         torch.cuda.synchronize()
         assert (conv.cpu().numpy() == 2).all()
+
+
+@pytest.mark.parametrize("m,d", [((1 << 21) + 77, 5), ((1 << 25) + 5, 5), ((1 << 26) + 3, 2)])
+def test_seed_form_more_seeds_than_a_launch(m, d):
+    """Past 2^21 workgroups the seeds go in several launches (2^32 threads are
+    the most a launch takes): seeds that repeat give the first ones' bits."""
+    n = 300
+    X = torch.randn(n, d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(d)).contiguous()
+    j = torch.arange(m, device=DEV) % n
+    S, conv, it, sh = api.step(X, X[j], 1.0, n_iter=2)
+    few = api.step(X, X, 1.0, n_iter=2, plain=True)[0]
+    assert float((S[:n] - few).abs().max()) < 1e-5
+    assert torch.equal(S, S[:n][j]) and torch.equal(it, it[:n][j]) and torch.equal(conv, conv[:n][j])
+
+
+def test_step_store_past_2_32_coordinates():
+    """m d > 2^32 coordinates of seeds in one call."""
+    m, d = (1 << 24) + 1, 256
+    X = torch.zeros(2, d, device=DEV)
+    X[1, 0] = 0.5
+    S, conv, it, sh = api.step(X, X[:1].expand(m, d).contiguous(), 1.0, n_iter=1)
+    assert int(it.min()) == 1 and torch.equal(S[-1], S[0])
+    assert float(S[-1, 0]) == pytest.approx(0.5 * np.exp(-0.125) / (1 + np.exp(-0.125)), rel=1e-5)
