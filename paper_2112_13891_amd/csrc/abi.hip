@@ -644,8 +644,21 @@ void fill_batch(Batch& b, int n, int d, int B, const StepShape& sh, const ms_par
 // kDenseFloats is 50 us of that.
 enum SeedForm { SEED_NONE, SEED_ROWS, SEED_RUNS, SEED_DENSE };
 constexpr long long kDenseFloats = 1LL << 28;   // seeds x points x D x updates
+
+// Tiles and sort positions are counted in 32 bits, rounding included.
+constexpr long long kSeedPointsMax = 1LL << 30;
+
+// The seed and screened forms fill tiles up with points at 1e19, and their
+// bounds are products of bf16 parts, which lose what is under 2^-126: a flat
+// window of that size (the Gaussian's units are its own bandwidth) takes the
+// forms that compare every pair in FP32.
+bool window_in_range(const ms_params* p) {
+    return p->kernel == MS_KERNEL_GAUSSIAN || (p->h >= 1e-12f && p->h <= 1e12f);
+}
+
 SeedForm seed_form(const ms_params* p, int n, int d, long long m, int updates, bool in_step) {
     if (p->plain || in_step || d > 32) return SEED_NONE;
+    if (n > kSeedPointsMax || !window_in_range(p)) return SEED_NONE;
     const long long all = m * n;   // < 2^62
     const bool small = all <= kDenseFloats / step_shape(d).DP / std::max(1, std::min(updates, 8));
     // directions are at most 2 apart: with that reach every seed would read every row
@@ -878,7 +891,7 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
         FMS_CHECK(cache_get(C, budget, SL_ACT1, B, &b.act[1]));
         FMS_CHECK(cache_get(C, budget, SL_SHIFT2, B, &b.shift2));
         FMS_CHECK(cache_get(C, budget, SL_PART, (size_t)part_floats, &b.part));
-        if (form == SEED_NONE && !bf16 && !p->plain && wide_screen_ok(sh.D, n, B)) {
+        if (form == SEED_NONE && !bf16 && !p->plain && window_in_range(p) && wide_screen_ok(sh.D, n, B)) {
             char* base;
             FMS_CHECK(cache_get(C, budget, SL_SCREEN, wide_screen_carve(b.screen, nullptr, sh.D, n, B), &base,
                                 screened, s));   // the points' part comes first
@@ -1260,7 +1273,7 @@ int step_core(A& ws, bool run, bool lean, const ms_params* p, const float* X, in
         return MS_OK;
     }
     const size_t rows = seedf ? (size_t)(n + 63) / 64 * 64 : (size_t)n;   // whole tiles
-    const bool screen = !lean && !bf16 && !p->plain && wide_screen_ok(sh.D, n, m);
+    const bool screen = !lean && !bf16 && !p->plain && window_in_range(p) && wide_screen_ok(sh.D, n, m);
     float* Xp;
     FMS_CHECK(ws.alloc(&Xp, rows * sh.DP));
     if (!screen) FMS_RUN(launch_pack_points(X, n, d, sh.DP, scale, Xp, s));
@@ -1436,6 +1449,7 @@ struct BatchedPrepared {
 // for this kind of input (those name shapes of the tile form).
 bool batched_seed_form(const ms_params* p, int d, long long n, long long M, int ncl, int R_force) {
     if (p->precision != MS_PREC_FP32 || d > 32 || n < 1 || M < 1) return false;
+    if (n > kSeedPointsMax || !window_in_range(p)) return false;
     if (R_force || p->tile_R || p->tile_chunk || p->tile_grid) return false;
     std::lock_guard<std::mutex> lock(g_tune_mu);
     return g_tune.find(tune_key(d, n, M, ncl, p->precision)) == g_tune.end();

@@ -107,3 +107,21 @@ def test_step_store_past_2_32_coordinates():
     S, conv, it, sh = api.step(X, X[:1].expand(m, d).contiguous(), 1.0, n_iter=1)
     assert int(it.min()) == 1 and torch.equal(S[-1], S[0])
     assert float(S[-1, 0]) == pytest.approx(0.5 * np.exp(-0.125) / (1 + np.exp(-0.125)), rel=1e-5)
+
+
+@pytest.mark.parametrize("d,n,m", [(2, 1001, 200), (2, 20001, 64), (16, 20001, 1000), (128, 5001, 64)])
+@pytest.mark.parametrize("unit", [1e18, 1e-20])
+def test_flat_window_of_any_size(d, n, m, unit):
+    """The tiles' padding (points at 1e19) never falls into a window, and no
+    bound is taken in units where bf16 products underflow."""
+    rng = np.random.default_rng(d)
+    X = rng.uniform(-0.1, 0.1, (n, d))
+    X[:, 0] = rng.uniform(-9.0, 9.0, n)
+    if d == 2:
+        X[:, 1] = rng.uniform(-9.0, 9.0, n)
+    X = torch.from_numpy((unit * X).astype(np.float32)).to(DEV)
+    S = X[torch.topk(X[:, 0], m).indices].contiguous()   # the seeds nearest to the padding
+    a = api.step(X, S, 3.0 * unit, kernel="flat", n_iter=1)
+    b = api.step(X, S, 3.0 * unit, kernel="flat", n_iter=1, plain=True)
+    assert int(b[2].min()) == 1 and torch.equal(a[2], b[2])
+    assert float((a[0] - b[0]).abs().max()) < 1e-5 * unit * 9.0
