@@ -71,9 +71,10 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 // split into two bf16 parts each,
 //     E = 2 x.m - |m|^2 - |x|^2 = -|x - m|^2
 // is a sum of hi.hi + hi.lo + lo.hi and of the norms split in three, off by less
-// than eps = 2^-13 (3 |x|^2 + 2 q) for a mode at squared distance q (the parts
-// left out are below 2^-17 of each factor, the matrix unit's sums below 2^-20
-// of their largest term, and |m|^2 <= 2 |x|^2 + 2 q).  A first pass over the
+// than eps = 2^-13 (3 |x|^2 + 2 q) for a mode at squared distance q (a bf16 part
+// is within 2^-8 of its value: lo.lo and what the lo parts leave out are below
+// 3 2^-16 of 2 |x||m|, the matrix unit's sums off by less than 2^-17 of their
+// largest term, and |x|^2 + |m|^2 <= 3 |x|^2 + 2 q).  A first pass over the
 // modes finds the largest E of every point (with MARGIN: the second largest);
 // a mode whose E lies more than 2 eps below it cannot be the nearest (second
 // nearest) in FP32 either.  The second pass lists the modes within that band,

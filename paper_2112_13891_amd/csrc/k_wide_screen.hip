@@ -8,11 +8,12 @@
 //   1. wide_mask_kernel: a bit per seed and point, set unless a lower bound of
 //      q rules the pair out.  The bound comes from one bf16 product per pair on
 //      the matrix cores, 2 s.x with s and x relative to the first row:
-//          q >= (1 - 2^-7) (|s|^2 + |x|^2) - (2 s.x)_bf16 .
-//      A bf16 factor is within 2^-9 of its value, so 2 s.x within
-//      2^-7 |s||x| (1 + 2^-9) <= 2^-8 (1 + 2^-9) (|s|^2 + |x|^2); the FP32 sum of
-//      256 products adds 2^-16 of that, and the other half of the 2^-7 covers
-//      the rounding of the norms.
+//          q >= (1 - 2^-7 - 2^-10) (|s|^2 + |x|^2) - (2 s.x)_bf16 .
+//      A bf16 factor is within 2^-8 of its value (8 significant bits), so 2 s.x
+//      is off by at most (2^-7 + 2^-16) 2 |s||x| <= (2^-7 + 2^-16) (|s|^2 + |x|^2):
+//      coordinates at 1 + 2^-8, which round down to 1, take nearly all of it.
+//      The FP32 sums (256 products, each norm's chain of 128) are off by less
+//      than 2^-14 of |s|^2 + |x|^2; the further 2^-10 covers them 16 times.
 //   2. wide_eval_kernel: a workgroup per seed lists its set bits in LDS and
 //      evaluates those pairs as the all-pairs form does, in FP32 differences;
 //      then the update, the shift and the convergence test, and the seed's
@@ -40,7 +41,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-constexpr float kNormShare = 1.0f - 1.0f / 128.0f;
+constexpr float kNormShare = 1.0f - 1.0f / 128.0f - 1.0f / 1024.0f;
 constexpr float kNever = 3e38f;          // no finite product reaches it
 constexpr float kZeroQ = 160.0f;         // exp2(-q) == +0 for q >= 150
 constexpr float kDropped = 34.0f;        // log2 of W over all that is left out, and 1 of margin

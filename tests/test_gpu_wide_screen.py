@@ -111,3 +111,28 @@ def test_screen_fit_counts_each_pair_once(n, d, B):
     g = api.fit(_gpu(X), 1.5 * np.sqrt(d / 32.0), n_initial=B, rng_seed=4, trace=True)
     assert (g.drawn_status != 2).all()
     assert g.pairs == int(g.drawn_iters.astype(np.int64).sum()) * n
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_screen_bound_at_the_worst_rounding(d, sign):
+    """Pairs at the edge of a flat window, far from the first row, with every
+    factor of the bf16 product rounded the same way as far as it goes: down
+    from 1 + 2^-8 (the product is short by 2^-7 of |s|^2 + |x|^2, nearly the
+    whole allowance) or up from 1 + 3 2^-8."""
+    n, m = 4000, 96
+    rng = np.random.default_rng(d)
+    mag = 64.0 * (1.0 + (2.0 ** -8 if sign > 0 else 3.0 * 2.0 ** -8))
+    X = np.zeros((n, d), np.float32)
+    X[1:] = mag
+    # neighbours differ in a few coordinates by the next binade's equally bad value
+    for i in range(1, n):
+        X[i, rng.choice(d, rng.integers(0, 6), replace=False)] *= 0.5
+    S0 = np.ascontiguousarray(X[1:m + 1])
+    # the window: the pairs that differ in at most 4 coordinates, in or just out
+    for h in (0.5 * mag * 2.0, 0.5 * mag * 2.0 * (1 - 1e-6), 0.5 * mag):
+        a = api.step(_gpu(X), _gpu(S0), h, kernel="flat", n_iter=1)
+        b = api.step(_gpu(X), _gpu(S0), h, kernel="flat", n_iter=1, plain=True)
+        assert torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+        # two orders of sums of up to 4,000 terms of FP32
+        assert float((a[0] - b[0]).abs().max()) < 1e-5 * mag
