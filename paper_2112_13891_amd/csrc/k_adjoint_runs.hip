@@ -461,12 +461,36 @@ void launch_modes(const AdjArgs& seeds, const AdjArgs& points, bool adjoint, int
 
 }  // namespace
 
+// Where the runs are the better form.  A workgroup takes one tile of 64 rows and
+// walks all of its near tiles, so they want many tiles on either side (few
+// seeds: 60,000 x 2,500, D = 16, update and adjoint 2,490 us against 968 over
+// all pairs), clouds that several runs divide (1,000 points: 1,135 and 903; 256
+// points, 1,030 clouds: 26 ms and 1.0), and pairs enough to pay for the index.
+// Update and adjoint over runs and over all pairs (k_adjoint.hip), us, clusters
+// that mostly overlap at D <= 8:
+//   D = 16: 8,192^2 562 / 383, 4 x 4,096^2 537 / 426, 8 x 4,096^2 687 / 746,
+//           11,600^2 487 / 796, 64 x 2,100^2 1,286 / 1,398, 65,536 x 16,384 1,458 / 6,055
+//   D = 32: 8,192^2 662 / 703, 4 x 4,096^2 647 / 711, 64 x 2,100^2 2,689 / 2,783
+//   D = 8:  8 x 4,096^2 590 / 420, 16,384^2 1,353 / 842, 16 x 10,000 x 4,096 1,613 / 1,678
+//   D = 3:  8 x 4,096^2 454 / 249, 16,384^2 998 / 514
+// At D <= 8 reach is wide against such clouds and nothing is left out; the runs
+// are kept for the larger clouds, where their sums by tiles are ten times closer
+// (8 x 16,384^2, D = 3: 1.2e-7 and 1.2e-6 off) and where clouds that are wide
+// against h gain (8 x 8,200^2, D = 3, centres 30 h apart: 570 and 1,708, two updates).
 bool adjoint_runs_ok(int nb, int n, int m, int d, bool adjoint, bool planned) {
     if (d > 32) return false;
     if ((long long)nb * std::max(n, m) > (1LL << 28)) return false;   // tile slots stay in 32 bits
-    // all pairs of 2^26 take about 180 us in the adjoint and 50 in the update at
-    // D = 16; the points' index takes 60 to 100 us unless it is there already
-    return (long long)nb * n * m >= (adjoint ? 1LL << 26 : (planned ? 1LL << 26 : 1LL << 27));
+    const int D = step_shape(d).D, least = std::min(n, m);
+    const long long pairs = (long long)nb * n * m;
+    if (D <= 8) {
+        // more seeds than points: few tiles of points with long lists (8,192 x
+        // 20,000, D = 3: 829 over runs, 323 over all pairs)
+        if (least < 8192 || m > n) return false;
+    } else {
+        if (least < 2048 || (long long)nb * least < 8192) return false;
+    }
+    // the update alone, without a plan: the index takes 60 to 100 us of it
+    return pairs >= (D == 16 || !(adjoint || planned) ? 1LL << 27 : 1LL << 26);
 }
 
 size_t adjoint_runs_bytes(int nb, int n, int m, int d, bool same, bool adjoint, bool planned) {

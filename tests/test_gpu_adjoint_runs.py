@@ -144,3 +144,32 @@ def test_runs_infinite_point_shares_a_run(d, bad):
     if max(bad) < 1e38:   # else g.dx overflows in FP32, in every form
         _close(dS[0], rS, "dS")
         _close(dX[0][keep], rX, "dX")
+
+
+# either side of the lines between the two forms: points of the least cloud,
+# tiles of the smaller side, more seeds than points, pairs
+@pytest.mark.parametrize("nb,n,m,d", [(2, 8192, 8192, 8), (3, 8300, 8195, 5), (2, 8191, 8191, 8), (1, 8192, 20000, 3),
+                                      (1, 65536, 8192, 16), (1, 65536, 8191, 16), (16, 2048, 4096, 16),
+                                      (16, 2047, 4200, 16), (32, 2100, 2100, 29), (300, 500, 500, 16),
+                                      (4100, 129, 130, 16), (70000 // 2, 33, 62, 3)])
+def test_lines_between_runs_and_all_pairs(nb, n, m, d):
+    X = _cloud(n + d, nb * n, d, 12).view(nb, n, d)
+    S = _cloud(n + d, nb * m, d, 12).view(nb, m, d) if m != n else X
+    G = torch.randn(nb, m, d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(6))
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    new = api.forward_update(X, S, 1.0)
+    dS, dX = api.step_adjoint(X, S, 1.0, G)
+    torch.cuda.synchronize()
+    # no more memory than a few hundred copies of the rows' partial sums
+    assert free - torch.cuda.mem_get_info()[0] < (1 << 29) + 64 * 4 * (nb * (n + m) * d)
+    for b in sorted({0, nb // 2, nb - 1}):
+        rn, rS, rX = _ref(X[b], S[b], 1.0, G[b])
+        _close(new[b], rn, "update")
+        # the rounding of a distance q/2 is the weight's times q/2: without a
+        # point within 3 h a seed's own gradient is off by more than its sums
+        s64, x64 = S[b].double(), X[b].double()
+        near = ((s64 * s64).sum(1)[:, None] + (x64 * x64).sum(1) - 2.0 * s64 @ x64.T).min(1)[0] < 9.0
+        assert int(near.sum()) * 2 > m
+        _close(dS[b][near], rS[near], "dS")
+        _close(dX[b], rX, "dX")
