@@ -1456,21 +1456,39 @@ bool batched_seed_form(const ms_params* p, int d, long long n, long long M, int 
 }
 
 // Whether a step call gains by the clouds' runs, which it builds for these
-// updates alone: fitted to calls of 20 to 150 clouds of up to 64,000 points, in
-// us.  The tile form takes about 140, the runs 60 and 0.105 per 1,000 points;
-// then per 10^6 pairs the tile form 0.3 (d = 2), 0.35 (3), 0.73 (8) and 1.15 (16),
-// the seed form 0.22, 0.16, 0.79 and 0.5: at d = 8 it leaves out half of the
-// tiles, but every seed reads its own ones through L2 (17 GB at 19 TB/s), where
-// the tile form reads a point once for 64 or more seeds.  Both forms, tile and
-// seed: 2.8 million points, 250 seeds a cloud, d = 3, one update 386 and 485,
-// two 628 and 600; 1.9 million, d = 8, three 979 and 1,150; 0.6 million, d = 8,
-// three 371 and 308.
+// updates alone.  Both forms' times were fitted as sums over (calls, updates,
+// clouds, points, points x updates, seeds x updates, pairs x updates) to 945
+// calls of 1 to 8,000 clouds of 50 to 50,000 points, 8 to 250 seeds a cloud and
+// 1, 3 and 10 updates (median error 5 to 18 %); this is their difference, less
+// 60 us for what the fit misses.  The tile form has the dearer updates (its plan
+// and finalize: 10 to 30 us each, and 16 us per 1,000 clouds), the runs the index
+// and, since a seed is a workgroup, 0.4 (d = 2) to 1.8 ns (32) a seed and update
+// whatever its cloud's size.  Per 10^6 pairs the tile form takes 0.15 (d = 2),
+// 0.18 (3), 0.37 (8), 0.71 (16) and 1.6 us (32), the seed form 0.20, 0.13, 0.72,
+// 0.44 and 0.90: at d = 8 it leaves out half of the tiles, but every seed reads
+// its own through L2, where the tile form reads a point once for 64 seeds.
+// Tile and seed form, us: 2,000 clouds of 400 x 16-D, 60 seeds, three updates 581
+// and 943; 8,000 of 50 x 8-D, 16 seeds, one 398 and 515, three 910 and 684; 60 of
+// 6,000 x 16-D, 200 seeds, three 571 and 332.  Over the 945 the choice takes 0.57
+// of the tile form's time, 1.01 of the better form's, and at most 1.15 of the
+// tile form's.
 bool batched_runs_pay(const int64_t* x_off, const int64_t* s_off, int ncl, int d, int n_iter) {
+    struct Line {
+        double call, update, point, point_update, seed_update, pair_update;   // us; the last four per 10^6
+    };
+    static constexpr Line lines[5] = {{55, 9, -67, 14, -330, -0.05},
+                                      {36, 12, -72, 17, -450, 0.054},
+                                      {34, 14, -38, 25, -580, -0.34},
+                                      {37, 16, -110, 68, -1190, 0.27},
+                                      {41, 22, -130, 160, -1500, 0.74}};
     const int D = step_shape(d).D;
+    const Line& l = lines[D <= 2 ? 0 : (D <= 4 ? 1 : (D <= 8 ? 2 : (D <= 16 ? 3 : 4)))];
     double pairs = 0.0;
     for (int c = 0; c < ncl; ++c) pairs += (double)(x_off[c + 1] - x_off[c]) * (double)(s_off[c + 1] - s_off[c]);
-    const double gain = D <= 2 ? 0.08 : (D <= 4 ? 0.19 : (D <= 8 ? -0.06 : 0.65));   // per 10^6 pairs
-    return 0.105e-3 * (double)x_off[ncl] - 80.0 < gain * 1e-6 * pairs * n_iter;
+    const double n = 1e-6 * (double)x_off[ncl], M = 1e-6 * (double)s_off[ncl], it = n_iter;
+    return l.call + it * l.update + ncl * (0.016 * it - 0.031) + n * (l.point + it * l.point_update) +
+               it * (M * l.seed_update + 1e-6 * pairs * l.pair_update) >
+           0.0;
 }
 
 // The BF16 form over many clouds (Gaussian, padded D in {8, 16, 32}): each

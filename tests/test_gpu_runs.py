@@ -151,3 +151,30 @@ def test_cosine_all_within_reach(d):
     b = api.step(_gpu(X), _gpu(S0[:5]), 0.4, n_iter=2, metric="cosine")
     p = api.step(_gpu(X), _gpu(S0), 0.4, n_iter=2, metric="cosine", plain=True)
     assert float((a[0] - p[0]).abs().max()) < 1e-5 and float((a[0][:5] - b[0]).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("d,ncl,n_each,m,n_iter,few", [(2, 40, 40000, 30, 1, 2), (3, 40, 40000, 20, 1, 2),
+                                                       (8, 30, 40000, 200, 3, 1), (16, 1500, 100, 60, 2, 20),
+                                                       (29, 1500, 100, 60, 2, 20)])
+def test_batched_calls_that_keep_the_tile_form(d, ncl, n_each, m, n_iter, few):
+    """Calls for which the index or a workgroup per seed costs more than it
+    saves, against their first clouds alone, which run over their pivot runs;
+    and both against an explicit launch shape, which always takes the tiles."""
+    c = np.random.default_rng(d).uniform(0.0, 30.0, (20, d))
+    rng = np.random.default_rng(d + 1)
+    sizes = n_each - rng.integers(0, 9, ncl)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    X = (c[rng.integers(0, 20, off[-1])] + 0.5 * rng.standard_normal((off[-1], d))).astype(np.float32)
+    S0 = np.concatenate([X[a + rng.choice(k, m, replace=False)] for a, k in zip(off[:-1], sizes)])
+    so = np.arange(ncl + 1) * m
+    Xg, Sg = _gpu(X), _gpu(S0)
+    a = api.step_batched(Xg, off, Sg, so, 1.2, n_iter=n_iter)
+    tiles = api.step_batched(Xg, off, Sg, so, 1.2, n_iter=n_iter, tile_R=1, tile_chunk=1024, tile_grid=2048)
+    for u, v in zip(a, tiles):
+        torch.testing.assert_close(u, v, rtol=0, atol=0, equal_nan=True)   # R never changes the bits
+    b = api.step_batched(Xg[:off[few]].contiguous(), off[:few + 1], Sg[:so[few]].contiguous(), so[:few + 1], 1.2,
+                         n_iter=n_iter)
+    k = few * m
+    assert torch.equal(a[2][:k], b[2])
+    # two FP32 orders of sums over a cluster of 2,000 points, coordinates up to 30
+    assert float((a[0][:k] - b[0]).abs().max()) < 1e-4
