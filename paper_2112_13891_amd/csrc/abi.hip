@@ -663,7 +663,12 @@ SeedForm seed_form(const ms_params* p, int n, int d, long long m, int updates, b
     const bool small = all <= kDenseFloats / step_shape(d).DP / std::max(1, std::min(updates, 8));
     // directions are at most 2 apart: with that reach every seed would read every row
     if (p->metric == MS_METRIC_COSINE && cull_reach(p->kernel, p->h) >= 2.0 && !small) return SEED_NONE;
-    if (d <= 4) return SEED_ROWS;
+    // few seeds, very many points: a workgroup per seed leaves half of the chip
+    // idle over long lists (4 x 10^6 points, 128 seeds, five updates, us, seeds
+    // and blocks: 50 blobs 983 and 1,300, evenly spread 2,725 and 1,456, one blob
+    // 6,398 and 1,649; 10^6 points 314 and 491, 613 and 522, 1,655 and 556;
+    // 512 seeds 324 and 805, 738 and 968, 1,754 and 1,143)
+    if (d <= 4) return n > (1 << 20) && m <= 256 ? SEED_NONE : SEED_ROWS;
     return small ? SEED_DENSE : SEED_RUNS;
 }
 
@@ -770,9 +775,10 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
     const float r2m = rm * rm, r2c = rc * rc;
 
     // d <= 4 and very many points: a seed lists thousands of balls a pass, and on
-    // data that fills its space it keeps many (an image's 2^20 colours 1.50 ms by
-    // blocks, 1.85 by seeds; 10^6 points in 50 clusters 2.0 and 1.3, 400,000 1.16
-    // and 0.69)
+    // data that fills its space, or in few clusters, it keeps many.  Fits by blocks
+    // and by seeds, ms: an image's 2^19 colours 0.90 and 0.93, 2^20 1.32 and 1.82,
+    // 2^21 2.13 and 3.84; 10^6 points in 50 clusters 1.59 and 0.91, in 5 0.54 and
+    // 0.70, in one 0.91 and 3.76; 3 x 10^6 in 50 7.46 and 7.60, in 5 1.23 and 1.82
     constexpr int kRowsFit = 1 << 19;
     const SeedForm form = d <= 4 && n > kRowsFit ? SEED_NONE :
         seed_form(p, n, d, all ? n : std::min<long long>(n, 4LL * p->n_initial), p->max_iter, p->gamma < 1.0f);
@@ -911,7 +917,7 @@ int fit_impl(const ms_params* p, const float* X, int n, int d, float* modes, int
         }
         FMS_HIP(launch_round_init(X, d, DP, all ? nullptr : pool[cur], dpos, B, bids, removed,
                                   bstate, b, need, p->max_iter, s));
-        const SeedShape ssh = seed_shape(base.D, B);
+        const SeedShape ssh = seed_shape(base.D, B, n);
         if (sorted && (!seedf || ssh.R > 1)) {
             // seeds that are close in space share waves (refine work, culled blocks)
             if (all)
@@ -1236,7 +1242,7 @@ int step_core(A& ws, bool run, bool lean, const ms_params* p, const float* X, in
         X = Xn;
     }
     const bool seedf = form == SEED_ROWS;
-    const SeedShape ssh = seed_shape(sh.D, m);
+    const SeedShape ssh = seed_shape(sh.D, m, n);
     if (form == SEED_RUNS || form == SEED_DENSE) {
         RunIndex ri;
         float* tiles = nullptr;

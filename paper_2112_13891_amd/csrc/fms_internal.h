@@ -246,7 +246,7 @@ struct SeedShape {
     int R;    // seeds per workgroup
     int nw;   // waves per workgroup
 };
-SeedShape seed_shape(int D, long long m);
+SeedShape seed_shape(int D, long long m, long long n);
 SeedShape seed_shape_batched(long long m);
 // Seeds of a step call in and out (Euclidean metric; cosine seeds are made
 // unit vectors by launch_seed_init_from_array).

@@ -70,7 +70,7 @@ constexpr int kXcdRun = 64;
 // Workgroups of one launch: fewer than 2^32 threads, with at most 16 waves each.
 constexpr int kSeedLaunch = 1 << 21;
 // wide rows need the registers that 16 waves in one workgroup would not have
-constexpr int seed_max_waves(int D, int R) { return R > 1 ? 4 : (D <= 4 ? kSeedMaxWaves : 8); }
+constexpr int seed_max_waves(int D, int R) { return D <= 4 && R == 1 ? kSeedMaxWaves : 8; }
 
 // LDS of a seed's list over runs: masks, entries, counts, pivot distances.
 __host__ __device__ constexpr size_t run_lds(int cap) { return ((size_t)cap / 64 * 8 + (size_t)cap * 12 + 16 + 15) / 16 * 16; }
@@ -828,11 +828,29 @@ hipError_t launch_tile_ball(float* T, int n, int D, float* geom, int ld, hipStre
 //   8,192    557 / 469 / 510 / 869          620 / 511 / 546
 // (64-seed tiles: 2,530 us an update at 8,192 seeds).  Two seeds share the
 // loads but leave two waves a SIMD: one seed per workgroup.
-SeedShape seed_shape(int D, long long m) {
+// At D <= 4 the number of points matters too: a seed alone reads all the points
+// within its reach, which grow with n, and from some n on that, not the walk
+// over the lists, is the time.  Then two or four neighbours share them.  Five
+// updates of clustered (50 blobs, 3-D), evenly spread (2-D) and entirely reached
+// points (one blob), us, seeds a workgroup and waves:
+//   n, m                  1, 4 or 8           2, 8            4, 8
+//   200,000   1,000     152   240   703   168  236  559
+//   400,000   2,000     306   722  2567                    276   467  1512
+//   1,000,000 1,000     459  1340  3151   379  787 2431
+//   1,000,000 2,000     662  2635  7601                    484   960  3587
+//   4,000,000 2,000    3147 13403 61153                   1610  4113 13926
+//                        4, 4                               4, 8
+//   400,000   4,000     385   772  2967                    420   739  2825
+//   1,000,000 4,000     748  1765  7301                    741  1625  6748
+//   4,000,000 8,192    3918 13339 52859                   3821 11764 50614
+// (the order of the seeds is 10 us: at 400,000 points two updates of 600 to
+// 1,500 clustered seeds were 7 to 11 % slower with it).
+SeedShape seed_shape(int D, long long m, long long n) {
     SeedShape sh;
     if (D <= 4) {
-        sh.R = m > 2048 ? 4 : 1;
-        sh.nw = m <= 512 ? 8 : 4;
+        const bool many = n > (1 << 19);
+        sh.R = m > 2048 ? 4 : (many && m > 512 ? (m > 1024 ? 4 : 2) : 1);
+        sh.nw = m <= 512 || (many && sh.R > 1) ? 8 : 4;
     } else {
         sh.R = 1;
         sh.nw = m <= 512 ? 8 : (m <= 2048 ? 4 : 2);
@@ -864,6 +882,7 @@ hipError_t launch_seed_iterate(SeedArgs a, int D, int kernel, const SeedShape& s
 #define FMS_CASE(DD, RR, RUNS) \
     if (D == DD && sh.R == RR && (a.poff != nullptr) == RUNS) return launch_seed_t<DD, RR, RUNS>(a, kernel, wgs, sh.nw, s);
     FMS_CASE(1, 1, false) FMS_CASE(2, 1, false) FMS_CASE(3, 1, false) FMS_CASE(4, 1, false)
+    FMS_CASE(1, 2, false) FMS_CASE(2, 2, false) FMS_CASE(3, 2, false) FMS_CASE(4, 2, false)
     FMS_CASE(1, 4, false) FMS_CASE(2, 4, false) FMS_CASE(3, 4, false) FMS_CASE(4, 4, false)
     FMS_CASE(1, 1, true) FMS_CASE(2, 1, true) FMS_CASE(3, 1, true) FMS_CASE(4, 1, true)
     FMS_CASE(8, 1, true) FMS_CASE(16, 1, true) FMS_CASE(32, 1, true)

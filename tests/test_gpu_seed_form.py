@@ -125,3 +125,22 @@ def test_flat_window_of_any_size(d, n, m, unit):
     b = api.step(X, S, 3.0 * unit, kernel="flat", n_iter=1, plain=True)
     assert int(b[2].min()) == 1 and torch.equal(a[2], b[2])
     assert float((a[0] - b[0]).abs().max()) < 1e-5 * unit * 9.0
+
+
+# either side of the lines on seeds a workgroup (512, 1,024, 2,048 seeds; 2^19
+# points) and of the one on few seeds over very many points
+@pytest.mark.parametrize("n,m,d", [(524288, 1024, 3), (524288, 2049, 3), (524289, 512, 2), (524289, 513, 1),
+                                   (530001, 1023, 2), (530001, 1024, 4), (530001, 1025, 3), (524289, 2047, 2),
+                                   (524289, 2048, 4), (524289, 2049, 1), (1048577, 256, 3), (1048577, 257, 2)])
+@pytest.mark.parametrize("kernel", ["gaussian", "flat"])
+def test_seeds_that_share_a_workgroup(n, m, d, kernel):
+    X = _gpu(blobs(n + d, n, d, k=40, box=300.0))
+    S = X[torch.randperm(n, device=DEV, generator=torch.Generator(device=DEV).manual_seed(m))[:m]].contiguous()
+    h = 1.5 if kernel == "gaussian" else 2.5
+    a = api.step(X, S, h, kernel=kernel, n_iter=2, tol=1e-30)
+    b = api.step(X, S, h, kernel=kernel, n_iter=2, tol=1e-30, plain=True)
+    assert torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+    # a window's edge is decided after one rounding on either side: a few points
+    # of 10^3 to 10^4 in a window may differ after the first update
+    tol = 1e-4 if kernel == "gaussian" else 2e-3
+    assert float((a[0] - b[0]).abs().max()) < tol * h
