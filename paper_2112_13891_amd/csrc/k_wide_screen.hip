@@ -28,9 +28,10 @@
 // L2: 625,000 kept pairs of 512 bytes an update there, 10.7 TB/s.
 // 50,001 points, 500 seeds, 40 clusters, D = 128: an update 830 us over all
 // pairs (k_step_wide.hip), 17.5 + 30 us here; two updates with their set-up 1,720
-// -> 133 us.  With every pair within reach an update costs a similar time or
-// less (D = 128: 2.5 ms -> 1.4 ms for three, D = 256 4.0 -> 1.8), at D = 64 a
-// quarter more (0.75 -> 0.93).
+// -> 133 us.  With every pair within reach three updates cost 2.4 -> 1.5 ms there
+// and 9.0 -> 3.2 ms at D = 256; at D = 64 0.69 -> 0.83 ms, since every seed reads
+// all rows (6.4 GB an update, 24 TB/s) where the all-pairs form reads a row once
+// for 64 seeds.
 
 #include "step_common.h"
 
@@ -243,28 +244,40 @@ __global__ __launch_bounds__(kThreads) void wide_mask_kernel(StepArgs a, int t, 
     }
 }
 
-// Sum over a row of 16 lanes, the same in each: every step adds two values
+// Sum over L neighbouring lanes, the same in each: every step adds two values
 // that commute.
 template <int CTRL>
 __device__ __forceinline__ float row_add(float v) {
     return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
-__device__ __forceinline__ float row16_sum(float v) {
-    v = row_add<0x128>(v);   // row_ror:8
-    v = row_add<0x124>(v);
-    v = row_add<0x122>(v);
-    return row_add<0x121>(v);
+template <int L>
+__device__ __forceinline__ float lanes_sum(float v) {
+    if constexpr (L == 16) {
+        v = row_add<0x128>(v);   // row_ror:8
+        v = row_add<0x124>(v);
+        v = row_add<0x122>(v);
+        return row_add<0x121>(v);
+    } else {
+        static_assert(L == 8);
+        v = row_add<0xb1>(v);    // quad_perm:[1,0,3,2]
+        v = row_add<0x4e>(v);    // quad_perm:[2,3,0,1]
+        return row_add<0x141>(v);   // row_half_mirror: the other quad of 8
+    }
 }
 
-// A workgroup per active seed.  16 lanes hold a pair, D / 16 coordinates each;
-// four pairs to a wave, U rows in flight per lane.
+// A workgroup per active seed.  LP lanes hold a pair, D / LP coordinates each;
+// 64 / LP pairs to a wave, U rows in flight per lane.  At least 8 coordinates a
+// lane: with 4 (D = 64 by 16 lanes) the lanes' sum and the exponential are a
+// third of the work (50,001 x 500 pairs, all near: KEEPME).
 template <int D, int KERN>
 __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, int t, WideScreen w) {
-    constexpr int C4 = D / 64;               // float4 groups per lane
+    constexpr int LP = D == 64 ? 8 : 16;     // lanes per pair
+    constexpr int G = 64 / LP;               // pairs of a wave
+    constexpr int C4 = D / (4 * LP);         // float4 groups per lane
     constexpr int U = D == 256 ? 2 : 4;
     const int m = active_count(a.ctl, t);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int sub = lane & 15, grp = lane >> 4;
+    const int sub = lane % LP, grp = lane / LP;
     __shared__ unsigned short list[kEvalPoints];
     __shared__ int wcnt[kEvalWaves];
     __shared__ float red[kEvalWaves][D + 1];
@@ -276,7 +289,7 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
         float s[4 * C4], acc[4 * C4], accw = 0.0f;
 #pragma unroll
         for (int q = 0; q < C4; ++q) {
-            const float4 v = reinterpret_cast<const float4*>(sj)[q * 16 + sub];
+            const float4 v = reinterpret_cast<const float4*>(sj)[q * LP + sub];
             s[4 * q] = v.x * a.scale;
             s[4 * q + 1] = v.y * a.scale;
             s[4 * q + 2] = v.z * a.scale;
@@ -312,14 +325,14 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
             }
             __syncthreads();
             len = __builtin_amdgcn_readfirstlane(len);
-            for (int i0 = wave * 4 * U; i0 < len; i0 += kEvalWaves * 4 * U) {
+            for (int i0 = wave * G * U; i0 < len; i0 += kEvalWaves * G * U) {
                 float4 x4[U][C4];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int i = i0 + u * 4 + grp;
+                    const int i = i0 + u * G + grp;
                     const long long p = (long long)w0 * 32 + list[i < len ? i : i0];
 #pragma unroll
-                    for (int q = 0; q < C4; ++q) x4[u][q] = X4[p * (D / 4) + q * 16 + sub];
+                    for (int q = 0; q < C4; ++q) x4[u][q] = X4[p * (D / 4) + q * LP + sub];
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -333,11 +346,11 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
                     }
 #pragma unroll
                     for (int k = 0; k < 4 * C4; ++k) q2 = fmaf(dx[k], dx[k], q2);
-                    q2 = row16_sum(q2);
+                    q2 = lanes_sum<LP>(q2);
                     float wt;
                     if (KERN == MS_KERNEL_GAUSSIAN) wt = __builtin_amdgcn_exp2f(-q2);
                     else wt = q2 <= a.h2 ? 1.0f : 0.0f;
-                    if (i0 + u * 4 + grp < len) {
+                    if (i0 + u * G + grp < len) {
                         accw += wt;
 #pragma unroll
                         for (int k = 0; k < 4 * C4; ++k) acc[k] = fmaf(wt, dx[k], acc[k]);
@@ -345,16 +358,16 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
                 }
             }
         }
-        // the four pairs of a wave, then the waves in order
+        // the pairs of a wave, then the waves in order
 #pragma unroll
-        for (int off = 16; off <= 32; off <<= 1) {
+        for (int off = LP; off <= 32; off <<= 1) {
             accw += __shfl_xor(accw, off);
 #pragma unroll
             for (int k = 0; k < 4 * C4; ++k) acc[k] += __shfl_xor(acc[k], off);
         }
         if (grp == 0) {
 #pragma unroll
-            for (int k = 0; k < 4 * C4; ++k) red[wave][(k >> 2) * 64 + sub * 4 + (k & 3)] = acc[k];
+            for (int k = 0; k < 4 * C4; ++k) red[wave][(k >> 2) * 4 * LP + sub * 4 + (k & 3)] = acc[k];
             if (sub == 0) red[wave][D] = accw;
         }
         __syncthreads();
