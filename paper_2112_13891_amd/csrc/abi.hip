@@ -690,8 +690,14 @@ void seed_args_order(SeedArgs& a, const RunSeeds& q) {
     a.ppair = q.ppair;
 }
 
-// A seed per wave needs seeds for most of the waves.
-constexpr int kOwnSeeds = 512;
+// A seed per wave needs seeds for the chip's 1,024 SIMDs: up to 2,048 of them it
+// takes the same time.  262,144 points, three updates, us, waves that share a seed
+// and waves with one each:
+//   D = 16, clusters  2           4           7             D = 32  2           4           7
+//     512 seeds     714 2,212   492 1,560   348   863         1,163 3,774   750 2,088   537 1,345
+//     1,000       1,585 2,211 1,026 1,465   648   865         3,857 3,776 2,225 2,082 1,354 1,346
+//     2,000       3,516 2,212 2,204 1,559 1,275   873         9,632 3,771 5,243 2,085 3,129 1,349
+constexpr int own_seeds(int D) { return D == 16 ? 1280 : 832; }
 
 void seed_args_runs(SeedArgs& a, const RunIndex& r) {
     a.T = r.tiles;
@@ -702,7 +708,7 @@ void seed_args_runs(SeedArgs& a, const RunIndex& r) {
     a.run_bound = r.run_bound;
     a.tile_start = r.tile_start;
     a.run_cap = (r.sz.pmax + kFarRuns + 63) / 64 * 64;
-    a.dense = a.m >= kOwnSeeds ? r.dense : nullptr;
+    a.dense = a.m >= own_seeds(r.D) ? r.dense : nullptr;
 }
 
 // Arguments of that form from the batch; the tiles are the packed (n small,

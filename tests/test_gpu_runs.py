@@ -178,3 +178,11 @@ def test_batched_calls_that_keep_the_tile_form(d, ncl, n_each, m, n_iter, few):
     assert torch.equal(a[2][:k], b[2])
     # two FP32 orders of sums over a cluster of 2,000 points, coordinates up to 30
     assert float((a[0][:k] - b[0]).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("d,n,m,k", [(16, 30001, 1279, 1), (16, 30001, 1280, 2), (32, 20000, 831, 2),
+                                     (32, 20000, 833, 1), (13, 30000, 1501, 4)])
+@pytest.mark.parametrize("kernel", ["gaussian", "flat"])
+def test_runs_many_tiles_in_reach_at_the_line(orc, d, n, m, k, kernel):
+    """Either side of the seeds from which each wave takes one of its own."""
+    test_runs_many_tiles_in_reach(orc, d, n, m, k, kernel)
