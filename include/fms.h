@@ -70,7 +70,10 @@ typedef enum {
 typedef enum {
     MS_PREC_FP32 = 0,        /* FP32 direct differences, FP32 accumulation */
     MS_PREC_BF16_REFINE = 1  /* BF16 MFMA products, FP32 recompute within
-                                refine_radius*h, FP32 accumulation */
+                                refine_radius*h, FP32 accumulation; where the
+                                FP32 form that runs all updates in one launch
+                                applies (ms_step, and ms_fit with gamma 1) it
+                                serves these requests too, exactly */
 } ms_precision;
 
 /* Method parameters.  Field order is part of the ABI. */
@@ -100,7 +103,8 @@ typedef struct {
                                  ms_assign: Euclidean only */
     int32_t graph;            /* ms_step_batched: 1 = capture the n_iter
                                  iterations in one HIP graph and launch it
-                                 once (the call then returns when it is done);
+                                 once (the call then returns when it is done),
+                                 in whichever form they run;
                                  the executable graph is kept per host thread
                                  and updated in place by later calls of the
                                  same topology (instantiated once per shape);
@@ -110,14 +114,21 @@ typedef struct {
                                  tile (1, 2 or 4, as the padded dimension
                                  allows: D <= 4 any, D = 8 or 16 1 or 2,
                                  D >= 32 1); 0 = the shape ms_tune_batched chose for
-                                 inputs of this kind, else a default.  The
-                                 results do not depend on it */
-    int32_t plain;            /* ms_fit, ms_step with MS_PREC_FP32: 1 = the
-                                 plain step, every pair computed in input
-                                 order (no spatial order, no block culling;
-                                 the skipped blocks contribute exact zeros,
-                                 so only the summation order differs); for
-                                 comparison.  Ignored by the BF16 form */
+                                 inputs of this kind, else the library's choice
+                                 of form (see ms_step_batched).  A shape given
+                                 here, in tile_chunk or in tile_grid, or
+                                 tuned, means the form over tiles, whose
+                                 results do not depend on tile_R */
+    int32_t plain;            /* ms_fit, ms_step: 1 = a launch per iteration
+                                 and, with MS_PREC_FP32, every pair computed
+                                 in input order (no spatial order, nothing
+                                 left out); for comparison.  Without it tiles
+                                 of points are left out whose pairs have
+                                 weight exactly 0 in FP32 or, for the
+                                 Gaussian kernel, add up to less than 2^-33
+                                 of the seed's sum of weights (an FP32 sum
+                                 rounds at 2^-25 of it), so the results differ
+                                 in the order and rounding of the sums */
     int32_t tile_chunk;       /* ms_step_batched, ms_fit_batched: points per
                                  point chunk of a cloud, 64..65536; 0 = the
                                  size ms_tune_batched chose for inputs of this
@@ -213,17 +224,20 @@ int ms_step(const ms_params *p, const float *X, int64_t n, int32_t d,
 /*
  * ms_step_noalloc -- ms_step for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc).  Same arguments, kernels and results as ms_step, but every
+ * hipMalloc).  Same arguments as ms_step, and its kernels and results where
+ * its workspace fits (below), but every
  * workspace buffer (packed and spatially ordered points, control block,
  * active lists, chunk partials) is carved out of one fixed device scratch
  * array of 32 MiB that the library holds on each GPU it runs on until the
  * process ends; the call itself makes no hipMalloc, hipFree or other
  * allocating call.  The caller still passes X and the seed arrays.
- *   Size limit: the call is sized before anything is launched; one that
- *   needs more than 32 MiB of workspace (for instance n = 200,000 points of
- *   d = 3 need about 8 MB in FP32 and 24 MB in the BF16 form; n x d of a
- *   few million floats and more do not fit) fails with MS_E_INVALID and a
- *   message that gives the bytes it needs.
+ *   Size limit: the call is sized before anything is launched.  One that
+ *   needs more than 32 MiB in the form that ms_step takes runs in the forms
+ *   that launch per iteration and need the least memory (in the call's
+ *   precision: the same results to the rounding of the sums, not bit for
+ *   bit); one that does not fit so either (200,000 points of d = 3 take
+ *   about 8 MB; n x d of a few million floats and more do not fit) fails
+ *   with MS_E_INVALID and a message that gives the bytes it needs.
  *   Concurrency: every call on one GPU uses that GPU's one scratch array and
  *   leaves its contents behind; calls that overlap on one GPU (other
  *   streams, other threads) race and must be serialized by the caller.
@@ -238,9 +252,7 @@ int ms_step_noalloc(const ms_params *p, const float *X, int64_t n, int32_t d, fl
  * c owns the points X[x_off[c], x_off[c+1]) and the seeds
  * seeds[s_off[c], s_off[c+1]), and each seed is updated with its own cloud's
  * points only, as ms_step on that cloud would (Section II-B update, per-seed
- * convergence of Algorithms 1-2; FP32 form).  Each iteration is one launch
- * of each kernel for all clouds, over work items (cloud, seed tile, point
- * chunk) planned on the device from per-cloud active counts.
+ * convergence of Algorithms 1-2).
  *
  *   X          device, (x_off[ncl]) x d float32, the clouds' points back to back.
  *   x_off      host, ncl + 1 nondecreasing point offsets, x_off[0] = 0.
@@ -250,7 +262,13 @@ int ms_step_noalloc(const ms_params *p, const float *X, int64_t n, int32_t d, fl
  *   ncl        1..8192 clouds.
  *   converged, iters, shift2: as ms_step, one entry per seed.
  * Uses p->h, kernel, tol, precision, graph, tile_R, tile_chunk, tile_grid.
- * MS_PREC_FP32: every pair in FP32 (the fused step of ms_step).
+ * MS_PREC_FP32, two forms.  Over tiles: each iteration is one launch of each
+ * kernel for all clouds, every pair in FP32, over work items (cloud, seed
+ * tile, point chunk) planned on the device from per-cloud active counts.  The
+ * seed form (d <= 32): all updates of all seeds in one launch, each over the
+ * tiles of its cloud's points within its reach (what is left out: see
+ * ms_params.plain).  A launch shape in p, or one tuned for inputs of this
+ * kind, takes the tiles; otherwise the sizes decide which is faster.
  * MS_PREC_BF16_REFINE: the BF16 form of ms_step for D > 4, per cloud, for
  * the Gaussian kernel at 5 <= d <= 32 (else MS_E_INVALID): each cloud's
  * points are put in spatial order within the cloud's own rows (nearest of
@@ -290,7 +308,10 @@ int ms_assign(const float *X, int64_t n, int32_t d, const float *modes,
  * set's seeds see only that set's points.  The element type is float32
  * (dtype_bytes = 4) or float64 (8).  The differentiable form of the method
  * (Section II-B unrolled T times with S_0 = X) is built from this call and
- * ms_step_adjoint.  Device pointers; stream-ordered and asynchronous.
+ * ms_step_adjoint.  Large float32 calls leave out pairs whose weight is 0 or
+ * that add up to less than 2^-33 of a seed's sum of weights; in the adjoint
+ * these are terms below 2^-33 of G.  Device pointers; stream-ordered and
+ * asynchronous.
  */
 int ms_forward_update(const void *X, int32_t nbatch, int64_t n, const void *S_in,
                       int64_t m, int32_t d, double h, void *S_out,
@@ -366,7 +387,8 @@ int ms_seed_draw(uint64_t *state, const int32_t *pool, int32_t len,
  * Section II-D; Algorithm 1 with all_points_as_seeds) for every cloud of a
  * batch, as ms_fit on each cloud alone would run it, the clouds' rounds
  * advancing together: every round's iterations of all clouds run through
- * the batched fused step (ms_step_batched's kernels), the seeds of cloud c
+ * ms_step_batched's kernels (FP32 at d <= 32: the seed form, unless a launch
+ * shape is given or tuned), the seeds of cloud c
  * are drawn with the SplitMix64 state rng_seed + c, each cloud merges its
  * converged seeds into its own modes, coverage and compaction act on its own
  * pool, and its seed-count rule is its own.  Labels are the nearest mode
@@ -403,8 +425,12 @@ int ms_fit_batched(const ms_params *p, const float *X, const int64_t *x_off, int
                    void *stream);
 
 /*
- * ms_tune_batched -- launch-shape tuning for ms_step_batched and
- * ms_fit_batched.
+ * ms_tune_batched -- launch-shape tuning of the form over tiles, for
+ * ms_step_batched and ms_fit_batched.  Later calls of the tuned kind take
+ * that form.  In FP32 at d <= 32 the seed form, which untuned calls choose by
+ * their sizes, is faster for most inputs (256 clouds of 200 to 2,000 2-D points,
+ * 32 seeds each, 30 updates: 0.49 ms a call, 0.86 over the best tiles): tune
+ * only kinds of input that are measured to gain by it.
  *
  * Times `trials` iterations (every seed active) of each launch shape on this
  * input -- the seeds per lane R that the padded dimension allows (see

@@ -313,7 +313,8 @@ def step_batched(X, x_off, seeds, s_off, h, kernel="gaussian", tol=1e-3, n_iter=
     seeds[s_off[c]:s_off[c+1]].  Offsets are host sequences of ncl + 1 ints.
     graph=True runs the n_iter iterations as one captured HIP graph; tile_R,
     tile_chunk and tile_grid force the seeds per lane, points per chunk and
-    step grid (0: tuned or default shape).  precision="bf16" takes the BF16
+    step grid of the form over tiles (0: the tuned shape or, untuned, the form
+    that the sizes choose).  precision="bf16" takes the BF16
     form (Gaussian kernel, 5 <= d <= 32; tile_R does not apply).
     Returns new tensors (seeds, converged uint8, iters int32, shift2 float32)."""
     import numpy as np
@@ -381,10 +382,11 @@ def fit_batched(X, x_off, h, kernel="gaussian", tol=1e-3, max_iter=100, merge_ra
 
 
 def tune_batched(X, x_off, seeds, s_off, h, kernel="gaussian", tol=1e-3, trials=4, precision="fp32"):
-    """ms_tune_batched: time each launch shape (seeds per lane, points per
-    chunk, step grid) on this input and keep the fastest for later
-    step_batched / fit_batched calls on inputs of the same kind and
-    precision (the BF16 form: seed tiles of 128, R = 2, only).
+    """ms_tune_batched: time each launch shape of the form over tiles (seeds
+    per lane, points per chunk, step grid) on this input and keep the fastest
+    for later step_batched / fit_batched calls on inputs of the same kind and
+    precision (the BF16 form: seed tiles of 128, R = 2, only).  FP32 calls of
+    d <= 32 that are not tuned may take the seed form, which is mostly faster.
     Returns (best R, {R: ms per iteration}, best chunk, best grid)."""
     import numpy as np
     torch = _torch()

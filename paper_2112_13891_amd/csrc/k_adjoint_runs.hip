@@ -4,9 +4,9 @@
 //
 // The points and the seeds are grouped into runs around sampled pivots
 // (k_runs.hip), 64 rows to a tile.  A workgroup holds one tile, a row per
-// lane, and its four waves stream the other side's tiles through wave-uniform
+// lane, and its eight waves stream the other side's tiles through wave-uniform
 // (scalar) loads, tile by tile in turn; the wave sums are added in wave order.
-// Every lane knows its distance from a run's pivot and the run's radius, so a
+// Every lane knows its distance from a run's centre and the run's radius, so a
 // run is passed over when it is out of every lane's reach, and a row when half
 // of its coordinates already put it there.  On the clouds of the batched
 // recipe (D = 16, 2..40 clusters, h = 1) a tenth of the pairs remains; on data

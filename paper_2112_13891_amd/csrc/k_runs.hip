@@ -1,5 +1,6 @@
 // k_runs.hip -- points grouped into 64-point tiles around sampled pivots, for
-// the seed form (k_seed.hip) at D >= 8, for one cloud or many (gfx950).
+// the seed form (k_seed.hip: one cloud at D >= 8, many at any D up to 32) and the
+// differentiable form (k_adjoint_runs.hip: any D up to 32) (gfx950).
 //
 // Each cloud samples one pivot per 128 points (at fixed strides, at most
 // 1,024).  A point belongs to the run of its nearest pivot, or, farther than

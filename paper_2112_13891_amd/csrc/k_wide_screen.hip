@@ -431,7 +431,8 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
                     else if (res == 2) a.status[j] = ST_CONVERGED;
                 }
             }
-            // the cosine step does not raise this density: no bound from the last W
+            // (the cosine step raises the density too, the kernel being convex in
+            // s.x on unit vectors; its next pass keeps the bound of the first one)
             const float Wk = a.metric == MS_METRIC_COSINE ? 0.0f : W;
             store_seed<D>(j, u, res == 1, seed_reach(KERN, a.h2, Wk, a.n), a.scale, a.Xp,
                           reinterpret_cast<__bf16*>(w.sf), w.crow);
