@@ -11,13 +11,15 @@ Printed (one JSON line):
   value            pair evaluations per second over the whole step, counted
                    as the method defines them: every active seed against all
                    n points at every iteration (Section II-B), divided by the
-                   measured step time; the pairs the kernels actually
-                   evaluated (culled blocks skipped) are reported beside it;
+                   measured step time; the share of the pairs that the
+                   kernels evaluated (the rest is out of reach) is reported
+                   beside it;
   time_to_cluster  the step time itself;
-  roofline         the fused step (step kernel and its reduction/finalize
-                   launch) at the workload's largest launch (512 seeds x
-                   200,000 points), timed with HIP events on the stream the
-                   library launches on;
+  roofline         one update in the seed form (a workgroup per seed, all of
+                   its updates in one launch) at the workload's largest
+                   launch (512 seeds x 200,000 points), timed with HIP events
+                   on the stream the library launches on; the rate counts the
+                   evaluated pairs;
   configs          the same figures for every workload of the method: the
                    2-D blobs, the 200K mixture, the 32-D embedding mixture
                    (largest launch 8,192 seeds x 262,144 points), the 512
@@ -64,8 +66,8 @@ COUNTERS = {
 # The sources each counted launch runs (its step kernels, their reduction and
 # finalize, and the spatial order that decides which blocks they skip).
 COUNTER_SOURCES = {
-    "c2": ["k_step.hip", "k_step_cull.hip", "k_step_bf16.hip", "k_sort.hip", "step_common.h"],
-    "c3": ["k_step_cull.hip", "k_step_bf16f.hip", "k_sort.hip", "step_common.h"],
+    "c2": ["k_seed.hip", "k_step.hip", "k_step_cull.hip", "k_step_bf16.hip", "k_sort.hip", "step_common.h"],
+    "c3": ["k_seed.hip", "k_runs.hip", "k_step_cull.hip", "k_step_bf16f.hip", "k_sort.hip", "step_common.h"],
 }
 
 
@@ -132,9 +134,9 @@ def algorithmic_bytes(m, n, d, tile=64):
 
 
 def roofline_entry(pairs, d, t_ms, m, n, prec, launch, kernel, counters=None):
-    """Algorithmic flops over the measured iteration against the FP32 vector
-    peak (the path is bound by plain ALU arithmetic); for the BF16 form also
-    the contraction flops against the dense bf16 MFMA peak."""
+    """Flops over the measured iteration against the FP32 vector peak (the
+    path is bound by plain ALU arithmetic): of the pairs that were evaluated
+    where `counters` has their share, else of all of the method's pairs."""
     t = t_ms * 1e-3
     tf = pairs * flops_per_pair(d) / t / 1e12
     ab = algorithmic_bytes(m, n, d, 128 if (prec == "bf16" and d > 4) else 64)
@@ -151,10 +153,30 @@ def roofline_entry(pairs, d, t_ms, m, n, prec, launch, kernel, counters=None):
     if c.get("mfma_flops_per_iteration"):
         e["mfma_tflops_executed"] = c["mfma_flops_per_iteration"] / t / 1e12
         e["mfma_executed_frac_of_bf16_peak"] = e["mfma_tflops_executed"] / BF16_MFMA_PEAK_TFLOPS
-    if c.get("evaluated_pair_fraction") is not None:
-        e["evaluated_pair_fraction"] = c["evaluated_pair_fraction"]
-        e["evaluated_pair_evals_per_s"] = pairs * c["evaluated_pair_fraction"] / t
+    e["counts"] = "every pair of the method"
+    share = c.get("evaluated_pair_fraction")
+    if share is not None:
+        e["counts"] = "evaluated pairs"
+        e["evaluated_pair_fraction"] = share
+        e["evaluated_pair_evals_per_s"] = pairs * share / t
+        e["algorithmic_tflops"] = tf
+        e["achieved"], e["frac"] = tf * share, tf * share / FP32_VEC_PEAK_TFLOPS
+        e.pop("contraction_tflops_on_mfma_form", None)   # no product of these runs on the matrix cores
+        e.pop("contraction_frac_of_bf16_mfma_peak", None)
     return e
+
+
+def evaluated(r):
+    """The share of the pairs that a fit of precision "bf16" evaluated: the seed
+    form, which serves it, counts them as exact pairs."""
+    return {"evaluated_pair_fraction": r.refined_pairs / max(1, r.pairs)}
+
+
+def unevaluated(entry):
+    """An entry whose form leaves pairs out and counts none: no share of a peak."""
+    entry["algorithmic_tflops"], entry["frac"] = entry["achieved"], None
+    entry["counts"] = "every pair of the method, also those left out: a rate, not a share of the peak"
+    return entry
 
 
 def time_kernel(api, torch, X, seeds, h, kernel, precision, iters, plain=False):
@@ -200,7 +222,7 @@ def fit_timing(api, torch, X, h, kernel, steps, **kw):
 def fit_summary(dt, r):
     return {"time_to_cluster_ms": dt * 1e3, "pair_evals_per_s": r.pairs / dt, "K": r.k,
             "rounds": [int(b) for b in r.round_B], "pairs_per_fit": r.pairs,
-            "exact_pair_fraction": r.refined_pairs / max(1, r.pairs)}
+            "exact_pair_fraction": r.refined_pairs / max(1, r.pairs)}   # seed form: the evaluated pairs
 
 
 def config_c1(api, torch, workloads, gpu_fits):
@@ -235,12 +257,13 @@ def config_c3(api, torch, workloads, gpu_fits, iters):
     m = 8192
     rng = np.random.default_rng(8192)
     seeds = torch.from_numpy(w.X[rng.choice(w.n, m, replace=False)]).cuda()
+    share = evaluated(gpu_fits[("c3", "bf16")])
     for prec in ("fp32", "bf16"):
         t = time_kernel(api, torch, X, seeds, w.h, w.kernel, prec, iters)
-        name = ("step_cull_kernel<32, 1, 1> + reduce_kernel + finalize_kernel" if prec == "fp32"
-                else "step_bf16f_kernel<32, false> + reduce_kernel + finalize_kernel")
         out[prec]["roofline"] = roofline_entry(m * w.n, w.d, t, m, w.n, prec, f"{m} seeds x {w.n} points",
-                                               name, counter_figures("c3", prec))
+                                               "one update in seed_iterate_kernel<32, 1, 1, true, false>; pairs of "
+                                               "the tiles in reach, as the fit counts them",
+                                               {**counter_figures("c3", prec), **share})
     out["bf16_kernel_speedup_vs_fp32"] = out["fp32"]["roofline"]["avg_ms"] / out["bf16"]["roofline"]["avg_ms"]
     log(f"c3: fp32 {out['fp32']['time_to_cluster_ms']:.2f} ms, bf16 {out['bf16']['time_to_cluster_ms']:.2f} ms; "
         f"8192-seed iteration fp32 {out['fp32']['roofline']['avg_ms']:.3f} ms, "
@@ -305,8 +328,8 @@ def config_c4(api, torch, workloads, gpu_fits):
                     "pair_evals_per_s": pairs / t_bf, "speedup_vs_fp32": t_it / t_bf,
                     "call_setup_ms": t_bf_setup * 1e3,
                     "max_seed_difference_to_fp32_after_5_iterations_over_h": bf_diff}}
-    e = roofline_entry(pairs, 16, t_it * 1e3, 0, 0, "fp32", "one batched iteration, every seed active",
-                       "bstep_kernel<16, 16, 1> + bfinal_kernel + bplan_kernel")
+    e = unevaluated(roofline_entry(pairs, 16, t_it * 1e3, 0, 0, "fp32", "one batched iteration, every seed active",
+                                   "one update in seed_iterate_kernel<16, 1, 1, true, false> over the clouds' runs"))
     e["algorithmic_bytes"] = sum(-(-len(s) // 64) * len(x) * 16 * 4 for s, x in zip(Ss, Xs))
     e["algorithmic_hbm_frac"] = e["algorithmic_bytes"] / t_it / 1e9 / HBM_PEAK_GBS
     out["roofline"] = e
@@ -365,10 +388,11 @@ def config_c5(api, torch, workloads):
     return {"workload": "64 clouds x 16,384 points, D=16, T=10 Gaussian steps, h=1, loss vs generating "
                         "centres; forward + adjoint with recompute",
             "ms_per_step": dt * 1e3, "forward_pair_evals_per_step": pairs,
-            "roofline": {"bound": "alu", "achieved": tf, "peak": FP32_VEC_PEAK_TFLOPS, "unit": "TFLOP/s",
-                         "frac": tf / FP32_VEC_PEAK_TFLOPS, "flops_per_pair": adjoint_flops_per_pair(d),
-                         "kernel": "10 forward updates + 10 adjoint steps (fwd_partial, ds_partial, "
-                                   "dx_partial and their reductions)", "avg_ms": dt * 1e3}}
+            "roofline": unevaluated({
+                "bound": "alu", "achieved": tf, "peak": FP32_VEC_PEAK_TFLOPS, "unit": "TFLOP/s",
+                "flops_per_pair": adjoint_flops_per_pair(d),
+                "kernel": "10 forward updates + 10 adjoint steps over pivot runs (adj_runs_kernel<16, 0..2>)",
+                "avg_ms": dt * 1e3})}
 
 
 def other_configs(api, torch, workloads):
@@ -751,13 +775,10 @@ def main():
     seeds = torch.from_numpy(w.X[rng.choice(n, m, replace=False)]).cuda()
     t_it = time_kernel(api, torch, X, seeds, w.h, w.kernel, args.precision, args.kernel_iters)
     pairs = m * n
-    step_name = "step_bf16_kernel<3, 1, 1>" if args.precision == "bf16" else "step_cull_kernel<3, 1, 1>"
-    roof = roofline_entry(pairs, d, t_it, m, n, args.precision, f"{m} seeds x {n} points",
-                          f"one fused-step iteration: {step_name} + finalize_fused_kernel<3, 4, 1> "
-                          "(chunk reduction and finalize in one launch)"
-                          + (" + ordered_compact_kernel<3> (the active list in list order)"
-                             if args.precision == "bf16" else ""),
-                          counter_figures("c2", args.precision))
+    update = "one update in seed_iterate_kernel<3, 1, 1, false, false>; share of the pairs as the fit counts it"
+    share = evaluated(results["bf16"][1])
+    roof = roofline_entry(pairs, d, t_it, m, n, args.precision, f"{m} seeds x {n} points", update,
+                          {**counter_figures("c2", args.precision), **share})
     log(f"kernel: {t_it * 1e3:.1f} us/iteration at {m}x{n}: {pairs / (t_it * 1e-3):.3e} pairs/s, "
         f"{roof['achieved']:.2f} TFLOP/s")
 
@@ -776,7 +797,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32" if args.precision == "fp32" else "bf16 products, f32 refine/accumulate",
+        "dtype": "f32",   # precision "bf16" is served by the exact FP32 seed form at this workload
         "data": "synthetic",
         "config": {"workload": "aniso3d: 200,000 points, D=3, 50 anisotropic Gaussian blobs "
                                "(centres U[0,1000]^3, per-axis sigma U[3,8], Dirichlet(2) weights), "
@@ -815,7 +836,7 @@ def main():
     # every workload of the method, each with its roofline entry
     c2 = {"workload": out["config"]["workload"], args.precision: {"roofline": roof},
           other: {"roofline": roofline_entry(pairs, d, t_other, m, n, other, f"{m} seeds x {n} points",
-                                             "one fused-step iteration", counter_figures("c2", other))}}
+                                             update, {**counter_figures("c2", other), **share})}}
     for p_, (dt_, r_) in results.items():
         c2[p_].update(fit_summary(dt_ / args.steps, r_))
     out["configs"] = {"C1": config_c1(api, torch, workloads, gpu_fits), "C2": c2,
