@@ -285,8 +285,8 @@ __global__ __launch_bounds__(kT) void assign_mfma_kernel(const float* __restrict
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
         const int p = base + ct * 32 + (lane & 31);
-        const bool over = scan[ct] || cnt[ct] > kAsgCand;
-        const bool all = over || __shfl_xor((int)over, 32);   // either half's list
+        const int over = (scan[ct] || cnt[ct] > kAsgCand) ? 1 : 0;
+        const bool all = (over | __shfl_xor(over, 32)) != 0;   // either half's list; every lane shuffles
         float x[D];
         const float* row = X + (long long)(p < n ? p : n - 1) * d;
         load_padded(row, x);

@@ -77,3 +77,25 @@ def test_values_that_are_not_finite():
     assert lab[5] == 0 and lab[9] == 0                    # no distance is a finite number
     keep = (want != dead) & (np.arange(1000) != 5) & (np.arange(1000) != 9)
     assert np.array_equal(lab[keep], want[keep]) and not (lab == dead).any()
+
+
+@pytest.mark.parametrize("d", [8, 16, 32, 64])
+@pytest.mark.parametrize("side", [0, 1])
+def test_one_half_of_the_candidates_overflows(d, side):
+    """The lanes l and l + 32 of a wave share a point and list the candidates of
+    different rows of a mode tile (rows j % 8 below 4, and the others).  More
+    alike modes than a list holds on one side only: both halves scan."""
+    X, M = _data(4 + d, 700, 256, d)
+    at = [j for j in range(256) if (j % 8 < 4) == (side == 0)]
+    near = X[:1] + 1e-3 * np.random.default_rng(side).standard_normal((len(at), d)).astype(np.float32)
+    M += 100.0                                            # the others are far
+    M[at[3:40]] = near[3:40]
+    _check(X, M)
+    # alike to the last bit: the lowest index, of either parity
+    for first in (at[3], at[4]):
+        N = M.copy()
+        N[at[3:40]] = M[0]
+        N[[j for j in at[3:40] if j >= first]] = X[0]
+        lab = api.assign(torch.from_numpy(X).to(DEV), torch.from_numpy(N).to(DEV)).cpu().numpy()
+        q = ((X[:, None, :].astype(np.float64) - N[None].astype(np.float64)) ** 2).sum(2)
+        assert (lab == q.argmin(1)).all()
