@@ -84,11 +84,29 @@ __host__ __device__ constexpr size_t run_lds(int cap) { return ((size_t)cap / 64
 // seeds, three 1,100 and 1,900.  Registers for two waves a SIMD: with three,
 // 250 bytes of scratch a lane and 15,500.
 constexpr int kOwnWaves = 4;
+
+// A lane adds at most this many tiles in a row; then its sums go to a second
+// set.  Where points repeat (quantised data), additions of equal terms all
+// round the same way, and the error grows with their number: one update of
+// seeds that see 1,108 tiles of seven different points was off by 8e-6 h, and
+// is by 2e-7 h now.  The second set is V registers a lane.  At D = 32 three
+// waves a SIMD leave none: there it is sums over rows of 16 lanes (`rows4`) in
+// LDS, 2.3 KB a wave (262,144 points, 2 clusters, 700 seeds, three updates:
+// 3,400 us without it, 3,700 in registers that spill, 3,260 so).  At D = 8 the
+// rows cost 9 % (8,192 seeds of 4,000 near points each), the registers 1 %.
+constexpr int kFoldTiles = 32;
+__host__ __device__ constexpr bool fold_rows(int D, bool PW) { return D == 32 && !PW; }
+__host__ __device__ constexpr int fold_quads(int D) { return (D + 4) / 4; }
+
 template <int D, int R, int KERN, bool RUNS, bool PW>
 __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(D)) void seed_iterate_kernel(SeedArgs a) {
     constexpr int DP = D <= 4 ? 4 : D;
     constexpr int G4 = DP / 4;
     constexpr int V = D + 1;
+    constexpr bool kFoldRows = fold_rows(D, PW);
+    constexpr int kFoldQuads = fold_quads(D);
+    static_assert(!kFoldRows || R == 1);
+    constexpr int NWMAX = seed_max_waves(D, R);
     static_assert(R * DP <= 64, "one wave holds the coordinates of the seeds");
     const int lane = threadIdx.x & 63;
     const int hwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -128,9 +146,9 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(
     }
     const bool culled = RUNS || a.geom != nullptr;
 
-    __shared__ float red[2][kSeedMaxWaves][R * V];
-    __shared__ float wub[R][kSeedMaxWaves];
-    __shared__ unsigned wcnt[kSeedMaxWaves];
+    __shared__ float red[2][NWMAX][R * V];
+    __shared__ float wub[R][NWMAX];
+    __shared__ unsigned wcnt[NWMAX];
     // rows: `list` holds tiles.  Runs: `list` holds the first tile of each
     // listed run and `list_pre` the tiles listed before it; a lower bound of a
     // seed's distance from every pivot stays in `dist_s`.  The top bits of an entry say which of
@@ -148,6 +166,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(
     unsigned* const list = RUNS ? reinterpret_cast<unsigned*>(dyn_s + cap / 64) : rows_list;
     int* const list_pre = reinterpret_cast<int*>(list + cap);   // cap + 1
     float* const dist_s = reinterpret_cast<float*>(list_pre + cap + 1);
+    float* const folded_s = reinterpret_cast<float*>(dyn) + (RUNS ? run_lds(cap) / 4 : 0) + hwave * kFoldQuads * 64 + lane;
 
     // lane (r, k) holds coordinate k of seed r, in every wave
     const int r_of = lane / DP, k_of = lane % DP;
@@ -406,6 +425,41 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int k = 0; k < V; ++k) acc[r][k] = 0.0f;
+        float sum[kFoldRows ? 1 : R][kFoldRows ? 1 : V];
+        if constexpr (kFoldRows) {
+#pragma unroll
+            for (int q = 0; q < kFoldQuads; ++q) folded_s[q * 64] = 0.0f;
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int k = 0; k < V; ++k) sum[r][k] = 0.0f;
+        }
+        int run = 0;   // tiles since the last fold, at most
+        auto fold = [&] {
+            if constexpr (kFoldRows) {
+                auto take = [&](int k) {
+                    if (k >= V) return 0.0f;
+                    const float v = acc[0][k];
+                    acc[0][k] = 0.0f;
+                    return v;
+                };
+#pragma unroll
+                for (int q = 0; q < kFoldQuads; ++q) {
+                    const float v0 = take(4 * q), v1 = take(4 * q + 1), v2 = take(4 * q + 2), v3 = take(4 * q + 3);
+                    folded_s[q * 64] += rows4(v0, v1, v2, v3);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int k = 0; k < V; ++k) {
+                        sum[r][k] += acc[r][k];
+                        acc[r][k] = 0.0f;
+                    }
+            }
+            run = 0;
+        };
 
         for (int g0 = 0; g0 < (RUNS ? 1 : groups); g0 += kSegGroups) {
             if constexpr (!RUNS) {
@@ -553,18 +607,34 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(
                 if (next < mine_n) na = fetch(xa, wa);
                 compute(xb, wb, nb);
                 if (!na) break;
+                if ((run += 2 * U) >= kFoldTiles) fold();
             }
+            run += 2 * U;
         }
 
         // lanes, then waves in order; every wave makes the same update
         const int par = it & 1;
+        if constexpr (kFoldRows) {
+            fold();
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                const float v = wave_add63(acc[r][k]);
-                if (lane == 63) red[par][hwave][r * V + k] = v;
+            for (int q = 0; q < kFoldQuads; ++q) {
+                float t = folded_s[q * 64];
+                t = dpp_add<0x128, 0xf>(t);   // row_ror:8
+                t = dpp_add<0x124, 0xf>(t);
+                t = dpp_add<0x122, 0xf>(t);
+                t = dpp_add<0x121, 0xf>(t);
+                const int k = 4 * q + rows4_value(lane);
+                if ((lane & 15) == 0 && k < V) red[par][hwave][k] = t;
             }
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    const float v = wave_add63(sum[r][k] + acc[r][k]);
+                    if (lane == 63) red[par][hwave][r * V + k] = v;
+                }
+        }
         sync();
         float v = 0.0f, W = 0.0f;
         if (r_of < R) {
@@ -755,7 +825,8 @@ __global__ void pack_tiles_kernel(const float* __restrict__ X, int n, int d, int
 
 template <int D, int R, bool RUNS, bool PW = false>
 hipError_t launch_seed_t(SeedArgs a, int kernel, int wgs, int nw, hipStream_t s) {
-    const size_t lds = RUNS ? run_lds(a.run_cap) * (PW ? nw : 1) : 0;
+    const size_t lds = (RUNS ? run_lds(a.run_cap) * (PW ? nw : 1) : 0) +
+                       (fold_rows(D, PW) ? (size_t)nw * fold_quads(D) * 256 : 0);
     // from the last seeds down, as within a launch: the far ones start first
     for (int w1 = wgs; w1 > 0; w1 = a.wg0) {
         a.wgs = std::min(w1, kSeedLaunch);

@@ -98,6 +98,20 @@ __device__ __forceinline__ float wave_add63(float v) {
     return v;
 }
 
+// The sums over lanes of four values in a register: row 0 (16 lanes) holds 16
+// partial sums of a, row 1 of c, row 2 of b, row 3 of d.
+__device__ __forceinline__ float rows4(float a, float b, float c, float d) {
+    auto halves = [](float x, float y) {   // lanes 0-31: of x, 32-63: of y
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    };
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(halves(a, b)), __float_as_uint(halves(c, d)),
+                                                    false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+// Which of the four a lane's row holds.
+__device__ __forceinline__ int rows4_value(int lane) { return 2 * (lane >> 4 & 1) + (lane >> 5); }
+
 __device__ __forceinline__ float lane_value(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }

@@ -144,3 +144,28 @@ def test_seeds_that_share_a_workgroup(n, m, d, kernel):
     # of 10^3 to 10^4 in a window may differ after the first update
     tol = 1e-4 if kernel == "gaussian" else 2e-3
     assert float((a[0] - b[0]).abs().max()) < tol * h
+
+
+# points, dimension, seeds (12 positions, repeated): rows, runs that share a
+# seed, a seed per wave
+@pytest.mark.parametrize("n,d,m", [(262144, 1, 12), (200000, 3, 600), (1100000, 2, 1200), (50000, 8, 24),
+                                   (50000, 16, 12), (50000, 16, 2400), (70881, 24, 12), (70881, 24, 2400)])
+def test_repeated_points_keep_the_sums(n, d, m):
+    """Points of seven values, all within reach: the additions of equal terms
+    round the same way, so that the error of a sum grows with the number of
+    additions in a row.  One update against FP64, within 1.5 times the error of
+    the form that evaluates every pair in short chunks, and 1e-6 h."""
+    rng = np.random.default_rng(n + d)
+    X = (4.0 * rng.standard_normal((7, d)))[rng.integers(0, 7, n)].astype(np.float32)
+    h = 5.0 * np.sqrt(d)
+    P = X[rng.choice(n, 12, replace=False)] + (0.1 * h * rng.standard_normal((12, d))).astype(np.float32)
+    val, cnt = np.unique(X, axis=0, return_counts=True)
+    val, P64 = val.astype(np.float64), P.astype(np.float64)
+    w = cnt * np.exp(-0.5 * ((P64[:, None] - val[None]) ** 2).sum(-1) / h ** 2)
+    ref = (w @ val) / w.sum(1, keepdims=True)
+    S0 = np.tile(P, (m // 12, 1))
+    err = []
+    for plain in (False, True):
+        S, conv, it, sh = api.step(_gpu(X), _gpu(S0), h, n_iter=1, plain=plain)
+        err.append(np.abs(S.cpu().numpy().reshape(m // 12, 12, d) - ref).max() / h)
+    assert err[0] <= 1.5 * err[1] + 1e-6, err
