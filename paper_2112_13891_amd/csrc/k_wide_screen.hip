@@ -49,6 +49,12 @@ constexpr float kDropped = 34.0f;        // log2 of W over all that is left out,
 constexpr float kFlatMargin = 1.001f;
 constexpr int kEvalWaves = 8;
 constexpr int kEvalPoints = 64 * kEvalWaves * 32;   // points listed at once: 32 bits a thread
+// A lane adds this many pairs in a row before its sums are added up across
+// lanes.  Where points repeat, additions of equal terms all round the same way:
+// one update of seeds that see 120,001 points of seven values (D = 128) was off
+// by 1.3e-5 h, and is by 1.1e-7 h now (50,001 x 500 pairs, all near, three
+// updates: 1,336 -> 1,404 us; D = 64 and 256 as before).
+constexpr int kEvalRun = 32;
 
 // Points as operands: per 32 points and block of 16 coordinates, lane l holds
 // point l % 32, coordinates 8 (l / 32) ... + 7.  One wave per 32 points.  With
@@ -268,13 +274,16 @@ __device__ __forceinline__ float lanes_sum(float v) {
 // A workgroup per active seed.  LP lanes hold a pair, D / LP coordinates each;
 // 64 / LP pairs to a wave, U rows in flight per lane.  At least 8 coordinates a
 // lane: with 4 (D = 64 by 16 lanes) the lanes' sum and the exponential are a
-// third of the work (50,001 x 500 pairs, all near: KEEPME).
+// third of the work (50,001 x 500 pairs, all near, three updates: 1,010 us, 834
+// with 8 lanes).
 template <int D, int KERN>
 __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, int t, WideScreen w) {
     constexpr int LP = D == 64 ? 8 : 16;     // lanes per pair
     constexpr int G = 64 / LP;               // pairs of a wave
     constexpr int C4 = D / (4 * LP);         // float4 groups per lane
     constexpr int U = D == 256 ? 2 : 4;
+    constexpr int V = 4 * C4 + 1;            // a lane's sums: coordinates, weight
+    constexpr int Q = (V + 3) / 4;
     const int m = active_count(a.ctl, t);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = lane % LP, grp = lane / LP;
@@ -286,7 +295,7 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
     for (int slot = blockIdx.x; slot < m; slot += gridDim.x) {
         const int j = a.act_in[slot];
         float* sj = a.S + (long long)j * D;
-        float s[4 * C4], acc[4 * C4], accw = 0.0f;
+        float s[4 * C4], acc[V], sum[Q];
 #pragma unroll
         for (int q = 0; q < C4; ++q) {
             const float4 v = reinterpret_cast<const float4*>(sj)[q * LP + sub];
@@ -296,7 +305,24 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
             s[4 * q + 3] = v.w * a.scale;
         }
 #pragma unroll
-        for (int k = 0; k < 4 * C4; ++k) acc[k] = 0.0f;
+        for (int k = 0; k < V; ++k) acc[k] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) sum[q] = 0.0f;
+        int run = 0;   // pairs a lane has added since the last fold
+        auto fold = [&] {
+            auto take = [&](int k) {
+                if (k >= V) return 0.0f;
+                const float v = acc[k];
+                acc[k] = 0.0f;
+                return v;
+            };
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const float a4 = take(4 * q), b4 = take(4 * q + 1), c4 = take(4 * q + 2), d4 = take(4 * q + 3);
+                sum[q] += rows4(a4, b4, c4, d4);
+            }
+            run = 0;
+        };
         const int words32 = 2 * w.words;
         for (int w0 = 0; w0 < words32; w0 += 64 * kEvalWaves) {
             // the points of the set bits, in order
@@ -351,24 +377,24 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
                     if (KERN == MS_KERNEL_GAUSSIAN) wt = __builtin_amdgcn_exp2f(-q2);
                     else wt = q2 <= a.h2 ? 1.0f : 0.0f;
                     if (i0 + u * G + grp < len) {
-                        accw += wt;
+                        acc[4 * C4] += wt;
 #pragma unroll
                         for (int k = 0; k < 4 * C4; ++k) acc[k] = fmaf(wt, dx[k], acc[k]);
                     }
                 }
+                if ((run += U) >= kEvalRun) fold();
             }
         }
         // the pairs of a wave, then the waves in order
+        fold();
 #pragma unroll
-        for (int off = LP; off <= 32; off <<= 1) {
-            accw += __shfl_xor(accw, off);
-#pragma unroll
-            for (int k = 0; k < 4 * C4; ++k) acc[k] += __shfl_xor(acc[k], off);
-        }
-        if (grp == 0) {
-#pragma unroll
-            for (int k = 0; k < 4 * C4; ++k) red[wave][(k >> 2) * 4 * LP + sub * 4 + (k & 3)] = acc[k];
-            if (sub == 0) red[wave][D] = accw;
+        for (int q = 0; q < Q; ++q) {
+            const float v = LP == 8 ? row_add<0x128>(sum[q]) : sum[q];   // row_ror:8
+            const int k = 4 * q + rows4_value(lane);
+            if ((lane & 15) < LP) {
+                if (k < 4 * C4) red[wave][(k >> 2) * 4 * LP + sub * 4 + (k & 3)] = v;
+                else if (k == 4 * C4 && sub == 0) red[wave][D] = v;
+            }
         }
         __syncthreads();
         if (wave == 0) {

@@ -136,3 +136,24 @@ def test_screen_bound_at_the_worst_rounding(d, sign):
         assert torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
         # two orders of sums of up to 4,000 terms of FP32
         assert float((a[0] - b[0]).abs().max()) < 1e-5 * mag
+
+
+@pytest.mark.parametrize("n,d,m", [(66382, 64, 4), (76426, 33, 40), (120001, 128, 12), (115371, 200, 1)])
+def test_repeated_points_keep_the_sums(n, d, m):
+    """Points of seven values, all within reach: the additions of equal terms
+    round the same way, so that the error of a sum grows with the number of
+    additions in a row.  One update against FP64, within 1.5 times the error of
+    the form that evaluates every pair in short chunks, and 1e-6 h."""
+    rng = np.random.default_rng(n + d)
+    X = (4.0 * rng.standard_normal((7, d)))[rng.integers(0, 7, n)].astype(np.float32)
+    h = 3.0 * np.sqrt(d)
+    S0 = X[rng.choice(n, m, replace=False)] + (0.1 * h * rng.standard_normal((m, d))).astype(np.float32)
+    val, cnt = np.unique(X, axis=0, return_counts=True)
+    val, S64 = val.astype(np.float64), S0.astype(np.float64)
+    w = cnt * np.exp(-0.5 * ((S64[:, None] - val[None]) ** 2).sum(-1) / h ** 2)
+    ref = (w @ val) / w.sum(1, keepdims=True)
+    err = []
+    for plain in (False, True):
+        S, conv, it, sh = api.step(_gpu(X), _gpu(S0), h, n_iter=1, plain=plain)
+        err.append(np.abs(S.cpu().numpy() - ref).max() / h)
+    assert err[0] <= 1.5 * err[1] + 1e-6, err
