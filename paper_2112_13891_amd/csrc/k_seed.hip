@@ -195,6 +195,11 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(
     const bool keep = RUNS || groups <= kSegGroups;
     int points = nball * 64;
     if constexpr (RUNS) points = (a.tile_start[run0 + nball + kFarRuns] - a.tile_start[run0]) * 64;
+    // A cloud with a point that is not finite (or overflows) has it in its last
+    // far run, whose bound is then 0: every seed of the cloud fails by it, also
+    // by a coordinate that the first half of a distance does not hold
+    bool whole = false;
+    if constexpr (RUNS && D >= 16) whole = a.run_bound[run0 + nball + kFarRuns - 1] == 0.0f;
     const float negligible = kSeedDropped + __builtin_amdgcn_logf((float)points) + 0.01f;
     const float4* __restrict__ T4 = reinterpret_cast<const float4*>(a.T);
 
@@ -324,6 +329,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(
                     reach[r] = a.flat_reach;
                     rq[r] = reach[r] * reach[r];
                 }
+                if (whole) rq[r] = __builtin_inff();
             }
             if constexpr (RUNS) {
                 // near runs by their balls, far runs by their bounds.  A

@@ -169,3 +169,25 @@ def test_repeated_points_keep_the_sums(n, d, m):
         S, conv, it, sh = api.step(_gpu(X), _gpu(S0), h, n_iter=1, plain=plain)
         err.append(np.abs(S.cpu().numpy().reshape(m // 12, 12, d) - ref).max() / h)
     assert err[0] <= 1.5 * err[1] + 1e-6, err
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("d,k", [(16, 15), (13, 12), (16, 8), (24, 17), (32, 31), (32, 2)])
+@pytest.mark.parametrize("kernel", ["gaussian", "flat"])
+def test_point_not_finite_in_either_half(d, k, kernel, bad):
+    """A point with a coordinate that is not finite fails every seed of its
+    cloud, whichever half of a distance holds the coordinate, and no seed of
+    another cloud.  Status, updates and coordinates as by all pairs."""
+    X = blobs(d, 20000, d, box=30.0)
+    S0 = X[np.random.default_rng(1).choice(20000, 300, replace=False)]
+    clean = X.copy()
+    X[777, k] = bad
+    h = 1.5 * np.sqrt(d / 4.0)
+    S, conv, it, sh = api.step(_gpu(X), _gpu(S0), h, kernel=kernel, n_iter=2)
+    P, pconv, pit, psh = api.step(_gpu(X), _gpu(S0), h, kernel=kernel, n_iter=2, plain=True)
+    assert (pconv == 2).all()
+    assert torch.equal(conv, pconv) and torch.equal(it, pit)
+    assert torch.equal(torch.isfinite(S), torch.isfinite(P))
+    both = api.step_batched(_gpu(np.concatenate([X, clean])), [0, 20000, 40000], _gpu(np.concatenate([S0, S0])),
+                            [0, 300, 600], h, kernel=kernel, n_iter=2)
+    assert (both[1][:300] == 2).all() and (both[1][300:] != 2).all()
