@@ -153,7 +153,11 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     // seed passes: the largest q that counts for the lane's seed
     const float toraw = 1.0f / (a.scale * a.scale);
     float rq = fminf(kZeroQ, a.neg + ub * ub), reach = sqrtf(rq);
-    float far_q = live ? rq * toraw : -1.0f;
+    // a cloud with a point that is not finite (in its last far run, whose bound
+    // is then 0): none of its pairs is left out by half a distance
+    const float least_q =
+        MODE != DX && D >= 16 && a.other.run_bound[run0 + P + kFarRuns - 1] == 0.0f ? __builtin_inff() : 0.0f;
+    float far_q = live ? fmaxf(rq * toraw, least_q) : -1.0f;
 
     // near: run e of this cloud is within some lane's reach
     auto is_near = [&](int e, float lim) {
@@ -213,7 +217,7 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
                 if (__ballot(live && better < rq)) {
                     rq = fminf(rq, fmaxf(better, 1.0f));
                     reach = sqrtf(rq);
-                    far_q = live ? rq * toraw : -1.0f;
+                    far_q = live ? fmaxf(rq * toraw, least_q) : -1.0f;
                     if (!is_near(e, reach)) return;
                 }
             }
@@ -380,10 +384,11 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
             }
             o[2 * DP] = live ? (float)iw : 0.0f;
             o[2 * DP + 1] = live ? -(float)gdel : 0.0f;
-            // a seed without weight (1/W not finite) is seen by every point
+            // a seed without weight (1/W not finite), or whose g.delta is not
+            // finite, is seen by every point
             float q = 0.0f;
             if (live)
-                q = (W > 0.0f && isfinite((float)iw))
+                q = (W > 0.0f && isfinite((float)iw) && isfinite((float)gdel))
                         ? fminf(kZeroQ, fmaxf(a.neg + 1.0f - __builtin_amdgcn_logf(W), 1.0f))
                         : __builtin_inff();
 #pragma unroll

@@ -146,6 +146,25 @@ def test_runs_infinite_point_shares_a_run(d, bad):
         _close(dX[0][keep], rX, "dX")
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d,k,m", [(16, 15, 8200), (16, 9, 8300), (32, 31, 8200)])
+def test_runs_not_finite_in_the_second_half(d, k, m, bad):
+    """A point with a coordinate that is not finite counts for every seed and
+    every gradient of its cloud, also by a coordinate in the second half of a
+    distance: finite where the all-pairs form (FP64) is."""
+    X = torch.stack([_cloud(6, 8200, d, 20), _cloud(7, 8200, d, 20)])
+    S = torch.cat([X, X], 1)[:, :m].contiguous()
+    X[0, 500, k] = bad
+    G = torch.randn(2, m, d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(5))
+    new = api.forward_update(X, S, 1.0)
+    dS, dX = api.step_adjoint(X, S, 1.0, G)
+    ref = api.forward_update(X.double(), S.double(), 1.0)
+    rS, rX = api.step_adjoint(X.double(), S.double(), 1.0, G.double())
+    for a, b in ((new, ref), (dS, rS), (dX, rX)):
+        assert torch.equal(torch.isfinite(a), torch.isfinite(b))
+        assert not torch.isfinite(b[0]).all() and torch.isfinite(b[1]).all()
+
+
 # either side of the lines between the two forms: points of the least cloud,
 # tiles of the smaller side, more seeds than points, pairs
 @pytest.mark.parametrize("nb,n,m,d", [(2, 8192, 8192, 8), (3, 8300, 8195, 5), (2, 8191, 8191, 8), (1, 8192, 20000, 3),
