@@ -63,6 +63,10 @@ template <int D>
 __global__ __launch_bounds__(kThreads) void wide_points_kernel(const float* __restrict__ X, int n, int d, float scale,
                                                                int tiles, float* __restrict__ Xp,
                                                                bf16x8* __restrict__ pf, float* __restrict__ nx) {
+    // differences of packed coordinates, rounded as the exact distances have
+    // them: fused with the scaling, a column of equal large values (1.6e9, h = 1)
+    // put points and seeds 2 ulp apart in the screen alone
+#pragma clang fp contract(off)
     constexpr int KB = D / 16;
     const int t = blockIdx.x * kWaves + (threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
     if (t >= tiles) return;
@@ -120,6 +124,7 @@ __device__ __forceinline__ float seed_reach(int kern, float h2, float W, int n) 
 template <int D>
 __device__ __forceinline__ void store_seed(int j, const float (&u)[D / 64], bool active, float reach, float scale,
                                            const float* __restrict__ Xp, __bf16* sf, float* crow) {
+#pragma clang fp contract(off)   // as in wide_points_kernel
     constexpr int KB = D / 16;
     const int lane = threadIdx.x & 63;
     float nn = 0.0f;

@@ -157,3 +157,22 @@ def test_repeated_points_keep_the_sums(n, d, m):
         S, conv, it, sh = api.step(_gpu(X), _gpu(S0), h, n_iter=1, plain=plain)
         err.append(np.abs(S.cpu().numpy() - ref).max() / h)
     assert err[0] <= 1.5 * err[1] + 1e-6, err
+
+
+@pytest.mark.parametrize("value", [1.6e9, 1e12, -1e16])
+@pytest.mark.parametrize("n,d,m,kernel", [(1, 64, 1, "gaussian"), (3001, 33, 97, "gaussian"), (5000, 128, 64, "flat")])
+def test_column_of_one_large_value(n, d, m, kernel, value):
+    """A column that holds one value throughout adds nothing to any distance,
+    however large it is against h: the results are those without the column."""
+    X = embed(n, n, d, 5)
+    X[:, d // 2] = value
+    S0 = X[np.random.default_rng(m).choice(n, m, replace=False)]
+    h = 1.5 * np.sqrt(d / 32.0) * (1.0 if kernel == "gaussian" else 2.0)
+    S, conv, it, sh = api.step(_gpu(X), _gpu(S0), h, kernel=kernel, n_iter=2)
+    X[:, d // 2] = 0.0
+    S0[:, d // 2] = 0.0
+    R, rconv, rit, rsh = api.step(_gpu(X), _gpu(S0), h, kernel=kernel, n_iter=2)
+    assert torch.equal(conv, rconv) and torch.equal(it, rit)
+    assert (S[:, d // 2] == value).all()
+    S[:, d // 2] = 0.0
+    assert (S - R).abs().max().item() <= 1e-5 * h
