@@ -53,7 +53,7 @@ constexpr int kEvalPoints = 64 * kEvalWaves * 32;   // points listed at once: 32
 // lanes.  Where points repeat, additions of equal terms all round the same way:
 // one update of seeds that see 120,001 points of seven values (D = 128) was off
 // by 1.3e-5 h, and is by 1.1e-7 h now (50,001 x 500 pairs, all near, three
-// updates: 1,336 -> 1,404 us; D = 64 and 256 as before).
+// updates: D = 128 1,374 -> 1,403 us, D = 64 and 256 within 1 %).
 constexpr int kEvalRun = 32;
 
 // Points as operands: per 32 points and block of 16 coordinates, lane l holds
@@ -313,7 +313,6 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
         for (int k = 0; k < V; ++k) acc[k] = 0.0f;
 #pragma unroll
         for (int q = 0; q < Q; ++q) sum[q] = 0.0f;
-        int run = 0;   // pairs a lane has added since the last fold
         auto fold = [&] {
             auto take = [&](int k) {
                 if (k >= V) return 0.0f;
@@ -326,7 +325,6 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
                 const float a4 = take(4 * q), b4 = take(4 * q + 1), c4 = take(4 * q + 2), d4 = take(4 * q + 3);
                 sum[q] += rows4(a4, b4, c4, d4);
             }
-            run = 0;
         };
         const int words32 = 2 * w.words;
         for (int w0 = 0; w0 < words32; w0 += 64 * kEvalWaves) {
@@ -356,42 +354,45 @@ __global__ __launch_bounds__(64 * kEvalWaves) void wide_eval_kernel(StepArgs a, 
             }
             __syncthreads();
             len = __builtin_amdgcn_readfirstlane(len);
-            for (int i0 = wave * G * U; i0 < len; i0 += kEvalWaves * G * U) {
-                float4 x4[U][C4];
+            // kEvalRun pairs a lane, then the fold (its test within one loop: 5 %)
+            for (int c0 = wave * G * U; c0 < len; c0 += kEvalWaves * G * kEvalRun) {
+                const int c1 = min(len, c0 + kEvalWaves * G * kEvalRun);
+                for (int i0 = c0; i0 < c1; i0 += kEvalWaves * G * U) {
+                    float4 x4[U][C4];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = i0 + u * G + grp;
-                    const long long p = (long long)w0 * 32 + list[i < len ? i : i0];
+                    for (int u = 0; u < U; ++u) {
+                        const int i = i0 + u * G + grp;
+                        const long long p = (long long)w0 * 32 + list[i < len ? i : i0];
 #pragma unroll
-                    for (int q = 0; q < C4; ++q) x4[u][q] = X4[p * (D / 4) + q * LP + sub];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    float dx[4 * C4], q2 = 0.0f;
-#pragma unroll
-                    for (int q = 0; q < C4; ++q) {
-                        dx[4 * q] = x4[u][q].x - s[4 * q];
-                        dx[4 * q + 1] = x4[u][q].y - s[4 * q + 1];
-                        dx[4 * q + 2] = x4[u][q].z - s[4 * q + 2];
-                        dx[4 * q + 3] = x4[u][q].w - s[4 * q + 3];
+                        for (int q = 0; q < C4; ++q) x4[u][q] = X4[p * (D / 4) + q * LP + sub];
                     }
 #pragma unroll
-                    for (int k = 0; k < 4 * C4; ++k) q2 = fmaf(dx[k], dx[k], q2);
-                    q2 = lanes_sum<LP>(q2);
-                    float wt;
-                    if (KERN == MS_KERNEL_GAUSSIAN) wt = __builtin_amdgcn_exp2f(-q2);
-                    else wt = q2 <= a.h2 ? 1.0f : 0.0f;
-                    if (i0 + u * G + grp < len) {
-                        acc[4 * C4] += wt;
+                    for (int u = 0; u < U; ++u) {
+                        float dx[4 * C4], q2 = 0.0f;
 #pragma unroll
-                        for (int k = 0; k < 4 * C4; ++k) acc[k] = fmaf(wt, dx[k], acc[k]);
+                        for (int q = 0; q < C4; ++q) {
+                            dx[4 * q] = x4[u][q].x - s[4 * q];
+                            dx[4 * q + 1] = x4[u][q].y - s[4 * q + 1];
+                            dx[4 * q + 2] = x4[u][q].z - s[4 * q + 2];
+                            dx[4 * q + 3] = x4[u][q].w - s[4 * q + 3];
+                        }
+#pragma unroll
+                        for (int k = 0; k < 4 * C4; ++k) q2 = fmaf(dx[k], dx[k], q2);
+                        q2 = lanes_sum<LP>(q2);
+                        float wt;
+                        if (KERN == MS_KERNEL_GAUSSIAN) wt = __builtin_amdgcn_exp2f(-q2);
+                        else wt = q2 <= a.h2 ? 1.0f : 0.0f;
+                        if (i0 + u * G + grp < len) {
+                            acc[4 * C4] += wt;
+#pragma unroll
+                            for (int k = 0; k < 4 * C4; ++k) acc[k] = fmaf(wt, dx[k], acc[k]);
+                        }
                     }
                 }
-                if ((run += U) >= kEvalRun) fold();
+                fold();
             }
         }
         // the pairs of a wave, then the waves in order
-        fold();
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const float v = LP == 8 ? row_add<0x128>(sum[q]) : sum[q];   // row_ror:8
