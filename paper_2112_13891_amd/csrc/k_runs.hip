@@ -130,6 +130,9 @@ __global__ __launch_bounds__(64) void run_pivots_kernel(const float* __restrict_
             if (pivots && live && k < D) pivots[(long long)k * ptot + poff[c] + j] = k < d ? row[k] * scale : 0.0f;
             if (pivot_rows && live && k < DP) pivot_rows[(long long)(poff[c] + j) * DP + k] = k < d ? row[k] : 0.0f;
             nn = fmaf(v, v, nn);
+            // a reference that overflows in packed units makes every distance
+            // from it NaN: all points of the cloud go to its last far run
+            if (live && k < d) nn = fmaf(0.0f, ref[k] * scale, nn);
             hi[e] = (__bf16)v;
             lo[e] = (__bf16)(v - (float)hi[e]);
         }

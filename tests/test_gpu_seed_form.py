@@ -191,3 +191,20 @@ def test_point_not_finite_in_either_half(d, k, kernel, bad):
     both = api.step_batched(_gpu(np.concatenate([X, clean])), [0, 20000, 40000], _gpu(np.concatenate([S0, S0])),
                             [0, 300, 600], h, kernel=kernel, n_iter=2)
     assert (both[1][:300] == 2).all() and (both[1][300:] != 2).all()
+
+
+@pytest.mark.parametrize("d,n", [(1, 2), (2, 100), (3, 5000), (5, 100), (16, 5000), (32, 20000)])
+@pytest.mark.parametrize("at", [0, 1])
+@pytest.mark.parametrize("last", [False, True])
+def test_packed_coordinate_that_overflows(d, n, at, last):
+    """A finite coordinate that overflows in packed units (3e38, h = 0.5) fails
+    the seeds of its cloud as an infinite one does, also where the point is the
+    cloud's first row, which the index takes distances from."""
+    X = blobs(d, n, d, k=2, box=2.0)
+    S0 = X[:2].copy()
+    X[at, d - 1 if last else 0] = 3e38
+    P, pconv, pit, psh = api.step(_gpu(X), _gpu(S0), 0.5, n_iter=1, plain=True)
+    for S, conv, it, sh in (api.step(_gpu(X), _gpu(S0), 0.5, n_iter=1),
+                            api.step_batched(_gpu(X), [0, n], _gpu(S0), [0, 2], 0.5, n_iter=1)):
+        assert torch.equal(conv, pconv) and torch.equal(it, pit)
+    assert (pconv == 2).all()
