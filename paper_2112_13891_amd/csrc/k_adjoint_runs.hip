@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     const const_f32_ptr bv = wave_uniform_const(a.other.ball_rows);
     const bool bounds = MODE != DX || a.other.run_bound != nullptr;
     // the nearest pivot (a point) of each lane, and the pivot nearest to any
-    float ub = 1e18f, first_d = 1e18f;
+    float ub = __builtin_inff(), first_d = 1e18f;
     int first = 0;
     for (int e = wave; bounds && e < P; e += kWv) {
         const float dist = dist_to(pv + (long long)(p0 + e) * DP);

@@ -303,7 +303,7 @@ __global__ __launch_bounds__(256) void run_near_kernel(const float* __restrict__
     vals[p] = (int)p;
     if (near_pivot) {   // seeds: the pivot itself, and an upper bound
         near_pivot[p] = pv;
-        dpiv[p] = fine ? __builtin_amdgcn_sqrtf(qe + eps) * 1.0001f : 1e18f;
+        dpiv[p] = fine ? __builtin_amdgcn_sqrtf(qe + eps) * 1.0001f : __builtin_inff();
     } else {
         float b = 0.0f;
         if (fine) b = is_far ? __builtin_amdgcn_sqrtf(fmaxf(qe - eps, 0.0f)) * 0.9999f

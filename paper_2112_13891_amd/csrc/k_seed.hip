@@ -211,7 +211,7 @@ __global__ __launch_bounds__(64 * seed_max_waves(D, R), PW ? 2 : seed_min_waves(
     for (int r = 0; r < R; ++r) {
         reach[r] = 0.0f;
         rq[r] = __builtin_inff();   // nothing is left out without geometry
-        ub[r] = 1e18f;
+        ub[r] = __builtin_inff();
         wprev[r] = -1.0f;
         last_sh2[r] = __builtin_nanf("");
         nit[r] = 0;

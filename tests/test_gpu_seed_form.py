@@ -208,3 +208,21 @@ def test_packed_coordinate_that_overflows(d, n, at, last):
                             api.step_batched(_gpu(X), [0, n], _gpu(S0), [0, 2], 0.5, n_iter=1)):
         assert torch.equal(conv, pconv) and torch.equal(it, pit)
     assert (pconv == 2).all()
+
+
+@pytest.mark.parametrize("d,n", [(5, 100), (16, 5000), (32, 20000)])
+@pytest.mark.parametrize("value", [1e17, 1e19, -1e20])
+def test_seed_and_point_far_beyond_the_others(d, n, value):
+    """A seed and one point share a coordinate far beyond any pivot: the point
+    alone moves the seed, however far the pivots are."""
+    X = blobs(d, n, d, k=2, box=2.0)
+    S0 = X[3:4].copy()
+    X[7, d - 1] = value
+    S0[0, d - 1] = value
+    h = 3.0 * np.sqrt(d)
+    P, pconv, pit, psh = api.step(_gpu(X), _gpu(S0), h, n_iter=1, plain=True)
+    for S, conv, it, sh in (api.step(_gpu(X), _gpu(S0), h, n_iter=1),
+                            api.step_batched(_gpu(X), [0, n], _gpu(S0), [0, 1], h, n_iter=1)):
+        assert torch.equal(conv, pconv) and torch.equal(it, pit)
+        assert (S - P)[:, :-1].abs().max().item() <= 1e-5 * h
+    assert (pconv != 2).all()
