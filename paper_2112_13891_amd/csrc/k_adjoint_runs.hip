@@ -43,6 +43,7 @@ constexpr int kT = 512;           // eight waves share a tile: short workgroups 
 constexpr int kWv = kT / 64;
 constexpr float kZeroQ = 160.0f;
 constexpr float kDropped = 33.0f;
+constexpr int kFoldTiles = 4;
 
 // One side of the pairs: runs in cloud order (k_runs.hip).
 struct Side {
@@ -99,7 +100,8 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     }
 
     constexpr int kGroups = (kRunPivotMax + kFarRuns + 63) / 64;
-    __shared__ float red[(kWv - 1) * VR * 64];
+    constexpr bool kTileSums = D <= 8;
+    __shared__ float red[(kTileSums ? kWv - 1 : kWv) * VR * 64];
     __shared__ float umin[kWv][64];
     __shared__ float wfirst_d[kWv];
     __shared__ int wfirst[kWv];
@@ -176,8 +178,10 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     // narrow rows: each tile's 64 terms are summed apart and then added, which
     // keeps the chains short (at D = 3 a wave adds thousands of terms; dL/dX of
     // overlapping clusters was off by 1.1e-6 without and the all-pairs form by
-    // 7.9e-7)
-    constexpr bool kTileSums = D <= 8;
+    // 7.9e-7).  Wide rows: every kFoldTiles tiles the sums are added into the
+    // wave's place in LDS (where points repeat, additions of equal terms all
+    // round the same way: 16,384 x 8,192 pairs of seven points, D = 32, dL/dS
+    // was off by 7.1e-6 and the all-pairs form by 2.5e-6)
     float acc[V], sum[kTileSums ? V : 1];
 #pragma unroll
     for (int k = 0; k < V; ++k) acc[k] = 0.0f;
@@ -185,6 +189,23 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
 #pragma unroll
         for (int k = 0; k < V; ++k) sum[k] = 0.0f;
     }
+    float* const place = red + wave * VR * 64 + lane;   // wide rows
+    float folded_W = 0.0f;
+    int unfolded = 0;
+    if constexpr (!kTileSums) {
+#pragma unroll
+        for (int k = 0; k < VR; ++k) place[k * 64] = 0.0f;
+    }
+    auto to_place = [&]() {
+        if (MODE != DX) folded_W += acc[MODE != DX ? D : 0];
+#pragma unroll
+        for (int k = 0; k < VR; ++k) {
+            place[k * 64] += MODE == DX ? fmaf(-a.ih2, acc[MODE == DX ? D + k : k], acc[k]) : acc[k];
+            acc[k] = 0.0f;
+            if (MODE == DX) acc[MODE == DX ? D + k : k] = 0.0f;
+        }
+        unfolded = 0;
+    };
     auto fold = [&]() {
         if constexpr (kTileSums) {
 #pragma unroll
@@ -192,11 +213,13 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
                 sum[k] += acc[k];
                 acc[k] = 0.0f;
             }
+        } else if (++unfolded == kFoldTiles) {
+            to_place();
         }
     };
     auto wave_W = [&]() {
         if constexpr (kTileSums && MODE != DX) return sum[D];
-        else return acc[MODE != DX ? D : 0];
+        else return folded_W + acc[MODE != DX ? D : 0];
     };
     int turn = 0;
     const const_f32_ptr rows = wave_uniform_const(a.other.rows);
@@ -330,24 +353,26 @@ __global__ __launch_bounds__(kT) void adj_runs_kernel(AdjArgs a) {
     if constexpr (kTileSums) {
 #pragma unroll
         for (int k = 0; k < V; ++k) acc[k] = sum[k];
-    }
-    if constexpr (MODE == DX) {
+        if constexpr (MODE == DX) {
 #pragma unroll
-        for (int k = 0; k < D; ++k) acc[k] = fmaf(-a.ih2, acc[D + k], acc[k]);
-    }
-    // the wave sums in wave order
-    if (wave > 0) {
+            for (int k = 0; k < D; ++k) acc[k] = fmaf(-a.ih2, acc[D + k], acc[k]);
+        }
+        // the wave sums in wave order
+        if (wave > 0) {
 #pragma unroll
-        for (int k = 0; k < VR; ++k) red[((wave - 1) * VR + k) * 64 + lane] = acc[k];
+            for (int k = 0; k < VR; ++k) red[((wave - 1) * VR + k) * 64 + lane] = acc[k];
+        }
+    } else {
+        to_place();
     }
     __syncthreads();
     if (wave > 0) return;
     // the last additions and the products of sums in FP64: they are few, and
     // sum w (g.dx) dx and (g.delta) delta cancel where delta is large
     auto tot = [&](int k) {
-        double v = acc[k];
+        double v = kTileSums ? acc[k] : 0.0f;
 #pragma unroll
-        for (int w = 0; w < kWv - 1; ++w) v += red[(w * VR + k) * 64 + lane];
+        for (int w = 0; w < (kTileSums ? kWv - 1 : kWv); ++w) v += red[(w * VR + k) * 64 + lane];
         return v;
     };
     if constexpr (MODE == DX) {

@@ -165,6 +165,27 @@ def test_runs_not_finite_in_the_second_half(d, k, m, bad):
         assert not torch.isfinite(b[0]).all() and torch.isfinite(b[1]).all()
 
 
+@pytest.mark.parametrize("nb,n,m,d,values", [(2, 16384, 8192, 32, 7), (1, 16384, 16384, 16, 7), (2, 16384, 8192, 13, 2),
+                                             (1, 32768, 8192, 8, 2)])
+def test_runs_repeated_points_keep_the_sums(nb, n, m, d, values):
+    """Points of few values, all within reach: additions of equal terms round
+    the same way, by about 7e-9 of the sum each, so that a lane's error grows
+    with its additions in a row.  256 rows and a few folds in a row make at most
+    2e-6 of a sum and of W, 4e-6 of an update; all 2,048 of a wave were 1.5e-5."""
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    V = 4.0 * torch.randn(values, d, device=DEV, generator=g)
+    X = V[torch.randint(values, (nb, n), device=DEV, generator=g)].contiguous()
+    h = 3.0 * d ** 0.5
+    S = X[:, torch.randint(n, (m,), device=DEV, generator=g)] + 0.2 * h * torch.randn(nb, m, d, device=DEV, generator=g)
+    G = torch.randn(nb, m, d, device=DEV, generator=g)
+    new = api.forward_update(X, S, h)
+    dS, dX = api.step_adjoint(X, S, h, G)
+    ref = api.forward_update(X.double(), S.double(), h)
+    rS, rX = api.step_adjoint(X.double(), S.double(), h, G.double())
+    assert ((new - S) - (ref - S.double())).norm() <= 4e-6 * (ref - S.double()).norm()
+    assert (dS - rS).norm() <= 3e-6 * G.norm() and (dX - rX).norm() <= 1e-6 * G.norm()
+
+
 # either side of the lines between the two forms: points of the least cloud,
 # tiles of the smaller side, more seeds than points, pairs
 @pytest.mark.parametrize("nb,n,m,d", [(2, 8192, 8192, 8), (3, 8300, 8195, 5), (2, 8191, 8191, 8), (1, 8192, 20000, 3),
